@@ -44,6 +44,15 @@ MI355GEMM_MFMA8_TILES(X)
 MI355GEMM_MFMA16_TILES(X)
 MI355GEMM_MFMA16P_TILES(X)
 #undef X
+#define X(BM, BN, WM, WN, G, P)                                        \
+  MI355GEMM_MFMA16T_DECLARE(bf16_t, BM, BN, WM, WN, G, P, true, false)  \
+  MI355GEMM_MFMA16T_DECLARE(bf16_t, BM, BN, WM, WN, G, P, false, false) \
+  MI355GEMM_MFMA16T_DECLARE(bf16_t, BM, BN, WM, WN, G, P, false, true)  \
+  MI355GEMM_MFMA16T_DECLARE(f16_t, BM, BN, WM, WN, G, P, true, false)   \
+  MI355GEMM_MFMA16T_DECLARE(f16_t, BM, BN, WM, WN, G, P, false, false)  \
+  MI355GEMM_MFMA16T_DECLARE(f16_t, BM, BN, WM, WN, G, P, false, true)
+MI355GEMM_MFMA16T_TILES(X)
+#undef X
 }  // namespace mi355gemm
 
 namespace {
@@ -124,6 +133,15 @@ hipError_t launch_f32_small(const gemm_plan& pl, const void* A, const void* B, v
             ((uintptr_t)B & 15) == 0;
   f32_small_kernel<<<pl.grid, pl.block, 0, s>>>(a);
   return hipGetLastError();
+}
+
+// 16-bit operands of which at least one is not K-contiguous
+template <typename T, int BM, int BN, int WM, int WN, int G, bool PERSIST>
+hipError_t launch_mfma16t(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias, hipStream_t s) {
+  const bool ak = pl.d.layout_a == GEMM_ROW_MAJOR, bk = pl.d.layout_b == GEMM_COL_MAJOR;
+  if (ak) return launch_mfma16<T, T, BM, BN, WM, WN, G, PERSIST, true, false>(pl, A, B, C, bias, s);
+  if (bk) return launch_mfma16<T, T, BM, BN, WM, WN, G, PERSIST, false, true>(pl, A, B, C, bias, s);
+  return launch_mfma16<T, T, BM, BN, WM, WN, G, PERSIST, false, false>(pl, A, B, C, bias, s);
 }
 
 template <typename TIn, int TM, int TN, int TK>
@@ -215,6 +233,13 @@ hipError_t launch_skinny_direct(const gemm_plan& pl, const void* A, const void* 
                       Mfma16Tile<bf16_t, BM, BN, WM, WN, G>::EPI_BYTES,                    \
     { nullptr, launch_mfma16<bf16_t, bf16_t, BM, BN, WM, WN, G, true>,                     \
       launch_mfma16<f16_t, f16_t, BM, BN, WM, WN, G, true> }, 1 }
+// either of the two for operands whose K is not contiguous (P: 0 = one tile per workgroup, 1 = persistent)
+#define MFMA16T_CFG(SUFFIX, BM, BN, WM, WN, G, P)                                           \
+  { "mfma16t_" #BM "x" #BN "x64_w" #WM "x" #WN SUFFIX, KIND_MFMA_T, BM, BN, 64,             \
+    64 * WM * WN, Mfma16Tile<bf16_t, BM, BN, WM, WN, G>::LDS_BYTES +                       \
+                      (P ? Mfma16Tile<bf16_t, BM, BN, WM, WN, G>::EPI_BYTES : 0),          \
+    { nullptr, launch_mfma16t<bf16_t, BM, BN, WM, WN, G, P != 0>,                          \
+      launch_mfma16t<f16_t, BM, BN, WM, WN, G, P != 0> }, P }
 // fp8 (E4M3) operands, bf16 or fp32 output: the same slabs in bytes (BK is twice as many values)
 #define MFMA8_CFG(BM, BN, BK, WM, WN, NS)                                                  \
   { "mfma8_" #BM "x" #BN "x" #BK "_w" #WM "x" #WN "_s" #NS, KIND_MFMA, BM, BN, BK,         \
@@ -271,6 +296,10 @@ const Config kConfigs[] = {
     SKINNY_DIRECT_CFG(2, 512, 4),
     SKINNY_DIRECT_CFG(3, 512, 4),
     SKINNY_DIRECT_CFG(2, 256, 8),
+    MFMA16T_CFG("_p", 256, 256, 2, 4, 2, 1),
+    MFMA16T_CFG("_p", 128, 128, 2, 2, 2, 1),
+    MFMA16T_CFG("", 256, 256, 2, 4, 2, 0),
+    MFMA16T_CFG("", 128, 128, 2, 2, 2, 0),
 };
 constexpr int kNumConfigs = (int)(sizeof(kConfigs) / sizeof(kConfigs[0]));
 
@@ -366,6 +395,21 @@ bool applicable(const Config& c, const gemm_desc_t& d) {
     return d.dtype_c == GEMM_F32 && d.lda % 4 == 0 && d.ldb % 4 == 0 && d.stride_a % 4 == 0 &&
            d.stride_b % 4 == 0 && (ak ? d.K : d.M) % 4 == 0 && (bk ? d.K : d.N) % 4 == 0;
   }
+  if (c.kind == KIND_MFMA_T) {
+    // Row-major C, at least one operand not K-contiguous; 16-byte pieces along each operand's contiguous
+    // index (its extent, leading dimension and batch stride multiples of 8), 32-bit lane offsets inside a slab.
+    const bool ak = d.layout_a == GEMM_ROW_MAJOR, bk = d.layout_b == GEMM_COL_MAJOR;
+    if ((ak && bk) || d.layout_c != GEMM_ROW_MAJOR) return false;
+    if ((ak ? d.K : d.M) % 8 || (bk ? d.K : d.N) % 8 || d.lda % 8 || d.ldb % 8 || d.stride_a % 8 || d.stride_b % 8)
+      return false;
+    const int64_t kMax = ((int64_t)1 << 31) - 512;
+    if (d.M >= kMax || d.N >= kMax || d.K >= kMax) return false;
+    const int64_t a_rows = ak ? c.bm : c.bk + 1, b_rows = bk ? c.bn : c.bk + 1;
+    if (a_rows * d.lda * 2 >= ((int64_t)1 << 32) || b_rows * d.ldb * 2 >= ((int64_t)1 << 32)) return false;
+    if (c.persist && (d.K % c.bk != 0 || d.K < 2 * c.bk)) return false;
+    const int64_t tiles = ((d.M + c.bm - 1) / c.bm) * ((d.N + c.bn - 1) / c.bn);
+    return (c.persist ? tiles * d.batch : tiles) < ((int64_t)1 << 31);
+  }
   // The MFMA and skinny kernels take K-contiguous A and B, row-major C, and move
   // 16-byte pieces: every row start must be 16-byte aligned.
   if (d.layout_a != GEMM_ROW_MAJOR || d.layout_b != GEMM_COL_MAJOR || d.layout_c != GEMM_ROW_MAJOR)
@@ -405,7 +449,7 @@ double mfma_cost(const Config& c, int64_t M, int64_t N, int64_t K, int64_t batch
   double eff = area >= 256 * 256 ? 1.0 : (area >= 256 * 192 ? 0.88 : (area >= 256 * 128 ? 0.75 : 0.84));
   // the 16x16x32 kernels: about a tenth faster per FLOP than the 32x32x16 ones at the same tile shape
   // (8192^3: 732 against 800 us); of the two 256x256 shapes the eight-wave one goes first
-  if (!std::strncmp(c.name, "mfma16_", 7)) eff *= c.threads == 256 && area >= 256 * 256 ? 1.08 : 1.10;
+  if (!std::strncmp(c.name, "mfma16", 6)) eff *= c.threads == 256 && area >= 256 * 256 ? 1.08 : 1.10;
   const double tiles = (double)((M + c.bm - 1) / c.bm) * (double)((N + c.bn - 1) / c.bn) * (double)batch;
   const double rounds = (double)(int64_t)((tiles + num_cus() * per_cu - 1) / (num_cus() * per_cu));
   // workgroups that actually share a CU (a lone workgroup runs about per_cu times faster)
@@ -418,7 +462,7 @@ int best_mfma(const gemm_desc_t& d, double* cost_out) {
   double best_cost = 0;
   for (int i = 0; i < kNumConfigs; ++i) {
     const Config& c = kConfigs[i];
-    if (c.kind != KIND_MFMA || !applicable(c, d)) continue;
+    if ((c.kind != KIND_MFMA && c.kind != KIND_MFMA_T) || !applicable(c, d)) continue;
     const double cost = mfma_cost(c, d.M, d.N, d.K, d.batch);
     if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
   }
@@ -451,6 +495,31 @@ int64_t split_columns(const gemm_desc_t& d, int big, double single_cost) {
   return split_cost < 0.93 * single_cost ? n_first : 0;
 }
 
+// The choice among the general kernels (fp32 operands, or layouts / leading dimensions / pointers the tiled
+// kernels do not take).
+int choose_general(const gemm_desc_t& d) {
+  //   * fp32, at most four 16x16 tiles per CU: 16x16 tiles with K split over the waves of a workgroup
+  //     (256^3: 5 us against 11 us for the next choice; 512^3: 11 to 12 against 19 us);
+  //   * very few 32x32 tiles (16-bit operands in layouts the tiled kernels do not take): the vector-ALU
+  //     kernel with 32x32 tiles and the long K step;
+  //   * fp32 in float4 groups: the fp32-MFMA kernel with double-buffered slabs, 128x128 tiles from two
+  //     tiles per CU on (4096^3: 1.13 to 1.18 ms = 116 to 122 TFLOP/s; the general kernel needs 1.47 ms),
+  //     64x64 tiles below (2048^3: 184 us, 1024^3: 42 us; general kernel 219 / 53 us);
+  //   * otherwise the general fp32-MFMA kernel: 64x64 tiles until there are four 128x128 tiles per CU.
+  const double tiles32 = (double)((d.M + 31) / 32) * (double)((d.N + 31) / 32) * d.batch;
+  const double tiles128 = (double)((d.M + 127) / 128) * (double)((d.N + 127) / 128) * d.batch;
+  if (tiles32 <= 1.0 * num_cus()) {             // (tiles32 = a quarter of the 16x16 tiles)
+    const int i = find_config("f32small_16x16x256");
+    if (i >= 0 && applicable(kConfigs[i], d)) return i;
+  }
+  if (tiles32 <= 2.0 * num_cus()) return find_config("simt_32x32x64");
+  {                                             // fp32 in float4 groups: 128x128 tiles from two per CU on
+    const int i = find_config(tiles128 >= 2.0 * num_cus() ? "f32mfma_128x128x32" : "f32mfma_64x64x32");
+    if (i >= 0 && applicable(kConfigs[i], d)) return i;
+  }
+  return find_config(tiles128 >= 4.0 * num_cus() ? "general_mfma32_128x128x16" : "general_mfma32_64x64x16");
+}
+
 // Built-in choice.  MFMA tile: cheapest under a small cost model (wave quantisation over
 // the 256 CUs, measured efficiency per tile shape); first entry of the table on ties.
 int choose(const gemm_desc_t& d) {
@@ -479,27 +548,7 @@ int choose(const gemm_desc_t& d) {
   }
   const int best = best_mfma(d, nullptr);
   if (best >= 0) return best;
-  // general kernels (fp32 operands, or layouts / leading dimensions the tiled kernels do not take).
-  //   * fp32, at most four 16x16 tiles per CU: 16x16 tiles with K split over the waves of a workgroup
-  //     (256^3: 5 us against 11 us for the next choice; 512^3: 11 to 12 against 19 us);
-  //   * very few 32x32 tiles (16-bit operands in layouts the tiled kernels do not take): the vector-ALU
-  //     kernel with 32x32 tiles and the long K step;
-  //   * fp32 in float4 groups: the fp32-MFMA kernel with double-buffered slabs, 128x128 tiles from two
-  //     tiles per CU on (4096^3: 1.13 to 1.18 ms = 116 to 122 TFLOP/s; the general kernel needs 1.47 ms),
-  //     64x64 tiles below (2048^3: 184 us, 1024^3: 42 us; general kernel 219 / 53 us);
-  //   * otherwise the general fp32-MFMA kernel: 64x64 tiles until there are four 128x128 tiles per CU.
-  const double tiles32 = (double)((d.M + 31) / 32) * (double)((d.N + 31) / 32) * d.batch;
-  const double tiles128 = (double)((d.M + 127) / 128) * (double)((d.N + 127) / 128) * d.batch;
-  if (tiles32 <= 1.0 * num_cus()) {             // (tiles32 = a quarter of the 16x16 tiles)
-    const int i = find_config("f32small_16x16x256");
-    if (i >= 0 && applicable(kConfigs[i], d)) return i;
-  }
-  if (tiles32 <= 2.0 * num_cus()) return find_config("simt_32x32x64");
-  {                                             // fp32 in float4 groups: 128x128 tiles from two per CU on
-    const int i = find_config(tiles128 >= 2.0 * num_cus() ? "f32mfma_128x128x32" : "f32mfma_64x64x32");
-    if (i >= 0 && applicable(kConfigs[i], d)) return i;
-  }
-  return find_config(tiles128 >= 4.0 * num_cus() ? "general_mfma32_128x128x16" : "general_mfma32_64x64x16");
+  return choose_general(d);
 }
 
 int fill_launch_shape(gemm_plan& pl) {
@@ -512,7 +561,7 @@ int fill_launch_shape(gemm_plan& pl) {
     const int64_t gx = (d.N + c.bn - 1) / c.bn, gy = (d.M + c.bm - 1) / c.bm;
     if (gy > 65535) return GEMM_ERR_BAD_DIM;   // grid.y / grid.z limits
     pl.grid = dim3((unsigned)gx, (unsigned)gy, (unsigned)d.batch);
-  } else if (c.kind == KIND_MFMA) {
+  } else if (c.kind == KIND_MFMA || c.kind == KIND_MFMA_T) {
     const int64_t tm = (d.M + c.bm - 1) / c.bm, tn = (d.N + c.bn - 1) / c.bn;
     int64_t wgs = tm * tn;
     if (c.persist) {
@@ -581,6 +630,7 @@ static int create_resolved(const gemm_desc_t& d, int config, bool allow_two_laun
   pl->cfg_index = config;
   pl->tail = nullptr;
   pl->tail_off_b = pl->tail_off_c = pl->tail_off_bias = 0;
+  pl->fallback = nullptr;
   pl->splits = 0;
   pl->inner = nullptr;
   pl->d_user = d;
@@ -588,12 +638,18 @@ static int create_resolved(const gemm_desc_t& d, int config, bool allow_two_laun
   pl->built_in = auto_choice && allow_two_launches;   // (second launches and split-K inner plans are parts, not plans)
   pl->tune_state = 0;
   pl->tuned = nullptr;
-  if (auto_choice && allow_two_launches && kConfigs[config].kind == KIND_MFMA) {
+  const Kind kind = kConfigs[config].kind;
+  if (kind == KIND_MFMA_T) {
+    // pointers need element alignment only, as for every problem these layouts were ever planned for
+    const int rc = create_resolved(d, choose_general(d), false, &pl->fallback);
+    if (rc != GEMM_OK) { gemm_destroy(pl); return rc; }
+  }
+  if (auto_choice && allow_two_launches && (kind == KIND_MFMA || kind == KIND_MFMA_T)) {
     double single_cost = 0;
     best_mfma(d, &single_cost);
     int big = -1;                                   // the first 256x256 shape of the table
     for (int i = 0; i < kNumConfigs && big < 0; ++i)
-      if (kConfigs[i].kind == KIND_MFMA && kConfigs[i].bm == 256 && kConfigs[i].bn == 256 &&
+      if (kConfigs[i].kind == kind && kConfigs[i].bm == 256 && kConfigs[i].bn == 256 &&
           applicable(kConfigs[i], d))
         big = i;
     const int64_t n_first = split_columns(d, big, single_cost);
@@ -601,13 +657,13 @@ static int create_resolved(const gemm_desc_t& d, int config, bool allow_two_laun
       config = big;
       pl->cfg = &kConfigs[config];
       pl->cfg_index = config;
-      // second launch: columns n_first .. N-1 (rows of the N x K weight matrix, columns of C)
+      // second launch: columns n_first .. N-1 (rows of the N x K weight matrix or columns of a K x N one, columns of C)
       gemm_desc_t rest = d;
       rest.N = d.N - n_first;
       gemm_plan_t* tail = nullptr;
       if (create_resolved(rest, best_mfma(rest, nullptr), false, &tail) == GEMM_OK) {
         pl->tail = tail;
-        pl->tail_off_b = n_first * d.ldb;
+        pl->tail_off_b = d.layout_b == GEMM_COL_MAJOR ? n_first * d.ldb : n_first;
         pl->tail_off_c = n_first;
         pl->tail_off_bias = n_first;
         pl->d.N = n_first;
@@ -793,6 +849,7 @@ static int run_plan(const gemm_plan_t* plan, const void* A, const void* B, void*
                     void* hip_stream) {
   if (!plan || !A || !B || !C) return GEMM_ERR_NULL;
   if (plan->inner) return GEMM_ERR_WORKSPACE;
+  if (plan->fallback && (((uintptr_t)A | (uintptr_t)B) & 15)) return run_plan(plan->fallback, A, B, C, bias, hip_stream);
   const gemm_desc_t& d = plan->d;
   if (epilogue_has_bias(d.epilogue) != (bias != nullptr)) return GEMM_ERR_NULL;
   // The tiled 16-bit kernels move 16-byte pieces; the general kernel only needs
@@ -1008,7 +1065,8 @@ int gemm_destroy(gemm_plan_t* plan) {
     if (plan->inner) {                 // a split-K plan is a copy of its inner plan's launch data
       gemm_destroy(plan->inner);
     } else {
-      delete plan->tail;
+      if (plan->tail) gemm_destroy(plan->tail);
+      if (plan->fallback) gemm_destroy(plan->fallback);
       if (plan->built_in && plan->tuned) gemm_destroy(plan->tuned);
     }
   }
@@ -1051,17 +1109,19 @@ int gemm_plan_info(const gemm_plan_t* plan, char* buf, size_t n) {
                          plan->splits, c.name, c.bm, c.bn, c.bk, plan->grid.x, plan->grid.y, plan->grid.z,
                          plan->block.x, c.lds_bytes, gemm_workspace_bytes(plan));
   }
+  char other[96] = "";
+  if (plan->fallback) std::snprintf(other, sizeof(other), " unaligned A or B: kernel=%s", plan->fallback->cfg->name);
   if (plan->tail) {
     const Config& t = *plan->tail->cfg;
     return std::snprintf(buf, n, "kernel=%s tile=%dx%dx%d grid=%u,%u,%u block=%u lds=%d columns=0..%lld "
-                         "+ kernel=%s grid=%u,%u,%u columns=%lld..", c.name, c.bm, c.bn, c.bk,
+                         "+ kernel=%s grid=%u,%u,%u columns=%lld..%s", c.name, c.bm, c.bn, c.bk,
                          plan->grid.x, plan->grid.y, plan->grid.z, plan->block.x, c.lds_bytes,
                          (long long)plan->d.N - 1, t.name, plan->tail->grid.x, plan->tail->grid.y,
-                         plan->tail->grid.z, (long long)plan->d.N);
+                         plan->tail->grid.z, (long long)plan->d.N, other);
   }
-  return std::snprintf(buf, n, "kernel=%s tile=%dx%dx%d grid=%u,%u,%u block=%u lds=%d", c.name,
+  return std::snprintf(buf, n, "kernel=%s tile=%dx%dx%d grid=%u,%u,%u block=%u lds=%d%s", c.name,
                        c.bm, c.bn, c.bk, plan->grid.x, plan->grid.y, plan->grid.z, plan->block.x,
-                       c.lds_bytes);
+                       c.lds_bytes, other);
 }
 
 }  // extern "C"

@@ -2,7 +2,7 @@
 // fp32 accumulate.
 //
 //   C = act(A . B + bias),  A row-major (K contiguous), B column-major (K contiguous: the
-//   "weight" matrix stored N x K), C row-major.
+//   "weight" matrix stored N x K), C row-major; also A column-major and / or B row-major.
 //
 // Same data path as mfma_kernel.hpp (direct-to-LDS slabs of 64 columns of K, two stages,
 // XOR-swizzled 16-byte chunks, 16-byte fragment reads, accumulators in AccVGPRs, hand-placed
@@ -51,11 +51,13 @@ __device__ __forceinline__ int swz16(int r) { return (r >> 1) & 7; }
 // for the next sub-step are requested, one behind each of its first MFMAs: MA row fragments
 // and, when the next sub-step begins a new k-step, the NT column fragments too (WITH_B).
 // Its own MFMAs run in the order in which their operands were requested one sub-step earlier.
-template <int MA, int NT, bool WITH_B>
+// RA, RB: LDS reads per row / column fragment (one 16-byte read, or two 8-byte transposing ones).
+template <int MA, int NT, bool WITH_B, int RA, int RB>
 struct SubOrder {
-  static constexpr int kReads = MA + (WITH_B ? NT : 0), kMfma = MA * NT;
+  static constexpr int kReads = MA * RA + (WITH_B ? NT * RB : 0), kMfma = MA * NT;
+  static constexpr int kPerMfma = (kReads + kMfma - 1) / kMfma;      // reads requested behind one MFMA
   struct Tables {
-    int r_isb[kReads], r_idx[kReads];
+    int r_isb[kReads], r_idx[kReads], r_part[kReads];
     int mm[kMfma], nn[kMfma];
     int need[kMfma];        // request position of the later of MFMA i's operands (-1: resident)
   };
@@ -64,19 +66,21 @@ struct SubOrder {
     int pos_a[MA] = {}, pos_b[NT] = {};
     for (int n = 0; n < NT; ++n) pos_b[n] = -1;
     int c = 0;
+    auto ask_a = [&](int i) { for (int q = 0; q < RA; ++q) { t.r_isb[c] = 0; t.r_idx[c] = i; t.r_part[c] = q; pos_a[i] = c++; } };
+    auto ask_b = [&](int i) { for (int q = 0; q < RB; ++q) { t.r_isb[c] = 1; t.r_idx[c] = i; t.r_part[c] = q; pos_b[i] = c++; } };
     if (WITH_B) {
-      // a0 b0 b1 a1 b2 a2 ...: the first MFMAs can start after two reads
+      // a0 b0 b1 a1 b2 a2 ...: the first MFMAs can start after two fragments
       for (int i = 0; i < (MA > NT ? MA : NT); ++i) {
         if (i == 0) {
-          t.r_isb[c] = 0; t.r_idx[c] = 0; pos_a[0] = c++;
-          t.r_isb[c] = 1; t.r_idx[c] = 0; pos_b[0] = c++;
+          ask_a(0);
+          ask_b(0);
         } else {
-          if (i < NT) { t.r_isb[c] = 1; t.r_idx[c] = i; pos_b[i] = c++; }
-          if (i < MA) { t.r_isb[c] = 0; t.r_idx[c] = i; pos_a[i] = c++; }
+          if (i < NT) ask_b(i);
+          if (i < MA) ask_a(i);
         }
       }
     } else {
-      for (int i = 0; i < MA; ++i) { t.r_isb[c] = 0; t.r_idx[c] = i; pos_a[i] = c++; }
+      for (int i = 0; i < MA; ++i) ask_a(i);
     }
     bool used[kMfma] = {};
     for (int i = 0; i < kMfma; ++i) {
@@ -119,21 +123,63 @@ struct Mfma16Tile {
   static_assert(BM % (RPI * kWaves) == 0 && BN % (RPI * kWaves) == 0, "slab rows must divide over waves");
   static_assert(WTM % 16 == 0 && WTN % 16 == 0 && MT % G == 0, "wave block in whole sub-steps");
   static_assert(NSUB % 2 == 0, "the row-fragment double buffer alternates per sub-step");
-  static_assert(MA * NT >= MA + NT, "a sub-step issues one fragment read behind each MFMA");
+  static_assert(MA * NT >= MA + NT, "a sub-step issues one or two fragment reads behind each MFMA");
   static_assert(LDS_BYTES + EPI_BYTES <= 160 * 1024, "LDS budget");
 };
+
+// The fragment registers of one operand: one 16-byte LDS read (K contiguous in memory) or two 8-byte
+// transposing reads, each four of the lane's eight values of K (K strided).
+template <int PARTS> struct FragReg;
+template <> struct FragReg<1> {
+  u32x4_t v;
+  __device__ __forceinline__ u32x4_t get() const { return v; }
+};
+template <> struct FragReg<2> {
+  u32x2_t h[2];
+  __device__ __forceinline__ u32x4_t get() const { return __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3); }
+};
+// Four 16-bit values per lane out of a 4 x 16 block per 16 lanes, transposed on the way: lane i of the 16
+// passes the address of values 4 (i % 4) .. +3 of row i / 4 and receives value i of the rows 0 .. 3.
+template <typename F>
+__device__ __forceinline__ void lds_read_tr16(F& dst, uint32_t addr, int offset) {
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(offset) : "memory");
+}
 
 // T: operand type; TO: the 16-bit output type (outputs may also be fp32: MfmaArgs::c_f32).
 // PERSIST: a workgroup walks over several tiles (tile ids blockIdx.x, blockIdx.x + gridDim.x,
 // ...) as one software pipeline: the slabs of the next tile are requested while the last slabs
 // of the current one are multiplied, and land while its epilogue runs, which stages C through an
 // LDS region of its own.  Needs K to be a whole number of slabs, at least two.
-template <typename T, typename TO, int BM, int BN, int WM, int WN, int G, bool PERSIST>
+// A_KF, B_KF: K is the contiguous index of A / of B in memory (A row-major, B column-major).  An operand
+// whose rows (A) or columns (B) are contiguous instead keeps that order in LDS: its slab is stored as
+// 1 KB blocks of 8 values of K x 64 rows (block = 8 * (row / 64) + k / 8, 128 bytes per value of K), so that
+// the direct-to-LDS loads still read whole 128-byte lines, and the fragments are read with
+// ds_read_b64_tr_b16, which transposes 4 x 16 blocks on the way to the registers.  The 32-byte piece
+// (16 rows) t of value k sits at piece t ^ key(k), key = bit 1 of k and (as bit 1) bit 3 of k: a read touches
+// 4 values of K per 16 lanes, whose 128-byte rows alternate between the halves of the banks, and the key
+// spreads the remaining factor of 4 over the pieces of a half.
+// Bound like the K-contiguous variant (power and matrix pipes: the same bytes, loads and MFMAs per slab, twice
+// the LDS read instructions at half the width): 8192^3 bf16 takes 721 us with B row-major, 726 us with A
+// column-major as well, 709 - 726 us K-contiguous on the same box.  These layouts used to run on the fp32
+// matrix-core instruction: 6144 x 4096 x 3001 with both operands strided 2475 us, here 133 us.
+template <typename T, typename TO, int BM, int BN, int WM, int WN, int G, bool PERSIST, bool A_KF = true, bool B_KF = true>
 __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   typedef Mfma16Tile<T, BM, BN, WM, WN, G> Cfg;
   constexpr int MT = Cfg::MT, NT = Cfg::NT, MA = Cfg::MA, CPR = Cfg::CPR, RPI = Cfg::RPI;
   constexpr int ROWB = Cfg::ROWB, BK = Cfg::BK, KK = Cfg::KK, NSUB = Cfg::NSUB;
   constexpr bool kTwoPerSimd = Cfg::kWaves > 4;          // two waves share a SIMD: alternate by priority
+  constexpr int RA = A_KF ? 1 : 2, RB = B_KF ? 1 : 2;    // LDS reads per fragment
+  static_assert((A_KF || (BM % 64 == 0 && Cfg::WTM % 64 == 0)) && (B_KF || (BN % 64 == 0 && Cfg::WTN % 64 == 0)) && BK == 64,
+                "K-strided operands are stored in blocks of 64 rows x 8 values of K");
+  // bytes from one slab of an operand to the next
+  const int64_t a_step = A_KF ? (int64_t)ROWB : p.lda * (int64_t)(BK * 2);
+  const int64_t b_step = B_KF ? (int64_t)ROWB : p.ldb * (int64_t)(BK * 2);
+  // K-strided operand: what lane `ln` of load `id` of a slab fetches (8 rows from `row` on of value `k`)
+  auto strided_unit = [](int id, int ln, int& k, int& row) __attribute__((always_inline)) {
+    const int kg = id & 7, j8 = ln >> 3, key = ((j8 >> 1) & 1) | ((kg & 1) << 1);
+    k = kg * 8 + j8;
+    row = (id >> 3) * 64 + ((ln & 7) ^ (key * 2)) * 8;
+  };
 
   __shared__ __attribute__((aligned(1024))) unsigned char smem[Cfg::LDS_BYTES + (PERSIST ? Cfg::EPI_BYTES : 0)];
 
@@ -171,10 +217,16 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     const int lb = PERSIST ? lid / n_tiles : batch;          // the problem this tile belongs to
     tile_coords(p, PERSIST ? lid - lb * n_tiles : vid, n_tiles, tm, tn);
     const int r0 = tm * BM, c0 = tn * BN;
-    ld_a = (const char*)((const T*)p.A + (int64_t)lb * p.stride_a + (int64_t)r0 * p.lda) + (int64_t)kt * ROWB;
-    ld_b = (const char*)((const T*)p.B + (int64_t)lb * p.stride_b + (int64_t)c0 * p.ldb) + (int64_t)kt * ROWB;
+    ld_a = (const char*)((const T*)p.A + (int64_t)lb * p.stride_a + (A_KF ? (int64_t)r0 * p.lda : (int64_t)r0)) + (int64_t)kt * a_step;
+    ld_b = (const char*)((const T*)p.B + (int64_t)lb * p.stride_b + (B_KF ? (int64_t)c0 * p.ldb : (int64_t)c0)) + (int64_t)kt * b_step;
 #pragma unroll
     for (int q = 0; q < Cfg::A_LOADS; ++q) {
+      if constexpr (!A_KF) {                      // (M is a multiple of 8 here: a unit of 8 rows is never split)
+        int k, row;
+        strided_unit(wave * Cfg::A_LOADS + q, ln, k, row);
+        a_off[q] = (uint32_t)(((int64_t)k * p.lda + min(row, p.M - 8 - r0)) * 2);
+        continue;
+      }
       const int r = (wave * Cfg::A_LOADS + q) * RPI + ln / CPR;
       const int c = (ln % CPR) ^ swz16(r);
       const int rr = min(r, p.M - 1 - r0);
@@ -182,6 +234,12 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     }
 #pragma unroll
     for (int q = 0; q < Cfg::B_LOADS; ++q) {
+      if constexpr (!B_KF) {
+        int k, row;
+        strided_unit(wave * Cfg::B_LOADS + q, ln, k, row);
+        b_off[q] = (uint32_t)(((int64_t)k * p.ldb + min(row, p.N - 8 - c0)) * 2);
+        continue;
+      }
       const int r = (wave * Cfg::B_LOADS + q) * RPI + ln / CPR;
       const int c = (ln % CPR) ^ swz16(r);
       const int rr = min(r, p.N - 1 - c0);
@@ -214,7 +272,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     return io;
   };
   auto slab_io = [&](int kt, int st) __attribute__((always_inline)) {
-    return slab_io_at(Ab + (int64_t)kt * ROWB, Bb + (int64_t)kt * ROWB, st);
+    return slab_io_at(Ab + (int64_t)kt * a_step, Bb + (int64_t)kt * b_step, st);
   };
   // One direct-to-LDS load (scalar base + 32-bit lane offset; M0 = LDS destination of the wave,
   // lane l lands at M0 + 16*l): q < A_LOADS fills the A slab, the rest the B slab.  M0 is written
@@ -232,27 +290,29 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   };
 
   // K tail: chunks past K must read as zero, which a direct-to-LDS load cannot do, so that one
-  // slab goes through registers.  (K is a multiple of 8: chunks are never split.)
+  // slab goes through registers.  (K is a multiple of 8 where an operand's K is contiguous: chunks are never split.)
   auto issue_loads_tail = [&](int kt, int stage) __attribute__((always_inline)) {
     const int kvalid = p.K - kt * BK;
-    const char* ga = Ab + (int64_t)kt * ROWB;
-    const char* gb = Bb + (int64_t)kt * ROWB;
+    const char* ga = Ab + (int64_t)kt * a_step;
+    const char* gb = Bb + (int64_t)kt * b_step;
     unsigned char* sa = smem + stage * Cfg::STAGE_BYTES + wave * (Cfg::A_LOADS * 1024);
     unsigned char* sb = smem + stage * Cfg::STAGE_BYTES + Cfg::A_BYTES + wave * (Cfg::B_LOADS * 1024);
 #pragma unroll
     for (int q = 0; q < Cfg::A_LOADS; ++q) {
       const int r = (wave * Cfg::A_LOADS + q) * RPI + lane / CPR;
-      const int c = (lane % CPR) ^ swz16(r);
+      int k = ((lane % CPR) ^ swz16(r)) * 8, row = 0;            // the piece's first value of K
+      if constexpr (!A_KF) strided_unit(wave * Cfg::A_LOADS + q, lane, k, row);
       u32x4_t v = {0u, 0u, 0u, 0u};
-      if (c * 8 < kvalid) v = *(const u32x4_t*)(ga + a_off[q]);
+      if (k < kvalid) v = *(const u32x4_t*)(ga + a_off[q]);
       *(u32x4_t*)(sa + q * 1024 + lane * 16) = v;
     }
 #pragma unroll
     for (int q = 0; q < Cfg::B_LOADS; ++q) {
       const int r = (wave * Cfg::B_LOADS + q) * RPI + lane / CPR;
-      const int c = (lane % CPR) ^ swz16(r);
+      int k = ((lane % CPR) ^ swz16(r)) * 8, row = 0;            // the piece's first value of K
+      if constexpr (!B_KF) strided_unit(wave * Cfg::B_LOADS + q, lane, k, row);
       u32x4_t v = {0u, 0u, 0u, 0u};
-      if (c * 8 < kvalid) v = *(const u32x4_t*)(gb + b_off[q]);
+      if (k < kvalid) v = *(const u32x4_t*)(gb + b_off[q]);
       *(u32x4_t*)(sb + q * 1024 + lane * 16) = v;
     }
   };
@@ -262,7 +322,9 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   // step's four.  Fragment m of the wave is 16*m rows further on: a constant offset.  The
   // address registers point into the stage being read and move to the other stage at each
   // hand-over (one vector add each), so a fragment read needs no address arithmetic.
-  uint32_t a_rd[KK], b_rd[KK];
+  // (K-strided operand: one register for each of the four 32-byte pieces of a 64-row block, see A_KF.)
+  constexpr int NA = A_KF ? KK : 4, NB = B_KF ? KK : 4;
+  uint32_t a_rd[NA], b_rd[NB];
   int rd_delta;                                  // to the other stage (alternates in sign)
   // point the address registers into stage `st` (`ln`: the lane id, see load_tile)
   auto set_read_stage = [&](int st, int ln) __attribute__((always_inline)) {
@@ -272,15 +334,26 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
       const int c = kk * 4 + fo;
-      a_rd[kk] = lds_base + st * Cfg::STAGE_BYTES + a_row * ROWB + ((c ^ swz16(a_row)) * 16);
-      b_rd[kk] = lds_base + st * Cfg::STAGE_BYTES + Cfg::A_BYTES + b_row * ROWB + ((c ^ swz16(b_row)) * 16);
+      if constexpr (A_KF) a_rd[kk] = lds_base + st * Cfg::STAGE_BYTES + a_row * ROWB + ((c ^ swz16(a_row)) * 16);
+      if constexpr (B_KF) b_rd[kk] = lds_base + st * Cfg::STAGE_BYTES + Cfg::A_BYTES + b_row * ROWB + ((c ^ swz16(b_row)) * 16);
+    }
+    if constexpr (!A_KF || !B_KF) {
+      const int j = fr >> 2, key = ((j >> 1) & 1) | ((fo & 1) << 1);
+      const int at = lds_base + st * Cfg::STAGE_BYTES + fo * 1024 + j * 128 + (fr & 3) * 8;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        if constexpr (!A_KF) a_rd[x] = at + (wm * Cfg::WTM / 64) * 8192 + ((x ^ key) * 32);
+        if constexpr (!B_KF) b_rd[x] = at + Cfg::A_BYTES + (wn * Cfg::WTN / 64) * 8192 + ((x ^ key) * 32);
+      }
     }
     rd_delta = st ? -Cfg::STAGE_BYTES : Cfg::STAGE_BYTES;
   };
   set_read_stage(0, lane);
   auto flip_read_stage = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) { a_rd[kk] += rd_delta; b_rd[kk] += rd_delta; }
+    for (int x = 0; x < NA; ++x) a_rd[x] += rd_delta;
+#pragma unroll
+    for (int x = 0; x < NB; ++x) b_rd[x] += rd_delta;
     rd_delta = -rd_delta;
   };
 
@@ -293,21 +366,28 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       for (int r = 0; r < 4; ++r) acc[m][n][r] = 0.0f;
 
   // Fragment registers: row fragments double-buffered per sub-step, column fragments per k-step.
-  u32x4_t af[2][MA], bf[2][NT];
+  FragReg<RA> af[2][MA];
+  FragReg<RB> bf[2][NT];
 
   // Sub-step u of a slab: k-step u / G, row group u % G.
   // the i-th read of the requests made for sub-step `u` (from the stage the address registers point into)
   auto read_one = [&](auto u_c, int i) __attribute__((always_inline)) {
     constexpr int u = decltype(u_c)::value;
     constexpr int kk = u / G, g = u % G;
-    typedef SubOrder<MA, NT, g == 0> Ord;
-    const int idx = Ord::t.r_idx[i];
-    if (Ord::t.r_isb[i]) lds_read_b128(bf[kk & 1][idx], b_rd[kk], idx * (16 * ROWB));
-    else lds_read_b128(af[u & 1][idx], a_rd[kk], (g * MA + idx) * (16 * ROWB));
+    typedef SubOrder<MA, NT, g == 0, RA, RB> Ord;
+    const int idx = Ord::t.r_idx[i], part = Ord::t.r_part[i];
+    if (Ord::t.r_isb[i]) {
+      if constexpr (B_KF) lds_read_b128(bf[kk & 1][idx].v, b_rd[kk], idx * (16 * ROWB));
+      else lds_read_tr16(bf[kk & 1][idx].h[part], b_rd[idx & 3], (idx >> 2) * 8192 + kk * 4096 + part * 512);
+    } else {
+      const int m = g * MA + idx;
+      if constexpr (A_KF) lds_read_b128(af[u & 1][idx].v, a_rd[kk], m * (16 * ROWB));
+      else lds_read_tr16(af[u & 1][idx].h[part], a_rd[m & 3], (m >> 2) * 8192 + kk * 4096 + part * 512);
+    }
   };
   auto read_all = [&](auto u_c) __attribute__((always_inline)) {
     constexpr int u = decltype(u_c)::value;
-    typedef SubOrder<MA, NT, (u % G) == 0> Ord;
+    typedef SubOrder<MA, NT, (u % G) == 0, RA, RB> Ord;
 #pragma unroll
     for (int i = 0; i < Ord::kReads; ++i) read_one(u_c, i);
   };
@@ -321,21 +401,24 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     constexpr int u = decltype(u_c)::value;
     constexpr int kk = u / G, g = u % G;
     constexpr int un = (u + 1) % NSUB;                    // the sub-step the reads are for
-    typedef SubOrder<MA, NT, g == 0> Ord;                 // how this sub-step's operands were requested
-    typedef SubOrder<MA, NT, (un % G) == 0> OrdN;         // this sub-step's own requests
+    typedef SubOrder<MA, NT, g == 0, RA, RB> Ord;         // how this sub-step's operands were requested
+    typedef SubOrder<MA, NT, (un % G) == 0, RA, RB> OrdN; // this sub-step's own requests
     const int nq = q1 - q0;
     int waited = -1;
 #pragma unroll
     for (int i = 0; i < Ord::kMfma; ++i) {
       const int m = Ord::t.mm[i], n = Ord::t.nn[i];
       if (Ord::t.need[i] > waited) {
-        // since the needed request: the rest of that sub-step's requests and min(i, kReads) of ours
-        const int after = (Ord::kReads - 1 - Ord::t.need[i]) + (reads ? (i < OrdN::kReads ? i : OrdN::kReads) : 0);
+        // since the needed request: the rest of that sub-step's requests and those of ours so far
+        const int ours = i * OrdN::kPerMfma;
+        const int after = (Ord::kReads - 1 - Ord::t.need[i]) + (reads ? (ours < OrdN::kReads ? ours : OrdN::kReads) : 0);
         wait_lgkmcnt_dyn(after);                 // (the counter holds 15 at most: larger values wait for 15)
         waited = Ord::t.need[i];
       }
-      Frag16<T>::mfma(bf[kk & 1][n], af[u & 1][m], acc[g * MA + m][n]);
-      if (reads && i < OrdN::kReads) read_one(std::integral_constant<int, un>(), i);
+      Frag16<T>::mfma(bf[kk & 1][n].get(), af[u & 1][m].get(), acc[g * MA + m][n]);
+#pragma unroll
+      for (int r = i * OrdN::kPerMfma; r < (i + 1) * OrdN::kPerMfma; ++r)
+        if (reads && r < OrdN::kReads) read_one(std::integral_constant<int, un>(), r);
 #pragma unroll
       for (int j = 0; j < nq; ++j)
         if ((int)((j + 0.5f) * Ord::kMfma / nq) == i) {
@@ -746,7 +829,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, z));
   };
   auto next_slab = [&]() __attribute__((always_inline)) {
-    ld_a += ROWB; ld_b += ROWB;
+    ld_a += a_step; ld_b += b_step;
     if (++ld_t == T_full) {
       ld_t = 0;
       ld_vid += gridDim.x;

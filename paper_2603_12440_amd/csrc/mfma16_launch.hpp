@@ -8,9 +8,8 @@
 
 namespace mi355gemm {
 
-template <typename T, typename TO, int BM, int BN, int WM, int WN, int G, bool PERSIST>
-hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void* C,
-                         const void* bias, hipStream_t s) {
+template <int BM, int BN>
+MfmaArgs mfma16_args(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias) {
   const gemm_desc_t& d = pl.d;
   MfmaArgs a;
   a.A = A; a.B = B; a.C = C; a.bias = (const float*)bias;
@@ -28,6 +27,15 @@ hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void
   a.xcd_remap = pl.xcd_remap;
   a.c_cached = pl.c_cached;
   a.batches = (int)d.batch;
+  return a;
+}
+
+// A_KF, B_KF: K is the contiguous index of A / B
+template <typename T, typename TO, int BM, int BN, int WM, int WN, int G, bool PERSIST, bool A_KF = true, bool B_KF = true>
+hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void* C,
+                         const void* bias, hipStream_t s) {
+  const gemm_desc_t& d = pl.d;
+  const MfmaArgs a = mfma16_args<BM, BN>(pl, A, B, C, bias);
   if constexpr (PERSIST) {
     // The persistent kernel only has the staged output routes (whole-line stores): C rows that are
     // not 16-byte aligned run one tile per workgroup instead.
@@ -35,11 +43,11 @@ hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void
     const bool staged = d.ldc % unit == 0 && d.stride_c % unit == 0 && ((uintptr_t)C & 15) == 0;
     if (!staged) {
       const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)d.batch, 1);
-      mfma16_gemm_kernel<T, TO, BM, BN, WM, WN, G, false><<<grid, pl.block, 0, s>>>(a);
+      mfma16_gemm_kernel<T, TO, BM, BN, WM, WN, G, false, A_KF, B_KF><<<grid, pl.block, 0, s>>>(a);
       return hipGetLastError();
     }
   }
-  mfma16_gemm_kernel<T, TO, BM, BN, WM, WN, G, PERSIST><<<pl.grid, pl.block, 0, s>>>(a);
+  mfma16_gemm_kernel<T, TO, BM, BN, WM, WN, G, PERSIST, A_KF, B_KF><<<pl.grid, pl.block, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -52,6 +60,20 @@ hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void
 #define MI355GEMM_MFMA16P_TILES(X) \
   X(256, 256, 2, 4, 2, true)       \
   X(128, 128, 2, 2, 2, true)
+
+// The same for operands whose K is not contiguous, one translation unit per operand type and layout pair
+// (mfma16t_*_inst.hip); the table's entry picks the pair from the plan's layouts.
+#define MI355GEMM_MFMA16T_TILES(X) \
+  X(256, 256, 2, 4, 2, false)      \
+  X(256, 256, 2, 4, 2, true)       \
+  X(128, 128, 2, 2, 2, false)      \
+  X(128, 128, 2, 2, 2, true)
+#define MI355GEMM_MFMA16T_DECLARE(T, BM, BN, WM, WN, G, P, AK, BK)                            \
+  extern template hipError_t launch_mfma16<T, T, BM, BN, WM, WN, G, P, AK, BK>(                \
+      const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
+#define MI355GEMM_MFMA16T_DEFINE(T, BM, BN, WM, WN, G, P, AK, BK)                             \
+  template hipError_t launch_mfma16<T, T, BM, BN, WM, WN, G, P, AK, BK>(                       \
+      const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
 
 #define MI355GEMM_MFMA16_DECLARE(T, TO, BM, BN, WM, WN, G, P)                               \
   extern template hipError_t launch_mfma16<T, TO, BM, BN, WM, WN, G, P>(                      \

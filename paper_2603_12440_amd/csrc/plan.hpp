@@ -11,9 +11,9 @@
 
 namespace mi355gemm {
 
-enum Kind { KIND_SIMT = 0, KIND_MFMA = 1, KIND_SKINNY = 2, KIND_SKINNY_PANEL = 3, KIND_F32_VEC = 4 };
+enum Kind { KIND_SIMT = 0, KIND_MFMA = 1, KIND_SKINNY = 2, KIND_SKINNY_PANEL = 3, KIND_F32_VEC = 4, KIND_MFMA_T = 5 };
 // (KIND_F32_VEC: the general kernels' grid, fp32 operands in 16-byte pieces; KIND_SKINNY: vector ALUs, a wave per row of W; KIND_SKINNY_PANEL: matrix cores, a workgroup per
-// 32-row panel of W)
+// 32-row panel of W; KIND_MFMA_T: the tiled 16-bit kernels for operands whose K is not contiguous)
 
 struct Config;
 
@@ -30,6 +30,8 @@ struct gemm_plan {
   // offsets of its B, C and bias.
   gemm_plan* tail;
   int64_t tail_off_b, tail_off_c, tail_off_bias;
+  // What runs the whole problem when A or B is not 16-byte aligned (KIND_MFMA_T): a plan on the general kernels.
+  gemm_plan* fallback;
   // Split-K: `d` is the caller's problem, `inner` the batched product of the K slices into
   // the fp32 workspace (cfg, grid, ... above are then those of the inner plan, for reporting).
   int splits;

@@ -1,0 +1,50 @@
+"""Which kernel a 16-bit product gets that is not K-contiguous in both operands: decided on the host, no GPU needed."""
+import pytest
+
+import paper_2603_12440_amd as g
+
+
+def info(**kw):
+    p = g.gemm_create(g.GemmDesc(**kw))
+    text = p.info()
+    g.gemm_destroy(p)
+    return text
+
+
+TILED = [dict(M=776, N=1032, K=456, layout_b=g.ROW_MAJOR), dict(M=776, N=1032, K=3001, layout_a=g.COL_MAJOR, layout_b=g.ROW_MAJOR),
+         dict(M=776, N=1033, K=456, layout_a=g.COL_MAJOR), dict(M=777, N=1032, K=456, layout_b=g.ROW_MAJOR, dtype=g.F16),
+         dict(M=776, N=1032, K=456, layout_b=g.ROW_MAJOR, batch=5, ldc=1033, dtype_c=g.F32)]
+GENERAL = [dict(M=776, N=1033, K=456, layout_b=g.ROW_MAJOR), dict(M=776, N=1032, K=457, layout_b=g.ROW_MAJOR),
+           dict(M=777, N=1032, K=456, layout_a=g.COL_MAJOR), dict(M=776, N=1032, K=456, layout_b=g.ROW_MAJOR, ldb=1033),
+           dict(M=776, N=1032, K=456, layout_b=g.ROW_MAJOR, batch=2, stride_b=1032 * 456 + 4),
+           dict(M=776, N=1032, K=456, layout_b=g.ROW_MAJOR, layout_c=g.COL_MAJOR),
+           dict(M=776, N=1032, K=456, layout_b=g.ROW_MAJOR, dtype=g.F32)]
+
+
+@pytest.mark.parametrize("kw", TILED)
+def test_tiled(kw):
+    """16-byte pieces along every operand's contiguous index; other pointers have a general kernel in the same plan."""
+    text = info(**kw)
+    assert "kernel=mfma16t_" in text and " unaligned A or B: kernel=" in text
+
+
+@pytest.mark.parametrize("kw", GENERAL)
+def test_general(kw):
+    assert "mfma16t_" not in info(**kw)
+
+
+def test_refusals_are_unchanged():
+    """The K-contiguous configurations still refuse these layouts, the new ones refuse everything else."""
+    names = g.config_names()
+    for kw, prefixes in ((TILED[0], ("mfma_", "mfma16_", "skinny", "mfma8")), (dict(M=256, N=256, K=256), ("mfma16t_",)),
+                         (GENERAL[0], ("mfma16t_",))):
+        for i, n in enumerate(names):
+            if n.startswith(prefixes):
+                with pytest.raises(g.GemmError) as e:
+                    g.gemm_create_config(g.GemmDesc(**kw), i)
+                assert e.value.status == -9
+    with pytest.raises(g.GemmError) as e:            # more rows than the general kernels' grid holds
+        g.gemm_create(g.GemmDesc(1 << 30, 8, 8, layout_b=g.ROW_MAJOR))
+    assert e.value.status == -2
+    with pytest.raises(g.GemmError):
+        g.gemm_create_splitk(g.GemmDesc(512, 512, 32768, layout_b=g.ROW_MAJOR), 0)
