@@ -26,6 +26,7 @@
 #include "general_mfma_kernel.hpp"
 #include "f32_mfma_kernel.hpp"
 #include "skinny_kernel.hpp"
+#include "ring_launch.hpp"
 #include "splitk_kernel.hpp"
 #include "device_check.hpp"
 
@@ -52,6 +53,32 @@ MI355GEMM_MFMA16P_TILES(X)
   MI355GEMM_MFMA16T_DECLARE(f16_t, BM, BN, WM, WN, G, P, false, false)  \
   MI355GEMM_MFMA16T_DECLARE(f16_t, BM, BN, WM, WN, G, P, false, true)
 MI355GEMM_MFMA16T_TILES(X)
+#undef X
+#define X(BM, BN, WM, WN, KS, NS, T1, T2)                                    \
+  MI355GEMM_RING_DECLARE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, true, true) \
+  MI355GEMM_RING_DECLARE(f16_t, f16_t, BM, BN, WM, WN, KS, NS, true, true)   \
+  MI355GEMM_RING_DECLARE(f8e4m3_t, bf16_t, BM, BN, WM, WN, KS, NS, true, true)
+MI355GEMM_RINGS(X)
+#undef X
+#define X(BM, BN, WM, WN, KS, NS, T1, T2)                                      \
+  MI355GEMM_RING_DECLARE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, true, false)  \
+  MI355GEMM_RING_DECLARE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, false, false) \
+  MI355GEMM_RING_DECLARE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, false, true)  \
+  MI355GEMM_RING_DECLARE(f16_t, f16_t, BM, BN, WM, WN, KS, NS, true, false)    \
+  MI355GEMM_RING_DECLARE(f16_t, f16_t, BM, BN, WM, WN, KS, NS, false, false)   \
+  MI355GEMM_RING_DECLARE(f16_t, f16_t, BM, BN, WM, WN, KS, NS, false, true)
+MI355GEMM_RINGS_T(X)
+#undef X
+#define X(BM, BN, WM, WN, G, S)                                         \
+  MI355GEMM_MFMA16S_DECLARE(bf16_t, BM, BN, WM, WN, G, S, true, true)   \
+  MI355GEMM_MFMA16S_DECLARE(bf16_t, BM, BN, WM, WN, G, S, true, false)  \
+  MI355GEMM_MFMA16S_DECLARE(bf16_t, BM, BN, WM, WN, G, S, false, false) \
+  MI355GEMM_MFMA16S_DECLARE(bf16_t, BM, BN, WM, WN, G, S, false, true)  \
+  MI355GEMM_MFMA16S_DECLARE(f16_t, BM, BN, WM, WN, G, S, true, true)    \
+  MI355GEMM_MFMA16S_DECLARE(f16_t, BM, BN, WM, WN, G, S, true, false)   \
+  MI355GEMM_MFMA16S_DECLARE(f16_t, BM, BN, WM, WN, G, S, false, false)  \
+  MI355GEMM_MFMA16S_DECLARE(f16_t, BM, BN, WM, WN, G, S, false, true)
+MI355GEMM_MFMA16S_TILES(X)
 #undef X
 }  // namespace mi355gemm
 
@@ -136,12 +163,19 @@ hipError_t launch_f32_small(const gemm_plan& pl, const void* A, const void* B, v
 }
 
 // 16-bit operands of which at least one is not K-contiguous
-template <typename T, int BM, int BN, int WM, int WN, int G, bool PERSIST>
+template <typename T, int BM, int BN, int WM, int WN, int G, bool PERSIST, int S = 2>
 hipError_t launch_mfma16t(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias, hipStream_t s) {
   const bool ak = pl.d.layout_a == GEMM_ROW_MAJOR, bk = pl.d.layout_b == GEMM_COL_MAJOR;
-  if (ak) return launch_mfma16<T, T, BM, BN, WM, WN, G, PERSIST, true, false>(pl, A, B, C, bias, s);
-  if (bk) return launch_mfma16<T, T, BM, BN, WM, WN, G, PERSIST, false, true>(pl, A, B, C, bias, s);
-  return launch_mfma16<T, T, BM, BN, WM, WN, G, PERSIST, false, false>(pl, A, B, C, bias, s);
+  if (ak) return launch_mfma16<T, T, BM, BN, WM, WN, G, PERSIST, true, false, S>(pl, A, B, C, bias, s);
+  if (bk) return launch_mfma16<T, T, BM, BN, WM, WN, G, PERSIST, false, true, S>(pl, A, B, C, bias, s);
+  return launch_mfma16<T, T, BM, BN, WM, WN, G, PERSIST, false, false, S>(pl, A, B, C, bias, s);
+}
+template <typename T, int BM, int BN, int WM, int WN, int KS, int NS>
+hipError_t launch_ring_t(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias, hipStream_t s) {
+  const bool ak = pl.d.layout_a == GEMM_ROW_MAJOR, bk = pl.d.layout_b == GEMM_COL_MAJOR;
+  if (ak) return launch_ring<T, T, BM, BN, WM, WN, KS, NS, true, false>(pl, A, B, C, bias, s);
+  if (bk) return launch_ring<T, T, BM, BN, WM, WN, KS, NS, false, true>(pl, A, B, C, bias, s);
+  return launch_ring<T, T, BM, BN, WM, WN, KS, NS, false, false>(pl, A, B, C, bias, s);
 }
 
 template <typename TIn, int TM, int TN, int TK>
@@ -261,6 +295,37 @@ hipError_t launch_skinny_direct(const gemm_plan& pl, const void* A, const void* 
 #define SKINNY_DIRECT_CFG(DEPTH, RB, WAVES)                                                \
   { "skinnydirect_d" #DEPTH "_b" #RB "_w" #WAVES, KIND_SKINNY_PANEL, 16, 32, RB / 2, 64 * WAVES, WAVES * 32 * RB, \
     { nullptr, launch_skinny_direct<bf16_t, DEPTH, RB, WAVES>, launch_skinny_direct<f16_t, DEPTH, RB, WAVES> } }
+// few rows of A: bm = rows of A, bn = rows of W per workgroup, bk = values of K per slab (16-bit)
+#define PANEL_CFG(MT, NT, RB, D, W)                                                        \
+  { "panel_" #MT "x" #NT "_b" #RB "_d" #D "_w" #W, KIND_PANEL, 16 * MT, 16 * NT, RB / 2, 64 * W, \
+    (W * 16 * NT * RB > W * MT * NT * 1024) ? W * 16 * NT * RB : W * MT * NT * 1024,       \
+    { nullptr, launch_panel<bf16_t, bf16_t, MT, NT, RB, D, W>,                             \
+      launch_panel<f16_t, f16_t, MT, NT, RB, D, W>, launch_panel<f8e4m3_t, bf16_t, MT, NT, RB, D, W> } },
+// more than two slabs in LDS, one workgroup per CU; NAME, KIND and launcher for either family of layouts
+#define MFMA16S_CFG(BM, BN, WM, WN, G, S)                                                  \
+  { "mfma16_" #BM "x" #BN "x64_w" #WM "x" #WN "_s" #S, KIND_MFMA, BM, BN, 64, 64 * WM * WN, \
+    Mfma16Tile<bf16_t, BM, BN, WM, WN, G, S>::LDS_BYTES,                                   \
+    { nullptr, launch_mfma16<bf16_t, bf16_t, BM, BN, WM, WN, G, false, true, true, S>,     \
+      launch_mfma16<f16_t, f16_t, BM, BN, WM, WN, G, false, true, true, S> }, 0, 0.33f, 0.0f },
+#define MFMA16TS_CFG(BM, BN, WM, WN, G, S)                                                 \
+  { "mfma16t_" #BM "x" #BN "x64_w" #WM "x" #WN "_s" #S, KIND_MFMA_T, BM, BN, 64, 64 * WM * WN, \
+    Mfma16Tile<bf16_t, BM, BN, WM, WN, G, S>::LDS_BYTES,                                   \
+    { nullptr, launch_mfma16t<bf16_t, BM, BN, WM, WN, G, false, S>,                        \
+      launch_mfma16t<f16_t, BM, BN, WM, WN, G, false, S> }, 0, 0.33f, 0.0f },
+// small tiles, slabs of K in a ring
+#define RING_ENTRY(NAME, KIND, T, BM, BN, WM, WN, KS, NS, T1, T2, ...)                     \
+  { NAME "_" #BM "x" #BN "_k" #KS "_w" #WM "x" #WN "_s" #NS, KIND, BM, BN, RingTile<T, BM, BN, WM, WN, KS, NS>::BK, \
+    64 * WM * WN, RingTile<T, BM, BN, WM, WN, KS, NS>::LDS_BYTES, { nullptr, __VA_ARGS__ }, 0, T1##f, T2##f },
+#define RING_CFG(BM, BN, WM, WN, KS, NS, T1, T2)                                           \
+  RING_ENTRY("mfma16", KIND_MFMA, bf16_t, BM, BN, WM, WN, KS, NS, T1, T2,                  \
+             launch_ring<bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, true, true>,              \
+             launch_ring<f16_t, f16_t, BM, BN, WM, WN, KS, NS, true, true>)
+#define RINGT_CFG(BM, BN, WM, WN, KS, NS, T1, T2)                                          \
+  RING_ENTRY("mfma16t", KIND_MFMA_T, bf16_t, BM, BN, WM, WN, KS, NS, T1, T2,               \
+             launch_ring_t<bf16_t, BM, BN, WM, WN, KS, NS>, launch_ring_t<f16_t, BM, BN, WM, WN, KS, NS>)
+#define RING8_CFG(BM, BN, WM, WN, KS, NS, T1, T2)                                          \
+  RING_ENTRY("mfma8", KIND_MFMA, f8e4m3_t, BM, BN, WM, WN, KS, NS, T1, T2, nullptr, nullptr, \
+             launch_ring<f8e4m3_t, bf16_t, BM, BN, WM, WN, KS, NS, true, true>)
 const Config kConfigs[] = {
     SIMT_CFG(64, 64, 16),
     SIMT_CFG(32, 32, 16),
@@ -300,6 +365,11 @@ const Config kConfigs[] = {
     MFMA16T_CFG("_p", 128, 128, 2, 2, 2, 1),
     MFMA16T_CFG("", 256, 256, 2, 4, 2, 0),
     MFMA16T_CFG("", 128, 128, 2, 2, 2, 0),
+    MI355GEMM_MFMA16S_TILES(MFMA16S_CFG)
+    MI355GEMM_MFMA16S_TILES(MFMA16TS_CFG)
+    MI355GEMM_RINGS(RING_CFG)
+    MI355GEMM_RINGS_T(RINGT_CFG)
+    MI355GEMM_RINGS(RING8_CFG)
 };
 constexpr int kNumConfigs = (int)(sizeof(kConfigs) / sizeof(kConfigs[0]));
 
@@ -408,7 +478,7 @@ bool applicable(const Config& c, const gemm_desc_t& d) {
     if (a_rows * d.lda * 2 >= ((int64_t)1 << 32) || b_rows * d.ldb * 2 >= ((int64_t)1 << 32)) return false;
     if (c.persist && (d.K % c.bk != 0 || d.K < 2 * c.bk)) return false;
     const int64_t tiles = ((d.M + c.bm - 1) / c.bm) * ((d.N + c.bn - 1) / c.bn);
-    return (c.persist ? tiles * d.batch : tiles) < ((int64_t)1 << 31);
+    return (c.persist || c.t1 > 0 ? tiles * d.batch : tiles) < ((int64_t)1 << 31);
   }
   // The MFMA and skinny kernels take K-contiguous A and B, row-major C, and move
   // 16-byte pieces: every row start must be 16-byte aligned.
@@ -429,7 +499,7 @@ bool applicable(const Config& c, const gemm_desc_t& d) {
     return false;
   if (c.persist && (d.K % c.bk != 0 || d.K < 2 * c.bk)) return false;   // whole slabs, at least two
   const int64_t tiles = ((d.M + c.bm - 1) / c.bm) * ((d.N + c.bn - 1) / c.bn);
-  return (c.persist ? tiles * d.batch : tiles) < ((int64_t)1 << 31);
+  return (c.persist || c.t1 > 0 ? tiles * d.batch : tiles) < ((int64_t)1 << 31);
 }
 
 int find_config(const char* name) {
@@ -438,23 +508,46 @@ int find_config(const char* name) {
   return -1;
 }
 
-// Cost model of one MFMA tile shape on an M x N x K (x batch) problem:
-// time ~ rounds over the CUs * work per round / measured relative efficiency of the tile
-// shape; a fixed per-tile cost (prologue latency, epilogue) is worth ~600 columns of K.
-// In these units one microsecond is about 2.7e6.
-double mfma_cost(const Config& c, int64_t M, int64_t N, int64_t K, int64_t batch) {
+// Cost model of one MFMA tile shape on an M x N x K (x batch) problem, in microseconds.
+//   * Kernels with two slabs in LDS: rounds over the CUs * work per round / measured relative efficiency of the tile
+//     shape; a fixed per-tile cost (prologue latency, epilogue) is worth ~600 columns of K.  A lone workgroup on a
+//     CU waits for its loads: 0.60 us per slab of the 128x128 tile, 1.1 us of the larger ones (K = 4096: 41 and 75 us).
+//   * Kernels with more slabs: launch (2.7 us) plus a measured time per slab, alone on a CU and (small rings) with a
+//     second workgroup beside it, over the tiles the busiest CU gets; each further round costs 2.4 us of prologue and
+//     epilogue that nothing overlaps (512x512x128, 64 problems, 64x64 tiles: 27 us).  The 128x128 tile takes 0.33 us a
+//     slab with half the CUs busy, 0.45 us with all of them (its panels come from L2: 256 workgroups take 17 TB/s) and
+//     0.6 us from the second round on, where the two-slab kernels are better (7195x7312x1448: 258 against 183 us).
+//     K-strided operands take half as long again per slab (137x4256x5000: 0.38 against 0.28 us; the 128x128 tile 0.53
+//     to 0.59 us).
+double mfma_cost(const Config& c, int64_t M, int64_t N, int64_t K, int64_t batch, int e) {
   const int area = c.bm * c.bn;
+  const double tiles = (double)((M + c.bm - 1) / c.bm) * (double)((N + c.bn - 1) / c.bn) * (double)batch;
+  const double cus = num_cus();
+  if (c.t1 > 0) {
+    const double slabs = (double)((K + c.bk - 1) / c.bk);
+    const double per_cu = (double)(int64_t)((tiles + cus - 1) / cus);
+    const bool t = c.kind == KIND_MFMA_T;
+    const double strided = t ? 1.5 : 1.0;
+    if (area >= 128 * 128) {
+      const double busy = fmin(1.0, fmax(0.0, tiles / cus - 0.5) * 2.0);
+      const double t1 = t ? 0.53 + 0.06 * busy : 0.33 + 0.12 * busy;
+      return per_cu > 1 ? per_cu * (slabs * 0.6 * strided + 5.0) : 4.0 + slabs * t1;
+    }
+    const double pairs = c.t2 > 0 ? (double)(int64_t)(per_cu / 2) : 0.0, singles = per_cu - 2 * pairs;
+    return 2.7 + (singles * c.t1 + pairs * c.t2) * slabs * strided + (singles + pairs - 1) * 2.4;
+  }
   const int per_cu = area <= 128 * 128 ? 2 : 1;                 // workgroups that fit one CU's LDS
   // (256x192 measured: 0.85 - 1.03 of the 256x256 tile per FLOP on 4096x6144x4096, 4096x14336x4096, 8192^3)
   double eff = area >= 256 * 256 ? 1.0 : (area >= 256 * 192 ? 0.88 : (area >= 256 * 128 ? 0.75 : 0.84));
   // the 16x16x32 kernels: about a tenth faster per FLOP than the 32x32x16 ones at the same tile shape
   // (8192^3: 732 against 800 us); of the two 256x256 shapes the eight-wave one goes first
   if (!std::strncmp(c.name, "mfma16", 6)) eff *= c.threads == 256 && area >= 256 * 256 ? 1.08 : 1.10;
-  const double tiles = (double)((M + c.bm - 1) / c.bm) * (double)((N + c.bn - 1) / c.bn) * (double)batch;
-  const double rounds = (double)(int64_t)((tiles + num_cus() * per_cu - 1) / (num_cus() * per_cu));
+  const double rounds = (double)(int64_t)((tiles + cus * per_cu - 1) / (cus * per_cu));
   // workgroups that actually share a CU (a lone workgroup runs about per_cu times faster)
-  const double sharing = tiles >= (double)num_cus() * per_cu ? per_cu : (tiles > num_cus() ? tiles / num_cus() : 1.0);
-  return rounds * area * sharing / eff * ((double)K + 600.0);
+  const double sharing = tiles >= cus * per_cu ? per_cu : (tiles > cus ? tiles / cus : 1.0);
+  const double work = rounds * area * sharing / eff * ((double)K + 600.0) / (e == 1 ? 5.4e6 : 2.7e6);
+  const double wait = rounds * ((double)K / c.bk * (area <= 128 * 128 ? (e == 1 ? 0.42 : 0.60) : 0.0) + 3.0);
+  return work > wait ? work : wait;
 }
 
 int best_mfma(const gemm_desc_t& d, double* cost_out) {
@@ -463,7 +556,7 @@ int best_mfma(const gemm_desc_t& d, double* cost_out) {
   for (int i = 0; i < kNumConfigs; ++i) {
     const Config& c = kConfigs[i];
     if ((c.kind != KIND_MFMA && c.kind != KIND_MFMA_T) || !applicable(c, d)) continue;
-    const double cost = mfma_cost(c, d.M, d.N, d.K, d.batch);
+    const double cost = mfma_cost(c, d.M, d.N, d.K, d.batch, esize(d.dtype_a));
     if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
   }
   if (cost_out) *cost_out = best_cost;
@@ -488,8 +581,8 @@ int64_t split_columns(const gemm_desc_t& d, int big, double single_cost) {
   rest.N = d.N - n_first;
   double rest_cost = 0;
   if (best_mfma(rest, &rest_cost) < 0) return 0;
-  const double launch = 3.0 * 2.7e6;
-  const double split_cost = mfma_cost(c, d.M, n_first, d.K, 1) + rest_cost + launch;
+  const double launch = 3.0;
+  const double split_cost = mfma_cost(c, d.M, n_first, d.K, 1, esize(d.dtype_a)) + rest_cost + launch;
   // (the model is optimistic about the second launch: where it sees 7.5 %, as for 4096 x 14336 x 4096,
   // 2 - 3 % were measured; where it sees 5 % against the 256x192 tile, the single launch wins by 8 %)
   return split_cost < 0.93 * single_cost ? n_first : 0;
@@ -575,6 +668,12 @@ int fill_launch_shape(gemm_plan& pl) {
     }
     pl.group_m = (int)(tm < 8 ? tm : 8);
     pl.xcd_remap = ((tm * tn) % 8 == 0) ? 1 : 0;
+    // a batch, one tile per workgroup, on the kernels with a deeper ring: whole problems per XCD as well (512x512x2048,
+    // 16 problems: 33 us with a problem's tiles spread over the XCDs)
+    if (c.t1 > 0 && d.batch > 1 && (tm * tn * d.batch) % 8 == 0) {
+      pl.grid = dim3((unsigned)(tm * tn * d.batch), 1, 1);
+      pl.xcd_remap = 3;
+    }
     // a batch on persistent workgroups: whole problems per XCD (their tiles share panels)
     if (c.persist && d.batch > 1 && (tm * tn * d.batch) % 8 == 0 && wgs % 8 == 0) pl.xcd_remap = 2;
   } else if (c.kind == KIND_SKINNY_PANEL) {
@@ -693,8 +792,7 @@ int gemm_create_config(const gemm_desc_t* desc, int config, gemm_plan_t** out_pl
 
 // Slices of K for a split-K plan: the count (up to 64, K a multiple of 8 x slices, whole
 // slabs per slice preferred) that minimises the tile cost model of the sliced product plus
-// the traffic of the fp32 partials (written once, read once: priced at 2 TB/s; in the model's units
-// one microsecond is 2.7e6).  512x512x32768 takes 46 / 31 / 29 / 38 us with 8 / 16 / 32 / 64 slices;
+// the traffic of the fp32 partials (written once, read once: priced at 4 TB/s).  512x512x32768 takes 46 / 31 / 29 / 38 us with 8 / 16 / 32 / 64 slices;
 // the model picks 16.
 static int choose_splits(const gemm_desc_t& d) {
   int best = 1;
@@ -710,7 +808,7 @@ static int choose_splits(const gemm_desc_t& d) {
       in.stride_a = in.stride_b = in.K;
       double cost = 0;
       if (best_mfma(in, &cost) < 0) continue;
-      cost += 2.0 * (double)s * (double)d.M * (double)d.N * 4.0 * (2.7e6 / 2.0e6);
+      cost += 2.0 * (double)s * (double)d.M * (double)d.N * 4.0 / 4.0e6;
       if (best_cost == 0 || cost < best_cost) { best = (int)s; best_cost = cost; }
     }
   }

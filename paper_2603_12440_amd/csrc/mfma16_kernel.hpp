@@ -102,9 +102,9 @@ struct SubOrder {
   static constexpr Tables t = make();
 };
 
-template <typename T, int BM, int BN, int WM, int WN, int G>
+template <typename T, int BM, int BN, int WM, int WN, int G, int STAGES = 2>
 struct Mfma16Tile {
-  static constexpr int BK = 64, NSTAGE = 2;
+  static constexpr int BK = 64, NSTAGE = STAGES;
   static constexpr int kWaves = WM * WN, kThreads = 64 * kWaves;
   static constexpr int WTM = BM / WM, WTN = BN / WN;     // per-wave block
   static constexpr int MT = WTM / 16, NT = WTN / 16;     // 16x16 MFMA tiles per wave
@@ -124,7 +124,7 @@ struct Mfma16Tile {
   static_assert(WTM % 16 == 0 && WTN % 16 == 0 && MT % G == 0, "wave block in whole sub-steps");
   static_assert(NSUB % 2 == 0, "the row-fragment double buffer alternates per sub-step");
   static_assert(MA * NT >= MA + NT, "a sub-step issues one or two fragment reads behind each MFMA");
-  static_assert(LDS_BYTES + EPI_BYTES <= 160 * 1024, "LDS budget");
+  static_assert(LDS_BYTES + (STAGES == 2 ? EPI_BYTES : 0) <= 160 * 1024, "LDS budget");
 };
 
 // The fragment registers of one operand: one 16-byte LDS read (K contiguous in memory) or two 8-byte
@@ -162,9 +162,12 @@ __device__ __forceinline__ void lds_read_tr16(F& dst, uint32_t addr, int offset)
 // the LDS read instructions at half the width): 8192^3 bf16 takes 721 us with B row-major, 726 us with A
 // column-major as well, 709 - 726 us K-contiguous on the same box.  These layouts used to run on the fp32
 // matrix-core instruction: 6144 x 4096 x 3001 with both operands strided 2475 us, here 133 us.
-template <typename T, typename TO, int BM, int BN, int WM, int WN, int G, bool PERSIST, bool A_KF = true, bool B_KF = true>
+// S: slabs in LDS.  Two for the large problems; a lone workgroup on a CU has nothing else to hide a load's latency
+// behind and takes four (one tile per workgroup only).
+template <typename T, typename TO, int BM, int BN, int WM, int WN, int G, bool PERSIST, bool A_KF = true, bool B_KF = true, int S = 2>
 __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
-  typedef Mfma16Tile<T, BM, BN, WM, WN, G> Cfg;
+  typedef Mfma16Tile<T, BM, BN, WM, WN, G, S> Cfg;
+  static_assert(S == 2 || !PERSIST, "a persistent workgroup streams through two stages");
   constexpr int MT = Cfg::MT, NT = Cfg::NT, MA = Cfg::MA, CPR = Cfg::CPR, RPI = Cfg::RPI;
   constexpr int ROWB = Cfg::ROWB, BK = Cfg::BK, KK = Cfg::KK, NSUB = Cfg::NSUB;
   constexpr bool kTwoPerSimd = Cfg::kWaves > 4;          // two waves share a SIMD: alternate by priority
@@ -214,8 +217,13 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   auto load_tile = [&](int vid, int ln, int kt) __attribute__((always_inline)) {
     int tm, tn;
     const int lid = PERSIST ? logical_tile(vid) : vid;
-    const int lb = PERSIST ? lid / n_tiles : batch;          // the problem this tile belongs to
-    tile_coords(p, PERSIST ? lid - lb * n_tiles : vid, n_tiles, tm, tn);
+    int lb = PERSIST ? lid / n_tiles : batch;                // the problem this tile belongs to
+    if constexpr (S == 2) {
+      tile_coords(p, PERSIST ? lid - lb * n_tiles : vid, n_tiles, tm, tn);
+    } else {
+      tile_and_batch(p, lb, tm, tn);
+      batch = lb;
+    }
     const int r0 = tm * BM, c0 = tn * BN;
     ld_a = (const char*)((const T*)p.A + (int64_t)lb * p.stride_a + (A_KF ? (int64_t)r0 * p.lda : (int64_t)r0)) + (int64_t)kt * a_step;
     ld_b = (const char*)((const T*)p.B + (int64_t)lb * p.stride_b + (B_KF ? (int64_t)c0 * p.ldb : (int64_t)c0)) + (int64_t)kt * b_step;
@@ -346,7 +354,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
         if constexpr (!B_KF) b_rd[x] = at + Cfg::A_BYTES + (wn * Cfg::WTN / 64) * 8192 + ((x ^ key) * 32);
       }
     }
-    rd_delta = st ? -Cfg::STAGE_BYTES : Cfg::STAGE_BYTES;
+    rd_delta = st == S - 1 ? -(S - 1) * Cfg::STAGE_BYTES : Cfg::STAGE_BYTES;
   };
   set_read_stage(0, lane);
   auto flip_read_stage = [&]() __attribute__((always_inline)) {
@@ -354,7 +362,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     for (int x = 0; x < NA; ++x) a_rd[x] += rd_delta;
 #pragma unroll
     for (int x = 0; x < NB; ++x) b_rd[x] += rd_delta;
-    rd_delta = -rd_delta;
+    if constexpr (S == 2) rd_delta = -rd_delta;
   };
 
   f32x4_t acc[MT][NT];
@@ -730,9 +738,9 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   };
 
   // ---- main loop ------------------------------------------------------------------------
-  // Slab t lives in LDS stage t % 2.  The hand-over to slab t+1 (own reads retired, own loads
+  // Slab t lives in LDS stage t % S.  The hand-over to slab t+1 (own reads retired, own loads
   // landed, all waves met) sits before the last sub-step of slab t, whose fragments are
-  // already in registers; stage t % 2 is free from then on and is refilled with slab t+2 over
+  // already in registers; stage t % S is free from then on and is refilled with slab t+S over
   // the next LW sub-steps (the last one of slab t and the first ones of slab t+1), which
   // leaves the remaining sub-steps before the next hand-over for the loads to land.
   // Priorities (two waves per SIMD): highest right after the hand-over, one lower per
@@ -741,13 +749,22 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   constexpr int LW = NSUB >= 4 ? NSUB - 1 : 1;           // sub-steps the loads of a slab are spread over
   int stage = 0, t = 0;
   SlabIo io_none{nullptr, nullptr, 0u, 0u};
-  // early: the rest of the loads of slab t+1 (begun after the previous hand-over) into the other
-  // stage; late: the first loads of slab t+2 into this stage after the hand-over
-  auto slab_body = [&](auto early_c, auto late_c) __attribute__((always_inline)) {
-    constexpr bool early = decltype(early_c)::value, late = decltype(late_c)::value;
+  auto next_read_stage = [&]() __attribute__((always_inline)) {      // (S > 2: forward by one, or back to stage 0)
+    const int by = stage + 1 == S ? -(S - 1) * Cfg::STAGE_BYTES : Cfg::STAGE_BYTES;
+#pragma unroll
+    for (int x = 0; x < NA; ++x) a_rd[x] += by;
+#pragma unroll
+    for (int x = 0; x < NB; ++x) b_rd[x] += by;
+  };
+  // early: the rest of the loads of slab t+S-1 (begun after the previous hand-over) into the stage before this
+  // one; late: the first loads of slab t+S into this stage after the hand-over; deep: the S-2 slabs after the next
+  // one are requested, so the wait for the next one leaves their loads in flight
+  auto slab_body = [&](auto early_c, auto late_c, auto deep_c) __attribute__((always_inline)) {
+    constexpr bool early = decltype(early_c)::value, late = decltype(late_c)::value, deep = decltype(deep_c)::value;
     SlabIo io_early = io_none, io_late = io_none;
-    if constexpr (early) io_early = slab_io(t + 1, stage ^ 1);
-    if constexpr (late) io_late = slab_io(t + 2, stage);
+    const int before = S == 2 ? stage ^ 1 : (stage == 0 ? S - 1 : stage - 1);
+    if constexpr (early) io_early = slab_io(t + S - 1, before);
+    if constexpr (late) io_late = slab_io(t + S, stage);
     static_for<0, NSUB - 1>([&](auto u_c) __attribute__((always_inline)) {
       constexpr int u = decltype(u_c)::value;
       set_prio(u < 3 ? 2 - u : 0);
@@ -757,44 +774,43 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       else
         sub_step(u_c, true, 0, 0, io_none);
     });
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(deep ? (S - 2) * kLoads : 0) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     set_prio(3);
-    flip_read_stage();
+    if constexpr (S == 2) flip_read_stage();
+    else next_read_stage();
     if constexpr (late) sub_step(std::integral_constant<int, NSUB - 1>(), true, 0, kLoads / LW, io_late);
     else sub_step(std::integral_constant<int, NSUB - 1>(), true, 0, 0, io_none);
-    stage ^= 1;
+    stage = S == 2 ? stage ^ 1 : (stage + 1 == S ? 0 : stage + 1);
   };
   typedef std::integral_constant<bool, true> yes_t;
   typedef std::integral_constant<bool, false> no_t;
 
   if constexpr (!PERSIST) {
   if (T_full > 0) {
-    {
-      const SlabIo io0 = slab_io(0, 0);
+    // the first S slabs (as many as there are); the first one has landed when the others' loads are left
+    static_for<0, S>([&](auto q_c) __attribute__((always_inline)) {
+      constexpr int sl = decltype(q_c)::value;
+      if (sl < T_full) {
+        const SlabIo io = slab_io(sl, sl);
 #pragma unroll
-      for (int q = 0; q < kLoads; ++q) issue_one_load(q, io0);
-    }
-    if (T_full > 1) {
-      const SlabIo io1 = slab_io(1, 1);
-#pragma unroll
-      for (int q = 0; q < kLoads; ++q) issue_one_load(q, io1);
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoads) : "memory");
-    } else {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
+        for (int q = 0; q < kLoads; ++q) issue_one_load(q, io);
+      }
+    });
+    if (T_full >= S) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 1) * kLoads) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     read_all(std::integral_constant<int, 0>());
-    if (T_full > 2) slab_body(no_t(), yes_t()); else slab_body(no_t(), no_t());
-    for (t = 1; t < T_full - 2; ++t) slab_body(yes_t(), yes_t());
-    if (T_full >= 3) { slab_body(yes_t(), no_t()); ++t; }
-    if (T_full >= 2) { slab_body(no_t(), no_t()); ++t; }
+    if (T_full > S) slab_body(no_t(), yes_t(), yes_t()); else slab_body(no_t(), no_t(), no_t());
+    for (t = 1; t < T_full - S; ++t) slab_body(yes_t(), yes_t(), yes_t());
+    if (T_full > S) { slab_body(yes_t(), no_t(), yes_t()); ++t; }
+    for (; t < T_full; ++t) slab_body(no_t(), no_t(), no_t());
     set_prio(0);
     // the last fragment reads (of a stage nobody multiplies) are still in flight
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    if (stage) flip_read_stage();              // the K tail reads stage 0
+    if (stage) set_read_stage(0, lane);        // the K tail reads stage 0
   }
   if (T_full * BK < p.K) {                     // K tail, through registers with zero fill
     __builtin_amdgcn_s_barrier();              // every wave is done with the LDS stages
@@ -814,7 +830,8 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     wait_lgkmcnt<0>();
   }
   int tm, tn;
-  tile_coords(p, blockIdx.x, n_tiles, tm, tn);
+  if constexpr (S == 2) tile_coords(p, blockIdx.x, n_tiles, tm, tn);
+  else tile_and_batch(p, batch, tm, tn);
   epilogue(tm * BM, tn * BN);
   } else {
   // ---- persistent: the tiles of this workgroup as one stream of slabs ------------------------

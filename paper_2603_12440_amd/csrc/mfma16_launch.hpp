@@ -31,7 +31,7 @@ MfmaArgs mfma16_args(const gemm_plan& pl, const void* A, const void* B, void* C,
 }
 
 // A_KF, B_KF: K is the contiguous index of A / B
-template <typename T, typename TO, int BM, int BN, int WM, int WN, int G, bool PERSIST, bool A_KF = true, bool B_KF = true>
+template <typename T, typename TO, int BM, int BN, int WM, int WN, int G, bool PERSIST, bool A_KF = true, bool B_KF = true, int S = 2>
 hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void* C,
                          const void* bias, hipStream_t s) {
   const gemm_desc_t& d = pl.d;
@@ -43,11 +43,11 @@ hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void
     const bool staged = d.ldc % unit == 0 && d.stride_c % unit == 0 && ((uintptr_t)C & 15) == 0;
     if (!staged) {
       const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)d.batch, 1);
-      mfma16_gemm_kernel<T, TO, BM, BN, WM, WN, G, false, A_KF, B_KF><<<grid, pl.block, 0, s>>>(a);
+      mfma16_gemm_kernel<T, TO, BM, BN, WM, WN, G, false, A_KF, B_KF, S><<<grid, pl.block, 0, s>>>(a);
       return hipGetLastError();
     }
   }
-  mfma16_gemm_kernel<T, TO, BM, BN, WM, WN, G, PERSIST, A_KF, B_KF><<<pl.grid, pl.block, 0, s>>>(a);
+  mfma16_gemm_kernel<T, TO, BM, BN, WM, WN, G, PERSIST, A_KF, B_KF, S><<<pl.grid, pl.block, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -73,6 +73,15 @@ hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void
       const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
 #define MI355GEMM_MFMA16T_DEFINE(T, BM, BN, WM, WN, G, P, AK, BK)                             \
   template hipError_t launch_mfma16<T, T, BM, BN, WM, WN, G, P, AK, BK>(                       \
+      const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
+
+// four slabs in LDS, one workgroup per CU: X(BM, BN, WM, WN, G, S)
+#define MI355GEMM_MFMA16S_TILES(X) X(128, 128, 2, 2, 2, 4)
+#define MI355GEMM_MFMA16S_DECLARE(T, BM, BN, WM, WN, G, S, AK, BK)                            \
+  extern template hipError_t launch_mfma16<T, T, BM, BN, WM, WN, G, false, AK, BK, S>(         \
+      const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
+#define MI355GEMM_MFMA16S_DEFINE(T, BM, BN, WM, WN, G, S, AK, BK)                             \
+  template hipError_t launch_mfma16<T, T, BM, BN, WM, WN, G, false, AK, BK, S>(                \
       const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
 
 #define MI355GEMM_MFMA16_DECLARE(T, TO, BM, BN, WM, WN, G, P)                               \

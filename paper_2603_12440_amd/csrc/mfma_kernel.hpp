@@ -30,7 +30,7 @@ struct MfmaArgs {
   int tiles_m, tiles_n;        // ceil(M/BM), ceil(N/BN)
   int group_m;                 // tile rows per scheduling group
   int xcd_remap;               // 1: spread consecutive tile ids within one XCD; 2 (persistent workgroups, a batch):
-                               // consecutive problems of the batch within one XCD
+                               // consecutive problems of the batch within one XCD; 3: the same, one tile per workgroup
   int c_cached;                // 1: fp32 C is read again right away (split-K partials): ordinary stores
   int batches;                 // problems in the batch (persistent workgroups walk over the tiles of all of them)
 };
@@ -136,6 +136,20 @@ __device__ __forceinline__ void tile_coords(const MfmaArgs& p, int wg, int n_wg,
   const int rem = id - g * in_group;
   tm = first_m + rem % rows;
   tn = rem / rows;
+}
+
+// One tile per workgroup, the tiles of a batch along blockIdx.y; or all of them along blockIdx.x (xcd_remap == 3, a
+// multiple of 8 in all), each XCD taking a contiguous run of whole problems, whose tiles share panels in its L2.
+__device__ __forceinline__ void tile_and_batch(const MfmaArgs& p, int& batch, int& tm, int& tn) {
+  const int n_tiles = p.tiles_m * p.tiles_n;
+  int id = blockIdx.x;
+  batch = blockIdx.y;
+  if (p.xcd_remap == 3) {
+    const int lid = (id & 7) * ((n_tiles * p.batches) >> 3) + (id >> 3);
+    batch = lid / n_tiles;
+    id = lid - batch * n_tiles;
+  }
+  tile_coords(p, id, n_tiles, tm, tn);
 }
 
 // ---- instruction order of one MFMA k-step -----------------------------------------

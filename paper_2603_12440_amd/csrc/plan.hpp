@@ -61,6 +61,9 @@ struct Config {
   int lds_bytes;
   launch_fn launch[4];    // per operand dtype (GEMM_F32 / BF16 / F16 / F8E4M3); NULL = not compiled
   int persist;            // 1: workgroups walk over several tiles (grid = workgroups resident at once)
+  // more than two slabs in LDS: microseconds a slab takes with one workgroup on a CU and with two (0: two do not
+  // fit); t1 == 0 for all other kernels
+  float t1, t2;
 };
 
 inline int esize(int dt) { return dt == GEMM_F32 ? 4 : (dt == GEMM_F8E4M3 ? 1 : 2); }

@@ -1,0 +1,14 @@
+// Instantiations of the ring kernel for one operand type, every pair of layouts.
+#include "ring_launch.hpp"
+
+namespace mi355gemm {
+#define X(BM, BN, WM, WN, KS, NS, T1, T2) MI355GEMM_RING_DEFINE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, true, true)
+MI355GEMM_RINGS(X)
+#undef X
+#define X(BM, BN, WM, WN, KS, NS, T1, T2)                                   \
+  MI355GEMM_RING_DEFINE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, true, false)  \
+  MI355GEMM_RING_DEFINE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, false, false) \
+  MI355GEMM_RING_DEFINE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, false, true)
+MI355GEMM_RINGS_T(X)
+#undef X
+}  // namespace mi355gemm
