@@ -12,7 +12,7 @@ SOURCES = [os.path.join(CSRC, f) for f in
            ("gemm_api.hip", "mfma_bf16_inst.hip", "mfma_f16_inst.hip", "mfma_f8_inst.hip",
             "mfma16_bf16_inst.hip", "mfma16_f16_inst.hip", "mfma16p_bf16_inst.hip", "mfma16p_f16_inst.hip",
             "mfma16t_nn_bf16_inst.hip", "mfma16t_nn_f16_inst.hip", "mfma16t_tn_bf16_inst.hip", "mfma16t_tn_f16_inst.hip",
-            "mfma16t_tt_bf16_inst.hip", "mfma16t_tt_f16_inst.hip", "mfma16s_bf16_inst.hip", "mfma16s_f16_inst.hip", "ring_bf16_inst.hip", "ring_f16_inst.hip", "ring_f8_inst.hip", "rope_api.hip", "probe_api.hip")]
+            "mfma16t_tt_bf16_inst.hip", "mfma16t_tt_f16_inst.hip", "mfma16s_bf16_inst.hip", "mfma16s_f16_inst.hip", "ring_bf16_inst.hip", "ring_f16_inst.hip", "ring_f8_inst.hip", "mfma16g_inst.hip", "rope_api.hip", "probe_api.hip")]
 OBJ_DIR = os.path.join(os.path.dirname(HERE), "_build")
 
 

@@ -69,6 +69,11 @@ MI355GEMM_RINGS(X)
   MI355GEMM_RING_DECLARE(f16_t, f16_t, BM, BN, WM, WN, KS, NS, false, true)
 MI355GEMM_RINGS_T(X)
 #undef X
+#define X(BM, BN, WM, WN, KS, T1, T2)                    \
+  MI355GEMM_MFMA16G_DECLARE(bf16_t, BM, BN, WM, WN, KS)  \
+  MI355GEMM_MFMA16G_DECLARE(f16_t, BM, BN, WM, WN, KS)
+MI355GEMM_MFMA16G_TILES(X)
+#undef X
 #define X(BM, BN, WM, WN, G, S)                                         \
   MI355GEMM_MFMA16S_DECLARE(bf16_t, BM, BN, WM, WN, G, S, true, true)   \
   MI355GEMM_MFMA16S_DECLARE(bf16_t, BM, BN, WM, WN, G, S, true, false)  \
@@ -326,6 +331,11 @@ hipError_t launch_skinny_direct(const gemm_plan& pl, const void* A, const void* 
 #define RING8_CFG(BM, BN, WM, WN, KS, NS, T1, T2)                                          \
   RING_ENTRY("mfma8", KIND_MFMA, f8e4m3_t, BM, BN, WM, WN, KS, NS, T1, T2, nullptr, nullptr, \
              launch_ring<f8e4m3_t, bf16_t, BM, BN, WM, WN, KS, NS, true, true>)
+// 16-bit operands of any alignment, two slabs
+#define MFMA16G_CFG(BM, BN, WM, WN, KS, T1, T2)                                            \
+  { "mfma16g_" #BM "x" #BN "_k" #KS "_w" #WM "x" #WN, KIND_MFMA_G, BM, BN, KS * 64, 64 * WM * WN, \
+    RingTile<bf16_t, BM, BN, WM, WN, KS, 2>::LDS_BYTES,                                    \
+    { nullptr, launch_mfma16g<bf16_t, BM, BN, WM, WN, KS>, launch_mfma16g<f16_t, BM, BN, WM, WN, KS> }, 0, T1##f, T2##f },
 const Config kConfigs[] = {
     SIMT_CFG(64, 64, 16),
     SIMT_CFG(32, 32, 16),
@@ -370,6 +380,7 @@ const Config kConfigs[] = {
     MI355GEMM_RINGS(RING_CFG)
     MI355GEMM_RINGS_T(RINGT_CFG)
     MI355GEMM_RINGS(RING8_CFG)
+    MI355GEMM_MFMA16G_TILES(MFMA16G_CFG)
 };
 constexpr int kNumConfigs = (int)(sizeof(kConfigs) / sizeof(kConfigs[0]));
 
@@ -454,6 +465,15 @@ int resolve(const gemm_desc_t* in, gemm_desc_t* out) {
   return GEMM_OK;
 }
 
+// The alignment the tiled 16-bit and fp8 kernels need: every operand's contiguous extent, leading dimension and
+// batch stride a whole number of 16-byte pieces (and C row-major).
+bool whole_pieces(const gemm_desc_t& d) {
+  const int64_t epc = 16 / esize(d.dtype_a);
+  const bool ak = d.layout_a == GEMM_ROW_MAJOR, bk = d.layout_b == GEMM_COL_MAJOR;
+  return d.layout_c == GEMM_ROW_MAJOR && (ak ? d.K : d.M) % epc == 0 && (bk ? d.K : d.N) % epc == 0 &&
+         d.lda % epc == 0 && d.ldb % epc == 0 && d.stride_a % epc == 0 && d.stride_b % epc == 0;
+}
+
 // Can instantiation c run problem d?
 bool applicable(const Config& c, const gemm_desc_t& d) {
   if (!c.launch[d.dtype_a]) return false;
@@ -465,13 +485,20 @@ bool applicable(const Config& c, const gemm_desc_t& d) {
     return d.dtype_c == GEMM_F32 && d.lda % 4 == 0 && d.ldb % 4 == 0 && d.stride_a % 4 == 0 &&
            d.stride_b % 4 == 0 && (ak ? d.K : d.M) % 4 == 0 && (bk ? d.K : d.N) % 4 == 0;
   }
+  if (c.kind == KIND_MFMA_G) {
+    // what the tiled kernels do not take; the row limit is that of the general kernels' grids, 32-bit lane offsets
+    const bool ak = d.layout_a == GEMM_ROW_MAJOR, bk = d.layout_b == GEMM_COL_MAJOR;
+    const int64_t kMax = ((int64_t)1 << 31) - 512, lim = (int64_t)1 << 32;
+    const int64_t a_rows = ak ? c.bm : c.bk + 1, b_rows = bk ? c.bn : c.bk + 1;
+    const int64_t tiles = ((d.M + c.bm - 1) / c.bm) * ((d.N + c.bn - 1) / c.bn);
+    return !whole_pieces(d) && d.M <= 65535 * 32 && d.N < kMax && d.K < kMax && a_rows * d.lda * 2 < lim &&
+           b_rows * d.ldb * 2 < lim && tiles * d.batch < ((int64_t)1 << 31);
+  }
   if (c.kind == KIND_MFMA_T) {
     // Row-major C, at least one operand not K-contiguous; 16-byte pieces along each operand's contiguous
     // index (its extent, leading dimension and batch stride multiples of 8), 32-bit lane offsets inside a slab.
     const bool ak = d.layout_a == GEMM_ROW_MAJOR, bk = d.layout_b == GEMM_COL_MAJOR;
-    if ((ak && bk) || d.layout_c != GEMM_ROW_MAJOR) return false;
-    if ((ak ? d.K : d.M) % 8 || (bk ? d.K : d.N) % 8 || d.lda % 8 || d.ldb % 8 || d.stride_a % 8 || d.stride_b % 8)
-      return false;
+    if ((ak && bk) || !whole_pieces(d)) return false;
     const int64_t kMax = ((int64_t)1 << 31) - 512;
     if (d.M >= kMax || d.N >= kMax || d.K >= kMax) return false;
     const int64_t a_rows = ak ? c.bm : c.bk + 1, b_rows = bk ? c.bn : c.bk + 1;
@@ -517,24 +544,26 @@ int find_config(const char* name) {
 //     epilogue that nothing overlaps (512x512x128, 64 problems, 64x64 tiles: 27 us).  The 128x128 tile takes 0.33 us a
 //     slab with half the CUs busy, 0.45 us with all of them (its panels come from L2: 256 workgroups take 17 TB/s) and
 //     0.6 us from the second round on, where the two-slab kernels are better (7195x7312x1448: 258 against 183 us).
-//     K-strided operands take half as long again per slab (137x4256x5000: 0.38 against 0.28 us; the 128x128 tile 0.53
-//     to 0.59 us).
-double mfma_cost(const Config& c, int64_t M, int64_t N, int64_t K, int64_t batch, int e) {
+//     An operand whose rows do not start on 128-byte lines costs 0.35 of that on top: every piece of 128 bytes
+//     touches two lines (384x4104x4104: 43 us, 384x4096x4096: 24 us).
+double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
+  const int64_t M = d.M, K = d.K, batch = d.batch;
+  const int e = esize(d.dtype_a);
   const int area = c.bm * c.bn;
   const double tiles = (double)((M + c.bm - 1) / c.bm) * (double)((N + c.bn - 1) / c.bn) * (double)batch;
   const double cus = num_cus();
+  const int off_line = ((d.lda * e) % 128 != 0) + ((d.ldb * e) % 128 != 0);
   if (c.t1 > 0) {
     const double slabs = (double)((K + c.bk - 1) / c.bk);
     const double per_cu = (double)(int64_t)((tiles + cus - 1) / cus);
-    const bool t = c.kind == KIND_MFMA_T;
-    const double strided = t ? 1.5 : 1.0;
-    if (area >= 128 * 128) {
+    const double pitch = c.kind == KIND_MFMA_G ? 1.0 : 1.0 + 0.35 * off_line;
+    if (area >= 128 * 128 && c.kind != KIND_MFMA_G) {
       const double busy = fmin(1.0, fmax(0.0, tiles / cus - 0.5) * 2.0);
-      const double t1 = t ? 0.53 + 0.06 * busy : 0.33 + 0.12 * busy;
-      return per_cu > 1 ? per_cu * (slabs * 0.6 * strided + 5.0) : 4.0 + slabs * t1;
+      const double t1 = (0.33 + 0.12 * busy) * pitch;
+      return per_cu > 1 ? per_cu * (slabs * fmax(0.6, t1) + 5.0) : 4.0 + slabs * t1;
     }
     const double pairs = c.t2 > 0 ? (double)(int64_t)(per_cu / 2) : 0.0, singles = per_cu - 2 * pairs;
-    return 2.7 + (singles * c.t1 + pairs * c.t2) * slabs * strided + (singles + pairs - 1) * 2.4;
+    return 2.7 + (singles * c.t1 + pairs * c.t2) * slabs * pitch + (singles + pairs - 1) * 2.4;
   }
   const int per_cu = area <= 128 * 128 ? 2 : 1;                 // workgroups that fit one CU's LDS
   // (256x192 measured: 0.85 - 1.03 of the 256x256 tile per FLOP on 4096x6144x4096, 4096x14336x4096, 8192^3)
@@ -546,7 +575,7 @@ double mfma_cost(const Config& c, int64_t M, int64_t N, int64_t K, int64_t batch
   // workgroups that actually share a CU (a lone workgroup runs about per_cu times faster)
   const double sharing = tiles >= cus * per_cu ? per_cu : (tiles > cus ? tiles / cus : 1.0);
   const double work = rounds * area * sharing / eff * ((double)K + 600.0) / (e == 1 ? 5.4e6 : 2.7e6);
-  const double wait = rounds * ((double)K / c.bk * (area <= 128 * 128 ? (e == 1 ? 0.42 : 0.60) : 0.0) + 3.0);
+  const double wait = rounds * ((double)K / c.bk * (area <= 128 * 128 ? (e == 1 ? 0.42 * (1.0 + 0.5 * off_line) : 0.60 * (1.0 + 0.2 * off_line)) : 0.0) + 3.0);
   return work > wait ? work : wait;
 }
 
@@ -555,8 +584,8 @@ int best_mfma(const gemm_desc_t& d, double* cost_out) {
   double best_cost = 0;
   for (int i = 0; i < kNumConfigs; ++i) {
     const Config& c = kConfigs[i];
-    if ((c.kind != KIND_MFMA && c.kind != KIND_MFMA_T) || !applicable(c, d)) continue;
-    const double cost = mfma_cost(c, d.M, d.N, d.K, d.batch, esize(d.dtype_a));
+    if ((c.kind != KIND_MFMA && c.kind != KIND_MFMA_T && c.kind != KIND_MFMA_G) || !applicable(c, d)) continue;
+    const double cost = mfma_cost(c, d, d.N);
     if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
   }
   if (cost_out) *cost_out = best_cost;
@@ -582,7 +611,7 @@ int64_t split_columns(const gemm_desc_t& d, int big, double single_cost) {
   double rest_cost = 0;
   if (best_mfma(rest, &rest_cost) < 0) return 0;
   const double launch = 3.0;
-  const double split_cost = mfma_cost(c, d.M, n_first, d.K, 1, esize(d.dtype_a)) + rest_cost + launch;
+  const double split_cost = mfma_cost(c, d, n_first) + rest_cost + launch;
   // (the model is optimistic about the second launch: where it sees 7.5 %, as for 4096 x 14336 x 4096,
   // 2 - 3 % were measured; where it sees 5 % against the 256x192 tile, the single launch wins by 8 %)
   return split_cost < 0.93 * single_cost ? n_first : 0;
@@ -640,6 +669,10 @@ int choose(const gemm_desc_t& d) {
     if (best >= 0) return best;
   }
   const int best = best_mfma(d, nullptr);
+  // operands of any alignment: up to 2^24 multiply-adds with a short K stay on the vector-ALU kernel (256x256x100: 6.5 us
+  // on either; 25x933x453: 28 us there, 10 us on the matrix cores)
+  if (best >= 0 && kConfigs[best].kind == KIND_MFMA_G && d.K <= 256 && (double)d.M * d.N * d.K * d.batch <= 16777216.0)
+    return choose_general(d);
   if (best >= 0) return best;
   return choose_general(d);
 }
@@ -648,13 +681,12 @@ int fill_launch_shape(gemm_plan& pl) {
   const gemm_desc_t& d = pl.d;
   const Config& c = *pl.cfg;
   pl.block = dim3(c.threads, 1, 1);
-  pl.group_m = 1;
   pl.xcd_remap = 0;
   if (c.kind == KIND_SIMT || c.kind == KIND_F32_VEC) {
     const int64_t gx = (d.N + c.bn - 1) / c.bn, gy = (d.M + c.bm - 1) / c.bm;
     if (gy > 65535) return GEMM_ERR_BAD_DIM;   // grid.y / grid.z limits
     pl.grid = dim3((unsigned)gx, (unsigned)gy, (unsigned)d.batch);
-  } else if (c.kind == KIND_MFMA || c.kind == KIND_MFMA_T) {
+  } else if (c.kind == KIND_MFMA || c.kind == KIND_MFMA_T || c.kind == KIND_MFMA_G) {
     const int64_t tm = (d.M + c.bm - 1) / c.bm, tn = (d.N + c.bn - 1) / c.bn;
     int64_t wgs = tm * tn;
     if (c.persist) {
@@ -666,8 +698,7 @@ int fill_launch_shape(gemm_plan& pl) {
     } else {
       pl.grid = dim3((unsigned)wgs, (unsigned)d.batch, 1);
     }
-    pl.group_m = (int)(tm < 8 ? tm : 8);
-    pl.xcd_remap = ((tm * tn) % 8 == 0) ? 1 : 0;
+    pl.xcd_remap = d.batch == 1 || (tm * tn) % 8 == 0 ? 1 : 0;
     // a batch, one tile per workgroup, on the kernels with a deeper ring: whole problems per XCD as well (512x512x2048,
     // 16 problems: 33 us with a problem's tiles spread over the XCDs)
     if (c.t1 > 0 && d.batch > 1 && (tm * tn * d.batch) % 8 == 0) {
@@ -952,7 +983,8 @@ static int run_plan(const gemm_plan_t* plan, const void* A, const void* B, void*
   if (epilogue_has_bias(d.epilogue) != (bias != nullptr)) return GEMM_ERR_NULL;
   // The tiled 16-bit kernels move 16-byte pieces; the general kernel only needs
   // element alignment.
-  const uintptr_t in_mask = plan->cfg->kind == KIND_SIMT || plan->cfg->kind == KIND_F32_VEC ? (uintptr_t)esize(d.dtype_a) - 1 : 15;
+  const Kind kind = plan->cfg->kind;
+  const uintptr_t in_mask = kind == KIND_SIMT || kind == KIND_F32_VEC || kind == KIND_MFMA_G ? (uintptr_t)esize(d.dtype_a) - 1 : 15;
   if (((uintptr_t)A & in_mask) || ((uintptr_t)B & in_mask) ||
       ((uintptr_t)C & ((uintptr_t)esize(d.dtype_c) - 1)) || ((uintptr_t)bias & 3))
     return GEMM_ERR_MISALIGNED;

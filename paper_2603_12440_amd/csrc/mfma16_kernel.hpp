@@ -741,12 +741,15 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   // Slab t lives in LDS stage t % S.  The hand-over to slab t+1 (own reads retired, own loads
   // landed, all waves met) sits before the last sub-step of slab t, whose fragments are
   // already in registers; stage t % S is free from then on and is refilled with slab t+S over
-  // the next LW sub-steps (the last one of slab t and the first ones of slab t+1), which
-  // leaves the remaining sub-steps before the next hand-over for the loads to land.
+  // the next LW sub-steps (the last one of slab t and, LW > 1, the first ones of slab t+1), which
+  // leaves the remaining sub-steps before the next hand-over for the loads to land.  With two stages
+  // that is all the time they have, and panels that come from HBM need most of it: the eight-wave tile
+  // spreads its loads over two sub-steps (operands outside the last-level cache, 4096x14336x4096: 402 us
+  // with three, 371 with two on one box; a single sub-step is 1 % slower again).
   // Priorities (two waves per SIMD): highest right after the hand-over, one lower per
   // sub-step, so the wave that is behind runs first.
   const int T_full = p.K / BK;
-  constexpr int LW = NSUB >= 4 ? NSUB - 1 : 1;           // sub-steps the loads of a slab are spread over
+  constexpr int LW = Cfg::kWaves == 8 ? 2 : (NSUB >= 4 ? NSUB - 1 : 1);   // sub-steps the loads of a slab are spread over
   int stage = 0, t = 0;
   SlabIo io_none{nullptr, nullptr, 0u, 0u};
   auto next_read_stage = [&]() __attribute__((always_inline)) {      // (S > 2: forward by one, or back to stage 0)

@@ -21,12 +21,13 @@ MfmaArgs mfma16_args(const gemm_plan& pl, const void* A, const void* B, void* C,
   a.act = epilogue_activation(d.epilogue);
   a.scale = d.scale;
   a.c_f32 = d.dtype_c == GEMM_F32;
+  a.c_col = d.layout_c == GEMM_COL_MAJOR;
   a.tiles_m = (int)((d.M + BM - 1) / BM);
   a.tiles_n = (int)((d.N + BN - 1) / BN);
-  a.group_m = pl.group_m;
   a.xcd_remap = pl.xcd_remap;
   a.c_cached = pl.c_cached;
   a.batches = (int)d.batch;
+  set_tile_order(a);
   return a;
 }
 

@@ -23,12 +23,13 @@ hipError_t launch_mfma(const gemm_plan& pl, const void* A, const void* B, void* 
   a.act = epilogue_activation(d.epilogue);
   a.scale = d.scale;
   a.c_f32 = d.dtype_c == GEMM_F32;
+  a.c_col = 0;
   a.tiles_m = (int)((d.M + BM - 1) / BM);
   a.tiles_n = (int)((d.N + BN - 1) / BN);
-  a.group_m = pl.group_m;
   a.xcd_remap = pl.xcd_remap;
   a.c_cached = pl.c_cached;
   a.batches = (int)d.batch;
+  set_tile_order(a);
   mfma_gemm_kernel<T, TO, BM, BN, BK, WM, WN, NS><<<pl.grid, pl.block, 0, s>>>(a);
   return hipGetLastError();
 }

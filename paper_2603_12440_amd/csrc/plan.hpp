@@ -11,9 +11,9 @@
 
 namespace mi355gemm {
 
-enum Kind { KIND_SIMT = 0, KIND_MFMA = 1, KIND_SKINNY = 2, KIND_SKINNY_PANEL = 3, KIND_F32_VEC = 4, KIND_MFMA_T = 5 };
+enum Kind { KIND_SIMT = 0, KIND_MFMA = 1, KIND_SKINNY = 2, KIND_SKINNY_PANEL = 3, KIND_F32_VEC = 4, KIND_MFMA_T = 5, KIND_MFMA_G = 6 };
 // (KIND_F32_VEC: the general kernels' grid, fp32 operands in 16-byte pieces; KIND_SKINNY: vector ALUs, a wave per row of W; KIND_SKINNY_PANEL: matrix cores, a workgroup per
-// 32-row panel of W; KIND_MFMA_T: the tiled 16-bit kernels for operands whose K is not contiguous)
+// 32-row panel of W; KIND_MFMA_T: the tiled 16-bit kernels for operands whose K is not contiguous; KIND_MFMA_G: 16-bit operands of any alignment)
 
 struct Config;
 
@@ -24,7 +24,7 @@ struct gemm_plan {
   const mi355gemm::Config* cfg;
   int cfg_index;
   dim3 grid, block;
-  int group_m, xcd_remap; // MFMA scheduling
+  int xcd_remap;          // MFMA scheduling
   // Optional second launch for the columns past d.N (a different tile shape for the part of
   // the problem that does not fill whole rounds of the CUs): its own plan, and the element
   // offsets of its B, C and bias.

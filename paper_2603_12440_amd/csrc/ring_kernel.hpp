@@ -48,11 +48,16 @@ struct RingTile {
   static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES;
   static_assert(A_LOADS * 8 * kWaves == KS * BM && B_LOADS * 8 * kWaves == KS * BN, "loads divide over the waves");
   static_assert(WTM % 16 == 0 && WTN % 16 == 0 && LDS_BYTES <= 160 * 1024, "");
-  static_assert(NSTAGE >= 3 && (NSTAGE - 1) * LOADS <= 63, "outstanding loads fit the counter");
+  static_assert((NSTAGE - 1) * LOADS <= 63, "outstanding loads fit the counter");
 };
 
 // A_KF, B_KF: K is the contiguous index of A / B (16-bit operands may have it strided: see mfma16_gemm_kernel)
-template <typename T, typename TO, int BM, int BN, int WM, int WN, int KS, int NSTAGE, bool A_KF, bool B_KF>
+// DIRECT = false: rows, extents and pointers of any alignment (two bytes), C in either layout.  The same slabs travel
+// global -> registers -> LDS, the next one requested while one is multiplied: 16-byte loads at two-byte alignment
+// inside the matrix, element by element in the last slab's pieces that reach past K.  Such problems ran on
+// the fp32 matrix-core instruction, element by element: 4001^3 bf16 2413 -> 204 us, B row-major 2510 -> 235 us,
+// 1000x1000x1001 83 -> 15 us.
+template <typename T, typename TO, int BM, int BN, int WM, int WN, int KS, int NSTAGE, bool A_KF, bool B_KF, bool DIRECT = true>
 __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
   typedef RingTile<T, BM, BN, WM, WN, KS, NSTAGE> Cfg;
   constexpr int MT = Cfg::MT, NT = Cfg::NT, LOADS = Cfg::LOADS, E = (int)sizeof(T);
@@ -69,46 +74,51 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
   int batch, tm, tn;
   tile_and_batch(p, batch, tm, tn);
   const int r0 = tm * BM, c0 = tn * BN;
-  const char* ga = (const char*)((const T*)p.A + (int64_t)batch * p.stride_a + (A_KF ? (int64_t)r0 * p.lda : (int64_t)r0));
-  const char* gb = (const char*)((const T*)p.B + (int64_t)batch * p.stride_b + (B_KF ? (int64_t)c0 * p.ldb : (int64_t)c0));
+  // K-strided operands of any alignment are addressed from a row that has eight behind it (where there are eight)
+  const int ra = DIRECT || A_KF ? r0 : min(r0, max(p.M - 8, 0)), rb = DIRECT || B_KF ? c0 : min(c0, max(p.N - 8, 0));
+  const char* ga = (const char*)((const T*)p.A + (int64_t)batch * p.stride_a + (A_KF ? (int64_t)ra * p.lda : (int64_t)ra));
+  const char* gb = (const char*)((const T*)p.B + (int64_t)batch * p.stride_b + (B_KF ? (int64_t)rb * p.ldb : (int64_t)rb));
   const int64_t a_step = A_KF ? (int64_t)(KS * 128) : p.lda * (int64_t)(Cfg::BK * E);
   const int64_t b_step = B_KF ? (int64_t)(KS * 128) : p.ldb * (int64_t)(Cfg::BK * E);
 
   // Load q of this wave fills 1 KB of a sub-slab: 8 rows of 128 bytes (K contiguous) or 8 values of K x 64 rows;
-  // rows past the edge are clamped.  kfirst: the first value of K (within the slab) the lane's piece holds.
-  auto a_unit = [&](int q, int ln, uint32_t& off, int& kfirst) __attribute__((always_inline)) {
+  // rows past the edge are clamped.  kfirst: the first value of K (within the slab) the lane's piece holds; row: the
+  // first row (within the tile) of a piece of 8 rows.
+  auto a_unit = [&](int q, int ln, uint32_t& off, int& kfirst, int& row) __attribute__((always_inline)) {
     const int id = wave * Cfg::A_LOADS + q, ks = id / (BM / 8), blk = id % (BM / 8);
     if constexpr (A_KF) {
       const int r = blk * 8 + ln / 8, c = (ln % 8) ^ swz16(r);
       kfirst = (ks * 8 + c) * EPC;
+      row = 0;
       off = (uint32_t)((int64_t)min(r, p.M - 1 - r0) * p.lda * E) + (uint32_t)(ks * 128 + c * 16);
     } else {
       const int kg = blk & 7, j8 = ln >> 3, key = ((j8 >> 1) & 1) | ((kg & 1) << 1);
       kfirst = ks * 64 + kg * 8 + j8;
-      const int row = (blk >> 3) * 64 + ((ln & 7) ^ (key * 2)) * 8;
-      off = (uint32_t)(((int64_t)kfirst * p.lda + min(row, p.M - 8 - r0)) * 2);
+      row = (blk >> 3) * 64 + ((ln & 7) ^ (key * 2)) * 8;
+      off = (uint32_t)(((int64_t)kfirst * p.lda + (DIRECT ? min(row, p.M - 8 - r0) : min(r0 + row, max(p.M - 8, 0)) - ra)) * 2);
     }
   };
-  auto b_unit = [&](int q, int ln, uint32_t& off, int& kfirst) __attribute__((always_inline)) {
+  auto b_unit = [&](int q, int ln, uint32_t& off, int& kfirst, int& row) __attribute__((always_inline)) {
     const int id = wave * Cfg::B_LOADS + q, ks = id / (BN / 8), blk = id % (BN / 8);
     if constexpr (B_KF) {
       const int r = blk * 8 + ln / 8, c = (ln % 8) ^ swz16(r);
       kfirst = (ks * 8 + c) * EPC;
+      row = 0;
       off = (uint32_t)((int64_t)min(r, p.N - 1 - c0) * p.ldb * E) + (uint32_t)(ks * 128 + c * 16);
     } else {
       const int kg = blk & 7, j8 = ln >> 3, key = ((j8 >> 1) & 1) | ((kg & 1) << 1);
       kfirst = ks * 64 + kg * 8 + j8;
-      const int row = (blk >> 3) * 64 + ((ln & 7) ^ (key * 2)) * 8;
-      off = (uint32_t)(((int64_t)kfirst * p.ldb + min(row, p.N - 8 - c0)) * 2);
+      row = (blk >> 3) * 64 + ((ln & 7) ^ (key * 2)) * 8;
+      off = (uint32_t)(((int64_t)kfirst * p.ldb + (DIRECT ? min(row, p.N - 8 - c0) : min(c0 + row, max(p.N - 8, 0)) - rb)) * 2);
     }
   };
   uint32_t a_off[Cfg::A_LOADS], b_off[Cfg::B_LOADS];
   {
-    int unused;
+    int unused, unused2;
 #pragma unroll
-    for (int q = 0; q < Cfg::A_LOADS; ++q) a_unit(q, lane, a_off[q], unused);
+    for (int q = 0; q < Cfg::A_LOADS; ++q) a_unit(q, lane, a_off[q], unused, unused2);
 #pragma unroll
-    for (int q = 0; q < Cfg::B_LOADS; ++q) b_unit(q, lane, b_off[q], unused);
+    for (int q = 0; q < Cfg::B_LOADS; ++q) b_unit(q, lane, b_off[q], unused, unused2);
   }
   const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_uchar_t*)smem;
   auto uniform_ptr = [](const char* q) __attribute__((always_inline)) {
@@ -181,6 +191,63 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
     }
   };
 
+  if constexpr (!DIRECT) {
+    struct __attribute__((packed, aligned(2))) Piece { u32x4_t v; };
+    u32x4_t av[Cfg::A_LOADS], bv[Cfg::B_LOADS];
+    // n valid values from `at` on, zeros behind them
+    auto partial = [](const char* at, int n) __attribute__((always_inline)) {
+      uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (e < n) w[e >> 1] |= (uint32_t)*(const uint16_t*)(at + e * 2) << (16 * (e & 1));
+      return u32x4_t{w[0], w[1], w[2], w[3]};
+    };
+    // One operand's pieces of slab t.  K contiguous: only the last slab reaches past K.  K strided: a piece that
+    // reaches past the last row is read from eight rows before the end and moved down (what ends up in rows past the
+    // edge does not matter, their results are dropped); values of K past the end are zeros.
+    auto load_op = [&](auto kf_c, auto loads_c, u32x4_t* v, const uint32_t* off_in, const char* base, int left, int rows, int first,
+                       auto unit) __attribute__((always_inline)) {
+      constexpr bool kf = decltype(kf_c)::value;
+      constexpr int loads = decltype(loads_c)::value;
+      constexpr int tile = loads * 8 * Cfg::kWaves / KS;
+      if (left >= Cfg::BK && (kf || first + tile <= rows)) {
+#pragma unroll
+        for (int q = 0; q < loads; ++q) v[q] = ((const Piece*)(base + off_in[q]))->v;
+        return;
+      }
+#pragma unroll
+      for (int q = 0; q < loads; ++q) {
+        uint32_t off; int k, row;
+        unit(q, lane, off, k, row);
+        if constexpr (kf) {
+          v[q] = partial(base + off, left - k);
+        } else if (rows < 8) {
+          v[q] = partial(base + off, k < left ? rows - first - row : 0);
+        } else {
+          unsigned __int128 w = 0;
+          if (k < left) w = __builtin_bit_cast(unsigned __int128, ((const Piece*)(base + off))->v);
+          v[q] = __builtin_bit_cast(u32x4_t, w >> (16 * min(7, max(0, first + row - (rows - 8)))));
+        }
+      }
+    };
+    auto load = [&](int t) __attribute__((always_inline)) {
+      const int left = p.K - t * Cfg::BK;
+      load_op(std::integral_constant<bool, A_KF>(), std::integral_constant<int, Cfg::A_LOADS>(), av, a_off, ga + (int64_t)t * a_step, left, p.M, r0, a_unit);
+      load_op(std::integral_constant<bool, B_KF>(), std::integral_constant<int, Cfg::B_LOADS>(), bv, b_off, gb + (int64_t)t * b_step, left, p.N, c0, b_unit);
+    };
+    const int T_all = (p.K + Cfg::BK - 1) / Cfg::BK;
+    load(0);
+    for (int t = 0; t < T_all; ++t) {
+      unsigned char* to = smem + (t & 1) * Cfg::STAGE_BYTES;       // (last read two slabs ago, a barrier in between)
+#pragma unroll
+      for (int q = 0; q < Cfg::A_LOADS; ++q) *(u32x4_t*)(to + (wave * Cfg::A_LOADS + q) * 1024 + lane * 16) = av[q];
+#pragma unroll
+      for (int q = 0; q < Cfg::B_LOADS; ++q) *(u32x4_t*)(to + Cfg::A_BYTES + (wave * Cfg::B_LOADS + q) * 1024 + lane * 16) = bv[q];
+      __syncthreads();
+      if (t + 1 < T_all) load(t + 1);
+      multiply(t & 1);
+    }
+  } else {
   const int T_full = p.K / Cfg::BK;
   const int ahead = NSTAGE - 1;
   for (int t = 0; t < ahead && t < T_full; ++t) issue(t);
@@ -208,22 +275,23 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
     const char* tb = gb;
 #pragma unroll
     for (int q = 0; q < Cfg::A_LOADS; ++q) {
-      uint32_t off; int k;
-      a_unit(q, lane, off, k);
+      uint32_t off; int k, row;
+      a_unit(q, lane, off, k, row);
       u32x4_t v = {0u, 0u, 0u, 0u};
       if (k < kvalid) v = *(const u32x4_t*)(ta + off);
       *(u32x4_t*)(smem + (wave * Cfg::A_LOADS + q) * 1024 + lane * 16) = v;
     }
 #pragma unroll
     for (int q = 0; q < Cfg::B_LOADS; ++q) {
-      uint32_t off; int k;
-      b_unit(q, lane, off, k);
+      uint32_t off; int k, row;
+      b_unit(q, lane, off, k, row);
       u32x4_t v = {0u, 0u, 0u, 0u};
       if (k < kvalid) v = *(const u32x4_t*)(tb + off);
       *(u32x4_t*)(smem + Cfg::A_BYTES + (wave * Cfg::B_LOADS + q) * 1024 + lane * 16) = v;
     }
     __syncthreads();
     multiply(0);
+  }
   }
 
   // Lane l of a 16x16 accumulator tile holds row l % 16 and columns 4 (l / 16) .. +3 (operands go in swapped).
@@ -244,6 +312,17 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
       float v[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = apply_activation(p.act, acc[m][n][e] + bv[e], p.scale);
+      if constexpr (!DIRECT) {
+        const int64_t si = p.c_col ? 1 : p.ldc, sj = p.c_col ? p.ldc : 1;
+        const int64_t o = (int64_t)batch * p.stride_c + i * si + j * sj;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (j + e >= p.N) break;
+          if (p.c_f32) ((float*)p.C)[o + e * sj] = v[e];
+          else ((TO*)p.C)[o + e * sj] = from_float<TO>(v[e]);
+        }
+        continue;
+      }
       const int64_t o = (int64_t)batch * p.stride_c + (int64_t)i * p.ldc + j;
       if (p.c_f32) {
         float* c = (float*)p.C + o;

@@ -23,6 +23,27 @@ hipError_t launch_ring(const gemm_plan& pl, const void* A, const void* B, void* 
 #define MI355GEMM_RINGS_T(X)                  \
   X(64, 64, 2, 4, 2, 4, 0.44, 0.0)            \
   X(64, 64, 2, 4, 1, 5, 0.28, 0.375)
+// operands of any alignment: X(BM, BN, WM, WN, KS, t1, t2)
+template <typename T, int BM, int BN, int WM, int WN, int KS>
+hipError_t launch_mfma16g(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias, hipStream_t s) {
+  const MfmaArgs a = mfma16_args<BM, BN>(pl, A, B, C, bias);
+  const bool ak = pl.d.layout_a == GEMM_ROW_MAJOR, bk = pl.d.layout_b == GEMM_COL_MAJOR;
+  if (ak && bk) ring_gemm_kernel<T, T, BM, BN, WM, WN, KS, 2, true, true, false><<<pl.grid, pl.block, 0, s>>>(a);
+  else if (ak) ring_gemm_kernel<T, T, BM, BN, WM, WN, KS, 2, true, false, false><<<pl.grid, pl.block, 0, s>>>(a);
+  else if (bk) ring_gemm_kernel<T, T, BM, BN, WM, WN, KS, 2, false, true, false><<<pl.grid, pl.block, 0, s>>>(a);
+  else ring_gemm_kernel<T, T, BM, BN, WM, WN, KS, 2, false, false, false><<<pl.grid, pl.block, 0, s>>>(a);
+  return hipGetLastError();
+}
+#define MI355GEMM_MFMA16G_TILES(X)     \
+  X(64, 64, 2, 2, 1, 0.40, 0.50)       \
+  X(128, 128, 2, 4, 1, 0.80, 1.0)
+#define MI355GEMM_MFMA16G_DECLARE(T, BM, BN, WM, WN, KS)                               \
+  extern template hipError_t launch_mfma16g<T, BM, BN, WM, WN, KS>(                    \
+      const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
+#define MI355GEMM_MFMA16G_DEFINE(T, BM, BN, WM, WN, KS)                                \
+  template hipError_t launch_mfma16g<T, BM, BN, WM, WN, KS>(                           \
+      const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
+
 #define MI355GEMM_RING_DECLARE(T, TO, BM, BN, WM, WN, KS, NS, AK, BK)                 \
   extern template hipError_t launch_ring<T, TO, BM, BN, WM, WN, KS, NS, AK, BK>(       \
       const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
