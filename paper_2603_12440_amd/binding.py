@@ -213,14 +213,32 @@ def _dev_ptr(x) -> Optional[int]:
     return x.data_ptr()
 
 
+_raw_stream = None          # (torch's raw-stream getter, its current-device getter), once torch is in
+
+
+def _current_stream() -> int:
+    """The hipStream_t of torch's current stream on the current device, asked anew on every call.  (Small products are
+    bound by the call itself: torch.cuda.current_stream() builds a Stream object for it, a third of the call's time.)"""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        torch.cuda.current_stream()          # initialises the runtime, raises where there is no GPU
+        _raw_stream = (getattr(torch._C, "_cuda_getCurrentRawStream", None) or
+                       (lambda device: torch.cuda.current_stream(device).cuda_stream),
+                       getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device)
+    get, device = _raw_stream
+    return get(device())
+
+
 def gemm_run(plan: Plan, A, B, C, bias=None, stream: Optional[int] = None) -> None:
     """Enqueue C = epilogue(A.B) on `stream` (a raw hipStream_t value; default:
     torch's current stream).  A, B, C, bias: torch device tensors or raw addresses."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
-    _check(load_library().gemm_run(plan.handle, _dev_ptr(A), _dev_ptr(B), _dev_ptr(C),
-                                   _dev_ptr(bias), stream or None))
+        stream = _current_stream()
+    status = (_lib or load_library()).gemm_run(plan.handle, _dev_ptr(A), _dev_ptr(B), _dev_ptr(C), _dev_ptr(bias),
+                                               stream or None)
+    if status:
+        _check(status)
 
 
 def gemm_run_workspace(plan: Plan, A, B, C, bias=None, workspace=None, workspace_bytes: Optional[int] = None,
@@ -228,8 +246,7 @@ def gemm_run_workspace(plan: Plan, A, B, C, bias=None, workspace=None, workspace
     """As gemm_run, with a caller-provided device workspace (a torch tensor or a raw address
     plus workspace_bytes) for plans that need one."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
+        stream = _current_stream()
     if workspace_bytes is None:
         workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(load_library().gemm_run_workspace(plan.handle, _dev_ptr(A), _dev_ptr(B), _dev_ptr(C), _dev_ptr(bias),
@@ -243,8 +260,7 @@ def gemm_run_fixed_scratch(plan: Plan, A, B, C, bias=None, stream: Optional[int]
     """As gemm_run_workspace, with the library's own fixed scratch buffer (no allocation anywhere;
     plans that need more than FIXED_SCRATCH_BYTES are refused)."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
+        stream = _current_stream()
     _check(load_library().gemm_run_fixed_scratch(plan.handle, _dev_ptr(A), _dev_ptr(B), _dev_ptr(C),
                                                  _dev_ptr(bias), stream or None))
 
@@ -254,8 +270,7 @@ def gemm_tune(desc: GemmDesc, A, B, C, bias=None, stream: Optional[int] = None,
     """Time every applicable tile configuration on the given device buffers; returns
     (best_config_index, {config_name: microseconds per launch})."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
+        stream = _current_stream()
     lib = load_library()
     n = lib.gemm_config_count()
     best = ctypes.c_int(-1)
@@ -308,8 +323,7 @@ def rope_apply(desc: RopeDesc, tensors, cos, sin, stream: Optional[int] = None) 
     """Enqueue the rotary embedding of one or two tensors (a list of RopeTensor) that share
     positions and tables, in one launch.  cos, sin: torch device tensors or raw addresses."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
+        stream = _current_stream()
     arr = (RopeTensor * len(tensors))(*tensors)
     _check(load_library().rope_apply(ctypes.byref(desc), arr, len(tensors), _dev_ptr(cos), _dev_ptr(sin),
                                      stream or None))
@@ -319,8 +333,7 @@ def probe_mfma_peak(dtype: int, sink, stream: Optional[int] = None, min_seconds:
                     refresh_operands: bool = False) -> float:
     """TFLOP/s of an MFMA-only register loop on the current device (blocks until done)."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
+        stream = _current_stream()
     out = ctypes.c_double(0.0)
     _check(load_library().probe_mfma_peak(dtype, int(refresh_operands), _dev_ptr(sink), stream or None,
                                           min_seconds, ctypes.byref(out)))
@@ -331,8 +344,7 @@ def probe_mfma16_peak(dtype: int, sink, stream: Optional[int] = None, min_second
                     refresh_operands: bool = False) -> float:
     """TFLOP/s of an MFMA-only register loop on the 16x16x32 shape on the current device (blocks until done)."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
+        stream = _current_stream()
     out = ctypes.c_double(0.0)
     _check(load_library().probe_mfma16_peak(dtype, int(refresh_operands), _dev_ptr(sink), stream or None,
                                           min_seconds, ctypes.byref(out)))
@@ -342,8 +354,7 @@ def probe_mfma16_peak(dtype: int, sink, stream: Optional[int] = None, min_second
 def probe_read_peak(src, nbytes: int, sink, stream: Optional[int] = None, min_seconds: float = 0.3) -> float:
     """GB/s of a streaming read of `nbytes` (>= 1 GiB) of the device buffer `src` (blocks until done)."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
+        stream = _current_stream()
     out = ctypes.c_double(0.0)
     _check(load_library().probe_read_peak(_dev_ptr(src), nbytes, _dev_ptr(sink), stream or None, min_seconds,
                                           ctypes.byref(out)))
