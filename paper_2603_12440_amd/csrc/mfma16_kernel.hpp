@@ -299,30 +299,30 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
 
   // K tail: chunks past K must read as zero, which a direct-to-LDS load cannot do, so that one
   // slab goes through registers.  (K is a multiple of 8 where an operand's K is contiguous: chunks are never split.)
-  auto issue_loads_tail = [&](int kt, int stage) __attribute__((always_inline)) {
+  // The four-wave tiles have the registers to request it before the first slab (PRE), which hides its latency.
+  constexpr bool PRE = !PERSIST && Cfg::kWaves == 4 && BM * BN <= 128 * 128;
+  u32x4_t tail_v[kLoads];
+  auto load_tail_q = [&](int kt, int q) __attribute__((always_inline)) {
     const int kvalid = p.K - kt * BK;
-    const char* ga = Ab + (int64_t)kt * a_step;
-    const char* gb = Bb + (int64_t)kt * b_step;
-    unsigned char* sa = smem + stage * Cfg::STAGE_BYTES + wave * (Cfg::A_LOADS * 1024);
-    unsigned char* sb = smem + stage * Cfg::STAGE_BYTES + Cfg::A_BYTES + wave * (Cfg::B_LOADS * 1024);
-#pragma unroll
-    for (int q = 0; q < Cfg::A_LOADS; ++q) {
+    u32x4_t v = {0u, 0u, 0u, 0u};
+    if (q < Cfg::A_LOADS) {
       const int r = (wave * Cfg::A_LOADS + q) * RPI + lane / CPR;
       int k = ((lane % CPR) ^ swz16(r)) * 8, row = 0;            // the piece's first value of K
       if constexpr (!A_KF) strided_unit(wave * Cfg::A_LOADS + q, lane, k, row);
-      u32x4_t v = {0u, 0u, 0u, 0u};
-      if (k < kvalid) v = *(const u32x4_t*)(ga + a_off[q]);
-      *(u32x4_t*)(sa + q * 1024 + lane * 16) = v;
+      if (k < kvalid) v = *(const u32x4_t*)(Ab + (int64_t)kt * a_step + a_off[q < Cfg::A_LOADS ? q : 0]);
+    } else {
+      const int qb = q >= Cfg::A_LOADS ? q - Cfg::A_LOADS : 0;
+      const int r = (wave * Cfg::B_LOADS + qb) * RPI + lane / CPR;
+      int k = ((lane % CPR) ^ swz16(r)) * 8, row = 0;
+      if constexpr (!B_KF) strided_unit(wave * Cfg::B_LOADS + qb, lane, k, row);
+      if (k < kvalid) v = *(const u32x4_t*)(Bb + (int64_t)kt * b_step + b_off[qb]);
     }
-#pragma unroll
-    for (int q = 0; q < Cfg::B_LOADS; ++q) {
-      const int r = (wave * Cfg::B_LOADS + q) * RPI + lane / CPR;
-      int k = ((lane % CPR) ^ swz16(r)) * 8, row = 0;            // the piece's first value of K
-      if constexpr (!B_KF) strided_unit(wave * Cfg::B_LOADS + q, lane, k, row);
-      u32x4_t v = {0u, 0u, 0u, 0u};
-      if (k < kvalid) v = *(const u32x4_t*)(gb + b_off[q]);
-      *(u32x4_t*)(sb + q * 1024 + lane * 16) = v;
-    }
+    return v;
+  };
+  auto store_tail_q = [&](int q, const u32x4_t& v) __attribute__((always_inline)) {       // into stage 0
+    unsigned char* to = q < Cfg::A_LOADS ? smem + wave * (Cfg::A_LOADS * 1024) + q * 1024
+                                         : smem + Cfg::A_BYTES + wave * (Cfg::B_LOADS * 1024) + (q - Cfg::A_LOADS) * 1024;
+    *(u32x4_t*)(to + lane * 16) = v;
   };
 
   // ---- LDS -> fragment addressing ---------------------------------------------------------
@@ -791,6 +791,12 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   typedef std::integral_constant<bool, false> no_t;
 
   if constexpr (!PERSIST) {
+  if constexpr (PRE) {
+    if (T_full * BK < p.K) {
+#pragma unroll
+      for (int q = 0; q < kLoads; ++q) tail_v[q] = load_tail_q(T_full, q);
+    }
+  }
   if (T_full > 0) {
     // the first S slabs (as many as there are); the first one has landed when the others' loads are left
     static_for<0, S>([&](auto q_c) __attribute__((always_inline)) {
@@ -818,7 +824,11 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   if (T_full * BK < p.K) {                     // K tail, through registers with zero fill
     __builtin_amdgcn_s_barrier();              // every wave is done with the LDS stages
     asm volatile("" ::: "memory");
-    issue_loads_tail(T_full, 0);
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) {
+      if constexpr (!PRE) tail_v[q] = load_tail_q(T_full, q);
+      store_tail_q(q, tail_v[q]);
+    }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");

@@ -250,6 +250,28 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
   } else {
   const int T_full = p.K / Cfg::BK;
   const int ahead = NSTAGE - 1;
+  // K tail: requested before everything else and kept in registers, so that its latency (3 us at the end of a call
+  // that takes 10) is hidden behind the slabs.  Pieces past K are zeros.
+  const int kvalid = p.K - T_full * Cfg::BK;
+  u32x4_t ta[Cfg::A_LOADS], tb[Cfg::B_LOADS];
+  if (kvalid > 0) {
+    const char* pa = ga + (int64_t)T_full * a_step;
+    const char* pb = gb + (int64_t)T_full * b_step;
+#pragma unroll
+    for (int q = 0; q < Cfg::A_LOADS; ++q) {
+      uint32_t off; int k, row;
+      a_unit(q, lane, off, k, row);
+      ta[q] = u32x4_t{0u, 0u, 0u, 0u};
+      if (k < kvalid) ta[q] = *(const u32x4_t*)(pa + off);
+    }
+#pragma unroll
+    for (int q = 0; q < Cfg::B_LOADS; ++q) {
+      uint32_t off; int k, row;
+      b_unit(q, lane, off, k, row);
+      tb[q] = u32x4_t{0u, 0u, 0u, 0u};
+      if (k < kvalid) tb[q] = *(const u32x4_t*)(pb + off);
+    }
+  }
   for (int t = 0; t < ahead && t < T_full; ++t) issue(t);
   int st = 0;                                            // stage of slab t
   for (int t = 0; t < T_full; ++t) {
@@ -266,29 +288,14 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
     multiply(st);
     st = st + 1 == NSTAGE ? 0 : st + 1;
   }
-  if (T_full * Cfg::BK < p.K) {                          // K tail, through registers with zero fill, in stage 0
+  if (kvalid > 0) {                                      // the K tail, in stage 0
     wait_lgkmcnt<0>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    const int kvalid = p.K - T_full * Cfg::BK;
-    const char* ta = ga;                                 // (the slabs are all requested: ga and gb are at the tail)
-    const char* tb = gb;
 #pragma unroll
-    for (int q = 0; q < Cfg::A_LOADS; ++q) {
-      uint32_t off; int k, row;
-      a_unit(q, lane, off, k, row);
-      u32x4_t v = {0u, 0u, 0u, 0u};
-      if (k < kvalid) v = *(const u32x4_t*)(ta + off);
-      *(u32x4_t*)(smem + (wave * Cfg::A_LOADS + q) * 1024 + lane * 16) = v;
-    }
+    for (int q = 0; q < Cfg::A_LOADS; ++q) *(u32x4_t*)(smem + (wave * Cfg::A_LOADS + q) * 1024 + lane * 16) = ta[q];
 #pragma unroll
-    for (int q = 0; q < Cfg::B_LOADS; ++q) {
-      uint32_t off; int k, row;
-      b_unit(q, lane, off, k, row);
-      u32x4_t v = {0u, 0u, 0u, 0u};
-      if (k < kvalid) v = *(const u32x4_t*)(tb + off);
-      *(u32x4_t*)(smem + Cfg::A_BYTES + (wave * Cfg::B_LOADS + q) * 1024 + lane * 16) = v;
-    }
+    for (int q = 0; q < Cfg::B_LOADS; ++q) *(u32x4_t*)(smem + Cfg::A_BYTES + (wave * Cfg::B_LOADS + q) * 1024 + lane * 16) = tb[q];
     __syncthreads();
     multiply(0);
   }
