@@ -25,6 +25,7 @@
 #include "simt_kernel.hpp"
 #include "general_mfma_kernel.hpp"
 #include "f32_mfma_kernel.hpp"
+#include "f32_ring_kernel.hpp"
 #include "skinny_kernel.hpp"
 #include "ring_launch.hpp"
 #include "splitk_kernel.hpp"
@@ -145,6 +146,18 @@ hipError_t launch_f32_mfma(const gemm_plan& pl, const void* A, const void* B, vo
     return launch_general_mfma_typed<float, float, TM, TN, 16>(pl, A, B, C, bias, s);
   const SimtArgs a = simt_args(pl, A, B, C, bias);
   const bool ak = d.layout_a == GEMM_ROW_MAJOR, bk = d.layout_b == GEMM_COL_MAJOR;   // K contiguous?
+  // slabs straight to LDS, where 32-bit offsets inside a slab suffice
+  const int64_t lim = (int64_t)1 << 32, kMax = ((int64_t)1 << 31) - 512;
+  if ((TM + 1) * d.lda * 4 < lim && (TN + 1) * d.ldb * 4 < lim && d.M < kMax && d.N < kMax && d.K < kMax) {
+    constexpr int MT = TM / 64, S = MT == 1 ? 3 : 2;    // three workgroups per CU, or two
+    MfmaArgs r = mfma16_args<TM, TN>(pl, A, B, C, bias);
+    r.xcd_remap = d.batch == 1 || (r.tiles_m * (int64_t)r.tiles_n) % 8 == 0;
+    if (ak && bk) f32_ring_kernel<true, true, MT, S><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
+    else if (ak) f32_ring_kernel<true, false, MT, S><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
+    else if (bk) f32_ring_kernel<false, true, MT, S><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
+    else f32_ring_kernel<false, false, MT, S><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
+    return hipGetLastError();
+  }
   if (ak && bk) f32_mfma_kernel<true, true, TM, TN><<<pl.grid, pl.block, 0, s>>>(a);
   else if (ak) f32_mfma_kernel<true, false, TM, TN><<<pl.grid, pl.block, 0, s>>>(a);
   else if (bk) f32_mfma_kernel<false, true, TM, TN><<<pl.grid, pl.block, 0, s>>>(a);
@@ -546,6 +559,24 @@ int find_config(const char* name) {
 //     0.6 us from the second round on, where the two-slab kernels are better (7195x7312x1448: 258 against 183 us).
 //     An operand whose rows do not start on 128-byte lines costs 0.35 of that on top: every piece of 128 bytes
 //     touches two lines (384x4104x4104: 43 us, 384x4096x4096: 24 us).
+double round_cost(const Config& c, const gemm_desc_t& d, int64_t N, double* rounds_out) {
+  const int64_t M = d.M, K = d.K;
+  const int e = esize(d.dtype_a), area = c.bm * c.bn;
+  const double tiles = (double)((M + c.bm - 1) / c.bm) * (double)((N + c.bn - 1) / c.bn) * (double)d.batch;
+  const double cus = num_cus();
+  const int per_cu = area <= 128 * 128 ? 2 : 1;                 // workgroups that fit one CU's LDS
+  // (256x192 measured: 0.85 - 1.03 of the 256x256 tile per FLOP on 4096x6144x4096, 4096x14336x4096, 8192^3)
+  double eff = area >= 256 * 256 ? 1.0 : (area >= 256 * 192 ? 0.88 : (area >= 256 * 128 ? 0.75 : 0.84));
+  // the 16x16x32 kernels: about a tenth faster per FLOP than the 32x32x16 ones at the same tile shape
+  // (8192^3: 732 against 800 us); of the two 256x256 shapes the eight-wave one goes first
+  if (!std::strncmp(c.name, "mfma16", 6)) eff *= c.threads == 256 && area >= 256 * 256 ? 1.08 : 1.10;
+  const double rounds = (double)(int64_t)((tiles + cus * per_cu - 1) / (cus * per_cu));
+  // workgroups that actually share a CU (a lone workgroup runs about per_cu times faster)
+  const double sharing = tiles >= cus * per_cu ? per_cu : (tiles > cus ? tiles / cus : 1.0);
+  *rounds_out = rounds;
+  return rounds * area * sharing / eff * ((double)K + 600.0) / (e == 1 ? 5.4e6 : 2.7e6);
+}
+
 double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
   const int64_t M = d.M, K = d.K, batch = d.batch;
   const int e = esize(d.dtype_a);
@@ -560,21 +591,13 @@ double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
     if (area >= 128 * 128 && c.kind != KIND_MFMA_G) {
       const double busy = fmin(1.0, fmax(0.0, tiles / cus - 0.5) * 2.0);
       const double t1 = (0.33 + 0.12 * busy) * pitch;
-      return per_cu > 1 ? per_cu * (slabs * fmax(0.6, t1) + 5.0) : 4.0 + slabs * t1;
+      return per_cu > 1 ? per_cu * (slabs * fmax(0.6, t1) + 5.0) : 4.6 + slabs * t1;
     }
     const double pairs = c.t2 > 0 ? (double)(int64_t)(per_cu / 2) : 0.0, singles = per_cu - 2 * pairs;
     return 2.7 + (singles * c.t1 + pairs * c.t2) * slabs * pitch + (singles + pairs - 1) * 2.4;
   }
-  const int per_cu = area <= 128 * 128 ? 2 : 1;                 // workgroups that fit one CU's LDS
-  // (256x192 measured: 0.85 - 1.03 of the 256x256 tile per FLOP on 4096x6144x4096, 4096x14336x4096, 8192^3)
-  double eff = area >= 256 * 256 ? 1.0 : (area >= 256 * 192 ? 0.88 : (area >= 256 * 128 ? 0.75 : 0.84));
-  // the 16x16x32 kernels: about a tenth faster per FLOP than the 32x32x16 ones at the same tile shape
-  // (8192^3: 732 against 800 us); of the two 256x256 shapes the eight-wave one goes first
-  if (!std::strncmp(c.name, "mfma16", 6)) eff *= c.threads == 256 && area >= 256 * 256 ? 1.08 : 1.10;
-  const double rounds = (double)(int64_t)((tiles + cus * per_cu - 1) / (cus * per_cu));
-  // workgroups that actually share a CU (a lone workgroup runs about per_cu times faster)
-  const double sharing = tiles >= cus * per_cu ? per_cu : (tiles > cus ? tiles / cus : 1.0);
-  const double work = rounds * area * sharing / eff * ((double)K + 600.0) / (e == 1 ? 5.4e6 : 2.7e6);
+  double rounds = 0;
+  const double work = round_cost(c, d, N, &rounds);
   const double wait = rounds * ((double)K / c.bk * (area <= 128 * 128 ? (e == 1 ? 0.42 * (1.0 + 0.5 * off_line) : 0.60 * (1.0 + 0.2 * off_line)) : 0.0) + 3.0);
   return work > wait ? work : wait;
 }
@@ -624,9 +647,9 @@ int choose_general(const gemm_desc_t& d) {
   //     (256^3: 5 us against 11 us for the next choice; 512^3: 11 to 12 against 19 us);
   //   * very few 32x32 tiles (16-bit operands in layouts the tiled kernels do not take): the vector-ALU
   //     kernel with 32x32 tiles and the long K step;
-  //   * fp32 in float4 groups: the fp32-MFMA kernel with double-buffered slabs, 128x128 tiles from two
-  //     tiles per CU on (4096^3: 1.13 to 1.18 ms = 116 to 122 TFLOP/s; the general kernel needs 1.47 ms),
-  //     64x64 tiles below (2048^3: 184 us, 1024^3: 42 us; general kernel 219 / 53 us);
+  //   * fp32 in float4 groups: the fp32-MFMA kernels with slabs straight to LDS, 128x128 tiles from four
+  //     tiles per CU on (4096^3: 0.94 to 0.96 ms = 143 to 147 TFLOP/s, 64x64 tiles 1.03 to 1.05, the general kernel 1.47),
+  //     64x64 tiles below (3000^3: 444 us, 2048^3: 143 to 149, 1024^3: 24; general kernel 658 / 213 / 53 us);
   //   * otherwise the general fp32-MFMA kernel: 64x64 tiles until there are four 128x128 tiles per CU.
   const double tiles32 = (double)((d.M + 31) / 32) * (double)((d.N + 31) / 32) * d.batch;
   const double tiles128 = (double)((d.M + 127) / 128) * (double)((d.N + 127) / 128) * d.batch;
@@ -635,8 +658,8 @@ int choose_general(const gemm_desc_t& d) {
     if (i >= 0 && applicable(kConfigs[i], d)) return i;
   }
   if (tiles32 <= 2.0 * num_cus()) return find_config("simt_32x32x64");
-  {                                             // fp32 in float4 groups: 128x128 tiles from two per CU on
-    const int i = find_config(tiles128 >= 2.0 * num_cus() ? "f32mfma_128x128x32" : "f32mfma_64x64x32");
+  {                                             // fp32 in float4 groups: 128x128 tiles from four per CU on
+    const int i = find_config(tiles128 >= 4.0 * num_cus() ? "f32mfma_128x128x32" : "f32mfma_64x64x32");
     if (i >= 0 && applicable(kConfigs[i], d)) return i;
   }
   return find_config(tiles128 >= 4.0 * num_cus() ? "general_mfma32_128x128x16" : "general_mfma32_64x64x16");
@@ -822,9 +845,10 @@ int gemm_create_config(const gemm_desc_t* desc, int config, gemm_plan_t** out_pl
 }
 
 // Slices of K for a split-K plan: the count (up to 64, K a multiple of 8 x slices, whole
-// slabs per slice preferred) that minimises the tile cost model of the sliced product plus
-// the traffic of the fp32 partials (written once, read once: priced at 4 TB/s).  512x512x32768 takes 46 / 31 / 29 / 38 us with 8 / 16 / 32 / 64 slices;
-// the model picks 16.
+// slabs per slice preferred) that minimises the round model of the two-slab tiles on the sliced product plus
+// the traffic of the fp32 partials (written once, read once: priced at 2 TB/s).  512x512x32768 takes 31 / 25 / 38 / 40 us
+// with 8 / 16 / 32 / 64 slices; the model picks 16.  (The count decides the workspace's size and how long the fp32 sums
+// are: it is not the four-slab kernels' model, which would take fewer slices and add more terms in each.)
 static int choose_splits(const gemm_desc_t& d) {
   int best = 1;
   double best_cost = 0;
@@ -838,8 +862,14 @@ static int choose_splits(const gemm_desc_t& d) {
       in.batch = (int32_t)s;
       in.stride_a = in.stride_b = in.K;
       double cost = 0;
-      if (best_mfma(in, &cost) < 0) continue;
-      cost += 2.0 * (double)s * (double)d.M * (double)d.N * 4.0 / 4.0e6;
+      for (int i = 0; i < kNumConfigs; ++i) {
+        if (kConfigs[i].kind != KIND_MFMA || kConfigs[i].t1 > 0 || !applicable(kConfigs[i], in)) continue;
+        double rounds = 0;
+        const double t = round_cost(kConfigs[i], in, in.N, &rounds) * (esize(d.dtype_a) == 1 ? 2.0 : 1.0);
+        if (cost == 0 || t < cost) cost = t;
+      }
+      if (cost == 0) continue;
+      cost += 2.0 * (double)s * (double)d.M * (double)d.N * 4.0 / 2.0e6;
       if (best_cost == 0 || cost < best_cost) { best = (int)s; best_cost = cost; }
     }
   }

@@ -1,0 +1,34 @@
+"""fp32 products with slabs of K straight to LDS: bit exact on small integers for every layout, around tile edges, K tails
+and the ring's fill and drain, for both tile sizes."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from helpers import run_gpu, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def g():
+    import paper_2603_12440_amd as g
+    g.load_library()
+    assert torch.cuda.is_available()
+    return g
+
+
+@pytest.mark.parametrize("la,lb", [("row", "row"), ("row", "col"), ("col", "row"), ("col", "col")])
+@pytest.mark.parametrize("M,N,K,batch", [(4, 4, 4, 1), (64, 64, 32, 1), (68, 132, 36, 1), (128, 64, 64, 8), (132, 260, 100, 3), (260, 72, 128, 2), (192, 128, 292, 1)])
+def test_exact(g, oracle, la, lb, M, N, K, batch):
+    for cfg in ("f32mfma_64x64x32", "f32mfma_128x128x32"):
+        for lc in ("row", "col"):
+            w = wl.Workload("t", M, N, K, dtype="f32", layout_a=la, layout_b=lb, batch=batch, epilogue="bias_relu",
+                            seed_a=M + 1, seed_b=N + 2)
+            sa, sb = wl.operand_shapes(w)
+            A = wl.small_integers(sa, w.seed_a, -2, 2, "f32")
+            B = wl.small_integers(sb, w.seed_b, -2, 2, "f32")
+            bias = wl.small_integers((N,), w.seed_bias, -3, 3, "f32")
+            print(f"{M}x{N}x{K} b{batch} {la}/{lb}/{lc} {cfg}", flush=True)
+            C = run_gpu(g, w, A, B, bias, config=g.config_names().index(cfg), layout_c=lc, pad_a=4, pad_b=8, pad_c=1)
+            assert np.array_equal(wl.to_float64(C), run_oracle(oracle, w, A, B, bias, want=("y",))["y"]), (cfg, lc)
