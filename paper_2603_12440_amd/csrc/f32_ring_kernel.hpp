@@ -4,7 +4,7 @@
 // f32_mfma_kernel.hpp stages its slabs through registers: every slab costs address arithmetic, LDS writes and a wait for
 // loads that were requested one slab earlier, on the critical path of a wave that has one 32x32 tile to multiply.  Here
 // the slabs go global -> LDS directly (NSTAGE - 1 of them on their way, one barrier each), as in ring_kernel.hpp.
-// 64x64 tiles (three stages, three workgroups per CU) 2000x1500x1100 77.8 -> 59.9 us, 1024^3 41 -> 24; 128x128 tiles (two
+// 64x64 tiles (three stages, three workgroups per CU) 2000x1500x1100 77.5 -> 58.2 us, 1024^3 41 -> 24; 128x128 tiles (two
 // stages, two workgroups) 4096^3 1183 -> 962 us = 143 TFLOP/s.  Bound by the fp32 matrix pipes (157 TFLOP/s) in the large,
 // by how evenly the tiles divide over the CUs and by one turn of barrier and LDS reads per slab in the small.
 // LDS: K contiguous, 128-byte rows of 32 values, 16-byte chunk c of row r at slot c ^ swz16(r); K strided, 1 KB blocks
