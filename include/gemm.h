@@ -198,7 +198,7 @@ int gemm_autotune_clear(void);
  * several passes with a device-wide synchronisation between them).
  *
  * gemm_create_splitk - as gemm_create, for batch == 1 problems the matrix-core kernels can
- *   take (16-bit or fp8 operands, K-contiguous A and B, every slice a whole number of 16-byte pieces).  splits >= 1, or
+ *   take (16-bit or fp8 operands, K-contiguous A and B, lda, ldb and every slice a whole number of 16-byte pieces).  splits >= 1, or
  *   0 for a built-in choice (which may be 1).  GEMM_ERR_UNSUPPORTED if the problem or the
  *   split cannot be served.
  * gemm_workspace_bytes - bytes of device memory the plan needs as workspace (0 for plans of

@@ -901,6 +901,11 @@ int gemm_create_splitk(const gemm_desc_t* desc, int splits, gemm_plan_t** out_pl
   in.epilogue = GEMM_EPI_NONE;
   in.stride_bias = 0;
   in.scale = 1.0f;
+  // What split-K takes is what the K-contiguous kernels with two slabs take (best_mfma alone would also offer the
+  // any-alignment kernels for leading dimensions that are not whole 16-byte pieces).
+  bool taken = false;
+  for (int i = 0; i < kNumConfigs && !taken; ++i) taken = kConfigs[i].kind == KIND_MFMA && kConfigs[i].t1 == 0 && applicable(kConfigs[i], in);
+  if (!taken) return GEMM_ERR_UNSUPPORTED;
   const int inner_cfg = best_mfma(in, nullptr);
   if (inner_cfg < 0) return GEMM_ERR_UNSUPPORTED;
   gemm_plan_t* inner = nullptr;

@@ -48,3 +48,22 @@ def test_refusals_are_unchanged():
     assert e.value.status == -2
     with pytest.raises(g.GemmError):
         g.gemm_create_splitk(g.GemmDesc(512, 512, 32768, layout_b=g.ROW_MAJOR), 0)
+
+
+@pytest.mark.parametrize("dtype", [g.BF16, g.F16, g.F8E4M3])
+def test_splitk_takes_whole_pieces_only(dtype):
+    """Every slice's rows start on 16-byte pieces, whatever kernels serve other alignments in gemm_create."""
+    def status(splits=0, **kw):
+        try:
+            p = g.gemm_create_splitk(g.GemmDesc(512, 512, 32768, dtype=dtype, **kw), splits)
+        except g.GemmError as e:
+            return e.status
+        assert "+mfma16_" in p.info() or "+mfma8_" in p.info(), p.info()
+        g.gemm_destroy(p)
+        return 0
+    for splits in (0, 1, 16):
+        assert status(splits) == 0 and status(splits, lda=32768 + 16, ldb=32768 + 48) == 0
+        assert status(splits, ldc=513) == 0 and status(splits, layout_c=g.COL_MAJOR) == 0      # (C is the reduction's)
+        for kw in (dict(lda=32769), dict(ldb=32769), dict(lda=32768 + 4), dict(ldb=32768 + 4)):
+            assert status(splits, **kw) == -4, (splits, kw)
+        assert status(splits, lda=1 << 26) == -4                  # a tile's rows beyond 32-bit offsets
