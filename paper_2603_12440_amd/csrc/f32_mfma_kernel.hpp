@@ -29,6 +29,12 @@ template <bool KFAST, int ROWS_> struct F32Stage {
   static constexpr int SIZE = KFAST ? ROWS * LD : TK * LD;      // floats per buffer
 };
 
+// LDS bytes of one operand's two slabs
+constexpr int f32_mfma_lds(int tile, bool k_fast) {
+  return 8 * (tile == 64 ? (k_fast ? F32Stage<true, 64>::SIZE : F32Stage<false, 64>::SIZE)
+                         : (k_fast ? F32Stage<true, 128>::SIZE : F32Stage<false, 128>::SIZE));
+}
+
 template <bool A_KFAST, bool B_KFAST, int TM, int TN>
 __global__ __launch_bounds__(256) void f32_mfma_kernel(SimtArgs p) {
   static_assert(TM % 64 == 0 && TN % 64 == 0, "2 x 2 waves of 32x32 tiles");

@@ -19,6 +19,9 @@
 
 namespace mi355gemm {
 
+// Slabs in LDS for a tile of this height: three workgroups fit a CU with 64x64 tiles, two with 128x128.
+constexpr int f32_ring_stages(int tile) { return tile == 64 ? 3 : 2; }
+
 // MT: 32x32 tiles of a wave in each direction (tile 64 MT x 64 MT, 2 x 2 waves)
 template <bool A_KF, bool B_KF, int MT, int NSTAGE>
 __global__ __launch_bounds__(256) void f32_ring_kernel(MfmaArgs p, int64_t c_si, int64_t c_sj) {

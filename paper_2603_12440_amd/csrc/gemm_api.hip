@@ -136,6 +136,12 @@ hipError_t launch_general_mfma(const gemm_plan& pl, const void* A, const void* B
   return launch_general_mfma_typed<TIn, TIn, TM, TN, TK>(pl, A, B, C, bias, s);
 }
 
+// Do the offsets inside a slab of a float4 problem fit the 32 bits of the kernel with slabs straight to LDS?
+bool f32_ring_fits(const gemm_desc_t& d, int tile) {
+  const int64_t lim = (int64_t)1 << 32, kMax = ((int64_t)1 << 31) - 512;
+  return (tile + 1) * d.lda * 4 < lim && (tile + 1) * d.ldb * 4 < lim && d.M < kMax && d.N < kMax && d.K < kMax;
+}
+
 // fp32 operands in 16-byte pieces (the plan's extents and leading dimensions allow it: applicable());
 // pointers that are not 16-byte aligned take the general kernel on the same grid
 template <int TM, int TN>
@@ -146,10 +152,8 @@ hipError_t launch_f32_mfma(const gemm_plan& pl, const void* A, const void* B, vo
     return launch_general_mfma_typed<float, float, TM, TN, 16>(pl, A, B, C, bias, s);
   const SimtArgs a = simt_args(pl, A, B, C, bias);
   const bool ak = d.layout_a == GEMM_ROW_MAJOR, bk = d.layout_b == GEMM_COL_MAJOR;   // K contiguous?
-  // slabs straight to LDS, where 32-bit offsets inside a slab suffice
-  const int64_t lim = (int64_t)1 << 32, kMax = ((int64_t)1 << 31) - 512;
-  if ((TM + 1) * d.lda * 4 < lim && (TN + 1) * d.ldb * 4 < lim && d.M < kMax && d.N < kMax && d.K < kMax) {
-    constexpr int MT = TM / 64, S = MT == 1 ? 3 : 2;    // three workgroups per CU, or two
+  if (f32_ring_fits(d, TM)) {
+    constexpr int MT = TM / 64, S = f32_ring_stages(TM);
     MfmaArgs r = mfma16_args<TM, TN>(pl, A, B, C, bias);
     r.xcd_remap = d.batch == 1 || (r.tiles_m * (int64_t)r.tiles_n) % 8 == 0;
     if (ak && bk) f32_ring_kernel<true, true, MT, S><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
@@ -256,10 +260,10 @@ hipError_t launch_skinny_direct(const gemm_plan& pl, const void* A, const void* 
     { launch_general_mfma<float, TM, TN, TK>, launch_general_mfma<bf16_t, TM, TN, TK>,     \
       launch_general_mfma<f16_t, TM, TN, TK> } }
 
-// fp32 operands and output moved as float4 groups: 128x128 tiles, slabs of 32 columns of K
+// fp32 operands and output moved as float4 groups, slabs of 32 columns of K
 #define F32_MFMA_CFG(TM, TN)                                                               \
   { "f32mfma_" #TM "x" #TN "x32", KIND_F32_VEC, TM, TN, kF32TileK, 256,                    \
-    (int)(sizeof(float) * 2 * (F32Stage<true, TM>::SIZE + F32Stage<true, TN>::SIZE)),      \
+    f32_ring_stages(TM) * (TM + TN) * 128,                                                 \
     { launch_f32_mfma<TM, TN>, nullptr, nullptr } }
 
 // small fp32 problems: 16x16 tiles, 256 columns of K per round of the four waves
@@ -540,6 +544,13 @@ bool applicable(const Config& c, const gemm_desc_t& d) {
   if (c.persist && (d.K % c.bk != 0 || d.K < 2 * c.bk)) return false;   // whole slabs, at least two
   const int64_t tiles = ((d.M + c.bm - 1) / c.bm) * ((d.N + c.bn - 1) / c.bn);
   return (c.persist || c.t1 > 0 ? tiles * d.batch : tiles) < ((int64_t)1 << 31);
+}
+
+// LDS bytes of the kernel a plan runs for 16-byte aligned operands
+int plan_lds_bytes(const gemm_plan& pl) {
+  const Config& c = *pl.cfg;
+  if (c.kind != KIND_F32_VEC || f32_ring_fits(pl.d, c.bm)) return c.lds_bytes;
+  return f32_mfma_lds(c.bm, pl.d.layout_a == GEMM_ROW_MAJOR) + f32_mfma_lds(c.bm, pl.d.layout_b == GEMM_COL_MAJOR);
 }
 
 int find_config(const char* name) {
@@ -1286,7 +1297,7 @@ int gemm_plan_info(const gemm_plan_t* plan, char* buf, size_t n) {
   }
   return std::snprintf(buf, n, "kernel=%s tile=%dx%dx%d grid=%u,%u,%u block=%u lds=%d%s", c.name,
                        c.bm, c.bn, c.bk, plan->grid.x, plan->grid.y, plan->grid.z, plan->block.x,
-                       c.lds_bytes, other);
+                       plan_lds_bytes(*plan), other);
 }
 
 }  // extern "C"

@@ -67,3 +67,14 @@ def test_splitk_takes_whole_pieces_only(dtype):
         for kw in (dict(lda=32769), dict(ldb=32769), dict(lda=32768 + 4), dict(ldb=32768 + 4)):
             assert status(splits, **kw) == -4, (splits, kw)
         assert status(splits, lda=1 << 26) == -4                  # a tile's rows beyond 32-bit offsets
+
+
+def test_fp32_plans_report_the_lds_of_the_kernel_they_run():
+    """Slabs of 32 columns of K.  Straight to LDS, 128 bytes a row: three of 64 + 64 rows or two of 128 + 128.  Where the
+    offsets inside a slab do not fit 32 bits: two slabs, rows of 36 values (K contiguous) or 32 rows padded by 4."""
+    for tile, lds in ((64, 3 * 128 * 128), (128, 2 * 256 * 128)):
+        for lda, want in ((0, lds), (1 << 24, 2 * 4 * (tile * 36 + 32 * (tile + 4)))):
+            p = g.gemm_create_config(g.GemmDesc(2000, 1500, 1100, dtype=g.F32, layout_b=g.ROW_MAJOR, lda=lda),
+                                     g.config_names().index(f"f32mfma_{tile}x{tile}x32"))
+            assert f" lds={want}" in p.info(), p.info()
+            g.gemm_destroy(p)
