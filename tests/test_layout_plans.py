@@ -78,3 +78,15 @@ def test_fp32_plans_report_the_lds_of_the_kernel_they_run():
                                      g.config_names().index(f"f32mfma_{tile}x{tile}x32"))
             assert f" lds={want}" in p.info(), p.info()
             g.gemm_destroy(p)
+
+
+@pytest.mark.parametrize("kw,kernel", [
+    (dict(M=613, N=21, K=15, batch=127), "general_mfma32_64x64x16"),               # 7.8 us; any-alignment tiles 15.0 and 19.2
+    (dict(M=2319, N=879, K=9, layout_c=g.COL_MAJOR), "general_mfma32_64x64x16"),   # 7.2; 8.5 and 10.4
+    (dict(M=697, N=41, K=37, batch=107), "mfma16g_64x64_k1_w2x2"),                 # 20.5; 24.9 with the larger tile
+    (dict(M=4951, N=2497, K=65), "mfma16g_"), (dict(M=4951, N=2497, K=613), "mfma16g_128x128_k1_w2x4")])
+def test_any_alignment_with_a_short_k(kw, kernel):
+    """Up to 64 values of K the general kernel and the two any-alignment tiles are weighed against each other."""
+    assert "kernel=" + kernel in info(**kw)
+    if "batch" not in kw:
+        assert "kernel=" + kernel in info(dtype_c=g.F32, **kw)
