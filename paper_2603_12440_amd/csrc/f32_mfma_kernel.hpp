@@ -4,8 +4,9 @@
 // element strides at 4 bytes per load and a barrier pair per 16 columns; this one needs the
 // contiguous index of each operand to run in whole, 16-byte aligned float4 groups (the host checks
 // leading dimensions and extents when it builds the plan and the pointers at launch, and falls back
-// to the general kernel otherwise).  f32_ring_kernel.hpp serves the same plans faster; this one those whose offsets
-// inside a slab do not fit 32 bits (leading dimensions beyond 8 million).  Paper taxonomy (Sec. 3.2): d_mem = 3, d_sync = 1.
+// to the general kernel otherwise).  f32_ring_kernel.hpp serves the same plans; this one is taken where four 64x64
+// workgroups on a CU beat three (a K of a slab or a few: f32_takes_ring()) and where the offsets inside a slab do not fit
+// 32 bits (leading dimensions beyond 8 million).  Paper taxonomy (Sec. 3.2): d_mem = 3, d_sync = 1.
 //
 // Layout in LDS follows the operand's layout in memory, so that both the global loads and the
 // LDS writes are 16 bytes per lane:

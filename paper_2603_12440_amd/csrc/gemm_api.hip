@@ -90,6 +90,8 @@ MI355GEMM_MFMA16S_TILES(X)
 
 namespace {
 
+int num_cus();
+
 // ---- launchers ---------------------------------------------------------------------
 
 // the argument block of the general kernels: layouts become element strides
@@ -136,10 +138,17 @@ hipError_t launch_general_mfma(const gemm_plan& pl, const void* A, const void* B
   return launch_general_mfma_typed<TIn, TIn, TM, TN, TK>(pl, A, B, C, bias, s);
 }
 
-// Do the offsets inside a slab of a float4 problem fit the 32 bits of the kernel with slabs straight to LDS?
-bool f32_ring_fits(const gemm_desc_t& d, int tile) {
+// Does a float4 problem run on the kernel with slabs straight to LDS?  Its offsets inside a slab have to fit 32 bits.  And
+// of its 64x64 tiles three fit a CU, four of the kernel that stages slabs through registers, which with a short K is ahead
+// where it needs fewer rounds of the CUs for that: 3 to 4 tiles per CU, K <= 32 0.81 of the time (38x25 tiles, K = 12: 9.4
+// against 12.0 us), 14x64 tiles with K = 64 / 128 / 192 1 / 1.27, 1 / 1.14, 1 / 1.07; 6 to 8 tiles per CU, K <= 32 0.90.  With
+// as many rounds the slabs straight to LDS win, also with a K of one slab (one tile per CU 1.09, 4 to 6 1.04).
+bool f32_takes_ring(const gemm_desc_t& d, int tile) {
   const int64_t lim = (int64_t)1 << 32, kMax = ((int64_t)1 << 31) - 512;
-  return (tile + 1) * d.lda * 4 < lim && (tile + 1) * d.ldb * 4 < lim && d.M < kMax && d.N < kMax && d.K < kMax;
+  if ((tile + 1) * d.lda * 4 >= lim || (tile + 1) * d.ldb * 4 >= lim || d.M >= kMax || d.N >= kMax || d.K >= kMax) return false;
+  const double per_cu = (double)((d.M + 63) / 64) * (double)((d.N + 63) / 64) * d.batch / num_cus();
+  const bool fewer_rounds = std::ceil(per_cu / 4) < std::ceil(per_cu / 3);
+  return tile != 64 || !fewer_rounds || d.K > (per_cu <= 4 ? 192 : 32);
 }
 
 // fp32 operands in 16-byte pieces (the plan's extents and leading dimensions allow it: applicable());
@@ -152,7 +161,7 @@ hipError_t launch_f32_mfma(const gemm_plan& pl, const void* A, const void* B, vo
     return launch_general_mfma_typed<float, float, TM, TN, 16>(pl, A, B, C, bias, s);
   const SimtArgs a = simt_args(pl, A, B, C, bias);
   const bool ak = d.layout_a == GEMM_ROW_MAJOR, bk = d.layout_b == GEMM_COL_MAJOR;   // K contiguous?
-  if (f32_ring_fits(d, TM)) {
+  if (f32_takes_ring(d, TM)) {
     constexpr int MT = TM / 64, S = f32_ring_stages(TM);
     MfmaArgs r = mfma16_args<TM, TN>(pl, A, B, C, bias);
     r.xcd_remap = d.batch == 1 || (r.tiles_m * (int64_t)r.tiles_n) % 8 == 0;
@@ -549,7 +558,7 @@ bool applicable(const Config& c, const gemm_desc_t& d) {
 // LDS bytes of the kernel a plan runs for 16-byte aligned operands
 int plan_lds_bytes(const gemm_plan& pl) {
   const Config& c = *pl.cfg;
-  if (c.kind != KIND_F32_VEC || f32_ring_fits(pl.d, c.bm)) return c.lds_bytes;
+  if (c.kind != KIND_F32_VEC || f32_takes_ring(pl.d, c.bm)) return c.lds_bytes;
   return f32_mfma_lds(c.bm, pl.d.layout_a == GEMM_ROW_MAJOR) + f32_mfma_lds(c.bm, pl.d.layout_b == GEMM_COL_MAJOR);
 }
 

@@ -69,15 +69,33 @@ def test_splitk_takes_whole_pieces_only(dtype):
         assert status(splits, lda=1 << 26) == -4                  # a tile's rows beyond 32-bit offsets
 
 
-def test_fp32_plans_report_the_lds_of_the_kernel_they_run():
-    """Slabs of 32 columns of K.  Straight to LDS, 128 bytes a row: three of 64 + 64 rows or two of 128 + 128.  Where the
-    offsets inside a slab do not fit 32 bits: two slabs, rows of 36 values (K contiguous) or 32 rows padded by 4."""
-    for tile, lds in ((64, 3 * 128 * 128), (128, 2 * 256 * 128)):
-        for lda, want in ((0, lds), (1 << 24, 2 * 4 * (tile * 36 + 32 * (tile + 4)))):
-            p = g.gemm_create_config(g.GemmDesc(2000, 1500, 1100, dtype=g.F32, layout_b=g.ROW_MAJOR, lda=lda),
-                                     g.config_names().index(f"f32mfma_{tile}x{tile}x32"))
-            assert f" lds={want}" in p.info(), p.info()
-            g.gemm_destroy(p)
+def fp32_lds(tile, M, N, K, **kw):
+    p = g.gemm_create_config(g.GemmDesc(M, N, K, dtype=g.F32, layout_b=g.ROW_MAJOR, **kw), g.config_names().index(f"f32mfma_{tile}x{tile}x32"))
+    lds = int(p.info().split(" lds=")[1].split()[0])
+    g.gemm_destroy(p)
+    return lds
+
+
+# slabs of 32 columns of K: straight to LDS, 128 bytes a row, three of 64 + 64 rows or two of 128 + 128; or staged through
+# registers, two slabs of rows of 36 values (K contiguous) and of 32 rows padded by 4
+STRAIGHT = {64: 3 * 128 * 128, 128: 2 * 256 * 128}
+STAGED = {tile: 2 * 4 * (tile * 36 + 32 * (tile + 4)) for tile in (64, 128)}
+
+
+@pytest.mark.parametrize("tile", [64, 128])
+def test_fp32_plans_report_the_lds_of_the_kernel_they_run(tile):
+    assert fp32_lds(tile, 2000, 1500, 1100) == STRAIGHT[tile]
+    assert fp32_lds(tile, 2000, 1500, 1100, lda=1 << 24) == STAGED[tile]       # offsets beyond 32 bits
+
+
+def test_fp32_kernel_with_a_short_k():
+    """64x64 tiles, 256 CUs: four workgroups of the staged kernel fit a CU, three of the other; tiles per CU beside each."""
+    for M, N, K, batch, want in ((896, 4096, 32, 1, STAGED), (896, 4096, 36, 1, STAGED), (896, 4096, 192, 1, STAGED), (896, 4096, 196, 1, STRAIGHT),  # 3.5
+                                 (768, 4096, 4, 1, STRAIGHT), (769, 4096, 4, 1, STAGED), (1024, 4096, 64, 1, STAGED), (1028, 4096, 4, 1, STRAIGHT),    # 3, 3.25, 4, 4.25
+                                 (128, 192, 4, 128, STRAIGHT), (128, 192, 64, 150, STAGED), (64, 64, 4, 1, STRAIGHT),                                  # 3, 3.5, 0
+                                 (1792, 4096, 32, 1, STAGED), (1792, 4096, 36, 1, STRAIGHT), (1536, 4096, 32, 1, STRAIGHT)):                           # 7, 7, 6
+        assert fp32_lds(64, M, N, K, batch=batch) == want[64], (M, N, K, batch)
+    assert fp32_lds(128, 896, 4096, 4) == STRAIGHT[128]
 
 
 @pytest.mark.parametrize("kw,kernel", [
