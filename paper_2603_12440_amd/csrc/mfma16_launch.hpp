@@ -27,7 +27,7 @@ MfmaArgs mfma16_args(const gemm_plan& pl, const void* A, const void* B, void* C,
   a.xcd_remap = pl.xcd_remap;
   a.c_cached = pl.c_cached;
   a.batches = (int)d.batch;
-  set_tile_order(a);
+  a.order = tile_order(pl, a.tiles_m, a.tiles_n);
   return a;
 }
 

@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "tile_order.hpp"
 
 namespace mi355gemm {
 
@@ -29,10 +30,10 @@ struct MfmaArgs {
   int c_col;                   // C column-major (kernels for operands of any alignment only)
   float scale;                 // scalar of the *_scale activations
   int tiles_m, tiles_n;        // ceil(M/BM), ceil(N/BN)
-  int xcd_remap;               // 1: see tile_coords; 2 (persistent workgroups, a batch):
+  TileOrder order;
+  int xcd_remap;               // 1: renumber over the XCDs (tile_of); 2 (persistent workgroups, a batch):
                                // consecutive problems of the batch within one XCD; 3: the same, one tile per workgroup
   int c_cached;                // 1: fp32 C is read again right away (split-K partials): ordinary stores
-  uint32_t div_group, div_rows, div_h;   // see tile_coords
   int batches;                 // problems in the batch (persistent workgroups walk over the tiles of all of them)
 };
 
@@ -118,48 +119,9 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// ---- tile scheduling -------------------------------------------------------------
-// Workgroups are handed to the 8 XCDs round-robin; each XCD has its own L2, all of them share the last-level cache.
-// 256 consecutive tile ids, what the chip works on at a time, are a compact region of up to 16 x 16 tiles (groups of 16
-// tile rows, every other group walked backwards), and the 32 tiles of a region that one XCD gets (xcd_remap == 1) are
-// an 8 x 4 block, which share 12 panels in its L2.  So a region touches 32 panels instead of all of A, and
-// the next region finds half of them in the last-level cache: with operands that are not in that cache when the
-// launch begins, 8192^3 takes 756 us (with the loads of a slab spread over two sub-steps instead of three; 769 us without); with every XCD walking its own eighth of the tiles it took 820 us.
-// x / d on the scalar unit (m = ceil(2^32 / d); 2^32 - 1 for d = 1): the estimate is off by one at most.  (A division by a
-// run-time value goes through vector registers, which the K loop of a persistent workgroup has none to spare of.)
-__device__ __forceinline__ int div_by(int x, int d, uint32_t m) {
-  const uint32_t q = (uint32_t)(((uint64_t)(uint32_t)x * m) >> 32);
-  const int r = x - (int)(q * (uint32_t)d);            // -d .. d
-  return (int)q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
-}
-// fills what tile_coords divides by; the last group's rows are the only ones that need not be 16
-inline void set_tile_order(MfmaArgs& a) {
-  auto m = [](int64_t d) { return d < 2 ? ~0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
-  const int rows = (a.tiles_m - 1) % 16 + 1;
-  a.div_group = m((int64_t)16 * a.tiles_n);
-  a.div_rows = m(4 * rows);
-  a.div_h = m(rows <= 8 ? rows : rows - 8);
-}
-__device__ __forceinline__ void tile_coords(const MfmaArgs& p, int wg, int n_wg,
-                                            int& tm, int& tn) {
-  int id = wg;
-  if (p.xcd_remap == 1) {                              // per round of 256 ids: one contiguous eighth per XCD
-    const int base = wg & ~255, size = min(256, n_wg - base);
-    if ((size & 7) == 0) id = base + (wg & 7) * (size >> 3) + ((wg - base) >> 3);
-  }
-  const int group = div_by(id, 16 * p.tiles_n, p.div_group);
-  id -= group * (16 * p.tiles_n);
-  const int rows = min(16, p.tiles_m - group * 16);
-  const int strip = div_by(id, 4 * rows, rows == 16 ? 1u << 26 : p.div_rows);        // 4 tile columns
-  id -= strip * (4 * rows);
-  const int cols = min(4, p.tiles_n - strip * 4);
-  const int half = id >= 8 * cols ? 1 : 0;             // 8 tile rows of the strip
-  id -= half * (8 * cols);
-  const int h = min(8, rows - half * 8);
-  const int col = div_by(id, h, h == 8 ? 1u << 29 : p.div_h);
-  tm = group * 16 + half * 8 + id - col * h;
-  tn = strip * 4 + col;
-  if (group & 1) tn = p.tiles_n - 1 - tn;
+// ---- tile scheduling (the orders and where each is taken: tile_order.hpp) -------------------
+__device__ __forceinline__ void tile_coords(const MfmaArgs& p, int wg, int n_wg, int& tm, int& tn) {
+  tile_of(p.order, p.tiles_m, p.tiles_n, p.xcd_remap == 1, wg, n_wg, tm, tn);
 }
 
 // One tile per workgroup, the tiles of a batch along blockIdx.y; or all of them along blockIdx.x (xcd_remap == 3, a

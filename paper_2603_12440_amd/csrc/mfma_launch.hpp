@@ -29,7 +29,7 @@ hipError_t launch_mfma(const gemm_plan& pl, const void* A, const void* B, void* 
   a.xcd_remap = pl.xcd_remap;
   a.c_cached = pl.c_cached;
   a.batches = (int)d.batch;
-  set_tile_order(a);
+  a.order = tile_order(pl, a.tiles_m, a.tiles_n);
   mfma_gemm_kernel<T, TO, BM, BN, BK, WM, WN, NS><<<pl.grid, pl.block, 0, s>>>(a);
   return hipGetLastError();
 }

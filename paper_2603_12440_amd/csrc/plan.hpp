@@ -8,6 +8,7 @@
 
 #include "../../include/gemm.h"
 #include "common.hpp"
+#include "tile_order.hpp"
 
 namespace mi355gemm {
 
@@ -67,5 +68,15 @@ struct Config {
 };
 
 inline int esize(int dt) { return dt == GEMM_F32 ? 4 : (dt == GEMM_F8E4M3 ? 1 : 2); }
+
+// the tile order of a plan's launch (a batch and fp32 operands always take regions)
+inline TileOrder tile_order(const gemm_plan& pl, int tiles_m, int tiles_n) {
+  const gemm_desc_t& d = pl.d;
+  const Config& c = *pl.cfg;
+  const bool strips = d.batch == 1 && d.dtype_a != GEMM_F32 &&
+                      takes_strips(tiles_m, tiles_n, c.bm * c.bn, 2 * c.lds_bytes <= 160 * 1024, d.K * esize(d.dtype_a),
+                                   d.ldc * esize(d.dtype_c) % 16 == 0);
+  return make_tile_order(tiles_m, tiles_n, strips);
+}
 
 }  // namespace mi355gemm

@@ -1,0 +1,87 @@
+// In which order the workgroups of one launch take the tiles of C.  Plain integer code, compiled for host and device.
+//
+// Workgroups are handed to the 8 XCDs round-robin; each XCD has its own L2, all of them share the last-level cache.
+// Two orders:
+//   * regions: 256 consecutive tile ids, what the chip works on at a time with one workgroup per CU, are a compact region
+//     of up to 16 x 16 tiles (groups of 16 tile rows, every other group walked backwards), and the 32 tiles of a region
+//     that one XCD gets are an 8 x 4 block, which share 12 panels in its L2.  So a region touches 32 panels instead of all
+//     of A, and the next region finds half of them in the last-level cache: with operands that are not in that cache when
+//     the launch begins, 8192^3 takes 756 us (820 us with every XCD walking its own eighth of the tiles).
+//   * strips: groups of 8 tile rows, each walked column by column over the full width, one renumbering over the whole grid
+//     (an eighth per XCD; none where the tiles do not divide by 8: then tile row r of a group is XCD r's).
+// Strips serve two kinds of launches (us with strips / with regions, operands in the last-level cache):
+//   * 128x128 tiles, two workgroups per CU, between one and two tiles per CU.  All of them run at once; the regions' second
+//     round would give an XCD a few tiles far from its first 32, whose panels nothing else in that L2 reads, and a launch takes
+//     as long as those: bf16, K = 2056, 24x11 tiles 33.8 / 40.3, 59x5 37.5 / 43.2; fp8, K = 2064, 24x11 21.1 / 25.2.  Not for
+//     grids at least twice as wide as high whose tiles do not divide by 8 (bf16, 5x59: 45.8 / 40.6).
+//   * K of at most 512 bytes, where writing C is most of the work: full-width rows of C are written closer together in time.
+//     41x61 tiles of 128x128 but 8 columns, K = 64: bf16 32.5 / 39.1, fp8 27.6 / 35.9; 9x28 tiles of 256x256, K = 64: bf16
+//     18.0 / 18.8.  Unless the tiles divide by 8 and C's rows are whole 16-byte pieces (regions up to 5 % ahead there).
+#pragma once
+
+#include <stdint.h>
+
+namespace mi355gemm {
+
+struct TileOrder {
+  int group_rows, strip;       // tile rows of a group; tile columns of a strip of it
+  int one_round;               // renumber over the whole grid (strips) or per 256 ids (regions)
+  uint32_t div_group, div_strip, div_rows, div_h;   // reciprocals of what tile_of divides by (the last group has fewer rows)
+};
+
+inline TileOrder make_tile_order(int tiles_m, int tiles_n, bool strips) {
+  auto m = [](int64_t d) { return d < 2 ? ~0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
+  TileOrder o;
+  o.group_rows = strips ? 8 : 16;
+  o.strip = strips ? tiles_n : 4;
+  o.one_round = strips;
+  const int rows = (tiles_m - 1) % o.group_rows + 1;
+  o.div_group = m((int64_t)o.group_rows * tiles_n);
+  o.div_strip = m((int64_t)o.strip * o.group_rows);
+  o.div_rows = m((int64_t)o.strip * rows);
+  o.div_h = m(rows <= 8 ? rows : rows - 8);
+  return o;
+}
+
+// Which of the two a launch takes.  two_per_cu: two workgroups of this kernel fit a CU; whole_rows: rows of C are whole
+// 16-byte pieces.
+inline bool takes_strips(int64_t tiles_m, int64_t tiles_n, int tile_area, bool two_per_cu, int64_t k_bytes, bool whole_rows) {
+  const int64_t n = tiles_m * tiles_n;
+  if (tile_area == 128 * 128 && two_per_cu && n > 256 && n < 512 && (n % 8 == 0 || tiles_n < 2 * tiles_m)) return true;
+  return tile_area >= 128 * 128 && k_bytes <= 512 && (n % 8 != 0 || !whole_rows);
+}
+
+// x / d on the scalar unit (m = ceil(2^32 / d); 2^32 - 1 for d = 1): the estimate is off by one at most.  (A division by a
+// run-time value goes through vector registers, which the K loop of a persistent workgroup has none to spare of.)
+__host__ __device__ __forceinline__ int div_by(int x, int d, uint32_t m) {
+  const uint32_t q = (uint32_t)(((uint64_t)(uint32_t)x * m) >> 32);
+  const int r = x - (int)(q * (uint32_t)d);            // -d .. d
+  return (int)q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
+}
+
+// The tile (tm, tn) of workgroup wg of tiles_m * tiles_n; spread: renumber over the XCDs.
+__host__ __device__ __forceinline__ void tile_of(const TileOrder& o, int tiles_m, int tiles_n, int spread, int wg, int n_wg,
+                                                     int& tm, int& tn) {
+  auto least = [](int a, int b) { return a < b ? a : b; };
+  int id = wg;
+  if (spread) {                                        // one contiguous eighth of a round per XCD
+    const int base = o.one_round ? 0 : wg & ~255, size = o.one_round ? n_wg : least(256, n_wg - base);
+    if ((size & 7) == 0) id = base + (wg & 7) * (size >> 3) + ((wg - base) >> 3);
+  }
+  const int G = o.group_rows, W = o.strip;
+  const int group = div_by(id, G * tiles_n, o.div_group);
+  id -= group * (G * tiles_n);
+  const int rows = least(G, tiles_m - group * G);
+  const int strip = div_by(id, W * rows, rows == G ? o.div_strip : o.div_rows);
+  id -= strip * (W * rows);
+  const int cols = least(W, tiles_n - strip * W);
+  const int half = id >= 8 * cols ? 1 : 0;             // 8 tile rows of the strip
+  id -= half * (8 * cols);
+  const int h = least(8, rows - half * 8);
+  const int col = div_by(id, h, h == 8 ? 1u << 29 : o.div_h);
+  tm = group * G + half * 8 + id - col * h;
+  tn = strip * W + col;
+  if (group & (G >> 4)) tn = tiles_n - 1 - tn;       // (regions: odd groups backwards)
+}
+
+}  // namespace mi355gemm

@@ -1,0 +1,74 @@
+// Checks the order in which workgroups take tiles, on the host: every tile exactly once, and what the choice between the two
+// orders is for.  Prints the number of grids checked, or what failed.
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+
+#include "../paper_2603_12440_amd/csrc/tile_order.hpp"
+
+using namespace mi355gemm;
+
+// tiles per XCD (workgroups are dealt round-robin), in the order in which they are taken
+static std::vector<std::vector<std::pair<int, int>>> walk(int tiles_m, int tiles_n, bool strips, int spread) {
+  const TileOrder o = make_tile_order(tiles_m, tiles_n, strips);
+  const int n = tiles_m * tiles_n;
+  std::vector<char> seen(n, 0);
+  std::vector<std::vector<std::pair<int, int>>> xcd(8);
+  for (int wg = 0; wg < n; ++wg) {
+    int tm = -1, tn = -1;
+    tile_of(o, tiles_m, tiles_n, spread, wg, n, tm, tn);
+    if (tm < 0 || tm >= tiles_m || tn < 0 || tn >= tiles_n || seen[tm * tiles_n + tn]++) {
+      std::printf("%dx%d strips %d spread %d: workgroup %d takes (%d, %d)\n", tiles_m, tiles_n, strips, spread, wg, tm, tn);
+      std::exit(1);
+    }
+    xcd[wg % 8].push_back({tm, tn});
+  }
+  return xcd;
+}
+
+// panels that one tile of an XCD reads and no other: nobody else brings them to that L2
+static int unshared(const std::vector<std::vector<std::pair<int, int>>>& xcd, int tiles_m, int tiles_n) {
+  int count = 0;
+  for (const auto& tiles : xcd) {
+    std::vector<int> rows(tiles_m, 0), cols(tiles_n, 0);
+    for (const auto& t : tiles) { ++rows[t.first]; ++cols[t.second]; }
+    for (const auto& t : tiles) count += (rows[t.first] == 1) + (cols[t.second] == 1);
+  }
+  return count;
+}
+
+int main() {
+  long grids = 0;
+  for (int m = 1; m <= 50; ++m)
+    for (int n = 1; n <= 50; ++n)
+      for (int strips = 0; strips < 2; ++strips)
+        for (int spread = 0; spread < 2; ++spread) { walk(m, n, strips, spread); ++grids; }
+  const int large[][2] = {{1, 70000}, {70000, 1}, {257, 300}, {300, 257}, {17, 4099}, {4099, 17}, {512, 512}, {2, 33333}, {9, 9001}};
+  for (const auto& g : large)
+    for (int strips = 0; strips < 2; ++strips)
+      for (int spread = 0; spread < 2; ++spread) { walk(g[0], g[1], strips, spread); ++grids; }
+  // two workgroups per CU and between one and two tiles per CU: all run at once, few panels are read by one tile of an XCD alone
+  long strips = 0, regions = 0;
+  for (int m = 1; m < 512; ++m)
+    for (int n = 1; n < 512; ++n)
+      if (m >= 5 && n >= 5 && takes_strips(m, n, 128 * 128, true, 4096, true)) {
+        ++grids;
+        strips += unshared(walk(m, n, true, 1), m, n);
+        regions += unshared(walk(m, n, false, 1), m, n);
+      }
+  if (strips * 2 > regions) { std::printf("panels read by one tile alone: strips %ld, regions %ld\n", strips, regions); return 1; }
+  // where the line lies
+  struct { int m, n, area; bool two; int k_bytes; bool whole, want; } rule[] = {
+      {24, 11, 128 * 128, true, 4096, true, true},    {24, 11, 128 * 128, false, 4096, true, false}, {24, 11, 256 * 256, false, 4096, true, false},
+      {16, 16, 128 * 128, true, 4096, true, false},   {32, 16, 128 * 128, true, 4096, true, false},  {5, 59, 128 * 128, true, 4096, true, false},
+      {8, 40, 128 * 128, true, 4096, true, true},     {59, 5, 128 * 128, true, 4096, true, true},    {41, 61, 128 * 128, true, 512, true, true},
+      {41, 61, 128 * 128, true, 514, true, false},    {40, 61, 128 * 128, true, 512, true, false},   {40, 61, 128 * 128, true, 512, false, true},
+      {17, 19, 256 * 256, false, 64, true, true},     {24, 11, 64 * 64, true, 64, false, false}};
+  for (const auto& r : rule)
+    if (takes_strips(r.m, r.n, r.area, r.two, r.k_bytes, r.whole) != r.want) {
+      std::printf("%dx%d tiles of area %d, K of %d bytes: expected %s\n", r.m, r.n, r.area, r.k_bytes, r.want ? "strips" : "regions");
+      return 1;
+    }
+  std::printf("%ld grids ok, panels read by one tile alone: strips %ld, regions %ld\n", grids, strips, regions);
+  return 0;
+}
