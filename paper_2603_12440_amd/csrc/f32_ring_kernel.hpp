@@ -25,6 +25,7 @@ constexpr int f32_ring_stages(int tile) { return tile == 64 ? 3 : 2; }
 // MT: 32x32 tiles of a wave in each direction (tile 64 MT x 64 MT, 2 x 2 waves)
 template <bool A_KF, bool B_KF, int MT, int NSTAGE>
 __global__ __launch_bounds__(256) void f32_ring_kernel(MfmaArgs p, int64_t c_si, int64_t c_sj) {
+  static_assert(NSTAGE == 2 || NSTAGE == 3, "at most one slab on its way behind the one waited for");
   constexpr int BM = 64 * MT, BN = 64 * MT, BK = 32;
   constexpr int A_BYTES = BM * 128, STAGE = 2 * A_BYTES, HALF = 2 * MT, LOADS = 2 * HALF;   // loads of A, and of both, per wave and slab
   __shared__ __attribute__((aligned(1024))) unsigned char smem[NSTAGE * STAGE];
@@ -138,9 +139,7 @@ __global__ __launch_bounds__(256) void f32_ring_kernel(MfmaArgs p, int64_t c_si,
   for (int t = 0; t < ahead && t < T_full; ++t) issue(t);
   int st = 0;
   for (int t = 0; t < T_full; ++t) {
-    const int later = min(T_full - 1 - t, ahead - 1);   // slabs requested after slab t
-    if (later == ahead - 1) wait_vmcnt<(NSTAGE - 2) * LOADS>();
-    else if (NSTAGE > 3 && later == ahead - 2) wait_vmcnt<(NSTAGE > 3 ? NSTAGE - 3 : 0) * LOADS>();
+    if (t + ahead <= T_full) wait_vmcnt<(NSTAGE - 2) * LOADS>();   // slab t + 1, if there is one, may be on its way
     else wait_vmcnt<0>();
     wait_lgkmcnt<0>();
     __builtin_amdgcn_s_barrier();

@@ -326,13 +326,7 @@ hipError_t launch_skinny_direct(const gemm_plan& pl, const void* A, const void* 
 #define SKINNY_DIRECT_CFG(DEPTH, RB, WAVES)                                                \
   { "skinnydirect_d" #DEPTH "_b" #RB "_w" #WAVES, KIND_SKINNY_PANEL, 16, 32, RB / 2, 64 * WAVES, WAVES * 32 * RB, \
     { nullptr, launch_skinny_direct<bf16_t, DEPTH, RB, WAVES>, launch_skinny_direct<f16_t, DEPTH, RB, WAVES> } }
-// few rows of A: bm = rows of A, bn = rows of W per workgroup, bk = values of K per slab (16-bit)
-#define PANEL_CFG(MT, NT, RB, D, W)                                                        \
-  { "panel_" #MT "x" #NT "_b" #RB "_d" #D "_w" #W, KIND_PANEL, 16 * MT, 16 * NT, RB / 2, 64 * W, \
-    (W * 16 * NT * RB > W * MT * NT * 1024) ? W * 16 * NT * RB : W * MT * NT * 1024,       \
-    { nullptr, launch_panel<bf16_t, bf16_t, MT, NT, RB, D, W>,                             \
-      launch_panel<f16_t, f16_t, MT, NT, RB, D, W>, launch_panel<f8e4m3_t, bf16_t, MT, NT, RB, D, W> } },
-// more than two slabs in LDS, one workgroup per CU; NAME, KIND and launcher for either family of layouts
+// 128x128 tiles with four slabs in LDS, one workgroup per CU
 #define MFMA16S_CFG(BM, BN, WM, WN, G, S)                                                  \
   { "mfma16_" #BM "x" #BN "x64_w" #WM "x" #WN "_s" #S, KIND_MFMA, BM, BN, 64, 64 * WM * WN, \
     Mfma16Tile<bf16_t, BM, BN, WM, WN, G, S>::LDS_BYTES,                                   \
@@ -610,7 +604,7 @@ double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
     const double pitch = c.kind == KIND_MFMA_G ? 1.0 : 1.0 + 0.35 * off_line;
     if (area >= 128 * 128 && c.kind != KIND_MFMA_G) {
       const double busy = fmin(1.0, fmax(0.0, tiles / cus - 0.5) * 2.0);
-      const double t1 = (0.33 + 0.12 * busy) * pitch;
+      const double t1 = (c.t1 + 0.12 * busy) * pitch;
       return per_cu > 1 ? per_cu * (slabs * fmax(0.6, t1) + 5.0) : 4.6 + slabs * t1;
     }
     const double pairs = c.t2 > 0 ? (double)(int64_t)(per_cu / 2) : 0.0, singles = per_cu - 2 * pairs;
