@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import workloads as wl
-from helpers import run_gpu, run_oracle
+from helpers import gpu_desc, run_gpu, run_oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -32,3 +32,31 @@ def test_exact(g, oracle, la, lb, M, N, K, batch):
             print(f"{M}x{N}x{K} b{batch} {la}/{lb}/{lc} {cfg}", flush=True)
             C = run_gpu(g, w, A, B, bias, config=g.config_names().index(cfg), layout_c=lc, pad_a=4, pad_b=8, pad_c=1)
             assert np.array_equal(wl.to_float64(C), run_oracle(oracle, w, A, B, bias, want=("y",))["y"]), (cfg, lc)
+
+
+@pytest.mark.parametrize("la,lb", [("row", "row"), ("row", "col"), ("col", "row"), ("col", "col")])
+@pytest.mark.parametrize("huge", ["a", "b"])
+def test_leading_dimensions_beyond_32_bit_offsets(g, oracle, la, lb, huge):
+    """A leading dimension of 2^24 elements: a tile's rows do not fit 32-bit offsets and the plans run the kernel that stages
+    its slabs through registers (both tile sizes, every layout pair; 2.4 to 4.9 GB of address space, few rows touched)."""
+    M, N, K, ld = 72, 68, 36, 1 << 24
+    w = wl.Workload("t", M, N, K, dtype="f32", layout_a=la, layout_b=lb, epilogue="bias_relu", seed_a=1, seed_b=2)
+    sa, sb = wl.operand_shapes(w)
+    A, B = wl.small_integers(sa, w.seed_a, -2, 2, "f32"), wl.small_integers(sb, w.seed_b, -2, 2, "f32")
+    bias = wl.small_integers((N,), w.seed_bias, -3, 3, "f32")
+    dev = torch.device("cuda:0")
+    Ad, Bd, biasd = A.to(dev), B.to(dev), bias.to(dev)
+    src = Ad if huge == "a" else Bd
+    wide = torch.empty(((src.shape[1] - 1) * ld + src.shape[2],), dtype=torch.float32, device=dev)
+    rows = wide.as_strided((src.shape[1], src.shape[2]), (ld, 1))
+    rows.copy_(src[0])
+    want = run_oracle(oracle, w, A, B, bias, want=("y",))["y"]
+    for cfg in ("f32mfma_64x64x32", "f32mfma_128x128x32"):
+        C = torch.full((1, M, N), -777.0, device=dev)
+        lds = {"lda": ld} if huge == "a" else {"ldb": ld}
+        plan = g.gemm_create_config(gpu_desc(g, w, **lds), g.config_names().index(cfg))
+        print(f"{la}/{lb} {huge} {plan.info()}", flush=True)
+        g.gemm_run(plan, rows if huge == "a" else Ad, rows if huge == "b" else Bd, C, biasd)
+        torch.cuda.synchronize()
+        g.gemm_destroy(plan)
+        assert np.array_equal(wl.to_float64(C.cpu()), want), cfg

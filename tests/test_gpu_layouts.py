@@ -89,3 +89,28 @@ def test_special_values_as_on_the_general_kernel(g, dtype):
     slow = run_gpu(g, w, A, B, None, out_dtype="f32", config=g.config_names().index("general_mfma32_64x64x16"))
     assert torch.equal(torch.isnan(fast), torch.isnan(slow))
     assert torch.equal(torch.nan_to_num(fast, nan=0.5), torch.nan_to_num(slow, nan=0.5))
+
+
+@pytest.mark.parametrize("la,lb", PAIRS)
+@pytest.mark.parametrize("M,N,batch", [(72, 136, 3), (136, 200, 5), (264, 72, 8), (40, 264, 8)])
+def test_batches_one_tile_per_workgroup(g, oracle, la, lb, M, N, batch):
+    """Every one-tile-per-workgroup kernel over a batch with a bias: a tile count that is a multiple of 8 gives the deep
+    kernels one grid over all problems (whole problems per XCD), any other one a grid row per problem."""
+    for cfg in configs(g, False):
+        w = wl.Workload("t", M, N, 200, layout_a=la, layout_b=lb, batch=batch, epilogue="bias_relu", seed_a=M, seed_b=N + 1)
+        info = exact(g, oracle, w, cfg, out_dtype="f32", pad_a=8, pad_c=1)
+        bm, bn = (int(x) for x in cfg.split("_")[1].split("x")[:2])
+        tiles = -(-M // bm) * -(-N // bn)
+        one_grid = cfg[-3:] in ("_s4", "_s5") and tiles * batch % 8 == 0
+        assert (f"grid={tiles * batch},1,1" if one_grid else f"grid={tiles},{batch},1") in info, info
+
+
+@pytest.mark.parametrize("la,lb", PAIRS)
+def test_two_launches_and_their_unaligned_fallback(g, oracle, la, lb):
+    """A plan whose last columns are a second launch (the offset into B depends on its layout): exact across the seam, and
+    one kernel for all columns where A or B is only element-aligned."""
+    w = wl.Workload("t", 1024, 17416, 136, layout_a=la, layout_b=lb, epilogue="bias_relu", seed_a=3, seed_b=4, seed_bias=5)
+    info = exact(g, oracle, w, None, out_dtype="f32", pad_c=8)
+    assert " + kernel=mfma16t_" in info and "columns=16384.." in info, info
+    exact(g, oracle, w, None, offset_a=1)
+    exact(g, oracle, w, None, offset_b=5)
