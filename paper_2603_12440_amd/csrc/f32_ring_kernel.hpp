@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void f32_ring_kernel(MfmaArgs p, int64_t c_si,
   const int fr = lane & 31, fh = lane >> 5;
   const int64_t batch = blockIdx.z;
   int tm, tn;
-  tile_coords(p, blockIdx.y * gridDim.x + blockIdx.x, p.tiles_m * p.tiles_n, tm, tn);
+  tile_coords<false>(p, blockIdx.y * gridDim.x + blockIdx.x, p.tiles_m * p.tiles_n, tm, tn);
   const int r0 = tm * BM, c0 = tn * BN;
   const char* ga = (const char*)((const float*)p.A + batch * p.stride_a + (A_KF ? (int64_t)r0 * p.lda : (int64_t)r0));
   const char* gb = (const char*)((const float*)p.B + batch * p.stride_b + (B_KF ? (int64_t)c0 * p.ldb : (int64_t)c0));

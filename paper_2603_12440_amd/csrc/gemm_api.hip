@@ -163,7 +163,7 @@ hipError_t launch_f32_mfma(const gemm_plan& pl, const void* A, const void* B, vo
   const bool ak = d.layout_a == GEMM_ROW_MAJOR, bk = d.layout_b == GEMM_COL_MAJOR;   // K contiguous?
   if (f32_takes_ring(d, TM)) {
     constexpr int MT = TM / 64, S = f32_ring_stages(TM);
-    MfmaArgs r = mfma16_args<TM, TN>(pl, A, B, C, bias);
+    MfmaArgs r = mfma16_args<TM, TN, false>(pl, A, B, C, bias);
     r.xcd_remap = d.batch == 1 || (r.tiles_m * (int64_t)r.tiles_n) % 8 == 0;
     if (ak && bk) f32_ring_kernel<true, true, MT, S><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
     else if (ak) f32_ring_kernel<true, false, MT, S><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);

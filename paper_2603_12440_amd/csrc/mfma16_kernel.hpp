@@ -170,6 +170,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   static_assert(S == 2 || !PERSIST, "a persistent workgroup streams through two stages");
   constexpr int MT = Cfg::MT, NT = Cfg::NT, MA = Cfg::MA, CPR = Cfg::CPR, RPI = Cfg::RPI;
   constexpr int ROWB = Cfg::ROWB, BK = Cfg::BK, KK = Cfg::KK, NSUB = Cfg::NSUB;
+  constexpr bool kEither = kEitherOrder<BM, BN, S, PERSIST>;
   constexpr bool kTwoPerSimd = Cfg::kWaves > 4;          // two waves share a SIMD: alternate by priority
   constexpr int RA = A_KF ? 1 : 2, RB = B_KF ? 1 : 2;    // LDS reads per fragment
   static_assert((A_KF || (BM % 64 == 0 && Cfg::WTM % 64 == 0)) && (B_KF || (BN % 64 == 0 && Cfg::WTN % 64 == 0)) && BK == 64,
@@ -219,9 +220,9 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     const int lid = PERSIST ? logical_tile(vid) : vid;
     int lb = PERSIST ? lid / n_tiles : batch;                // the problem this tile belongs to
     if constexpr (S == 2) {
-      tile_coords(p, PERSIST ? lid - lb * n_tiles : vid, n_tiles, tm, tn);
+      tile_coords<kEither>(p, PERSIST ? lid - lb * n_tiles : vid, n_tiles, tm, tn);
     } else {
-      tile_and_batch(p, lb, tm, tn);
+      tile_and_batch<kEither>(p, lb, tm, tn);
       batch = lb;
     }
     const int r0 = tm * BM, c0 = tn * BN;
@@ -843,8 +844,8 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     wait_lgkmcnt<0>();
   }
   int tm, tn;
-  if constexpr (S == 2) tile_coords(p, blockIdx.x, n_tiles, tm, tn);
-  else tile_and_batch(p, batch, tm, tn);
+  if constexpr (S == 2) tile_coords<kEither>(p, blockIdx.x, n_tiles, tm, tn);
+  else tile_and_batch<kEither>(p, batch, tm, tn);
   epilogue(tm * BM, tn * BN);
   } else {
   // ---- persistent: the tiles of this workgroup as one stream of slabs ------------------------
@@ -917,7 +918,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     int tm, tn;
     const int lid = logical_tile(vid);
     batch = lid / n_tiles;
-    tile_coords(p, lid - batch * n_tiles, n_tiles, tm, tn);
+    tile_coords<kEither>(p, lid - batch * n_tiles, n_tiles, tm, tn);
     epilogue(tm * BM, tn * BN);
     if (!last) {
       // the lane-dependent offsets and addresses are derived afresh here (from an opaque copy of the

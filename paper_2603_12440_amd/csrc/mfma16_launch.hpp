@@ -8,7 +8,8 @@
 
 namespace mi355gemm {
 
-template <int BM, int BN>
+// EITHER: the kernel takes both tile orders
+template <int BM, int BN, bool EITHER>
 MfmaArgs mfma16_args(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias) {
   const gemm_desc_t& d = pl.d;
   MfmaArgs a;
@@ -24,10 +25,9 @@ MfmaArgs mfma16_args(const gemm_plan& pl, const void* A, const void* B, void* C,
   a.c_col = d.layout_c == GEMM_COL_MAJOR;
   a.tiles_m = (int)((d.M + BM - 1) / BM);
   a.tiles_n = (int)((d.N + BN - 1) / BN);
-  a.xcd_remap = pl.xcd_remap;
   a.c_cached = pl.c_cached;
   a.batches = (int)d.batch;
-  a.order = tile_order(pl, a.tiles_m, a.tiles_n);
+  set_tile_order<BM, BN, EITHER>(a, pl);
   return a;
 }
 
@@ -36,7 +36,7 @@ template <typename T, typename TO, int BM, int BN, int WM, int WN, int G, bool P
 hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void* C,
                          const void* bias, hipStream_t s) {
   const gemm_desc_t& d = pl.d;
-  const MfmaArgs a = mfma16_args<BM, BN>(pl, A, B, C, bias);
+  const MfmaArgs a = mfma16_args<BM, BN, kEitherOrder<BM, BN, S, PERSIST>>(pl, A, B, C, bias);
   if constexpr (PERSIST) {
     // The persistent kernel only has the staged output routes (whole-line stores): C rows that are
     // not 16-byte aligned run one tile per workgroup instead.

@@ -32,7 +32,7 @@ struct MfmaArgs {
   int tiles_m, tiles_n;        // ceil(M/BM), ceil(N/BN)
   TileOrder order;
   int xcd_remap;               // 1: renumber over the XCDs (tile_of); 2 (persistent workgroups, a batch):
-                               // consecutive problems of the batch within one XCD; 3: the same, one tile per workgroup
+                               // consecutive problems of the batch within one XCD; 3: the same, one tile per workgroup; 4: as 1, in strips
   int c_cached;                // 1: fp32 C is read again right away (split-K partials): ordinary stores
   int batches;                 // problems in the batch (persistent workgroups walk over the tiles of all of them)
 };
@@ -120,12 +120,15 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 }
 
 // ---- tile scheduling (the orders and where each is taken: tile_order.hpp) -------------------
+template <bool EITHER>
 __device__ __forceinline__ void tile_coords(const MfmaArgs& p, int wg, int n_wg, int& tm, int& tn) {
-  tile_of(p.order, p.tiles_m, p.tiles_n, p.xcd_remap == 1, wg, n_wg, tm, tn);
+  const bool strips = EITHER && p.xcd_remap == 4;
+  tile_of<EITHER>(p.order, p.tiles_m, p.tiles_n, p.xcd_remap == 1 || strips, strips, wg, n_wg, tm, tn);
 }
 
 // One tile per workgroup, the tiles of a batch along blockIdx.y; or all of them along blockIdx.x (xcd_remap == 3, a
 // multiple of 8 in all), each XCD taking a contiguous run of whole problems, whose tiles share panels in its L2.
+template <bool EITHER>
 __device__ __forceinline__ void tile_and_batch(const MfmaArgs& p, int& batch, int& tm, int& tn) {
   const int n_tiles = p.tiles_m * p.tiles_n;
   int id = blockIdx.x;
@@ -135,7 +138,7 @@ __device__ __forceinline__ void tile_and_batch(const MfmaArgs& p, int& batch, in
     batch = lid / n_tiles;
     id = lid - batch * n_tiles;
   }
-  tile_coords(p, id, n_tiles, tm, tn);
+  tile_coords<EITHER>(p, id, n_tiles, tm, tn);
 }
 
 // ---- instruction order of one MFMA k-step -----------------------------------------
@@ -219,7 +222,10 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // T: operand type; TO: the 16-bit output type (outputs may also be fp32: MfmaArgs::c_f32).
-template <typename T, typename TO, int BM, int BN, int BK, int WM, int WN, int NSTAGE>
+// EITHER: launches may walk the tiles in strips or in regions; otherwise in regions only.  (fp8 has both variants: nothing
+// overlaps the start of a tile here, and the choice cost 4096x14336x4096 0.8 us of 183; 16-bit operands mostly run on the
+// other kernel.)
+template <typename T, typename TO, int BM, int BN, int BK, int WM, int WN, int NSTAGE, bool EITHER>
 __global__ __launch_bounds__(64 * WM * WN) void mfma_gemm_kernel(MfmaArgs p) {
   typedef MfmaTile<T, BM, BN, BK, WM, WN, NSTAGE> Cfg;
   constexpr int MT = Cfg::MT, NT = Cfg::NT, CPR = Cfg::CPR, RPI = Cfg::RPI;
@@ -234,7 +240,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma_gemm_kernel(MfmaArgs p) {
   const int wm = wave / WN, wn = wave % WN;
 
   int tm, tn;
-  tile_coords(p, blockIdx.x, gridDim.x, tm, tn);
+  tile_coords<EITHER>(p, blockIdx.x, gridDim.x, tm, tn);
   const int row0 = tm * BM, col0 = tn * BN;
   const int64_t batch = blockIdx.y;
 

@@ -26,11 +26,16 @@ hipError_t launch_mfma(const gemm_plan& pl, const void* A, const void* B, void* 
   a.c_col = 0;
   a.tiles_m = (int)((d.M + BM - 1) / BM);
   a.tiles_n = (int)((d.N + BN - 1) / BN);
-  a.xcd_remap = pl.xcd_remap;
   a.c_cached = pl.c_cached;
   a.batches = (int)d.batch;
-  a.order = tile_order(pl, a.tiles_m, a.tiles_n);
-  mfma_gemm_kernel<T, TO, BM, BN, BK, WM, WN, NS><<<pl.grid, pl.block, 0, s>>>(a);
+  set_tile_order<BM, BN, kEitherOrder<BM, BN, 2, false>>(a, pl);
+  if constexpr (sizeof(T) == 1) {                        // fp8: a variant with regions only (see the kernel)
+    if (a.xcd_remap != 4) {
+      mfma_gemm_kernel<T, TO, BM, BN, BK, WM, WN, NS, false><<<pl.grid, pl.block, 0, s>>>(a);
+      return hipGetLastError();
+    }
+  }
+  mfma_gemm_kernel<T, TO, BM, BN, BK, WM, WN, NS, true><<<pl.grid, pl.block, 0, s>>>(a);
   return hipGetLastError();
 }
 

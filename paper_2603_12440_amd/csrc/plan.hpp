@@ -69,14 +69,16 @@ struct Config {
 
 inline int esize(int dt) { return dt == GEMM_F32 ? 4 : (dt == GEMM_F8E4M3 ? 1 : 2); }
 
-// the tile order of a plan's launch (a batch and fp32 operands always take regions)
-inline TileOrder tile_order(const gemm_plan& pl, int tiles_m, int tiles_n) {
+// Sets the tile order of a launch of a kernel with BM x BN tiles, once `a` has its tile counts.  (A batch and fp32 operands
+// always take regions.)
+template <int BM, int BN, bool EITHER, typename Args>
+void set_tile_order(Args& a, const gemm_plan& pl) {
   const gemm_desc_t& d = pl.d;
-  const Config& c = *pl.cfg;
-  const bool strips = d.batch == 1 && d.dtype_a != GEMM_F32 &&
-                      takes_strips(tiles_m, tiles_n, c.bm * c.bn, 2 * c.lds_bytes <= 160 * 1024, d.K * esize(d.dtype_a),
-                                   d.ldc * esize(d.dtype_c) % 16 == 0);
-  return make_tile_order(tiles_m, tiles_n, strips);
+  const bool strips = EITHER && pl.xcd_remap == 1 && d.batch == 1 && d.dtype_a != GEMM_F32 &&
+                      takes_strips(a.tiles_m, a.tiles_n, BM * BN, 2 * pl.cfg->lds_bytes <= 160 * 1024,
+                                   d.K * esize(d.dtype_a), d.ldc * esize(d.dtype_c) % 16 == 0);
+  a.xcd_remap = strips ? 4 : pl.xcd_remap;
+  a.order = make_tile_order(a.tiles_m, a.tiles_n, strips);
 }
 
 }  // namespace mi355gemm

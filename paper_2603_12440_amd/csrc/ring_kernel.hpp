@@ -72,7 +72,7 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   int batch, tm, tn;
-  tile_and_batch(p, batch, tm, tn);
+  tile_and_batch<kEitherOrder<BM, BN, NSTAGE, false>>(p, batch, tm, tn);
   const int r0 = tm * BM, c0 = tn * BN;
   // K-strided operands of any alignment are addressed from a row that has eight behind it (where there are eight)
   const int ra = DIRECT || A_KF ? r0 : min(r0, max(p.M - 8, 0)), rb = DIRECT || B_KF ? c0 : min(c0, max(p.N - 8, 0));

@@ -8,7 +8,7 @@ namespace mi355gemm {
 
 template <typename T, typename TO, int BM, int BN, int WM, int WN, int KS, int NS, bool A_KF, bool B_KF>
 hipError_t launch_ring(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias, hipStream_t s) {
-  ring_gemm_kernel<T, TO, BM, BN, WM, WN, KS, NS, A_KF, B_KF><<<pl.grid, pl.block, 0, s>>>(mfma16_args<BM, BN>(pl, A, B, C, bias));
+  ring_gemm_kernel<T, TO, BM, BN, WM, WN, KS, NS, A_KF, B_KF><<<pl.grid, pl.block, 0, s>>>(mfma16_args<BM, BN, kEitherOrder<BM, BN, NS, false>>(pl, A, B, C, bias));
   return hipGetLastError();
 }
 
@@ -26,7 +26,7 @@ hipError_t launch_ring(const gemm_plan& pl, const void* A, const void* B, void* 
 // operands of any alignment: X(BM, BN, WM, WN, KS, t1, t2)
 template <typename T, int BM, int BN, int WM, int WN, int KS>
 hipError_t launch_mfma16g(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias, hipStream_t s) {
-  const MfmaArgs a = mfma16_args<BM, BN>(pl, A, B, C, bias);
+  const MfmaArgs a = mfma16_args<BM, BN, kEitherOrder<BM, BN, 2, false>>(pl, A, B, C, bias);
   const bool ak = pl.d.layout_a == GEMM_ROW_MAJOR, bk = pl.d.layout_b == GEMM_COL_MAJOR;
   if (ak && bk) ring_gemm_kernel<T, T, BM, BN, WM, WN, KS, 2, true, true, false><<<pl.grid, pl.block, 0, s>>>(a);
   else if (ak) ring_gemm_kernel<T, T, BM, BN, WM, WN, KS, 2, true, false, false><<<pl.grid, pl.block, 0, s>>>(a);

@@ -24,24 +24,19 @@
 namespace mi355gemm {
 
 struct TileOrder {
-  int group_rows, strip;       // tile rows of a group; tile columns of a strip of it
-  int one_round;               // renumber over the whole grid (strips) or per 256 ids (regions)
-  uint32_t div_group, div_strip, div_rows, div_h;   // reciprocals of what tile_of divides by (the last group has fewer rows)
+  uint32_t div_group, div_rows, div_h;   // reciprocals of what tile_of divides by: tiles of a group, of a strip of the last one, its rows
 };
 
 inline TileOrder make_tile_order(int tiles_m, int tiles_n, bool strips) {
   auto m = [](int64_t d) { return d < 2 ? ~0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
-  TileOrder o;
-  o.group_rows = strips ? 8 : 16;
-  o.strip = strips ? tiles_n : 4;
-  o.one_round = strips;
-  const int rows = (tiles_m - 1) % o.group_rows + 1;
-  o.div_group = m((int64_t)o.group_rows * tiles_n);
-  o.div_strip = m((int64_t)o.strip * o.group_rows);
-  o.div_rows = m((int64_t)o.strip * rows);
-  o.div_h = m(rows <= 8 ? rows : rows - 8);
-  return o;
+  const int G = strips ? 8 : 16, rows = (tiles_m - 1) % G + 1;
+  return TileOrder{m((int64_t)G * tiles_n), m((int64_t)(strips ? tiles_n : 4) * rows), m(rows <= 8 ? rows : rows - 8)};
 }
+
+// Kernels whose launches may take strips: large tiles with two slabs in LDS.  (The persistent 256x256 kernels never gained more
+// than 3 % by them and pay for the choice.)
+template <int BM, int BN, int SLABS, bool PERSIST>
+constexpr bool kEitherOrder = BM * BN >= 128 * 128 && SLABS == 2 && !(PERSIST && BM * BN == 256 * 256);
 
 // Which of the two a launch takes.  two_per_cu: two workgroups of this kernel fit a CU; whole_rows: rows of C are whole
 // 16-byte pieces.
@@ -59,20 +54,25 @@ __host__ __device__ __forceinline__ int div_by(int x, int d, uint32_t m) {
   return (int)q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
 }
 
-// The tile (tm, tn) of workgroup wg of tiles_m * tiles_n; spread: renumber over the XCDs.
-__host__ __device__ __forceinline__ void tile_of(const TileOrder& o, int tiles_m, int tiles_n, int spread, int wg, int n_wg,
-                                                     int& tm, int& tn) {
+// The tile (tm, tn) of workgroup wg of tiles_m * tiles_n; spread: renumber over the XCDs; EITHER: the launch may have strips.
+// This runs before a workgroup's first loads, so every scalar counts: without EITHER the regions' sizes are constants (as
+// arguments they cost a launch of one 256x256 tile per workgroup 0.1 us of 11.7), and with it they follow from one flag.  A
+// branch between the two orders doubled the time of the persistent kernels.
+template <bool EITHER>
+__host__ __device__ __forceinline__ void tile_of(const TileOrder& o, int tiles_m, int tiles_n, bool spread, bool strips, int wg,
+                                                 int n_wg, int& tm, int& tn) {
   auto least = [](int a, int b) { return a < b ? a : b; };
+  const bool whole = EITHER && strips;
+  const int G = whole ? 8 : 16, W = whole ? tiles_n : 4;       // tile rows of a group; tile columns of a strip of it
   int id = wg;
-  if (spread) {                                        // one contiguous eighth of a round per XCD
-    const int base = o.one_round ? 0 : wg & ~255, size = o.one_round ? n_wg : least(256, n_wg - base);
+  if (spread) {                                        // one contiguous eighth per XCD: of the grid, or of a round of 256 ids
+    const int base = whole ? 0 : wg & ~255, size = whole ? n_wg : least(256, n_wg - base);
     if ((size & 7) == 0) id = base + (wg & 7) * (size >> 3) + ((wg - base) >> 3);
   }
-  const int G = o.group_rows, W = o.strip;
   const int group = div_by(id, G * tiles_n, o.div_group);
   id -= group * (G * tiles_n);
   const int rows = least(G, tiles_m - group * G);
-  const int strip = div_by(id, W * rows, rows == G ? o.div_strip : o.div_rows);
+  const int strip = div_by(id, W * rows, rows == G ? (whole ? o.div_group : 1u << 26) : o.div_rows);
   id -= strip * (W * rows);
   const int cols = least(W, tiles_n - strip * W);
   const int half = id >= 8 * cols ? 1 : 0;             // 8 tile rows of the strip
@@ -81,7 +81,7 @@ __host__ __device__ __forceinline__ void tile_of(const TileOrder& o, int tiles_m
   const int col = div_by(id, h, h == 8 ? 1u << 29 : o.div_h);
   tm = group * G + half * 8 + id - col * h;
   tn = strip * W + col;
-  if (group & (G >> 4)) tn = tiles_n - 1 - tn;       // (regions: odd groups backwards)
+  if (group & (G >> 4)) tn = tiles_n - 1 - tn;         // (regions: odd groups backwards)
 }
 
 }  // namespace mi355gemm

@@ -16,7 +16,12 @@ static std::vector<std::vector<std::pair<int, int>>> walk(int tiles_m, int tiles
   std::vector<std::vector<std::pair<int, int>>> xcd(8);
   for (int wg = 0; wg < n; ++wg) {
     int tm = -1, tn = -1;
-    tile_of(o, tiles_m, tiles_n, spread, wg, n, tm, tn);
+    tile_of<true>(o, tiles_m, tiles_n, spread, strips, wg, n, tm, tn);
+    if (!strips) {                                     // what the kernels with regions only compute
+      int m = -1, k = -1;
+      tile_of<false>(o, tiles_m, tiles_n, spread, false, wg, n, m, k);
+      if (m != tm || k != tn) tm = -1;
+    }
     if (tm < 0 || tm >= tiles_m || tn < 0 || tn >= tiles_n || seen[tm * tiles_n + tn]++) {
       std::printf("%dx%d strips %d spread %d: workgroup %d takes (%d, %d)\n", tiles_m, tiles_n, strips, spread, wg, tm, tn);
       std::exit(1);
