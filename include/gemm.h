@@ -107,15 +107,16 @@ typedef struct {
  * N x K), row-major C, and move 16-byte pieces: K, lda, ldb and the batch strides of A and B
  * must be multiples of 16 bytes' worth of elements (8 for bf16 / fp16, 16 for fp8), and at
  * gemm_run A and B must be 16-byte aligned (GEMM_ERR_MISALIGNED otherwise).  M <= 16 goes to
- * the HBM-bound skinny kernels, everything else to the tiled MFMA kernel.  16-bit operands of
+ * the HBM-bound skinny kernels, everything else to the tiled MFMA kernels.  16-bit operands of
  * which one or both are not K-contiguous (a row-major product, a layer's backward pass; C row-major)
- * run on the tiled MFMA kernel too when the extent along each operand's contiguous index, its leading
+ * run on the tiled MFMA kernels too when the extent along each operand's contiguous index, its leading
  * dimension and its batch stride are multiples of 8; A and B need element alignment only there (a plan
- * holds a general kernel for pointers that are not 16-byte aligned).  Every other
- * combination (fp32 operands, column-major C, odd leading dimensions) is served by the general
- * true-fp32 kernels (vector-ALU FMA for small problems, the fp32 matrix-core instruction
- * otherwise), which need element alignment only; fp8 operands have no such fallback
- * (GEMM_ERR_UNSUPPORTED).
+ * holds a general kernel for pointers that are not 16-byte aligned).  Every other 16-bit problem (odd
+ * extents, leading dimensions or strides, column-major C) runs on the 16-bit matrix instruction as well,
+ * with its operands staged through registers, or, where it is small or its K short, on the general
+ * kernels; both need element alignment only.  Products are exact and sums fp32 on all of them.  fp32
+ * operands are multiplied as fp32 (vector-ALU FMA or the fp32 matrix-core instruction), in any layout
+ * and at element alignment.  fp8 operands other than the above have no kernel (GEMM_ERR_UNSUPPORTED).
  */
 
 /*
