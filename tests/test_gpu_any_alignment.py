@@ -46,3 +46,16 @@ def test_built_in_choice(g, oracle):
     for kw in (dict(K=333), dict(N=517, layout_b="row"), dict(M=301, layout_a="col")):
         w = wl.Workload("t", **{**dict(M=304, N=520, K=336, seed_a=1, seed_b=2), **kw})
         assert "kernel=mfma16g_" in exact(g, oracle, w, None), kw
+
+
+@pytest.mark.parametrize("kw,kernel", [(dict(M=613, N=21, K=15, batch=127), "general_mfma32_64x64x16"),
+                                       (dict(M=2319, N=879, K=9, layout_c="col"), "general_mfma32_64x64x16"),
+                                       (dict(M=697, N=41, K=37, batch=107), "mfma16g_64x64_k1_w2x2"),
+                                       (dict(M=1501, N=1203, K=63, layout_a="col", layout_b="row"), "mfma16g_"),
+                                       (dict(M=2463, N=1111, K=64, layout_b="row"), "mfma16g_")])
+def test_built_in_choice_with_a_short_k(g, oracle, kw, kernel):
+    """Up to 64 values of K, more than the vector-ALU kernel's share: one of three kernels, aligned or not."""
+    lc = kw.pop("layout_c", "row")
+    w = wl.Workload("t", **kw, seed_a=3, seed_b=4)
+    assert "kernel=" + kernel in exact(g, oracle, w, None, layout_c=lc, out_dtype="f32")
+    exact(g, oracle, w, None, layout_c=lc, pad_a=1, pad_b=3, pad_c=1, offset_a=1, offset_b=3)

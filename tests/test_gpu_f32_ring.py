@@ -60,3 +60,20 @@ def test_leading_dimensions_beyond_32_bit_offsets(g, oracle, la, lb, huge):
         torch.cuda.synchronize()
         g.gemm_destroy(plan)
         assert np.array_equal(wl.to_float64(C.cpu()), want), cfg
+
+
+@pytest.mark.parametrize("la,lb,lc", [("row", "row", "row"), ("row", "col", "col"), ("col", "row", "row"), ("col", "col", "row")])
+@pytest.mark.parametrize("M,N,K,batch", [(828, 4100, 4, 1), (828, 4100, 36, 1), (124, 188, 192, 150), (828, 4100, 196, 1)])
+def test_built_in_choice_around_the_short_k_rule(g, oracle, la, lb, lc, M, N, K, batch):
+    """Three to four 64x64 tiles per CU: the staged kernel up to K = 192, slabs straight to LDS above; displaced operands run the
+    general kernel on either plan's grid."""
+    w = wl.Workload("t", M, N, K, dtype="f32", layout_a=la, layout_b=lb, batch=batch, epilogue="bias_relu", seed_a=M, seed_b=N)
+    sa, sb = wl.operand_shapes(w)
+    A, B = wl.small_integers(sa, w.seed_a, -2, 2, "f32"), wl.small_integers(sb, w.seed_b, -2, 2, "f32")
+    bias = wl.small_integers((N,), w.seed_bias, -3, 3, "f32")
+    want = run_oracle(oracle, w, A, B, bias, want=("y",))["y"]
+    for kw in (dict(pad_a=4, pad_c=1), dict(offset_a=1), dict(offset_b=3)):
+        print(f"{M}x{N}x{K} b{batch} {la}/{lb}/{lc} {kw}", flush=True)
+        C, info = run_gpu(g, w, A, B, bias, layout_c=lc, return_plan_info=True, **kw)
+        assert "kernel=f32mfma_64x64x32" in info and (int(info.split(" lds=")[1].split()[0]) == 49152) == (K > 192), info
+        assert np.array_equal(wl.to_float64(C), want), (kw, info)
