@@ -287,7 +287,8 @@ hipError_t launch_skinny_direct(const gemm_plan& pl, const void* A, const void* 
 // the same product on the 16x16x32 MFMA shape (slabs of 64 columns of K, two stages)
 #define MFMA16_CFG(BM, BN, WM, WN, G)                                                      \
   { "mfma16_" #BM "x" #BN "x64_w" #WM "x" #WN, KIND_MFMA, BM, BN, 64,                      \
-    64 * WM * WN, Mfma16Tile<bf16_t, BM, BN, WM, WN, G>::LDS_BYTES,                        \
+    64 * WM * WN, Mfma16Tile<bf16_t, BM, BN, WM, WN, G>::LDS_BYTES +                       \
+                      Mfma16Tile<bf16_t, BM, BN, WM, WN, G>::DUMP_BYTES,                   \
     { nullptr, launch_mfma16<bf16_t, bf16_t, BM, BN, WM, WN, G, false>,                    \
       launch_mfma16<f16_t, f16_t, BM, BN, WM, WN, G, false> }, 0 }
 // persistent workgroups (K a whole number of slabs, at least two): the grid is the number of
@@ -302,7 +303,8 @@ hipError_t launch_skinny_direct(const gemm_plan& pl, const void* A, const void* 
 #define MFMA16T_CFG(SUFFIX, BM, BN, WM, WN, G, P)                                           \
   { "mfma16t_" #BM "x" #BN "x64_w" #WM "x" #WN SUFFIX, KIND_MFMA_T, BM, BN, 64,             \
     64 * WM * WN, Mfma16Tile<bf16_t, BM, BN, WM, WN, G>::LDS_BYTES +                       \
-                      (P ? Mfma16Tile<bf16_t, BM, BN, WM, WN, G>::EPI_BYTES : 0),          \
+                      (P ? Mfma16Tile<bf16_t, BM, BN, WM, WN, G>::EPI_BYTES                \
+                         : Mfma16Tile<bf16_t, BM, BN, WM, WN, G>::DUMP_BYTES),             \
     { nullptr, launch_mfma16t<bf16_t, BM, BN, WM, WN, G, P != 0>,                          \
       launch_mfma16t<f16_t, BM, BN, WM, WN, G, P != 0> }, P }
 // fp8 (E4M3) operands, bf16 or fp32 output: the same slabs in bytes (BK is twice as many values)

@@ -119,6 +119,10 @@ struct Mfma16Tile {
   static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES;
   // the epilogue's staging area of a persistent workgroup: one 16-row band of every wave's block in fp32
   static constexpr int EPI_BYTES = kWaves * 16 * WTN * 4;
+  // Prefetch into L2 (see the kernel): two slabs in LDS and one workgroup per CU.  What the prefetches write to LDS lands
+  // in 256 bytes behind the slabs that nothing reads (a persistent workgroup: in the staging area, idle during the K loop).
+  static constexpr bool PREFETCH = NSTAGE == 2 && kWaves == 8;
+  static constexpr int DUMP_BYTES = PREFETCH ? 256 : 0;
   static_assert(sizeof(T) == 2, "16-bit operands");
   static_assert(BM % (RPI * kWaves) == 0 && BN % (RPI * kWaves) == 0, "slab rows must divide over waves");
   static_assert(WTM % 16 == 0 && WTN % 16 == 0 && MT % G == 0, "wave block in whole sub-steps");
@@ -185,7 +189,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     row = (id >> 3) * 64 + ((ln & 7) ^ (key * 2)) * 8;
   };
 
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[Cfg::LDS_BYTES + (PERSIST ? Cfg::EPI_BYTES : 0)];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[Cfg::LDS_BYTES + (PERSIST ? Cfg::EPI_BYTES : Cfg::DUMP_BYTES)];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -200,8 +204,23 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   // A batch on persistent workgroups (xcd_remap == 2; grid and tile count multiples of 8): the 8 XCDs
   // (round-robin dispatch: XCD = tile id mod 8) each take a contiguous run of the problems, so that the
   // tiles of one problem, which share its panels, meet in one L2 instead of fetching them 8 times.
-  auto logical_tile = [&](int vid) __attribute__((always_inline)) {
+  auto logical_tile = [&](const MfmaArgs& p, int vid) __attribute__((always_inline)) {
     return p.xcd_remap == 2 ? (vid & 7) * (total_tiles >> 3) + (vid >> 3) : vid;
+  };
+  // What finding a tile's panels needs of the arguments.  A persistent workgroup reads them from the argument block again for
+  // every tile (the kernel's only argument sits at the start of the kernarg segment), so that they do not occupy scalar
+  // registers during the K loops.
+  typedef __attribute__((address_space(4))) const volatile MfmaArgs kernarg_t;
+  auto tile_args = [&]() __attribute__((always_inline)) {
+    MfmaArgs q = p;
+    if constexpr (PERSIST) {
+      kernarg_t* pv = (kernarg_t*)__builtin_amdgcn_kernarg_segment_ptr();
+      q.A = pv->A; q.B = pv->B; q.M = pv->M; q.N = pv->N; q.lda = pv->lda; q.ldb = pv->ldb;
+      q.stride_a = pv->stride_a; q.stride_b = pv->stride_b; q.tiles_m = pv->tiles_m; q.tiles_n = pv->tiles_n;
+      q.order.div_group = pv->order.div_group; q.order.div_rows = pv->order.div_rows; q.order.div_h = pv->order.div_h;
+      q.xcd_remap = pv->xcd_remap;
+    }
+    return q;
   };
 
   // ---- global -> LDS addressing (as in mfma_kernel.hpp, with this kernel's swizzle) -------
@@ -213,11 +232,25 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   const char* ld_a;                              // first byte of the next slab to request, A and B
   const char* ld_b;
   uint32_t a_off[Cfg::A_LOADS], b_off[Cfg::B_LOADS];
+  // Prefetch: a slab's loads have less than one slab's time to land in LDS, which is not enough for lines that come from HBM
+  // (4096x3072x6144: 148 us with operands from HBM, 117 from the last-level cache).  So once per slab each wave touches
+  // lines of the next slab but one, ahead of the loads that will want them; waves of the lower half touch A's, the others
+  // B's.  The touch is a 4-byte load per lane into an LDS area nobody reads, so that no register is written later; it is the
+  // youngest load at the hand-over, which leaves it in flight.  A panel is shared by the tiles that one XCD works on at a
+  // time (A's by 4, B's by 8: tile_order.hpp), so each workgroup touches its share of the 128-byte lines only: 512 lines
+  // per workgroup and slab, all of them, cost 2.5 % where the operands are cached, this share 1 to 2 %.
+  // Operands from HBM: 4096x3072x6144 148 -> 127 us, 4096x4096x6144 158 -> 144, 8192^3 748 -> 737; touching two or three
+  // slabs ahead is no better (8192^3: 718 / 723 / 726).
+  constexpr bool PF = Cfg::PREFETCH;
+  uint32_t pf_off = 0;                           // this lane's line within its operand's slab
+  const bool pf_a = wave < Cfg::kWaves / 2;
   // (`ln`: the lane id; a persistent workgroup recomputes the offsets from a fresh copy of it after
   // each epilogue, so that they need not stay in registers across it.)  Leaves ld_a / ld_b at slab `kt`.
   auto load_tile = [&](int vid, int ln, int kt) __attribute__((always_inline)) {
+    MfmaArgs p = tile_args();
     int tm, tn;
-    const int lid = PERSIST ? logical_tile(vid) : vid;
+    const int n_tiles = p.tiles_m * p.tiles_n;
+    const int lid = PERSIST ? logical_tile(p, vid) : vid;
     int lb = PERSIST ? lid / n_tiles : batch;                // the problem this tile belongs to
     if constexpr (S == 2) {
       tile_coords<kEither>(p, PERSIST ? lid - lb * n_tiles : vid, n_tiles, tm, tn);
@@ -226,6 +259,21 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       batch = lb;
     }
     const int r0 = tm * BM, c0 = tn * BN;
+    if constexpr (PF) {
+      // Lines of a slab: one per row where K is contiguous, else one per value of K and 64 rows.  2^sh workgroups share them.
+      const int sh = pf_a || p.tiles_m < 8 ? 2 : 3, wave_lines = 2 * (pf_a ? BM : BN) / Cfg::kWaves;
+      const int line = (wave % (Cfg::kWaves / 2)) * wave_lines +
+                       min(((ln >> sh) << sh) + ((pf_a ? tn : tm) & ((1 << sh) - 1)), wave_lines - 1);
+      const int64_t ld = pf_a ? p.lda : p.ldb;
+      const int left = pf_a ? p.M - r0 : p.N - c0;
+      auto row_line = [&]() __attribute__((always_inline)) { return (uint32_t)((int64_t)min(line, left - 1) * ld * 2); };
+      auto k_line = [&](int per_k) __attribute__((always_inline)) {
+        return (uint32_t)(((int64_t)(line / per_k) * ld + min(line % per_k * 64, left - 8)) * 2);
+      };
+      if constexpr (A_KF && B_KF) pf_off = row_line();
+      else if (pf_a) pf_off = A_KF ? row_line() : k_line(BM / 64);
+      else pf_off = B_KF ? row_line() : k_line(BN / 64);
+    }
     ld_a = (const char*)((const T*)p.A + (int64_t)lb * p.stride_a + (A_KF ? (int64_t)r0 * p.lda : (int64_t)r0)) + (int64_t)kt * a_step;
     ld_b = (const char*)((const T*)p.B + (int64_t)lb * p.stride_b + (B_KF ? (int64_t)c0 * p.ldb : (int64_t)c0)) + (int64_t)kt * b_step;
 #pragma unroll
@@ -296,6 +344,15 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3"
                    :: "s"(io.lb), "n"((q - Cfg::A_LOADS) * 1024), "v"(b_off[q >= Cfg::A_LOADS ? q - Cfg::A_LOADS : 0]), "s"(io.gb) : "memory", "m0", "scc");
     }
+  };
+
+  // this wave's prefetch of the slab at ga / gb
+  auto prefetch = [&](const char* ga, const char* gb) __attribute__((always_inline)) {
+    const char* g = uniform_ptr(pf_a ? ga : gb);
+    // (a persistent workgroup: the wave's own staging buffer, as other waves may still be in the last tile's epilogue)
+    const uint32_t dump = (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)(lds_base + Cfg::LDS_BYTES + (PERSIST ? wave * (Cfg::EPI_BYTES / Cfg::kWaves) : 0)));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" :: "s"(dump), "v"(pf_off), "s"(g) : "memory", "m0");
   };
 
   // K tail: chunks past K must read as zero, which a direct-to-LDS load cannot do, so that one
@@ -450,7 +507,6 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     // What the epilogue needs of the arguments.  A persistent workgroup reads them from the argument
     // block again for every tile (the kernel's only argument sits at the start of the kernarg segment),
     // so that they do not occupy scalar registers during the K loops.
-    typedef __attribute__((address_space(4))) const volatile MfmaArgs kernarg_t;
     MfmaArgs pe = p;
     if constexpr (PERSIST) {
       kernarg_t* pv = (kernarg_t*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -773,12 +829,13 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       constexpr int u = decltype(u_c)::value;
       set_prio(u < 3 ? 2 - u : 0);
       constexpr int q0 = kLoads * (u + 1) / LW, q1 = kLoads * (u + 2) / LW;
+      if constexpr (PF && late && u == LW - 1) prefetch(Ab + (int64_t)(t + 2) * a_step, Bb + (int64_t)(t + 2) * b_step);
       if constexpr (early && u + 1 < LW)
         sub_step(u_c, true, q0 < kLoads ? q0 : kLoads, q1 < kLoads ? q1 : kLoads, io_early);
       else
         sub_step(u_c, true, 0, 0, io_none);
     });
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(deep ? (S - 2) * kLoads : 0) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(deep ? (S - 2) * kLoads + (PF && late ? 1 : 0) : 0) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     set_prio(3);
@@ -878,6 +935,10 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       constexpr int u = decltype(u_c)::value;
       set_prio(u < 3 ? 2 - u : 0);
       constexpr int q0 = kLoads * (u + 1) / LW, q1 = kLoads * (u + 2) / LW;
+      if constexpr (PF && u == LW - 1 && !tile_end) {        // (of the tile's last slab: once more, not past it)
+        const bool more = ld_t + 1 < T_full;
+        prefetch(more ? ld_a + a_step : ld_a, more ? ld_b + b_step : ld_b);
+      }
       if constexpr (u + 1 < LW)
         sub_step(u_c, true, q0 < kLoads ? q0 : kLoads, q1 < kLoads ? q1 : kLoads, io_early, early);
       else
@@ -885,7 +946,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     });
     if (late) next_slab();                     // the early part was the rest of a slab: on to the next one
     const SlabIo io_late = slab_io_at(ld_a, ld_b, stage);
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(PF && !tile_end ? 1 : 0) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     set_prio(3);
@@ -916,9 +977,11 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     set_prio(0);
     wait_lgkmcnt<0>();
     int tm, tn;
-    const int lid = logical_tile(vid);
+    const MfmaArgs pt = tile_args();
+    const int n_tiles = pt.tiles_m * pt.tiles_n;
+    const int lid = logical_tile(pt, vid);
     batch = lid / n_tiles;
-    tile_coords<kEither>(p, lid - batch * n_tiles, n_tiles, tm, tn);
+    tile_coords<kEither>(pt, lid - batch * n_tiles, n_tiles, tm, tn);
     epilogue(tm * BM, tn * BN);
     if (!last) {
       // the lane-dependent offsets and addresses are derived afresh here (from an opaque copy of the
