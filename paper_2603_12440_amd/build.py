@@ -78,12 +78,13 @@ def build_library(verbose: bool = False, only: tuple = ()) -> str:
         asm = os.path.join(OBJ_DIR, os.path.splitext(os.path.basename(src))[0] + "-hip-amdgcn-amd-amdhsa-gfx950.s")
         if os.path.exists(asm):
             with open(asm) as f:
-                hazards += [f"{os.path.basename(asm)}:{h}" for h in lds_load_hazards(f.read())]
+                text = f.read()
+            hazards += [f"{os.path.basename(asm)}:{h}" for h in lds_load_hazards(text) + accumulator_hazards(text)]
     if hazards:
         if os.path.exists(LIB):
             os.remove(LIB)
         raise RuntimeError("a direct-to-LDS load reads a scalar register fewer than 5 wait states after a vector-ALU "
-                           "instruction wrote it:\n  " + "\n  ".join(hazards[:20]))
+                           "instruction wrote it, or an MFMA an accumulator fewer than 2 after a vector-ALU instruction wrote it:\n  " + "\n  ".join(hazards[:20]))
     res = subprocess.run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC",
                           "-Wl,--version-script=" + os.path.join(CSRC, "exports.map"), "-o", LIB] + objs,
                          capture_output=True, text=True)
@@ -119,6 +120,27 @@ def lds_load_hazards(asm: str) -> list:
             dist += (int(n.group(1)) + 1) if n else 1
             if dist >= 5:
                 break
+    return bad
+
+
+def accumulator_hazards(asm: str) -> list:
+    """Lines of generated assembly where an MFMA takes an accumulator register that a `v_accvgpr_write` / `v_accvgpr_mov` wrote
+    fewer than 2 wait states earlier: the MFMAs are assembly statements, in front of which the compiler puts no wait states."""
+    import re
+    bad = []
+    for w in re.finditer(r"v_accvgpr_(?:write|mov)_b32(?:_e32)?\s+a(\d+)[^\n]*\n", asm):
+        reg, states, at = int(w.group(1)), 0, w.end()
+        while states < 2 and at < len(asm):
+            end = asm.find("\n", at)
+            l = asm[at:end if end >= 0 else len(asm)].split(";")[0].strip()
+            at = end + 1 if end >= 0 else len(asm)
+            if not l or l.startswith((".", "//")) or l.endswith(":"):
+                continue
+            m = re.match(r"v_mfma\S+\s+a\[(\d+):(\d+)\]", l)
+            if m and int(m.group(1)) <= reg <= int(m.group(2)):
+                bad.append(f"{l}   ({states} wait states after {w.group(0).strip()})")
+            n = re.match(r"s_nop\s+(\d+)", l)
+            states += 1 + (int(n.group(1)) if n else 0)
     return bad
 
 

@@ -302,7 +302,7 @@ hipError_t launch_skinny_direct(const gemm_plan& pl, const void* A, const void* 
 // either of the two for operands whose K is not contiguous (P: 0 = one tile per workgroup, 1 = persistent)
 #define MFMA16T_CFG(SUFFIX, BM, BN, WM, WN, G, P)                                           \
   { "mfma16t_" #BM "x" #BN "x64_w" #WM "x" #WN SUFFIX, KIND_MFMA_T, BM, BN, 64,             \
-    64 * WM * WN, Mfma16Tile<bf16_t, BM, BN, WM, WN, G>::LDS_BYTES +                       \
+    64 * WM * WN, Mfma16Tile<bf16_t, BM, BN, WM, WN, G, 2, false>::LDS_BYTES +             \
                       (P ? Mfma16Tile<bf16_t, BM, BN, WM, WN, G>::EPI_BYTES                \
                          : Mfma16Tile<bf16_t, BM, BN, WM, WN, G>::DUMP_BYTES),             \
     { nullptr, launch_mfma16t<bf16_t, BM, BN, WM, WN, G, P != 0>,                          \
@@ -397,6 +397,12 @@ const Config kConfigs[] = {
     MFMA16T_CFG("_p", 128, 128, 2, 2, 2, 1),
     MFMA16T_CFG("", 256, 256, 2, 4, 2, 0),
     MFMA16T_CFG("", 128, 128, 2, 2, 2, 0),
+    MFMA16P_CFG(224, 256, 2, 4, 2),
+    MFMA16P_CFG(192, 256, 2, 4, 2),
+    MFMA16_CFG(224, 256, 2, 4, 2),
+    MFMA16_CFG(192, 256, 2, 4, 2),
+    MFMA16T_CFG("_p", 192, 256, 2, 4, 2, 1),
+    MFMA16T_CFG("", 192, 256, 2, 4, 2, 0),
     MI355GEMM_MFMA16S_TILES(MFMA16S_CFG)
     MI355GEMM_MFMA16S_TILES(MFMA16TS_CFG)
     MI355GEMM_RINGS(RING_CFG)
@@ -575,6 +581,17 @@ int find_config(const char* name) {
 //     0.6 us from the second round on, where the two-slab kernels are better (7195x7312x1448: 258 against 183 us).
 //     An operand whose rows do not start on 128-byte lines costs 0.35 of that on top: every piece of 128 bytes
 //     touches two lines (384x4104x4104: 43 us, 384x4096x4096: 24 us).
+//   * The eight-wave tiles of 192 to 256 x 256 (wide_cost): launch (3 us), and a round takes its slabs plus what writing C of
+//     a full round takes (7 us for 256x256 tiles), and the latency of its first loads where workgroups are not persistent.  A slab takes 1.39 us (256x256), 1.23 (224x256) and 1.10 us (192x256) with
+//     all CUs busy and a fifth of that more per operand whose rows do not start on 128-byte lines; a round that fills the
+//     CUs to f takes 0.6 + 0.4 f of a full one.  Within 5 % of what 17 shapes took with operands from HBM, the worst 13 %.
+double wide_cost(const Config& c, const gemm_desc_t& d, double tiles, int off_line) {
+  const double area = (double)c.bm * c.bn / 65536.0, slab = c.bm == 256 ? 1.39 : (c.bm == 224 ? 1.23 : 1.10);
+  const double rounds = tiles / num_cus(), whole = std::floor(rounds), part = rounds - whole;
+  const double turn = (double)((d.K + c.bk - 1) / c.bk) * slab * (1.0 + 0.2 * off_line) + 7.0 * area + (c.persist ? 0.0 : 3.5);
+  return 3.0 + turn * (whole + (part > 0 ? 0.6 + 0.4 * part : 0.0));
+}
+
 double round_cost(const Config& c, const gemm_desc_t& d, int64_t N, double* rounds_out) {
   const int64_t M = d.M, K = d.K;
   const int e = esize(d.dtype_a), area = c.bm * c.bn;
@@ -584,13 +601,16 @@ double round_cost(const Config& c, const gemm_desc_t& d, int64_t N, double* roun
   // (256x192 measured: 0.85 - 1.03 of the 256x256 tile per FLOP on 4096x6144x4096, 4096x14336x4096, 8192^3)
   double eff = area >= 256 * 256 ? 1.0 : (area >= 256 * 192 ? 0.88 : (area >= 256 * 128 ? 0.75 : 0.84));
   // the 16x16x32 kernels: about a tenth faster per FLOP than the 32x32x16 ones at the same tile shape
-  // (8192^3: 732 against 800 us); of the two 256x256 shapes the eight-wave one goes first
-  if (!std::strncmp(c.name, "mfma16", 6)) eff *= c.threads == 256 && area >= 256 * 256 ? 1.08 : 1.10;
+  // (8192^3: 732 against 800 us)
+  if (!std::strncmp(c.name, "mfma16", 6)) eff *= 1.10;
   const double rounds = (double)(int64_t)((tiles + cus * per_cu - 1) / (cus * per_cu));
   // workgroups that actually share a CU (a lone workgroup runs about per_cu times faster)
   const double sharing = tiles >= cus * per_cu ? per_cu : (tiles > cus ? tiles / cus : 1.0);
   *rounds_out = rounds;
-  return rounds * area * sharing / eff * ((double)K + 600.0) / (e == 1 ? 5.4e6 : 2.7e6);
+  // (a persistent tile's epilogue overlaps the next one's loads, which counts where K is short: 2048 x 12000 x 256 21.7 us, 22.9
+  // on 224x256 tiles)
+  const double fixed = c.persist && K <= 512 ? 350.0 : 600.0;
+  return rounds * area * sharing / eff * ((double)K + fixed) / (e == 1 ? 5.4e6 : 2.7e6);
 }
 
 double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
@@ -612,8 +632,10 @@ double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
     const double pairs = c.t2 > 0 ? (double)(int64_t)(per_cu / 2) : 0.0, singles = per_cu - 2 * pairs;
     return 2.7 + (singles * c.t1 + pairs * c.t2) * slabs * pitch + (singles + pairs - 1) * 2.4;
   }
+  // (of the two 256x256 shapes the eight-wave one goes first)
+  if (!std::strncmp(c.name, "mfma16", 6) && area > 128 * 128) return wide_cost(c, d, tiles, off_line) * (c.threads == 512 ? 1.0 : 1.02);
   double rounds = 0;
-  const double work = round_cost(c, d, N, &rounds);
+  const double work = round_cost(c, d, N, &rounds) * (e == 2 ? 1.0 + (area > 128 * 128 ? 0.2 : 0.08) * off_line : 1.0);
   const double wait = rounds * ((double)K / c.bk * (area <= 128 * 128 ? (e == 1 ? 0.42 * (1.0 + 0.5 * off_line) : 0.60 * (1.0 + 0.2 * off_line)) : 0.0) + 3.0);
   return work > wait ? work : wait;
 }
@@ -649,11 +671,11 @@ int64_t split_columns(const gemm_desc_t& d, int big, double single_cost) {
   rest.N = d.N - n_first;
   double rest_cost = 0;
   if (best_mfma(rest, &rest_cost) < 0) return 0;
-  const double launch = 3.0;
+  const double launch = 2.0;                      // (beside what the estimate of the second launch already holds)
   const double split_cost = mfma_cost(c, d, n_first) + rest_cost + launch;
-  // (the model is optimistic about the second launch: where it sees 7.5 %, as for 4096 x 14336 x 4096,
-  // 2 - 3 % were measured; where it sees 5 % against the 256x192 tile, the single launch wins by 8 %)
-  return split_cost < 0.93 * single_cost ? n_first : 0;
+  // (what the model sees as even is even or a little better as two launches, whose second one starts while the first one's last
+  // workgroups finish: 4096 x 14336 x 4096 350 us against 355, 4096 x 6144 x 4096 162 against 161 to 166)
+  return split_cost < 1.03 * single_cost ? n_first : 0;
 }
 
 // The choice among the general kernels (fp32 operands, or layouts / leading dimensions / pointers the tiled

@@ -55,7 +55,6 @@ __device__ __forceinline__ int swz16(int r) { return (r >> 1) & 7; }
 template <int MA, int NT, bool WITH_B, int RA, int RB>
 struct SubOrder {
   static constexpr int kReads = MA * RA + (WITH_B ? NT * RB : 0), kMfma = MA * NT;
-  static constexpr int kPerMfma = (kReads + kMfma - 1) / kMfma;      // reads requested behind one MFMA
   struct Tables {
     int r_isb[kReads], r_idx[kReads], r_part[kReads];
     int mm[kMfma], nn[kMfma];
@@ -102,19 +101,26 @@ struct SubOrder {
   static constexpr Tables t = make();
 };
 
-template <typename T, int BM, int BN, int WM, int WN, int G, int STAGES = 2>
+template <typename T, int BM, int BN, int WM, int WN, int G, int STAGES = 2, bool A_KF = true>
 struct Mfma16Tile {
   static constexpr int BK = 64, NSTAGE = STAGES;
   static constexpr int kWaves = WM * WN, kThreads = 64 * kWaves;
   static constexpr int WTM = BM / WM, WTN = BN / WN;     // per-wave block
   static constexpr int MT = WTM / 16, NT = WTN / 16;     // 16x16 MFMA tiles per wave
-  static constexpr int MA = MT / G;                      // row fragments per sub-step
+  static constexpr int MA = (MT + G - 1) / G;            // row fragments per sub-step, at most
+  static constexpr int group_rows(int g) { return (MT + G - 1 - g) / G; }      // of sub-step g of a k-step (7 = 4 + 3)
+  static constexpr int group_first(int g) { return g == 0 ? 0 : group_first(g - 1) + group_rows(g - 1); }
   static constexpr int KK = BK / 32;                     // k-steps (32 columns) per slab
   static constexpr int NSUB = KK * G;                    // sub-steps per slab
   static constexpr int ROWB = BK * 2;                    // bytes per slab row
   static constexpr int CPR = ROWB / 16, RPI = 64 / CPR;  // chunks per row, rows per wave-wide load
-  static constexpr int A_LOADS = BM / RPI / kWaves, B_LOADS = BN / RPI / kWaves;
-  static constexpr int A_BYTES = BM * ROWB, B_BYTES = BN * ROWB;
+  // Rows of A in LDS: a K-strided A is stored in blocks of 64 rows.  K-contiguous, a wave-wide load fills 8 rows; where
+  // those do not divide over the waves, the waves take them in turn and the last ones issue one load less.
+  static constexpr int ROWS = A_KF ? BM : (BM + 63) / 64 * 64;
+  static constexpr int A_UNITS = ROWS / RPI, A_LOADS = (A_UNITS + kWaves - 1) / kWaves, B_LOADS = BN / RPI / kWaves;
+  static constexpr bool UNEVEN = A_UNITS % kWaves != 0;
+  static constexpr int A_ID_WAVE = UNEVEN ? 1 : A_LOADS, A_ID_Q = UNEVEN ? kWaves : 1;    // load q of a wave is unit wave * A_ID_WAVE + q * A_ID_Q
+  static constexpr int A_BYTES = ROWS * ROWB, B_BYTES = BN * ROWB;
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
   static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES;
   // the epilogue's staging area of a persistent workgroup: one 16-row band of every wave's block in fp32
@@ -124,10 +130,12 @@ struct Mfma16Tile {
   static constexpr bool PREFETCH = NSTAGE == 2 && kWaves == 8;
   static constexpr int DUMP_BYTES = PREFETCH ? 256 : 0;
   static_assert(sizeof(T) == 2, "16-bit operands");
-  static_assert(BM % (RPI * kWaves) == 0 && BN % (RPI * kWaves) == 0, "slab rows must divide over waves");
-  static_assert(WTM % 16 == 0 && WTN % 16 == 0 && MT % G == 0, "wave block in whole sub-steps");
+  static_assert(BM % (8 * RPI) == 0 || BM % 32 == 0, "whole wave-wide loads");
+  static_assert(BN % (RPI * kWaves) == 0, "slab rows of B must divide over waves");
+  static_assert(!UNEVEN || (NSTAGE == 2 && A_LOADS == B_LOADS), "the load that some waves leave out is the last of a slab's second half");
+  static_assert(WTM % 16 == 0 && WTN % 16 == 0 && MT >= G, "wave block in whole sub-steps");
   static_assert(NSUB % 2 == 0, "the row-fragment double buffer alternates per sub-step");
-  static_assert(MA * NT >= MA + NT, "a sub-step issues one or two fragment reads behind each MFMA");
+  static_assert(group_rows(G - 1) * NT >= MA + NT, "a sub-step issues one or two fragment reads behind each MFMA");
   static_assert(LDS_BYTES + (STAGES == 2 ? EPI_BYTES : 0) <= 160 * 1024, "LDS budget");
 };
 
@@ -170,14 +178,14 @@ __device__ __forceinline__ void lds_read_tr16(F& dst, uint32_t addr, int offset)
 // behind and takes four (one tile per workgroup only).
 template <typename T, typename TO, int BM, int BN, int WM, int WN, int G, bool PERSIST, bool A_KF = true, bool B_KF = true, int S = 2>
 __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
-  typedef Mfma16Tile<T, BM, BN, WM, WN, G, S> Cfg;
+  typedef Mfma16Tile<T, BM, BN, WM, WN, G, S, A_KF> Cfg;
   static_assert(S == 2 || !PERSIST, "a persistent workgroup streams through two stages");
   constexpr int MT = Cfg::MT, NT = Cfg::NT, MA = Cfg::MA, CPR = Cfg::CPR, RPI = Cfg::RPI;
   constexpr int ROWB = Cfg::ROWB, BK = Cfg::BK, KK = Cfg::KK, NSUB = Cfg::NSUB;
   constexpr bool kEither = kEitherOrder<BM, BN, S, PERSIST>;
   constexpr bool kTwoPerSimd = Cfg::kWaves > 4;          // two waves share a SIMD: alternate by priority
   constexpr int RA = A_KF ? 1 : 2, RB = B_KF ? 1 : 2;    // LDS reads per fragment
-  static_assert((A_KF || (BM % 64 == 0 && Cfg::WTM % 64 == 0)) && (B_KF || (BN % 64 == 0 && Cfg::WTN % 64 == 0)) && BK == 64,
+  static_assert((B_KF || (BN % 64 == 0 && Cfg::WTN % 64 == 0)) && BK == 64,
                 "K-strided operands are stored in blocks of 64 rows x 8 values of K");
   // bytes from one slab of an operand to the next
   const int64_t a_step = A_KF ? (int64_t)ROWB : p.lda * (int64_t)(BK * 2);
@@ -195,6 +203,9 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
+  // which 1 KB of A's slab this wave's load q fills, and whether there is such a piece
+  auto a_unit = [&](int q) __attribute__((always_inline)) { return wave * Cfg::A_ID_WAVE + q * Cfg::A_ID_Q; };
+  auto has_unit = [&](int q) __attribute__((always_inline)) { return !Cfg::UNEVEN || q < Cfg::A_LOADS - 1 || a_unit(q) < Cfg::A_UNITS; };
   // One tile per workgroup: the batch is the grid's second index.  A persistent workgroup walks over
   // the tiles of every problem of the batch (tile id = problem * n_tiles + tile within the problem);
   // `batch` is then the problem of the tile being written out.
@@ -244,24 +255,30 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   constexpr bool PF = Cfg::PREFETCH;
   uint32_t pf_off = 0;                           // this lane's line within its operand's slab
   const bool pf_a = wave < Cfg::kWaves / 2;
-  // (`ln`: the lane id; a persistent workgroup recomputes the offsets from a fresh copy of it after
-  // each epilogue, so that they need not stay in registers across it.)  Leaves ld_a / ld_b at slab `kt`.
-  auto load_tile = [&](int vid, int ln, int kt) __attribute__((always_inline)) {
-    MfmaArgs p = tile_args();
-    int tm, tn;
+  int ld_tm, ld_tn, ld_batch;                    // which tile that is, of which problem
+  auto locate = [&](int vid) __attribute__((always_inline)) {
+    const MfmaArgs p = tile_args();
     const int n_tiles = p.tiles_m * p.tiles_n;
-    const int lid = PERSIST ? logical_tile(p, vid) : vid;
-    int lb = PERSIST ? lid / n_tiles : batch;                // the problem this tile belongs to
-    if constexpr (S == 2) {
-      tile_coords<kEither>(p, PERSIST ? lid - lb * n_tiles : vid, n_tiles, tm, tn);
+    if constexpr (PERSIST) {
+      const int lid = logical_tile(p, vid);
+      ld_batch = lid / n_tiles;
+      tile_coords<kEither>(p, lid - ld_batch * n_tiles, n_tiles, ld_tm, ld_tn);
+    } else if constexpr (S == 2) {
+      ld_batch = batch;
+      tile_coords<kEither>(p, vid, n_tiles, ld_tm, ld_tn);
     } else {
-      tile_and_batch<kEither>(p, lb, tm, tn);
-      batch = lb;
+      tile_and_batch<kEither>(p, ld_batch, ld_tm, ld_tn);
     }
+  };
+  // Leaves ld_a / ld_b at slab `kt` of that tile.  (`ln`: the lane id; a persistent workgroup recomputes the offsets from a fresh
+  // copy of it after each epilogue, so that they need not stay in registers across it.)
+  auto load_tile = [&](int ln, int kt) __attribute__((always_inline)) {
+    const MfmaArgs p = tile_args();
+    const int tm = ld_tm, tn = ld_tn, lb = ld_batch;
     const int r0 = tm * BM, c0 = tn * BN;
     if constexpr (PF) {
       // Lines of a slab: one per row where K is contiguous, else one per value of K and 64 rows.  2^sh workgroups share them.
-      const int sh = pf_a || p.tiles_m < 8 ? 2 : 3, wave_lines = 2 * (pf_a ? BM : BN) / Cfg::kWaves;
+      const int sh = pf_a || p.tiles_m < 8 ? 2 : 3, wave_lines = 2 * (pf_a ? Cfg::ROWS : BN) / Cfg::kWaves;
       const int line = (wave % (Cfg::kWaves / 2)) * wave_lines +
                        min(((ln >> sh) << sh) + ((pf_a ? tn : tm) & ((1 << sh) - 1)), wave_lines - 1);
       const int64_t ld = pf_a ? p.lda : p.ldb;
@@ -271,7 +288,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
         return (uint32_t)(((int64_t)(line / per_k) * ld + min(line % per_k * 64, left - 8)) * 2);
       };
       if constexpr (A_KF && B_KF) pf_off = row_line();
-      else if (pf_a) pf_off = A_KF ? row_line() : k_line(BM / 64);
+      else if (pf_a) pf_off = A_KF ? row_line() : k_line(Cfg::ROWS / 64);
       else pf_off = B_KF ? row_line() : k_line(BN / 64);
     }
     ld_a = (const char*)((const T*)p.A + (int64_t)lb * p.stride_a + (A_KF ? (int64_t)r0 * p.lda : (int64_t)r0)) + (int64_t)kt * a_step;
@@ -280,11 +297,11 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     for (int q = 0; q < Cfg::A_LOADS; ++q) {
       if constexpr (!A_KF) {                      // (M is a multiple of 8 here: a unit of 8 rows is never split)
         int k, row;
-        strided_unit(wave * Cfg::A_LOADS + q, ln, k, row);
+        strided_unit(a_unit(q), ln, k, row);
         a_off[q] = (uint32_t)(((int64_t)k * p.lda + min(row, p.M - 8 - r0)) * 2);
         continue;
       }
-      const int r = (wave * Cfg::A_LOADS + q) * RPI + ln / CPR;
+      const int r = a_unit(q) * RPI + ln / CPR;
       const int c = (ln % CPR) ^ swz16(r);
       const int rr = min(r, p.M - 1 - r0);
       a_off[q] = (uint32_t)(((int64_t)rr * p.lda + c * 8) * 2);
@@ -303,7 +320,8 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       b_off[q] = (uint32_t)(((int64_t)rr * p.ldb + c * 8) * 2);
     }
   };
-  load_tile(blockIdx.x, lane, 0);
+  locate(blockIdx.x);
+  load_tile(lane, 0);
   const char* const Ab = ld_a;                   // (the first tile's panels: the one-tile path indexes them by slab)
   const char* const Bb = ld_b;
 
@@ -323,7 +341,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     SlabIo io;
     io.ga = uniform_ptr(ga);
     io.gb = uniform_ptr(gb);
-    io.la = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_base + st * Cfg::STAGE_BYTES + wave * (Cfg::A_LOADS * 1024)));
+    io.la = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_base + st * Cfg::STAGE_BYTES + wave * (Cfg::A_ID_WAVE * 1024)));
     io.lb = (uint32_t)__builtin_amdgcn_readfirstlane(
         (int)(lds_base + st * Cfg::STAGE_BYTES + Cfg::A_BYTES + wave * (Cfg::B_LOADS * 1024)));
     return io;
@@ -336,10 +354,13 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   // by a scalar add; one wait state must pass before the load reads it.  The address pair must
   // not have been written by a vector instruction within five cycles of the load (the hardware
   // does not check): slab_io produces it long before, and the build scans the generated code for it.
-  auto issue_one_load = [&](int q, const SlabIo& io) __attribute__((always_inline)) {
+  // (UNEVEN: B's loads go first, so that the load some waves leave out is the last of the slab.)
+  auto issue_one_load = [&](int i, const SlabIo& io) __attribute__((always_inline)) {
+    const int q = Cfg::UNEVEN ? (i + Cfg::A_LOADS) % kLoads : i;
     if (q < Cfg::A_LOADS) {
+      if (!has_unit(q)) return;
       asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3"
-                   :: "s"(io.la), "n"(q * 1024), "v"(a_off[q < Cfg::A_LOADS ? q : 0]), "s"(io.ga) : "memory", "m0", "scc");
+                   :: "s"(io.la), "n"(q * Cfg::A_ID_Q * 1024), "v"(a_off[q < Cfg::A_LOADS ? q : 0]), "s"(io.ga) : "memory", "m0", "scc");
     } else {
       asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3"
                    :: "s"(io.lb), "n"((q - Cfg::A_LOADS) * 1024), "v"(b_off[q >= Cfg::A_LOADS ? q - Cfg::A_LOADS : 0]), "s"(io.gb) : "memory", "m0", "scc");
@@ -364,9 +385,9 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     const int kvalid = p.K - kt * BK;
     u32x4_t v = {0u, 0u, 0u, 0u};
     if (q < Cfg::A_LOADS) {
-      const int r = (wave * Cfg::A_LOADS + q) * RPI + lane / CPR;
+      const int r = a_unit(q) * RPI + lane / CPR;
       int k = ((lane % CPR) ^ swz16(r)) * 8, row = 0;            // the piece's first value of K
-      if constexpr (!A_KF) strided_unit(wave * Cfg::A_LOADS + q, lane, k, row);
+      if constexpr (!A_KF) strided_unit(a_unit(q), lane, k, row);
       if (k < kvalid) v = *(const u32x4_t*)(Ab + (int64_t)kt * a_step + a_off[q < Cfg::A_LOADS ? q : 0]);
     } else {
       const int qb = q >= Cfg::A_LOADS ? q - Cfg::A_LOADS : 0;
@@ -378,7 +399,8 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     return v;
   };
   auto store_tail_q = [&](int q, const u32x4_t& v) __attribute__((always_inline)) {       // into stage 0
-    unsigned char* to = q < Cfg::A_LOADS ? smem + wave * (Cfg::A_LOADS * 1024) + q * 1024
+    if (q < Cfg::A_LOADS && !has_unit(q)) return;
+    unsigned char* to = q < Cfg::A_LOADS ? smem + a_unit(q) * 1024
                                          : smem + Cfg::A_BYTES + wave * (Cfg::B_LOADS * 1024) + (q - Cfg::A_LOADS) * 1024;
     *(u32x4_t*)(to + lane * 16) = v;
   };
@@ -408,7 +430,8 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       const int at = lds_base + st * Cfg::STAGE_BYTES + fo * 1024 + j * 128 + (fr & 3) * 8;
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
-        if constexpr (!A_KF) a_rd[x] = at + (wm * Cfg::WTM / 64) * 8192 + ((x ^ key) * 32);
+        // (fragment m of the wave is the 32-byte piece f % 4 of block f / 4, f = wm * MT + m; x = m % 4)
+        if constexpr (!A_KF) a_rd[x] = at + ((wm * MT + x) >> 2) * 8192 + ((((wm * MT + x) & 3) ^ key) * 32);
         if constexpr (!B_KF) b_rd[x] = at + Cfg::A_BYTES + (wn * Cfg::WTN / 64) * 8192 + ((x ^ key) * 32);
       }
     }
@@ -430,6 +453,14 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     for (int n = 0; n < NT; ++n)
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[m][n][r] = 0.0f;
+  // The MFMAs are assembly statements the compiler's hazard recogniser cannot see: all zeros are written here, well before the
+  // first product (left to itself the compiler put a register's zero right in front of the MFMA that reads it, which then
+  // took the old value).
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) asm volatile("" : "+a"(acc[m][n]));
+  asm volatile("s_nop 7" ::: "memory");
 
   // Fragment registers: row fragments double-buffered per sub-step, column fragments per k-step.
   FragReg<RA> af[2][MA];
@@ -440,20 +471,20 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   auto read_one = [&](auto u_c, int i) __attribute__((always_inline)) {
     constexpr int u = decltype(u_c)::value;
     constexpr int kk = u / G, g = u % G;
-    typedef SubOrder<MA, NT, g == 0, RA, RB> Ord;
+    typedef SubOrder<Cfg::group_rows(g), NT, g == 0, RA, RB> Ord;
     const int idx = Ord::t.r_idx[i], part = Ord::t.r_part[i];
     if (Ord::t.r_isb[i]) {
       if constexpr (B_KF) lds_read_b128(bf[kk & 1][idx].v, b_rd[kk], idx * (16 * ROWB));
       else lds_read_tr16(bf[kk & 1][idx].h[part], b_rd[idx & 3], (idx >> 2) * 8192 + kk * 4096 + part * 512);
     } else {
-      const int m = g * MA + idx;
+      const int m = Cfg::group_first(g) + idx;
       if constexpr (A_KF) lds_read_b128(af[u & 1][idx].v, a_rd[kk], m * (16 * ROWB));
       else lds_read_tr16(af[u & 1][idx].h[part], a_rd[m & 3], (m >> 2) * 8192 + kk * 4096 + part * 512);
     }
   };
   auto read_all = [&](auto u_c) __attribute__((always_inline)) {
     constexpr int u = decltype(u_c)::value;
-    typedef SubOrder<MA, NT, (u % G) == 0, RA, RB> Ord;
+    typedef SubOrder<Cfg::group_rows(u % G), NT, (u % G) == 0, RA, RB> Ord;
 #pragma unroll
     for (int i = 0; i < Ord::kReads; ++i) read_one(u_c, i);
   };
@@ -467,8 +498,9 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     constexpr int u = decltype(u_c)::value;
     constexpr int kk = u / G, g = u % G;
     constexpr int un = (u + 1) % NSUB;                    // the sub-step the reads are for
-    typedef SubOrder<MA, NT, g == 0, RA, RB> Ord;         // how this sub-step's operands were requested
-    typedef SubOrder<MA, NT, (un % G) == 0, RA, RB> OrdN; // this sub-step's own requests
+    typedef SubOrder<Cfg::group_rows(g), NT, g == 0, RA, RB> Ord;   // how this sub-step's operands were requested
+    typedef SubOrder<Cfg::group_rows(un % G), NT, (un % G) == 0, RA, RB> OrdN; // this sub-step's own requests
+    constexpr int per_mfma = (OrdN::kReads + Ord::kMfma - 1) / Ord::kMfma;         // requests behind one MFMA
     const int nq = q1 - q0;
     int waited = -1;
 #pragma unroll
@@ -476,14 +508,14 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       const int m = Ord::t.mm[i], n = Ord::t.nn[i];
       if (Ord::t.need[i] > waited) {
         // since the needed request: the rest of that sub-step's requests and those of ours so far
-        const int ours = i * OrdN::kPerMfma;
+        const int ours = i * per_mfma;
         const int after = (Ord::kReads - 1 - Ord::t.need[i]) + (reads ? (ours < OrdN::kReads ? ours : OrdN::kReads) : 0);
         wait_lgkmcnt_dyn(after);                 // (the counter holds 15 at most: larger values wait for 15)
         waited = Ord::t.need[i];
       }
-      Frag16<T>::mfma(bf[kk & 1][n].get(), af[u & 1][m].get(), acc[g * MA + m][n]);
+      Frag16<T>::mfma(bf[kk & 1][n].get(), af[u & 1][m].get(), acc[Cfg::group_first(g) + m][n]);
 #pragma unroll
-      for (int r = i * OrdN::kPerMfma; r < (i + 1) * OrdN::kPerMfma; ++r)
+      for (int r = i * per_mfma; r < (i + 1) * per_mfma; ++r)
         if (reads && r < OrdN::kReads) read_one(std::integral_constant<int, un>(), r);
 #pragma unroll
       for (int j = 0; j < nq; ++j)
@@ -816,33 +848,33 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
 #pragma unroll
     for (int x = 0; x < NB; ++x) b_rd[x] += by;
   };
-  // early: the rest of the loads of slab t+S-1 (begun after the previous hand-over) into the stage before this
-  // one; late: the first loads of slab t+S into this stage after the hand-over; deep: the S-2 slabs after the next
-  // one are requested, so the wait for the next one leaves their loads in flight
-  auto slab_body = [&](auto early_c, auto late_c, auto deep_c) __attribute__((always_inline)) {
-    constexpr bool early = decltype(early_c)::value, late = decltype(late_c)::value, deep = decltype(deep_c)::value;
-    SlabIo io_early = io_none, io_late = io_none;
+  // early: the rest of the loads of slab t+S-1 (begun after the previous hand-over) into the stage before this one, so that
+  // the S-2 slabs after the next one are requested and the wait for the next one leaves their loads in flight; late: the first
+  // loads of slab t+S into this stage after the hand-over.  (One body for all slabs but the last S, one for those, each in a loop of
+  // its own: with copies of the body in the branches of a condition the compiler moved accumulators between registers where
+  // the branches met, with none of the wait states that MFMAs in assembly need around such moves.)
+  auto slab_body = [&](auto late_c, bool early) __attribute__((always_inline)) {
+    constexpr bool late = decltype(late_c)::value;
     const int before = S == 2 ? stage ^ 1 : (stage == 0 ? S - 1 : stage - 1);
-    if constexpr (early) io_early = slab_io(t + S - 1, before);
-    if constexpr (late) io_late = slab_io(t + S, stage);
+    const SlabIo io_early = slab_io(t + S - 1, before), io_late = slab_io(t + S, stage);
     static_for<0, NSUB - 1>([&](auto u_c) __attribute__((always_inline)) {
       constexpr int u = decltype(u_c)::value;
       set_prio(u < 3 ? 2 - u : 0);
       constexpr int q0 = kLoads * (u + 1) / LW, q1 = kLoads * (u + 2) / LW;
       if constexpr (PF && late && u == LW - 1) prefetch(Ab + (int64_t)(t + 2) * a_step, Bb + (int64_t)(t + 2) * b_step);
-      if constexpr (early && u + 1 < LW)
-        sub_step(u_c, true, q0 < kLoads ? q0 : kLoads, q1 < kLoads ? q1 : kLoads, io_early);
+      if constexpr (u + 1 < LW)
+        sub_step(u_c, true, q0 < kLoads ? q0 : kLoads, q1 < kLoads ? q1 : kLoads, io_early, early);
       else
         sub_step(u_c, true, 0, 0, io_none);
     });
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(deep ? (S - 2) * kLoads + (PF && late ? 1 : 0) : 0) : "memory");
+    if (early) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * kLoads + (PF && late ? 1 : 0)) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     set_prio(3);
     if constexpr (S == 2) flip_read_stage();
     else next_read_stage();
-    if constexpr (late) sub_step(std::integral_constant<int, NSUB - 1>(), true, 0, kLoads / LW, io_late);
-    else sub_step(std::integral_constant<int, NSUB - 1>(), true, 0, 0, io_none);
+    sub_step(std::integral_constant<int, NSUB - 1>(), true, 0, late ? kLoads / LW : 0, io_late);
     stage = S == 2 ? stage ^ 1 : (stage + 1 == S ? 0 : stage + 1);
   };
   typedef std::integral_constant<bool, true> yes_t;
@@ -856,29 +888,28 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     }
   }
   if (T_full > 0) {
-    // the first S slabs (as many as there are); the first one has landed when the others' loads are left
+    // the first S-1 slabs (as many as there are) and the first part of the next; the first one has landed when the others'
+    // loads are left
     static_for<0, S>([&](auto q_c) __attribute__((always_inline)) {
       constexpr int sl = decltype(q_c)::value;
       if (sl < T_full) {
         const SlabIo io = slab_io(sl, sl);
 #pragma unroll
-        for (int q = 0; q < kLoads; ++q) issue_one_load(q, io);
+        for (int q = 0; q < (sl == S - 1 ? kLoads / LW : kLoads); ++q) issue_one_load(q, io);
       }
     });
-    if (T_full >= S) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 1) * kLoads) : "memory");
+    if (T_full >= S) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * kLoads + kLoads / LW) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     read_all(std::integral_constant<int, 0>());
-    if (T_full > S) slab_body(no_t(), yes_t(), yes_t()); else slab_body(no_t(), no_t(), no_t());
-    for (t = 1; t < T_full - S; ++t) slab_body(yes_t(), yes_t(), yes_t());
-    if (T_full > S) { slab_body(yes_t(), no_t(), yes_t()); ++t; }
-    for (; t < T_full; ++t) slab_body(no_t(), no_t(), no_t());
-    set_prio(0);
-    // the last fragment reads (of a stage nobody multiplies) are still in flight
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    if (stage) set_read_stage(0, lane);        // the K tail reads stage 0
   }
+  for (t = 0; t < T_full - S; ++t) slab_body(yes_t(), true);
+  for (; t < T_full; ++t) slab_body(no_t(), t + S <= T_full);
+  set_prio(0);
+  // the last fragment reads (of a stage nobody multiplies) are still in flight
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  if (stage) set_read_stage(0, lane);          // the K tail reads stage 0
   if (T_full * BK < p.K) {                     // K tail, through registers with zero fill
     __builtin_amdgcn_s_barrier();              // every wave is done with the LDS stages
     asm volatile("" ::: "memory");
@@ -900,10 +931,8 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     });
     wait_lgkmcnt<0>();
   }
-  int tm, tn;
-  if constexpr (S == 2) tile_coords<kEither>(p, blockIdx.x, n_tiles, tm, tn);
-  else tile_and_batch<kEither>(p, batch, tm, tn);
-  epilogue(tm * BM, tn * BN);
+  batch = ld_batch;
+  epilogue(ld_tm * BM, ld_tn * BN);
   } else {
   // ---- persistent: the tiles of this workgroup as one stream of slabs ------------------------
   // The loads run two slabs ahead of the MFMAs and simply carry on into the next tile's panels:
@@ -911,6 +940,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   // offsets describe the slab the loads are at; they move on one slab at a time and switch to
   // the next tile when this one's slabs are all requested.
   int ld_vid = blockIdx.x, ld_t = 0;
+  int cur_tm = ld_tm, cur_tn = ld_tn, cur_batch = ld_batch;     // the tile being multiplied
   auto fresh_lane_id = []() __attribute__((always_inline)) {
     unsigned z = 0;
     asm volatile("" : "+v"(z));
@@ -921,7 +951,10 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     if (++ld_t == T_full) {
       ld_t = 0;
       ld_vid += gridDim.x;
-      if (ld_vid < total_tiles) load_tile(ld_vid, fresh_lane_id(), 0);   // (no lane id kept in a register across the loop)
+      if (ld_vid < total_tiles) {
+        locate(ld_vid);
+        load_tile(fresh_lane_id(), 0);           // (no lane id kept in a register across the loop)
+      }
     }
   };
   // tile_end (compile time): the last slab of a tile; its last sub-step requests no fragments (the
@@ -976,18 +1009,14 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     body(yes_t(), !last, !last);
     set_prio(0);
     wait_lgkmcnt<0>();
-    int tm, tn;
-    const MfmaArgs pt = tile_args();
-    const int n_tiles = pt.tiles_m * pt.tiles_n;
-    const int lid = logical_tile(pt, vid);
-    batch = lid / n_tiles;
-    tile_coords<kEither>(pt, lid - batch * n_tiles, n_tiles, tm, tn);
-    epilogue(tm * BM, tn * BN);
+    batch = cur_batch;
+    epilogue(cur_tm * BM, cur_tn * BN);
+    cur_tm = ld_tm; cur_tn = ld_tn; cur_batch = ld_batch;     // (the loads are in the next tile by now)
     if (!last) {
       // the lane-dependent offsets and addresses are derived afresh here (from an opaque copy of the
       // lane id, so that the compiler cannot keep the earlier ones alive across the epilogue instead)
       const int lane_now = fresh_lane_id();
-      load_tile(ld_vid, lane_now, ld_t);
+      load_tile(lane_now, ld_t);
       set_read_stage(stage, lane_now);
 #pragma unroll
       for (int m = 0; m < MT; ++m)

@@ -56,10 +56,14 @@ hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void
 // stages), one tile per workgroup or a persistent workgroup walking over several
 #define MI355GEMM_MFMA16_TILES(X) \
   X(256, 256, 2, 4, 2, false)     \
+  X(224, 256, 2, 4, 2, false)     \
+  X(192, 256, 2, 4, 2, false)     \
   X(256, 256, 2, 2, 2, false)     \
   X(128, 128, 2, 2, 2, false)
 #define MI355GEMM_MFMA16P_TILES(X) \
   X(256, 256, 2, 4, 2, true)       \
+  X(224, 256, 2, 4, 2, true)       \
+  X(192, 256, 2, 4, 2, true)       \
   X(128, 128, 2, 2, 2, true)
 
 // The same for operands whose K is not contiguous, one translation unit per operand type and layout pair
@@ -67,6 +71,8 @@ hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void
 #define MI355GEMM_MFMA16T_TILES(X) \
   X(256, 256, 2, 4, 2, false)      \
   X(256, 256, 2, 4, 2, true)       \
+  X(192, 256, 2, 4, 2, false)      \
+  X(192, 256, 2, 4, 2, true)       \
   X(128, 128, 2, 2, 2, false)      \
   X(128, 128, 2, 2, 2, true)
 #define MI355GEMM_MFMA16T_DECLARE(T, BM, BN, WM, WN, G, P, AK, BK)                            \

@@ -36,7 +36,7 @@ inline TileOrder make_tile_order(int tiles_m, int tiles_n, bool strips) {
 // Kernels whose launches may take strips: large tiles with two slabs in LDS.  (The persistent 256x256 kernels never gained more
 // than 3 % by them and pay for the choice.)
 template <int BM, int BN, int SLABS, bool PERSIST>
-constexpr bool kEitherOrder = BM * BN >= 128 * 128 && SLABS == 2 && !(PERSIST && BM * BN == 256 * 256);
+constexpr bool kEitherOrder = BM * BN >= 128 * 128 && SLABS == 2 && !(PERSIST && BM * BN > 128 * 128);
 
 // Which of the two a launch takes.  two_per_cu: two workgroups of this kernel fit a CU; whole_rows: rows of C are whole
 // 16-byte pieces.
@@ -67,7 +67,8 @@ __host__ __device__ __forceinline__ void tile_of(const TileOrder& o, int tiles_m
   int id = wg;
   if (spread) {                                        // one contiguous eighth per XCD: of the grid, or of a round of 256 ids
     const int base = whole ? 0 : wg & ~255, size = whole ? n_wg : least(256, n_wg - base);
-    if ((size & 7) == 0) id = base + (wg & 7) * (size >> 3) + ((wg - base) >> 3);
+    if (!whole) id = base + (wg & 7) * (size >> 3) + least(wg & 7, size & 7) + ((wg - base) >> 3);   // (the first size % 8 XCDs take one more)
+    else if ((size & 7) == 0) id = (wg & 7) * (size >> 3) + (wg >> 3);
   }
   const int group = div_by(id, G * tiles_n, o.div_group);
   id -= group * (G * tiles_n);

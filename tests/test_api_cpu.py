@@ -286,6 +286,15 @@ def test_build_guard_flags_kernels_that_use_scratch_memory():
     assert kernels_with_scratch("") == []
 
 
+def test_build_guard_flags_accumulators_written_right_before_an_mfma():
+    from paper_2603_12440_amd.build import accumulator_hazards
+    mfma = "\tv_mfma_f32_16x16x32_bf16 a[4:7], v[0:3], v[8:11], a[4:7]\n"
+    assert len(accumulator_hazards("\tv_accvgpr_mov_b32 a4, a8\n" + mfma)) == 1
+    assert len(accumulator_hazards("\tv_accvgpr_write_b32 a7, 0\n\t;comment\n\ts_waitcnt lgkmcnt(0)\n" + mfma)) == 1
+    assert accumulator_hazards("\tv_accvgpr_write_b32 a7, 0\n\ts_nop 1\n" + mfma) == []
+    assert accumulator_hazards("\tv_accvgpr_mov_b32 a8, a4\n\tv_accvgpr_read_b32 v1, a4\n" + mfma) == []
+
+
 def test_tuning_mode_switch_and_environment(g):
     """Tuning mode is off by default, follows GEMM_TUNE at first use, and the switch returns the
     previous setting; the table of remembered problems starts empty (no device needed)."""
