@@ -607,9 +607,10 @@ double round_cost(const Config& c, const gemm_desc_t& d, int64_t N, double* roun
   // workgroups that actually share a CU (a lone workgroup runs about per_cu times faster)
   const double sharing = tiles >= cus * per_cu ? per_cu : (tiles > cus ? tiles / cus : 1.0);
   *rounds_out = rounds;
-  // (a persistent tile's epilogue overlaps the next one's loads, which counts where K is short: 2048 x 12000 x 256 21.7 us, 22.9
-  // on 224x256 tiles)
-  const double fixed = c.persist && K <= 512 ? 350.0 : 600.0;
+  // (a short K: less of a tile's fixed cost is left uncovered than the 600 columns fitted to long ones.  2048 x 12000 x 256 21.7 us
+  // persistent, 22.9 on 224x256 tiles; 6528 x 6240 x 275 40.6 us with one tile per workgroup, 53.5 on 256x256; 1024 x 17416 x 136
+  // 28 us on these, 26 as two launches)
+  const double fixed = area <= 128 * 128 && K <= 512 && (c.persist || K >= 192) ? 350.0 : 600.0;
   return rounds * area * sharing / eff * ((double)K + fixed) / (e == 1 ? 5.4e6 : 2.7e6);
 }
 
@@ -783,6 +784,11 @@ int fill_launch_shape(gemm_plan& pl) {
       pl.grid = dim3((unsigned)wgs, (unsigned)d.batch, 1);
     }
     pl.xcd_remap = d.batch == 1 || (tm * tn) % 8 == 0 ? 1 : 0;
+    // less than a round of small tiles, not a multiple of 8 and not wider than high: dealt round-robin, an XCD gets the same tile
+    // rows of every strip, which reads A once (5712x584x785, 45x5 tiles: 13.9 us, 14.5 with contiguous runs per XCD;
+    // 577x400x984 7.7 / 8.2).  Wider ones: 100x5000x4096 24.6 / 17.1; 256x256 tiles, 23x10 of them: 114 / 106.
+    if (d.batch == 1 && tm * tn < 256 && (tm * tn) % 8 != 0 && tn <= tm && c.bm * c.bn <= 128 * 128 && d.K * esize(d.dtype_a) > 512)
+      pl.xcd_remap = 0;
     // a batch, one tile per workgroup, on the kernels with a deeper ring: whole problems per XCD as well (512x512x2048,
     // 16 problems: 33 us with a problem's tiles spread over the XCDs)
     if (c.t1 > 0 && d.batch > 1 && (tm * tn * d.batch) % 8 == 0) {
