@@ -588,9 +588,10 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       }
     };
 
-    const bool through_lds = !pe.c_f32 && (pe.ldc % 8 == 0) && (pe.stride_c % 8 == 0) &&
-                             (((uintptr_t)pe.C & 15) == 0);
-    const bool through_lds32 = pe.c_f32 && (pe.ldc % 4 == 0) && (pe.stride_c % 4 == 0) && (((uintptr_t)pe.C & 15) == 0);
+    // Rows of C start at any element: the 16-byte stores take element alignment.  (They used to go element by element where rows
+    // were not whole 16-byte pieces, one tile per workgroup: see launch_mfma16.)
+    typedef u32x4_t __attribute__((aligned(2))) u32x4_any_t;
+    typedef f32x4_t __attribute__((aligned(4))) f32x4_any_t;
     constexpr int OROWB = Cfg::WTN * 2;           // bytes per 16-bit row of the wave's block (128 or 256)
     constexpr int CH = OROWB / 16;
     constexpr int OROWB32 = Cfg::WTN * 4;         // bytes per fp32 row (256 or 512)
@@ -659,7 +660,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
         if (inside) {
 #pragma unroll
           for (int it = 0; it < kIt16; ++it)
-            __builtin_nontemporal_store(val[it], (u32x4_t*)(wave_c + (lane_off[it] + (uint32_t)m * band_step)));
+            __builtin_nontemporal_store(val[it], (u32x4_any_t*)(wave_c + (lane_off[it] + (uint32_t)m * band_step)));
           return;
         }
 #pragma unroll
@@ -671,7 +672,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
           if (i < pe.M && j < pe.N) {
             TO* c = Cb + (int64_t)i * pe.ldc + j;
             if (j + 8 <= pe.N) {
-              __builtin_nontemporal_store(val[it], (u32x4_t*)c);   // C is not read again here: keep it from displacing A and B in L2
+              __builtin_nontemporal_store(val[it], (u32x4_any_t*)c);   // C is not read again here: keep it from displacing A and B in L2
             } else {                               // ragged right edge: element by element
 #pragma unroll
               for (int t2 = 0; t2 < 8; ++t2) {
@@ -726,7 +727,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
           const int r = e / CH32, q = e % CH32;
           const f32x4_t val = *(const f32x4_t*)(wt + r * OROWB32 + ((q ^ (r & 15)) * 16));
           if (inside) {
-            f32x4_t* c = (f32x4_t*)(wave_c + (lane_off[it] + (uint32_t)m * band_step));
+            f32x4_any_t* c = (f32x4_any_t*)(wave_c + (lane_off[it] + (uint32_t)m * band_step));
             if (pe.c_cached) *c = val;             // split-K partials are read by the next kernel
             else __builtin_nontemporal_store(val, c);
             continue;
@@ -736,8 +737,8 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
           if (i < pe.M && j < pe.N) {
             float* c = Cf + (int64_t)i * pe.ldc + j;
             if (j + 4 <= pe.N) {
-              if (pe.c_cached) *(f32x4_t*)c = val;
-              else __builtin_nontemporal_store(val, (f32x4_t*)c);
+              if (pe.c_cached) *(f32x4_any_t*)c = val;
+              else __builtin_nontemporal_store(val, (f32x4_any_t*)c);
             } else {
 #pragma unroll
               for (int t2 = 0; t2 < 4; ++t2)
@@ -747,57 +748,10 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
         }
       });
     };
-    // straight from the accumulator layout (C rows that are not 16-byte aligned)
-    auto drain = [&](auto actf) __attribute__((always_inline)) {
-      const bool vec_ok = (pe.ldc % 4 == 0) && (((uintptr_t)pe.C & 15) == 0) && (pe.stride_c % 4 == 0);
-#pragma unroll
-      for (int n = 0; n < NT; ++n) {
-        const int j = col0 + wn * Cfg::WTN + n * 16 + eq * 4;
-        float bv[4];
-        bias4(j, bv);
-#pragma unroll
-        for (int m = 0; m < MT; ++m) {
-          float v[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = actf(acc[m][n][e] + bv[e]);
-          const int i = row0 + wm * Cfg::WTM + m * 16 + er;
-          if (i >= pe.M || j >= pe.N) continue;
-          const bool full = (j + 3 < pe.N);
-          const int64_t o = (int64_t)batch * pe.stride_c + (int64_t)i * pe.ldc + j;
-          if (pe.c_f32) {
-            float* c = (float*)pe.C + o;
-            if (full && vec_ok) {
-              f32x4_t w = {v[0], v[1], v[2], v[3]};
-              *(f32x4_t*)c = w;
-            } else {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (j + e < pe.N) c[e] = v[e];
-            }
-          } else {
-            TO* c = (TO*)pe.C + o;
-            if (full && vec_ok) {
-              u32x2_t w = {pack2<TO>(v[0], v[1]), pack2<TO>(v[2], v[3])};
-              *(u32x2_t*)c = w;
-            } else {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (j + e < pe.N) c[e] = from_float<TO>(v[e]);
-            }
-          }
-        }
-      }
-    };
-    // dest: 0 = memory from the accumulator layout, 1 = 16-bit through LDS, 2 = fp32 through LDS
+    // dest: 1 = 16-bit, 2 = fp32
     auto drain_to = [&](auto actf, auto dest) __attribute__((always_inline)) {
-      constexpr int kDest = decltype(dest)::value;
-      if constexpr (kDest == 2) {
-        drain32_all(actf);
-      } else if constexpr (kDest == 1) {
-        drain16_all(actf);
-      } else {
-        drain(actf);
-      }
+      if constexpr (decltype(dest)::value == 2) drain32_all(actf);
+      else drain16_all(actf);
     };
     auto drain_by_activation = [&](auto dest) __attribute__((always_inline)) {
       switch (act) {
@@ -810,16 +764,11 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       }
     };
 
-    if (!through_lds && !through_lds32) {
-      // (a persistent workgroup is only launched for C rows that take the staged routes below)
-      if constexpr (!PERSIST) drain_by_activation(std::integral_constant<int, 0>());
-      return;
-    }
     if constexpr (!PERSIST) {
       __builtin_amdgcn_s_barrier();              // all waves are done reading the slab stages
       asm volatile("" ::: "memory");
     }
-    if (through_lds32) {
+    if (pe.c_f32) {
       drain_by_activation(std::integral_constant<int, 2>());
       return;
     }

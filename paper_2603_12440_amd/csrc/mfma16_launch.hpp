@@ -35,19 +35,7 @@ MfmaArgs mfma16_args(const gemm_plan& pl, const void* A, const void* B, void* C,
 template <typename T, typename TO, int BM, int BN, int WM, int WN, int G, bool PERSIST, bool A_KF = true, bool B_KF = true, int S = 2>
 hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void* C,
                          const void* bias, hipStream_t s) {
-  const gemm_desc_t& d = pl.d;
   const MfmaArgs a = mfma16_args<BM, BN, kEitherOrder<BM, BN, S, PERSIST>>(pl, A, B, C, bias);
-  if constexpr (PERSIST) {
-    // The persistent kernel only has the staged output routes (whole-line stores): C rows that are
-    // not 16-byte aligned run one tile per workgroup instead.
-    const int64_t unit = a.c_f32 ? 4 : 8;
-    const bool staged = d.ldc % unit == 0 && d.stride_c % unit == 0 && ((uintptr_t)C & 15) == 0;
-    if (!staged) {
-      const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)d.batch, 1);
-      mfma16_gemm_kernel<T, TO, BM, BN, WM, WN, G, false, A_KF, B_KF, S><<<grid, pl.block, 0, s>>>(a);
-      return hipGetLastError();
-    }
-  }
   mfma16_gemm_kernel<T, TO, BM, BN, WM, WN, G, PERSIST, A_KF, B_KF, S><<<pl.grid, pl.block, 0, s>>>(a);
   return hipGetLastError();
 }

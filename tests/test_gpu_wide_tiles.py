@@ -53,6 +53,10 @@ def test_slabs_tails_and_edges(g, dtype, la, lb):
             w = wl.Workload("t", M, N, K, dtype=dtype, layout_a=la, layout_b=lb, epilogue="bias_relu", seed_a=K, seed_b=M)
             run_exact(g, w, cfg, out_dtype="f32")
             run_exact(g, w, cfg)
+        for N in (257, 519):                                # rows of C that start at any element
+            w = wl.Workload("t", bm + 8, N if lb == "col" else N // 8 * 8, 256, dtype=dtype, layout_a=la, layout_b=lb, epilogue="bias_relu", seed_a=N, seed_b=3)
+            run_exact(g, w, cfg, pad_c=1)
+            run_exact(g, w, cfg, pad_c=3, out_dtype="f32")
         run_exact(g, wl.Workload("t", bm + 8, 264, 192, dtype=dtype, layout_a=la, layout_b=lb, batch=3, seed_a=1, seed_b=2), cfg, out_dtype="f32")
 
 
