@@ -588,8 +588,8 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       }
     };
 
-    // Rows of C start at any element: the 16-byte stores take element alignment.  (They used to go element by element where rows
-    // were not whole 16-byte pieces, one tile per workgroup: see launch_mfma16.)
+    // Rows of C start at any element: the 16-byte stores take element alignment.  (Element by element where rows
+    // were not whole 16-byte pieces: 2432x2431x4096 60 us, 51 this way; 3000x9001x256 62 and 37.)
     typedef u32x4_t __attribute__((aligned(2))) u32x4_any_t;
     typedef f32x4_t __attribute__((aligned(4))) f32x4_any_t;
     constexpr int OROWB = Cfg::WTN * 2;           // bytes per 16-bit row of the wave's block (128 or 256)

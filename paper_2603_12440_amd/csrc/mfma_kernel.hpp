@@ -541,8 +541,9 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma_gemm_kernel(MfmaArgs p) {
     }
   };
 
-  const bool through_lds = !p.c_f32 && (p.ldc % 8 == 0) && (p.stride_c % 8 == 0) &&
-                           (((uintptr_t)p.C & 15) == 0);
+  // (rows of C start at any element: the 16-byte stores take element alignment)
+  typedef u32x4_t __attribute__((aligned(2))) u32x4_any_t;
+  typedef f32x4_t __attribute__((aligned(4))) f32x4_any_t;
   constexpr int OROWB = Cfg::WTN * 2;           // bytes per row of the wave's block
   constexpr int CH = OROWB / 16;                // 16-byte chunks per row (8, 12 or 16)
   constexpr int OSW = CH % 8 == 0 ? 7 : 3;      // chunk-slot swizzle mask: stays inside the row for CH = 12
@@ -553,7 +554,6 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma_gemm_kernel(MfmaArgs p) {
   // fp32 output goes through the same LDS pieces in passes of MP 32-row tiles (a wave's share of
   // the stages holds a quarter to a half of its block in fp32): 16-byte writes in accumulator
   // order, 16-byte reads in row order, stores that cover whole lines.
-  const bool through_lds32 = p.c_f32 && (p.ldc % 4 == 0) && (p.stride_c % 4 == 0) && (((uintptr_t)p.C & 15) == 0);
   constexpr int OROWB32 = Cfg::WTN * 4;         // bytes per fp32 row of the wave's block
   constexpr int CH32 = OROWB32 / 16;            // 16-byte chunks per row (16, 24 or 32)
   constexpr int OSW32 = CH32 % 16 == 0 ? 15 : 7;
@@ -602,8 +602,8 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma_gemm_kernel(MfmaArgs p) {
         if (j + 4 <= p.N) {
           // C is normally not read again here: non-temporal, so that it does not displace A and B
           // in L2; split-K partials are read by the next kernel and should stay cached
-          if (p.c_cached) *(f32x4_t*)c = val;
-          else __builtin_nontemporal_store(val, (f32x4_t*)c);
+          if (p.c_cached) *(f32x4_any_t*)c = val;
+          else __builtin_nontemporal_store(val, (f32x4_any_t*)c);
         } else {
 #pragma unroll
           for (int t = 0; t < 4; ++t)
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma_gemm_kernel(MfmaArgs p) {
       if (i < p.M && j < p.N) {
         TO* c = Cb + (int64_t)i * p.ldc + j;
         if (j + 8 <= p.N) {
-          __builtin_nontemporal_store(val, (u32x4_t*)c);   // C is not read again here: keep it from displacing A and B in L2
+          __builtin_nontemporal_store(val, (u32x4_any_t*)c);   // C is not read again here: keep it from displacing A and B in L2
         } else {                                 // ragged right edge: element by element
 #pragma unroll
           for (int t = 0; t < 8; ++t) {
@@ -658,61 +658,13 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma_gemm_kernel(MfmaArgs p) {
       }
     }
   };
-  // straight from the accumulator layout (C rows that are not 16-byte aligned)
-  auto drain = [&](auto actf) __attribute__((always_inline)) {
-    const bool vec_ok = (p.ldc % 4 == 0) && (((uintptr_t)p.C & 15) == 0) && (p.stride_c % 4 == 0);
-#pragma unroll
-    for (int n = 0; n < NT; ++n) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int j = col0 + wn * Cfg::WTN + n * 32 + g * 8 + eh * 4;
-        float bv[4];
-        bias4(j, bv);
-#pragma unroll
-        for (int m = 0; m < MT; ++m) {
-          float v[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = actf(acc[m][n][g * 4 + e] + bv[e]);
-          {
-            const int i = row0 + wm * Cfg::WTM + m * 32 + er;
-            if (i >= p.M || j >= p.N) continue;
-            const bool full = (j + 3 < p.N);
-            const int64_t o = batch * p.stride_c + (int64_t)i * p.ldc + j;
-            if (p.c_f32) {
-              float* c = (float*)p.C + o;
-              if (full && vec_ok) {
-                f32x4_t w = {v[0], v[1], v[2], v[3]};
-                *(f32x4_t*)c = w;
-              } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                  if (j + e < p.N) c[e] = v[e];
-              }
-            } else {
-              TO* c = (TO*)p.C + o;
-              if (full && vec_ok) {
-                u32x2_t w = {pack2<TO>(v[0], v[1]), pack2<TO>(v[2], v[3])};
-                *(u32x2_t*)c = w;
-              } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                  if (j + e < p.N) c[e] = from_float<TO>(v[e]);
-              }
-            }
-          }
-        }
-      }
-    }
-  };
-  // dest: 0 = memory from the accumulator layout, 1 = 16-bit through LDS, 2 = fp32 through LDS
+  // dest: 1 = 16-bit, 2 = fp32
   auto drain_to = [&](auto actf, auto dest) __attribute__((always_inline)) {
     constexpr int kDest = decltype(dest)::value;
     if constexpr (kDest == 2) {
       static_for<0, MT / MP>([&](auto pass_c) __attribute__((always_inline)) { drain32(actf, pass_c); });
-    } else if constexpr (kDest == 1) {
-      static_for<0, MT>([&](auto pass_c) __attribute__((always_inline)) { drain16(actf, pass_c); });
     } else {
-      drain(actf);
+      static_for<0, MT>([&](auto pass_c) __attribute__((always_inline)) { drain16(actf, pass_c); });
     }
   };
   auto drain_by_activation = [&](auto dest) __attribute__((always_inline)) {
@@ -726,13 +678,9 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma_gemm_kernel(MfmaArgs p) {
     }
   };
 
-  if (!through_lds && !through_lds32) {
-    drain_by_activation(std::integral_constant<int, 0>());
-    return;
-  }
   __builtin_amdgcn_s_barrier();                // all waves are done reading the slab stages
   asm volatile("" ::: "memory");
-  if (through_lds32) {
+  if (p.c_f32) {
     drain_by_activation(std::integral_constant<int, 2>());
     return;
   }

@@ -303,7 +303,9 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
 
   // Lane l of a 16x16 accumulator tile holds row l % 16 and columns 4 (l / 16) .. +3 (operands go in swapped).
   const float* bias = p.has_bias ? p.bias + (int64_t)batch * p.stride_bias : nullptr;
-  const bool vec = p.ldc % 4 == 0 && p.stride_c % 4 == 0 && ((uintptr_t)p.C & 15) == 0;
+  // (rows of C start at any element: the stores of four columns take element alignment)
+  typedef f32x4_t __attribute__((aligned(4))) f32x4_any_t;
+  typedef u32x2_t __attribute__((aligned(2))) u32x2_any_t;
 #pragma unroll
   for (int n = 0; n < NT; ++n) {
     const int j = c0 + wn * Cfg::WTN + n * 16 + fo * 4;
@@ -311,7 +313,7 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
     float bv[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) bv[e] = bias && j + e < p.N ? bias[j + e] : 0.0f;
-    const bool full = j + 3 < p.N && vec;
+    const bool full = j + 3 < p.N;
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
       const int i = r0 + wm * Cfg::WTM + m * 16 + fr;
@@ -319,14 +321,13 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
       float v[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = apply_activation(p.act, acc[m][n][e] + bv[e], p.scale);
-      if constexpr (!DIRECT) {
-        const int64_t si = p.c_col ? 1 : p.ldc, sj = p.c_col ? p.ldc : 1;
-        const int64_t o = (int64_t)batch * p.stride_c + i * si + j * sj;
+      if (!DIRECT && p.c_col) {                        // a lane's columns are ldc apart
+        const int64_t o = (int64_t)batch * p.stride_c + i + j * p.ldc;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           if (j + e >= p.N) break;
-          if (p.c_f32) ((float*)p.C)[o + e * sj] = v[e];
-          else ((TO*)p.C)[o + e * sj] = from_float<TO>(v[e]);
+          if (p.c_f32) ((float*)p.C)[o + e * p.ldc] = v[e];
+          else ((TO*)p.C)[o + e * p.ldc] = from_float<TO>(v[e]);
         }
         continue;
       }
@@ -334,7 +335,7 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
       if (p.c_f32) {
         float* c = (float*)p.C + o;
         if (full) {
-          *(f32x4_t*)c = f32x4_t{v[0], v[1], v[2], v[3]};
+          *(f32x4_any_t*)c = f32x4_t{v[0], v[1], v[2], v[3]};
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
@@ -343,7 +344,7 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
       } else {
         TO* c = (TO*)p.C + o;
         if (full) {
-          *(u32x2_t*)c = u32x2_t{pack2<TO>(v[0], v[1]), pack2<TO>(v[2], v[3])};
+          *(u32x2_any_t*)c = u32x2_t{pack2<TO>(v[0], v[1]), pack2<TO>(v[2], v[3])};
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
