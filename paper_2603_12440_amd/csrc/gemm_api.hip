@@ -609,8 +609,8 @@ double round_cost(const Config& c, const gemm_desc_t& d, int64_t N, double* roun
   *rounds_out = rounds;
   // (a short K: less of a tile's fixed cost is left uncovered than the 600 columns fitted to long ones.  2048 x 12000 x 256 21.7 us
   // persistent, 22.9 on 224x256 tiles; 6528 x 6240 x 275 40.6 us with one tile per workgroup, 53.5 on 256x256; 1024 x 17416 x 136
-  // 28 us on these, 26 as two launches)
-  const double fixed = area <= 128 * 128 && K <= 512 && (c.persist || K >= 192) ? 350.0 : 600.0;
+  // 28 us on these, 26 as two launches.  Not for batches, the slices of split-K among them.)
+  const double fixed = d.batch == 1 && area <= 128 * 128 && K <= 512 && (c.persist || K >= 192) ? 350.0 : 600.0;
   return rounds * area * sharing / eff * ((double)K + fixed) / (e == 1 ? 5.4e6 : 2.7e6);
 }
 
