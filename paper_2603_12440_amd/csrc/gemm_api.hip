@@ -592,7 +592,8 @@ double wide_cost(const Config& c, const gemm_desc_t& d, double tiles, int off_li
   return 3.0 + turn * (whole + (part > 0 ? 0.6 + 0.4 * part : 0.0));
 }
 
-double round_cost(const Config& c, const gemm_desc_t& d, int64_t N, double* rounds_out) {
+// (fixed: a tile's fixed cost in columns of K)
+double round_cost(const Config& c, const gemm_desc_t& d, int64_t N, double fixed, double* rounds_out) {
   const int64_t M = d.M, K = d.K;
   const int e = esize(d.dtype_a), area = c.bm * c.bn;
   const double tiles = (double)((M + c.bm - 1) / c.bm) * (double)((N + c.bn - 1) / c.bn) * (double)d.batch;
@@ -607,10 +608,6 @@ double round_cost(const Config& c, const gemm_desc_t& d, int64_t N, double* roun
   // workgroups that actually share a CU (a lone workgroup runs about per_cu times faster)
   const double sharing = tiles >= cus * per_cu ? per_cu : (tiles > cus ? tiles / cus : 1.0);
   *rounds_out = rounds;
-  // (a short K: less of a tile's fixed cost is left uncovered than the 600 columns fitted to long ones.  2048 x 12000 x 256 21.7 us
-  // persistent, 22.9 on 224x256 tiles; 6528 x 6240 x 275 40.6 us with one tile per workgroup, 53.5 on 256x256; 1024 x 17416 x 136
-  // 28 us on these, 26 as two launches.  Not for batches, the slices of split-K among them.)
-  const double fixed = d.batch == 1 && area <= 128 * 128 && K <= 512 && (c.persist || K >= 192) ? 350.0 : 600.0;
   return rounds * area * sharing / eff * ((double)K + fixed) / (e == 1 ? 5.4e6 : 2.7e6);
 }
 
@@ -635,8 +632,12 @@ double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
   }
   // (of the two 256x256 shapes the eight-wave one goes first)
   if (!std::strncmp(c.name, "mfma16", 6) && area > 128 * 128) return wide_cost(c, d, tiles, off_line) * (c.threads == 512 ? 1.0 : 1.02);
+  // (a short K: less of a tile's fixed cost is left uncovered than the 600 columns fitted to long ones.  2048 x 12000 x 256 21.7 us
+  // persistent, 22.9 on 224x256 tiles; 6528 x 6240 x 275 40.6 us with one tile per workgroup, 53.5 on 256x256; 1024 x 17416 x 136
+  // 28 us on these, 26 as two launches.  Not for batches, the slices of split-K among them.)
+  const double fixed = d.batch == 1 && area <= 128 * 128 && K <= 512 && (c.persist || K >= 192) ? 350.0 : 600.0;
   double rounds = 0;
-  const double work = round_cost(c, d, N, &rounds) * (e == 2 ? 1.0 + (area > 128 * 128 ? 0.2 : 0.08) * off_line : 1.0);
+  const double work = round_cost(c, d, N, fixed, &rounds) * (e == 2 ? 1.0 + (area > 128 * 128 ? 0.2 : 0.08) * off_line : 1.0);
   const double wait = rounds * ((double)K / c.bk * (area <= 128 * 128 ? (e == 1 ? 0.42 * (1.0 + 0.5 * off_line) : 0.60 * (1.0 + 0.2 * off_line)) : 0.0) + 3.0);
   return work > wait ? work : wait;
 }
@@ -914,8 +915,10 @@ int gemm_create_config(const gemm_desc_t* desc, int config, gemm_plan_t** out_pl
 // Slices of K for a split-K plan: the count (up to 64, K a multiple of 8 x slices, whole
 // slabs per slice preferred) that minimises the round model of the two-slab tiles on the sliced product plus
 // the traffic of the fp32 partials (written once, read once: priced at 2 TB/s).  512x512x32768 takes 31 / 25 / 38 / 40 us
-// with 8 / 16 / 32 / 64 slices; the model picks 16.  (The count decides the workspace's size and how long the fp32 sums
-// are: it is not the four-slab kernels' model, which would take fewer slices and add more terms in each.)
+// with 8 / 16 / 32 / 64 slices; the model picks 16.  (The count decides the workspace's size, whether the fixed scratch buffer
+// holds it and how long the fp32 sums are, so it must not move when the choice of kernels is refitted: neither the four-slab
+// kernels' model, which would take fewer slices and add more terms in each, nor tiles of 192 or 224 rows, nor the short-K
+// terms of the estimate above take part.)
 static int choose_splits(const gemm_desc_t& d) {
   int best = 1;
   double best_cost = 0;
@@ -930,9 +933,10 @@ static int choose_splits(const gemm_desc_t& d) {
       in.stride_a = in.stride_b = in.K;
       double cost = 0;
       for (int i = 0; i < kNumConfigs; ++i) {
-        if (kConfigs[i].kind != KIND_MFMA || kConfigs[i].t1 > 0 || !applicable(kConfigs[i], in)) continue;
+        const Config& c = kConfigs[i];
+        if (c.kind != KIND_MFMA || c.t1 > 0 || c.bm % 128 != 0 || !applicable(c, in)) continue;
         double rounds = 0;
-        const double t = round_cost(kConfigs[i], in, in.N, &rounds) * (esize(d.dtype_a) == 1 ? 2.0 : 1.0);
+        const double t = round_cost(c, in, in.N, 600.0, &rounds) * (esize(d.dtype_a) == 1 ? 2.0 : 1.0);
         if (cost == 0 || t < cost) cost = t;
       }
       if (cost == 0) continue;

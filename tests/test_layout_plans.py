@@ -69,6 +69,19 @@ def test_splitk_takes_whole_pieces_only(dtype):
         assert status(splits, lda=1 << 26) == -4                  # a tile's rows beyond 32-bit offsets
 
 
+@pytest.mark.parametrize("M,N,K,dtype,slices", [
+    (874, 2559, 17320, g.BF16, 1), (520, 3489, 14120, g.BF16, 1), (1057, 2840, 120504, g.F16, 1), (190, 3698, 122880, g.F16, 5),
+    (2983, 3491, 77696, g.F16, 2), (3779, 2212, 14784, g.F16, 3), (314, 537, 512, g.F16, 2), (25, 3217, 512, g.F16, 4),
+    (226, 686, 512, g.BF16, 2), (65, 1617, 512, g.F8E4M3, 4), (1160, 177, 512, g.F8E4M3, 2), (512, 512, 32768, g.BF16, 16)])
+def test_number_of_slices(M, N, K, dtype, slices):
+    """The library's own number of slices fixes the workspace, whether the fixed scratch buffer (32 MiB) holds it and the length
+    of the fp32 sums: it stays what it is when tiles or the estimates behind gemm_create's choice change.  (Sizes at which
+    tiles of 192 and 224 rows or a short-K term would move it, four of them across 32 MiB.)"""
+    p = g.gemm_create_splitk(g.GemmDesc(M, N, K, dtype=dtype))
+    assert f"kernel=splitk_{slices}+" in p.info() and g.gemm_workspace_bytes(p) == slices * M * N * 4
+    g.gemm_destroy(p)
+
+
 def fp32_lds(tile, M, N, K, **kw):
     p = g.gemm_create_config(g.GemmDesc(M, N, K, dtype=g.F32, layout_b=g.ROW_MAJOR, **kw), g.config_names().index(f"f32mfma_{tile}x{tile}x32"))
     lds = int(p.info().split(" lds=")[1].split()[0])
