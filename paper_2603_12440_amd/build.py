@@ -5,6 +5,8 @@ import os
 import shutil
 import subprocess
 
+from .asm_check import Listing, accumulator_hazards, lds_load_hazards
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmi355gemm.so")
@@ -78,70 +80,20 @@ def build_library(verbose: bool = False, only: tuple = ()) -> str:
         asm = os.path.join(OBJ_DIR, os.path.splitext(os.path.basename(src))[0] + "-hip-amdgcn-amd-amdhsa-gfx950.s")
         if os.path.exists(asm):
             with open(asm) as f:
-                text = f.read()
-            hazards += [f"{os.path.basename(asm)}:{h}" for h in lds_load_hazards(text) + accumulator_hazards(text)]
+                listing = Listing(f.read())
+            hazards += [f"{os.path.basename(asm)}:{h}" for h in lds_load_hazards(None, listing) + accumulator_hazards(None, listing)]
     if hazards:
         if os.path.exists(LIB):
             os.remove(LIB)
         raise RuntimeError("a direct-to-LDS load reads a scalar register fewer than 5 wait states after a vector-ALU "
-                           "instruction wrote it, or an MFMA an accumulator fewer than 2 after a vector-ALU instruction wrote it:\n  " + "\n  ".join(hazards[:20]))
+                           "instruction wrote it, an MFMA a register fewer than 2 after one wrote it, or another instruction an "
+                           "accumulator fewer than 19 after an MFMA wrote it:\n  " + "\n  ".join(hazards[:20]))
     res = subprocess.run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC",
                           "-Wl,--version-script=" + os.path.join(CSRC, "exports.map"), "-o", LIB] + objs,
                          capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("linking failed:\n" + res.stderr)
     return LIB
-
-
-def lds_load_hazards(asm: str) -> list:
-    """Lines of generated assembly where a `global_load_lds_*` takes its scalar base address from a register
-    that a `v_readlane` / `v_readfirstlane` wrote fewer than 5 wait states earlier.  The kernels issue these
-    loads from inline assembly, which the compiler's hazard recogniser does not see into; a vector-memory
-    instruction may not read a scalar register that soon after a vector-ALU write of it."""
-    import re
-    lines = [l.strip() for l in asm.splitlines()]
-    ins = [(i, l) for i, l in enumerate(lines)
-           if l and not l.startswith((";", ".", "//")) and not l.endswith(":")]
-    bad = []
-    for k, (i, l) in enumerate(ins):
-        if not l.startswith("global_load_lds"):
-            continue
-        m = re.search(r"s\[(\d+):(\d+)\]", l)
-        if not m:
-            continue
-        regs = {int(m.group(1)), int(m.group(2))}
-        dist = 0
-        for kk in range(k - 1, max(k - 12, -1), -1):
-            prev = ins[kk][1]
-            w = re.match(r"v_read(?:first)?lane_b32\s+s(\d+)", prev)
-            if w and int(w.group(1)) in regs and dist < 5:
-                bad.append(f"{i + 1}: {l}   (after line {ins[kk][0] + 1}: {prev})")
-            n = re.match(r"s_nop\s+(\d+)", prev)
-            dist += (int(n.group(1)) + 1) if n else 1
-            if dist >= 5:
-                break
-    return bad
-
-
-def accumulator_hazards(asm: str) -> list:
-    """Lines of generated assembly where an MFMA takes an accumulator register that a `v_accvgpr_write` / `v_accvgpr_mov` wrote
-    fewer than 2 wait states earlier: the MFMAs are assembly statements, in front of which the compiler puts no wait states."""
-    import re
-    bad = []
-    for w in re.finditer(r"v_accvgpr_(?:write|mov)_b32(?:_e32)?\s+a(\d+)[^\n]*\n", asm):
-        reg, states, at = int(w.group(1)), 0, w.end()
-        while states < 2 and at < len(asm):
-            end = asm.find("\n", at)
-            l = asm[at:end if end >= 0 else len(asm)].split(";")[0].strip()
-            at = end + 1 if end >= 0 else len(asm)
-            if not l or l.startswith((".", "//")) or l.endswith(":"):
-                continue
-            m = re.match(r"v_mfma\S+\s+a\[(\d+):(\d+)\]", l)
-            if m and int(m.group(1)) <= reg <= int(m.group(2)):
-                bad.append(f"{l}   ({states} wait states after {w.group(0).strip()})")
-            n = re.match(r"s_nop\s+(\d+)", l)
-            states += 1 + (int(n.group(1)) if n else 0)
-    return bad
 
 
 def kernels_with_scratch(remarks: str) -> list:

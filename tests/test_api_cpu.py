@@ -295,6 +295,31 @@ def test_build_guard_flags_accumulators_written_right_before_an_mfma():
     assert accumulator_hazards("\tv_accvgpr_mov_b32 a8, a4\n\tv_accvgpr_read_b32 v1, a4\n" + mfma) == []
 
 
+def test_build_guards_follow_branches():
+    """Moves where paths meet: behind an unconditional branch, on a loop's back edge, behind a jump beyond a branch's reach; both
+    ways out of a conditional branch; and the other half, an accumulator touched while an MFMA's result is on its way."""
+    from paper_2603_12440_amd.build import accumulator_hazards, lds_load_hazards
+    mfma = "\t;;#ASMSTART\n\tv_mfma_f32_16x16x32_bf16 a[4:7], v[0:3], v[8:11], a[4:7]\n\t;;#ASMEND\n"
+    far = "\ts_getpc_b64 s[4:5]\n.Lpost0:\n\ts_add_u32 s4, s4, (.LBB0_2-.Lpost0)&4294967295\n\ts_addc_u32 s5, s5, (.LBB0_2-.Lpost0)>>32\n\ts_setpc_b64 s[4:5]\n"
+    read = "\tv_accvgpr_read_b32 v1, a4\n"
+    for text, n in (("\tv_accvgpr_mov_b32 a4, a8\n\ts_branch .LBB0_2\n.LBB0_1:\n\ts_endpgm\n.LBB0_2:\n" + mfma, 1),
+                    ("\tv_accvgpr_mov_b32 a4, a8\n\ts_branch .LBB0_2\n.LBB0_1:\n" + mfma + "\ts_endpgm\n.LBB0_2:\n\ts_endpgm\n", 0),
+                    (".LBB0_1:\n" + mfma + "\ts_nop 15\n\ts_nop 7\n\tv_accvgpr_mov_b32 a4, a8\n\ts_cbranch_scc1 .LBB0_1\n\ts_endpgm\n", 1),
+                    ("\tv_mov_b32_e32 v9, 0\n\ts_cbranch_scc1 .LBB0_1\n" + mfma + ".LBB0_1:\n\ts_endpgm\n", 1),          # an operand
+                    ("\tv_accvgpr_write_b32 a6, 0\n\ts_nop 1\n\ts_cbranch_scc1 .LBB0_2\n\ts_endpgm\n.LBB0_2:\n" + mfma, 0),
+                    (mfma + "\tv_accvgpr_mov_b32 a8, a4\n", 1), (mfma + read, 1), (mfma + "\tglobal_store_dwordx4 v0, a[4:7], s[0:1]\n", 1),
+                    (mfma + "\ts_nop 15\n\ts_nop 2\n" + read, 0), (mfma + "\ts_nop 15\n\ts_nop 1\n" + read, 1),
+                    (mfma + "\tv_accvgpr_read_b32 v1, a8\n", 0), (mfma + mfma, 0),
+                    (mfma + "\ts_cbranch_vccz .LBB0_1\n\ts_endpgm\n.LBB0_1:\n\ts_nop 7\n" + read, 1),
+                    (mfma + far + "\ts_endpgm\n.LBB0_2:\n" + read, 1)):
+        assert len(accumulator_hazards(text)) == n, text
+    load = "\tglobal_load_lds_dwordx4 v2, s[6:7]\n"
+    for text, n in (("\tv_readfirstlane_b32 s7, v1\n\ts_branch .LBB0_2\n.LBB0_1:\n\ts_endpgm\n.LBB0_2:\n\ts_nop 0\n" + load, 1),
+                    ("\tv_readfirstlane_b32 s7, v1\n\ts_nop 4\n" + load, 0), ("\tv_readfirstlane_b32 s8, v1\n" + load, 0),
+                    ("\tv_cmp_gt_u32_e64 s[6:7], s2, v1\n" + load, 1), ("\tv_add_u32_e32 v2, s6, v3\n" + load, 0)):
+        assert len(lds_load_hazards(text)) == n, text
+
+
 def test_tuning_mode_switch_and_environment(g):
     """Tuning mode is off by default, follows GEMM_TUNE at first use, and the switch returns the
     previous setting; the table of remembered problems starts empty (no device needed)."""
