@@ -219,8 +219,8 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     return p.xcd_remap == 2 ? (vid & 7) * (total_tiles >> 3) + (vid >> 3) : vid;
   };
   // What finding a tile's panels needs of the arguments.  A persistent workgroup reads them from the argument block again for
-  // every tile (the kernel's only argument sits at the start of the kernarg segment), so that they do not occupy scalar
-  // registers during the K loops.
+  // every tile but its first (the kernel's only argument sits at the start of the kernarg segment), so that they do not occupy
+  // scalar registers during the K loops.
   typedef __attribute__((address_space(4))) const volatile MfmaArgs kernarg_t;
   auto tile_args = [&]() __attribute__((always_inline)) {
     MfmaArgs q = p;
@@ -256,8 +256,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   uint32_t pf_off = 0;                           // this lane's line within its operand's slab
   const bool pf_a = wave < Cfg::kWaves / 2;
   int ld_tm, ld_tn, ld_batch;                    // which tile that is, of which problem
-  auto locate = [&](int vid) __attribute__((always_inline)) {
-    const MfmaArgs p = tile_args();
+  auto locate = [&](const MfmaArgs& p, int vid) __attribute__((always_inline)) {
     const int n_tiles = p.tiles_m * p.tiles_n;
     if constexpr (PERSIST) {
       const int lid = logical_tile(p, vid);
@@ -272,8 +271,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   };
   // Leaves ld_a / ld_b at slab `kt` of that tile.  (`ln`: the lane id; a persistent workgroup recomputes the offsets from a fresh
   // copy of it after each epilogue, so that they need not stay in registers across it.)
-  auto load_tile = [&](int ln, int kt) __attribute__((always_inline)) {
-    const MfmaArgs p = tile_args();
+  auto load_tile = [&](const MfmaArgs& p, int ln, int kt) __attribute__((always_inline)) {
     const int tm = ld_tm, tn = ld_tn, lb = ld_batch;
     const int r0 = tm * BM, c0 = tn * BN;
     if constexpr (PF) {
@@ -320,8 +318,8 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       b_off[q] = (uint32_t)(((int64_t)rr * p.ldb + c * 8) * 2);
     }
   };
-  locate(blockIdx.x);
-  load_tile(lane, 0);
+  locate(p, blockIdx.x);
+  load_tile(p, lane, 0);
   const char* const Ab = ld_a;                   // (the first tile's panels: the one-tile path indexes them by slab)
   const char* const Bb = ld_b;
 
@@ -901,26 +899,26 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       ld_t = 0;
       ld_vid += gridDim.x;
       if (ld_vid < total_tiles) {
-        locate(ld_vid);
-        load_tile(fresh_lane_id(), 0);           // (no lane id kept in a register across the loop)
+        const MfmaArgs q = tile_args();
+        locate(q, ld_vid);
+        load_tile(q, fresh_lane_id(), 0);        // (no lane id kept in a register across the loop)
       }
     }
   };
   // tile_end (compile time): the last slab of a tile; its last sub-step requests no fragments (the
   // next tile's first ones are read after the epilogue, which then has no fragment registers to
-  // keep alive).  early / late (run time; true in every slab but the last two of the last tile):
+  // keep alive).  touch (compile time): whether a slab of this tile is left to prefetch: in all but the
+  // last two (the loads of the last one are under way by then; touching it again cost 64 x (512x512x128),
+  // two slabs, 0.1 us of 12).  early / late (run time; true in every slab but the last two of the last tile):
   // whether the rest of one slab's loads and the first part of the next one's are requested.
-  auto body = [&](auto end_c, bool early, bool late) __attribute__((always_inline)) {
-    constexpr bool tile_end = decltype(end_c)::value;
+  auto body = [&](auto touch_c, auto end_c, bool early, bool late) __attribute__((always_inline)) {
+    constexpr bool touch = PF && decltype(touch_c)::value, tile_end = decltype(end_c)::value;
     const SlabIo io_early = slab_io_at(ld_a, ld_b, stage ^ 1);
     static_for<0, NSUB - 1>([&](auto u_c) __attribute__((always_inline)) {
       constexpr int u = decltype(u_c)::value;
       set_prio(u < 3 ? 2 - u : 0);
       constexpr int q0 = kLoads * (u + 1) / LW, q1 = kLoads * (u + 2) / LW;
-      if constexpr (PF && u == LW - 1 && !tile_end) {        // (of the tile's last slab: once more, not past it)
-        const bool more = ld_t + 1 < T_full;
-        prefetch(more ? ld_a + a_step : ld_a, more ? ld_b + b_step : ld_b);
-      }
+      if constexpr (touch && u == LW - 1) prefetch(ld_a + a_step, ld_b + b_step);
       if constexpr (u + 1 < LW)
         sub_step(u_c, true, q0 < kLoads ? q0 : kLoads, q1 < kLoads ? q1 : kLoads, io_early, early);
       else
@@ -928,7 +926,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     });
     if (late) next_slab();                     // the early part was the rest of a slab: on to the next one
     const SlabIo io_late = slab_io_at(ld_a, ld_b, stage);
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(PF && !tile_end ? 1 : 0) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(touch ? 1 : 0) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     set_prio(3);
@@ -953,9 +951,9 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   for (int vid = blockIdx.x; vid < total_tiles; vid += gridDim.x) {
     const bool last = vid + (int)gridDim.x >= total_tiles;
     read_all(std::integral_constant<int, 0>());
-    for (t = 0; t < T_full - 2; ++t) body(no_t(), true, true);
-    body(no_t(), true, !last);
-    body(yes_t(), !last, !last);
+    for (t = 0; t < T_full - 2; ++t) body(yes_t(), no_t(), true, true);
+    body(no_t(), no_t(), true, !last);
+    body(no_t(), yes_t(), !last, !last);
     set_prio(0);
     wait_lgkmcnt<0>();
     batch = cur_batch;
@@ -965,7 +963,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       // the lane-dependent offsets and addresses are derived afresh here (from an opaque copy of the
       // lane id, so that the compiler cannot keep the earlier ones alive across the epilogue instead)
       const int lane_now = fresh_lane_id();
-      load_tile(lane_now, ld_t);
+      load_tile(tile_args(), lane_now, ld_t);
       set_read_stage(stage, lane_now);
 #pragma unroll
       for (int m = 0; m < MT; ++m)
