@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import re
 import shutil
 import subprocess
 
@@ -16,6 +17,13 @@ SOURCES = [os.path.join(CSRC, f) for f in
             "mfma16t_nn_bf16_inst.hip", "mfma16t_nn_f16_inst.hip", "mfma16t_tn_bf16_inst.hip", "mfma16t_tn_f16_inst.hip",
             "mfma16t_tt_bf16_inst.hip", "mfma16t_tt_f16_inst.hip", "mfma16s_bf16_inst.hip", "mfma16s_f16_inst.hip", "ring_bf16_inst.hip", "ring_f16_inst.hip", "ring_f8_inst.hip", "mfma16g_inst.hip", "rope_api.hip", "probe_api.hip")]
 OBJ_DIR = os.path.join(os.path.dirname(HERE), "_build")
+
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
+         # packed-fp32 VALU forms stay off
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-Wall", "-Wno-unused-function", "-Rpass-analysis=kernel-resource-usage",
+         # keep the generated device assembly next to the object: it is scanned below
+         "-save-temps=obj"]
 
 
 def _hipcc() -> str:
@@ -42,19 +50,13 @@ def build_library(verbose: bool = False, only: tuple = ()) -> str:
     other objects are taken as they are; for development, when a change touches one unit)."""
     from concurrent.futures import ThreadPoolExecutor
     os.makedirs(OBJ_DIR, exist_ok=True)
-    flags = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
-             # packed-fp32 VALU forms stay off
-             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-             "-Wall", "-Wno-unused-function", "-Rpass-analysis=kernel-resource-usage",
-             # keep the generated device assembly next to the object: it is scanned below
-             "-save-temps=obj"]
     noise = ("is not a recognized feature for this target", "-Rpass-analysis=kernel-resource-usage")
 
     def compile_one(src):
         obj = os.path.join(OBJ_DIR, os.path.basename(src) + ".o")
         if only and os.path.basename(src) not in only and os.path.exists(obj):
             return src, obj, subprocess.CompletedProcess([], 0, "", "")
-        res = subprocess.run([_hipcc()] + flags + ["-c", src, "-o", obj], capture_output=True, text=True)
+        res = subprocess.run([_hipcc()] + FLAGS + ["-c", src, "-o", obj], capture_output=True, text=True)
         return src, obj, res
 
     with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as pool:
@@ -68,6 +70,8 @@ def build_library(verbose: bool = False, only: tuple = ()) -> str:
             print(err)
         objs.append(obj)
         remarks.append(res.stderr)
+        if res.args and "Function Name:" not in res.stderr:
+            raise RuntimeError(f"no resource usage reported for {os.path.basename(src)}: it cannot be checked for scratch memory")
     bad = kernels_with_scratch("\n".join(remarks))
     if bad:
         if os.path.exists(LIB):
@@ -98,17 +102,14 @@ def build_library(verbose: bool = False, only: tuple = ()) -> str:
 
 def kernels_with_scratch(remarks: str) -> list:
     """Names of kernels whose resource-usage remarks show scratch memory or vector-register spills
-    (scalar registers spilled into vector-register lanes stay in registers and are fine)."""
+    (scalar registers spilled into vector-register lanes stay in registers and are fine).  The compiler writes
+    "file:line: remark: text", and with -save-temps, where it compiles in steps, "remark: file:line: text"."""
     bad, name = [], None
-    for line in remarks.splitlines():
-        if "remark:" not in line:
-            continue
-        text = line.split("remark:", 1)[1].strip()
-        if text.startswith("Function Name:"):
-            name = text.split(":", 1)[1].split("[")[0].strip()
-        elif name and text.split(":")[0] in ("ScratchSize [bytes/lane]", "VGPRs Spill"):
-            if int(text.split(":")[1].split("[")[0]) != 0 and name not in bad:
-                bad.append(name)
+    for what, value in re.findall(r"remark:.*?\b(Function Name|ScratchSize \[bytes/lane\]|VGPRs Spill): *([^\s\[]+)", remarks):
+        if what == "Function Name":
+            name = value
+        elif int(value) != 0 and name not in bad:
+            bad.append(name)
     return bad
 
 

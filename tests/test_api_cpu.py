@@ -286,6 +286,21 @@ def test_build_guard_flags_kernels_that_use_scratch_memory():
     assert kernels_with_scratch("") == []
 
 
+def test_build_guard_reads_the_remarks_the_build_produces(tmp_path):
+    """With -save-temps the remarks put the place behind "remark:"; a kernel that spills, compiled with the build's flags."""
+    import subprocess
+    from paper_2603_12440_amd import build
+    remarks = "\n".join(f"remark: a.hpp:1:0: {t} [-Rpass-analysis=kernel-resource-usage]" for t in (
+        "Function Name: kernel_ok", "    ScratchSize [bytes/lane]: 0", "    VGPRs Spill: 0",
+        "Function Name: kernel_spill", "    TotalSGPRs: 106", "    ScratchSize [bytes/lane]: 308", "    SGPRs Spill: 2", "    VGPRs Spill: 76"))
+    assert build.kernels_with_scratch(remarks) == ["kernel_spill"]
+    src = tmp_path / "k.hip"
+    src.write_text("#include <hip/hip_runtime.h>\n__global__ void kernel_ok(float* p) { p[threadIdx.x] = 1.0f; }\n"
+                   "__global__ void kernel_stack(float* p, int n) { volatile float a[64]; for (int i = 0; i < n; ++i) a[i & 63] = p[i]; p[0] = a[n & 63]; }\n")
+    res = subprocess.run([build._hipcc()] + build.FLAGS + ["-c", str(src), "-o", str(tmp_path / "k.o")], capture_output=True, text=True)
+    assert res.returncode == 0 and len(build.kernels_with_scratch(res.stderr)) == 1, res.stderr
+
+
 def test_build_guard_flags_accumulators_written_right_before_an_mfma():
     from paper_2603_12440_amd.build import accumulator_hazards
     mfma = "\tv_mfma_f32_16x16x32_bf16 a[4:7], v[0:3], v[8:11], a[4:7]\n"
