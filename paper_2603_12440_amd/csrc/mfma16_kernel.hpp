@@ -229,7 +229,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       q.A = pv->A; q.B = pv->B; q.M = pv->M; q.N = pv->N; q.lda = pv->lda; q.ldb = pv->ldb;
       q.stride_a = pv->stride_a; q.stride_b = pv->stride_b; q.tiles_m = pv->tiles_m; q.tiles_n = pv->tiles_n;
       q.order.div_group = pv->order.div_group; q.order.div_rows = pv->order.div_rows; q.order.div_h = pv->order.div_h;
-      q.xcd_remap = pv->xcd_remap;
+      q.xcd_remap = pv->xcd_remap; q.touch = pv->touch;
     }
     return q;
   };
@@ -248,8 +248,11 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   // lines of the next slab but one, ahead of the loads that will want them; waves of the lower half touch A's, the others
   // B's.  The touch is a 4-byte load per lane into an LDS area nobody reads, so that no register is written later; it is the
   // youngest load at the hand-over, which leaves it in flight.  A panel is shared by the tiles that one XCD works on at a
-  // time (A's by 4, B's by 8: tile_order.hpp), so each workgroup touches its share of the 128-byte lines only: 512 lines
-  // per workgroup and slab, all of them, cost 2.5 % where the operands are cached, this share 1 to 2 %.
+  // time (A's by 4, B's by 8, or as many as there are: tile_order.hpp), so each workgroup touches its share of the 128-byte
+  // lines only: 512 lines per workgroup and slab, all of them, cost 2.5 % where the operands are cached, this share 1 to 2 %.
+  // (A quarter of the lines whatever the number of tiles left most of B untouched where there are few tile rows: 192x57344x4096
+  // 126 us, 119 this way; 512x28672x4096 108 / 97, 300x57344x2048 102 / 86, 64 x (512x512x256) 19.6 / 17.2; short batches with
+  // cached operands lose up to 3 %: 60 x (256x1024x512) 20.2 / 20.9.)
   // Operands from HBM: 4096x3072x6144 148 -> 127 us, 4096x4096x6144 158 -> 144, 8192^3 748 -> 737; touching two or three
   // slabs ahead is no better (8192^3: 718 / 723 / 726).
   constexpr bool PF = Cfg::PREFETCH;
@@ -275,10 +278,10 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     const int tm = ld_tm, tn = ld_tn, lb = ld_batch;
     const int r0 = tm * BM, c0 = tn * BN;
     if constexpr (PF) {
-      // Lines of a slab: one per row where K is contiguous, else one per value of K and 64 rows.  2^sh workgroups share them.
-      const int sh = pf_a || p.tiles_m < 8 ? 2 : 3, wave_lines = 2 * (pf_a ? Cfg::ROWS : BN) / Cfg::kWaves;
+      // Lines of a slab: one per row where K is contiguous, else one per value of K and 64 rows.
+      const int wave_lines = 2 * (pf_a ? Cfg::ROWS : BN) / Cfg::kWaves;
       const int line = (wave % (Cfg::kWaves / 2)) * wave_lines +
-                       min(((ln >> sh) << sh) + ((pf_a ? tn : tm) & ((1 << sh) - 1)), wave_lines - 1);
+                       touched_line(ln, pf_a ? tn : tm, pf_a ? p.touch & 15 : p.touch >> 4, wave_lines);
       const int64_t ld = pf_a ? p.lda : p.ldb;
       const int left = pf_a ? p.M - r0 : p.N - c0;
       auto row_line = [&]() __attribute__((always_inline)) { return (uint32_t)((int64_t)min(line, left - 1) * ld * 2); };

@@ -27,6 +27,7 @@ MfmaArgs mfma16_args(const gemm_plan& pl, const void* A, const void* B, void* C,
   a.tiles_n = (int)((d.N + BN - 1) / BN);
   a.c_cached = pl.c_cached;
   a.batches = (int)d.batch;
+  a.touch = touch_shift(a.tiles_n, 4) + (touch_shift(a.tiles_m, 8) << 4);
   set_tile_order<BM, BN, EITHER>(a, pl);
   return a;
 }

@@ -35,6 +35,7 @@ struct MfmaArgs {
                                // consecutive problems of the batch within one XCD; 3: the same, one tile per workgroup; 4: as 1, in strips
   int c_cached;                // 1: fp32 C is read again right away (split-K partials): ordinary stores
   int batches;                 // problems in the batch (persistent workgroups walk over the tiles of all of them)
+  int touch;                   // touch_shift of a panel of A, and of B from bit 4 on (kernels that prefetch into L2)
 };
 
 // ---- MFMA wrappers -----------------------------------------------------------

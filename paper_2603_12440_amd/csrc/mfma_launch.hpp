@@ -28,6 +28,7 @@ hipError_t launch_mfma(const gemm_plan& pl, const void* A, const void* B, void* 
   a.tiles_n = (int)((d.N + BN - 1) / BN);
   a.c_cached = pl.c_cached;
   a.batches = (int)d.batch;
+  a.touch = 0;
   set_tile_order<BM, BN, kEitherOrder<BM, BN, 2, false>>(a, pl);
   if constexpr (sizeof(T) == 1) {                        // fp8: a variant with regions only (see the kernel)
     if (a.xcd_remap != 4) {

@@ -87,4 +87,16 @@ __host__ __device__ __forceinline__ void tile_of(const TileOrder& o, int tiles_m
   if (group & (G >> 4)) tn = tiles_n - 1 - tn;         // (regions: odd groups backwards)
 }
 
+// Prefetching a panel that several tiles read (mfma16_kernel.hpp): as many of the `tiles` along it as divide by a power of two up
+// to `at_most` (4 or 8), which one XCD works on at a time, share its lines.  The power's exponent; and which of a wave's `lines`
+// lines (at most 64) lane `lane` touches for the workgroup on tile `tile`.
+inline int touch_shift(int tiles, int at_most) {
+  const int n = tiles < at_most ? tiles : at_most;
+  return (n >= 2) + (n >= 4) + (n >= 8);
+}
+__host__ __device__ __forceinline__ int touched_line(int lane, int tile, int shift, int lines) {
+  const int line = ((lane >> shift) << shift) + (tile & ((1 << shift) - 1));
+  return line < lines ? line : lines - 1;
+}
+
 }  // namespace mi355gemm

@@ -74,6 +74,24 @@ int main() {
       std::printf("%dx%d tiles of area %d, K of %d bytes: expected %s\n", r.m, r.n, r.area, r.k_bytes, r.want ? "strips" : "regions");
       return 1;
     }
+  // the lines of a panel that neighbouring tiles touch: all of them, whatever the number of tiles, and none by more than a
+  // workgroup has to
+  for (int tiles = 1; tiles <= 20; ++tiles)
+    for (int at_most = 4; at_most <= 8; at_most *= 2)
+      for (int lines : {48, 56, 64}) {
+        std::vector<int> by(lines, 0);
+        for (int tile = 0; tile < tiles && tile < at_most; ++tile)
+          for (int lane = 0; lane < 64; ++lane) {
+            const int l = touched_line(lane, tile, touch_shift(tiles, at_most), lines);
+            if (l < 0 || l >= lines) { std::printf("%d tiles: line %d of %d\n", tiles, l, lines); return 1; }
+            by[l] |= 1 << tile;
+          }
+        for (int l = 0; l < lines; ++l)
+          if (!by[l] || (l + 1 < lines && (tiles & (tiles - 1)) == 0 && (by[l] & (by[l] - 1)))) {
+            std::printf("%d tiles, at most %d: line %d of %d touched by the set %x\n", tiles, at_most, l, lines, by[l]);
+            return 1;
+          }
+      }
   std::printf("%ld grids ok, panels read by one tile alone: strips %ld, regions %ld\n", grids, strips, regions);
   return 0;
 }
