@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <array>
 #include <cstdio>
 #include <cstdlib>
 #include <cmath>
@@ -570,30 +571,61 @@ int find_config(const char* name) {
   return -1;
 }
 
-// Cost model of one MFMA tile shape on an M x N x K (x batch) problem, in microseconds.
-//   * Kernels with two slabs in LDS: rounds over the CUs * work per round / measured relative efficiency of the tile
-//     shape; a fixed per-tile cost (prologue latency, epilogue) is worth ~600 columns of K.  A lone workgroup on a
-//     CU waits for its loads: 0.60 us per slab of the 128x128 tile, 1.1 us of the larger ones (K = 4096: 41 and 75 us).
-//   * Kernels with more slabs: launch (2.7 us) plus a measured time per slab, alone on a CU and (small rings) with a
-//     second workgroup beside it, over the tiles the busiest CU gets; each further round costs 2.4 us of prologue and
-//     epilogue that nothing overlaps (512x512x128, 64 problems, 64x64 tiles: 27 us).  The 128x128 tile takes 0.33 us a
-//     slab with half the CUs busy, 0.45 us with all of them (its panels come from L2: 256 workgroups take 17 TB/s) and
-//     0.6 us from the second round on, where the two-slab kernels are better (7195x7312x1448: 258 against 183 us).
-//     An operand whose rows do not start on 128-byte lines costs 0.35 of that on top: every piece of 128 bytes
-//     touches two lines (384x4104x4104: 43 us, 384x4096x4096: 24 us).
-//   * The eight-wave tiles of 192 to 256 x 256 (wide_cost): launch (3 us), and a round takes its slabs plus what writing C of
-//     a full round takes (7 us for 256x256 tiles), and the latency of its first loads where workgroups are not persistent.  A slab takes 1.39 us (256x256), 1.23 (224x256) and 1.10 us (192x256) with
-//     all CUs busy and a fifth of that more per operand whose rows do not start on 128-byte lines; a round that fills the
-//     CUs to f takes 0.6 + 0.4 f of a full one.  Within 5 % of what 17 shapes took with operands from HBM, the worst 13 %.
-double wide_cost(const Config& c, const gemm_desc_t& d, double tiles, int off_line) {
-  const double area = (double)c.bm * c.bn / 65536.0, slab = c.bm == 256 ? 1.39 : (c.bm == 224 ? 1.23 : 1.10);
-  const double rounds = tiles / num_cus(), whole = std::floor(rounds), part = rounds - whole;
-  const double turn = (double)((d.K + c.bk - 1) / c.bk) * slab * (1.0 + 0.2 * off_line) + 7.0 * area + (c.persist ? 0.0 : 3.5);
-  return 3.0 + turn * (whole + (part > 0 ? 0.6 + 0.4 * part : 0.0));
+// Cost models of one MFMA tile shape on an M x N x K (x batch) problem, in microseconds.
+//
+// tile_cost, 16-bit operands on tiles of 64x64 and larger: a launch, and as many turns of the workgroups that the chip holds at once
+// as there are tiles for, each of `tile` us (first loads, C) and `slab` us per slab, a fifth more per operand whose rows do not start
+// on 128-byte lines, and more for fp32 results; a turn that fills the chip to f takes part + (1 - part) f of a full one.  At the
+// other end the bytes of A, B and C.  Fitted to the times of 16000 drawn products (K from 32 to 16384, batches, all layouts, operands
+// from HBM; those within 30 % of the fastest): 11 % rms for each of these kernels.  Against the fastest kernel the choice costs on
+// average 2.0 % for K of 64 to 768, 0.5 % for one to five rounds of 256x256 tiles, 1.0 % for other layers, 2.1 % for batches and
+// 2.5 % for those with a K up to 8192 (with constants fitted to a long K, a step at K = 512 and no part turns for 128x128 tiles it
+// was 3.9, 0.9, 1.8, 3.8 and 2.9 %: 202 x (387x104x32) 10.4 us, 19.2 so).
+const double kLaunchUs = 2.8;
+struct TileTimes { const char* name; double tile, slab, part; };
+const TileTimes kTileTimes[] = {
+    {"mfma16_128x128x64_w2x2", 3.77, 0.959, 0.53}, {"mfma16_128x128x64_w2x2_p", 3.30, 0.956, 0.61}, {"mfma16_128x128x64_w2x2_s4", 3.16, 0.531, 0.78},
+    {"mfma16_192x256x64_w2x4", 5.76, 1.217, 0.62}, {"mfma16_192x256x64_w2x4_p", 5.10, 1.151, 0.71}, {"mfma16_224x256x64_w2x4", 6.54, 1.284, 0.65},
+    {"mfma16_224x256x64_w2x4_p", 6.05, 1.274, 0.66}, {"mfma16_256x256x64_w2x2", 9.53, 1.477, 0.67}, {"mfma16_256x256x64_w2x4", 7.98, 1.456, 0.57},
+    {"mfma16_256x256x64_w2x4_p", 6.92, 1.445, 0.59}, {"mfma16_64x64_k1_w2x4_s5", 1.87, 0.473, 0.36}, {"mfma16_64x64_k2_w2x4_s4", 1.41, 0.546, 0.60},
+    {"mfma16t_128x128x64_w2x2", 3.08, 0.905, 0.50}, {"mfma16t_128x128x64_w2x2_p", 2.61, 0.929, 0.57}, {"mfma16t_128x128x64_w2x2_s4", 2.85, 0.501, 0.69},
+    {"mfma16t_192x256x64_w2x4", 6.04, 1.085, 0.55}, {"mfma16t_192x256x64_w2x4_p", 4.62, 1.031, 0.73}, {"mfma16t_256x256x64_w2x4", 8.38, 1.279, 0.53},
+    {"mfma16t_256x256x64_w2x4_p", 6.34, 1.246, 0.61}, {"mfma16t_64x64_k1_w2x4_s5", 1.51, 0.507, 0.37}, {"mfma16t_64x64_k2_w2x4_s4", 1.14, 0.583, 0.63},
+    {"mfma_128x128x64_w2x2_s2", 4.48, 0.968, 0.50}, {"mfma_256x128x64_w2x2_s2", 5.67, 0.993, 0.82}, {"mfma_256x192x64_w4x2_s2", 6.16, 1.271, 0.62},
+    {"mfma_256x256x64_w2x4_s2", 8.48, 1.521, 0.55},
+    {"mfma_256x256x64_w2x2_s2", 8.48, 1.521, 0.55},     // (not timed: as the shape with eight waves, which goes first)
+};
+const TileTimes* tile_times(const Config& c) {
+  static const std::array<const TileTimes*, kNumConfigs> of = [] {
+    std::array<const TileTimes*, kNumConfigs> r{};
+    for (const TileTimes& t : kTileTimes)
+      if (const int i = find_config(t.name); i >= 0) r[(size_t)i] = &t;
+    return r;
+  }();
+  return of[(size_t)(&c - kConfigs)];
 }
 
-// (fixed: a tile's fixed cost in columns of K)
-double round_cost(const Config& c, const gemm_desc_t& d, int64_t N, double fixed, double* rounds_out) {
+// What the bytes of A, B and C take (TB/s), and that together with the time of the work: near the larger of the two.
+double with_memory(double work, const gemm_desc_t& d, int64_t N) {
+  const double M = (double)d.M, n = (double)N, K = (double)d.K;
+  const double c = d.dtype_c == GEMM_F32 ? M * n * 4.0 / 4.24 : M * n * 2.0 / 2.22;
+  const double memory = kLaunchUs + (double)d.batch * ((M + n) * K * 2.0 / 3.68 + c) / 1e6;
+  return std::sqrt(std::cbrt(std::pow(work, 6) + std::pow(memory, 6)));
+}
+
+double tile_cost(const Config& c, const TileTimes& t, const gemm_desc_t& d, int64_t N, double tiles, int off_line) {
+  const double at_once = 160 * 1024 / c.lds_bytes, area = (double)c.bm * c.bn / (128 * 128);
+  const double turns = tiles / (num_cus() * at_once), whole = std::floor(turns), part = turns - whole;
+  // (of a batch: the kernels that give an XCD whole problems, where tiles divide by 8, find shared panels in its L2)
+  const bool apart = d.batch > 1 && !((c.persist || c.t1 > 0) && std::fmod(tiles, 8.0) == 0);
+  const double turn = t.tile + t.slab * (double)((d.K + c.bk - 1) / c.bk) * (1.0 + 0.171 * off_line + (apart ? 0.26 : 0.0)) +
+                      (d.dtype_c == GEMM_F32 ? 1.5 * area * at_once : 0.0);
+  return with_memory(kLaunchUs + turn * (whole + (part > 0 ? t.part + (1.0 - t.part) * part : 0.0)), d, N);
+}
+
+// round_cost, fp8 and the number of split-K slices: rounds over the CUs * work per round / measured relative efficiency of the tile
+// shape; a fixed per-tile cost (prologue latency, epilogue) is worth ~600 columns of K.
+double round_cost(const Config& c, const gemm_desc_t& d, int64_t N, double* rounds_out) {
   const int64_t M = d.M, K = d.K;
   const int e = esize(d.dtype_a), area = c.bm * c.bn;
   const double tiles = (double)((M + c.bm - 1) / c.bm) * (double)((N + c.bn - 1) / c.bn) * (double)d.batch;
@@ -608,9 +640,15 @@ double round_cost(const Config& c, const gemm_desc_t& d, int64_t N, double fixed
   // workgroups that actually share a CU (a lone workgroup runs about per_cu times faster)
   const double sharing = tiles >= cus * per_cu ? per_cu : (tiles > cus ? tiles / cus : 1.0);
   *rounds_out = rounds;
-  return rounds * area * sharing / eff * ((double)K + fixed) / (e == 1 ? 5.4e6 : 2.7e6);
+  return rounds * area * sharing / eff * ((double)K + 600.0) / (e == 1 ? 5.4e6 : 2.7e6);
 }
 
+// The others: fp8; rings of 32 columns and for operands of any alignment, which are weighed by the time of a slab with one workgroup
+// on a CU and with two (launch 2.7 us; each further round costs 2.4 us of prologue and epilogue that nothing overlaps: 512x512x128,
+// 64 problems, 64x64 tiles: 27 us).  An operand whose rows do not start on 128-byte lines costs a ring 0.35 on top: every piece of
+// 128 bytes touches two lines (384x4104x4104: 43 us, 384x4096x4096: 24 us).  In a batch, the slices of split-K among them, a slab
+// takes a quarter more: 1500 split-K products are then 0.7 % from the better of two estimates' choices, 3.3 % without.  A lone fp8 workgroup on a CU waits for its loads:
+// 0.42 us per slab of the 128x128 tile.
 double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
   const int64_t M = d.M, K = d.K, batch = d.batch;
   const int e = esize(d.dtype_a);
@@ -618,27 +656,19 @@ double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
   const double tiles = (double)((M + c.bm - 1) / c.bm) * (double)((N + c.bn - 1) / c.bn) * (double)batch;
   const double cus = num_cus();
   const int off_line = ((d.lda * e) % 128 != 0) + ((d.ldb * e) % 128 != 0);
+  if (const TileTimes* t = tile_times(c)) return tile_cost(c, *t, d, N, tiles, off_line);
   if (c.t1 > 0) {
     const double slabs = (double)((K + c.bk - 1) / c.bk);
     const double per_cu = (double)(int64_t)((tiles + cus - 1) / cus);
-    const double pitch = c.kind == KIND_MFMA_G ? 1.0 : 1.0 + 0.35 * off_line;
-    if (area >= 128 * 128 && c.kind != KIND_MFMA_G) {
-      const double busy = fmin(1.0, fmax(0.0, tiles / cus - 0.5) * 2.0);
-      const double t1 = (c.t1 + 0.12 * busy) * pitch;
-      return per_cu > 1 ? per_cu * (slabs * fmax(0.6, t1) + 5.0) : 4.6 + slabs * t1;
-    }
+    const bool tiled16 = e == 2 && c.kind != KIND_MFMA_G, many = tiled16 && batch > 1;
+    const double pitch = c.kind == KIND_MFMA_G ? 1.0 : 1.0 + 0.35 * off_line + (many ? 0.25 : 0.0);
     const double pairs = c.t2 > 0 ? (double)(int64_t)(per_cu / 2) : 0.0, singles = per_cu - 2 * pairs;
-    return 2.7 + (singles * c.t1 + pairs * c.t2) * slabs * pitch + (singles + pairs - 1) * 2.4;
+    const double work = 2.7 + (singles * c.t1 + pairs * c.t2) * slabs * pitch + (singles + pairs - 1) * 2.4 + (many ? 0.7 : 0.0);
+    return tiled16 ? with_memory(work, d, N) : work;           // (those are weighed against tile_cost's)
   }
-  // (of the two 256x256 shapes the eight-wave one goes first)
-  if (!std::strncmp(c.name, "mfma16", 6) && area > 128 * 128) return wide_cost(c, d, tiles, off_line) * (c.threads == 512 ? 1.0 : 1.02);
-  // (a short K: less of a tile's fixed cost is left uncovered than the 600 columns fitted to long ones.  2048 x 12000 x 256 21.7 us
-  // persistent, 22.9 on 224x256 tiles; 6528 x 6240 x 275 40.6 us with one tile per workgroup, 53.5 on 256x256; 1024 x 17416 x 136
-  // 28 us on these, 26 as two launches.  Not for batches, the slices of split-K among them.)
-  const double fixed = d.batch == 1 && area <= 128 * 128 && K <= 512 && (c.persist || K >= 192) ? 350.0 : 600.0;
   double rounds = 0;
-  const double work = round_cost(c, d, N, fixed, &rounds) * (e == 2 ? 1.0 + (area > 128 * 128 ? 0.2 : 0.08) * off_line : 1.0);
-  const double wait = rounds * ((double)K / c.bk * (area <= 128 * 128 ? (e == 1 ? 0.42 * (1.0 + 0.5 * off_line) : 0.60 * (1.0 + 0.2 * off_line)) : 0.0) + 3.0);
+  const double work = round_cost(c, d, N, &rounds);
+  const double wait = rounds * ((double)K / c.bk * (area <= 128 * 128 ? 0.42 * (1.0 + 0.5 * off_line) : 0.0) + 3.0);
   return work > wait ? work : wait;
 }
 
@@ -673,11 +703,13 @@ int64_t split_columns(const gemm_desc_t& d, int big, double single_cost) {
   rest.N = d.N - n_first;
   double rest_cost = 0;
   if (best_mfma(rest, &rest_cost) < 0) return 0;
-  const double launch = 2.0;                      // (beside what the estimate of the second launch already holds)
-  const double split_cost = mfma_cost(c, d, n_first) + rest_cost + launch;
-  // (what the model sees as even is even or a little better as two launches, whose second one starts while the first one's last
-  // workgroups finish: 4096 x 14336 x 4096 350 us against 355, 4096 x 6144 x 4096 162 against 161 to 166)
-  return split_cost < 1.03 * single_cost ? n_first : 0;
+  // What the second launch takes beyond the two estimates, which count a launch each and no overlap.  Where the line lies, over drawn
+  // products that can take two launches (1 to 6 rounds, K from 64 to 8192; taken, more than 2 % faster so, more than 2 % slower):
+  // 16-bit results 1671: 307, 179, 24 with 1 us; 611, 211, 201 with -2; 218, 144, 14 with 3.  fp32 results 971: 408, 191, 107 with -2
+  // (mean -1.4 %); 302, 168, 46 with -1; 135, 105, 9 with 2 (-1.1 %); 1024x17416x136 takes 29.0 us, 31.7 in one.  fp8, 73 products:
+  // 25, 15, 1 with 7; 54, 16, 27 with 2.
+  const double launch = d.dtype_a == GEMM_F8E4M3 ? 7.0 : d.dtype_c == GEMM_F32 ? -2.0 : 0.5;
+  return mfma_cost(c, d, n_first) + rest_cost + launch < single_cost ? n_first : 0;
 }
 
 // The choice among the general kernels (fp32 operands, or layouts / leading dimensions / pointers the tiled
@@ -936,7 +968,7 @@ static int choose_splits(const gemm_desc_t& d) {
         const Config& c = kConfigs[i];
         if (c.kind != KIND_MFMA || c.t1 > 0 || c.bm % 128 != 0 || !applicable(c, in)) continue;
         double rounds = 0;
-        const double t = round_cost(c, in, in.N, 600.0, &rounds) * (esize(d.dtype_a) == 1 ? 2.0 : 1.0);
+        const double t = round_cost(c, in, in.N, &rounds) * (esize(d.dtype_a) == 1 ? 2.0 : 1.0);
         if (cost == 0 || t < cost) cost = t;
       }
       if (cost == 0) continue;

@@ -121,3 +121,33 @@ def test_any_alignment_with_a_short_k(kw, kernel):
     assert "kernel=" + kernel in info(**kw)
     if "batch" not in kw:
         assert "kernel=" + kernel in info(dtype_c=g.F32, **kw)
+
+
+@pytest.mark.parametrize("kw,kernel", [
+    (dict(M=387, N=104, K=32, batch=202), "mfma16_128x128x64_w2x2"),               # 10.4 us; 64x64 ring 19.2
+    (dict(M=525, N=72, K=40, batch=233), "mfma16_128x128x64_w2x2"),                # 14.2; 24.2
+    (dict(M=699, N=311, K=144, batch=46), "mfma16_128x128x64_w2x2"),               # 21.9; 64x64 ring 26.5
+    (dict(M=413, N=340, K=48, batch=139), "mfma16_128x128x64_w2x2"),               # 23.7; 224x256 31.0
+    (dict(M=1092, N=12052, K=312, dtype=g.F16, dtype_c=g.F32), "mfma16_224x256x64_w2x4"),    # 26.4; 128x128 36.9
+    (dict(M=3422, N=8920, K=408, dtype_c=g.F32), "mfma16_2"),                      # tiles of 256 columns 59.4; 128x128 69.7
+    (dict(M=3399, N=11442, K=6256), "mfma16_224x256x64_w2x4"),                     # 494; 128x128 625
+    (dict(M=476, N=2077, K=10840), "mfma16_64x64_k1_w2x4_s5")])                    # 93; 128x128, four slabs 127
+def test_choice_among_tiles(kw, kernel):
+    """Products at which the estimate has to see a batch, a short K, fp32 results or a partial round as they are (us on one box)."""
+    assert "kernel=" + kernel in info(**kw)
+
+
+@pytest.mark.parametrize("M,N", [(6528, 6240), (1024, 17416), (2048, 12000)])
+def test_choice_does_not_step_with_k(M, N):
+    """K from 448 to 576: whole slabs on one tile, and others on one tile."""
+    assert len({info(M=M, N=N, K=k).split()[0] for k in range(448, 577, 64)}) == 1
+    assert len({info(M=M, N=N, K=k).split()[0] for k in range(448, 577, 8) if k % 64}) == 1
+
+
+def test_second_launch_of_a_wide_product():
+    """One launch, or whole rounds on 256x256 tiles and the rest as a second one: as measured."""
+    for kw, two in ((dict(M=2048, N=14336, K=2048), False),                        # 92.2 us; 95.1 in two
+                    (dict(M=4096, N=14336, K=4096, dtype=g.F8E4M3), True), (dict(M=4096, N=4608, K=4096), True),
+                    (dict(M=1024, N=17416, K=136, layout_b=g.ROW_MAJOR, dtype_c=g.F32), True),     # 29.0; 31.7 in one
+                    (dict(M=1024, N=17416, K=136, layout_b=g.ROW_MAJOR), False)):                  # 24.5; 25.5 in two
+        assert ("columns=" in info(**kw)) == two, kw
