@@ -817,10 +817,7 @@ int fill_launch_shape(gemm_plan& pl) {
       pl.grid = dim3((unsigned)wgs, (unsigned)d.batch, 1);
     }
     pl.xcd_remap = d.batch == 1 || (tm * tn) % 8 == 0 ? 1 : 0;
-    // less than a round of small tiles, not a multiple of 8 and not wider than high: dealt round-robin, an XCD gets the same tile
-    // rows of every strip, which reads A once (5712x584x785, 45x5 tiles: 13.9 us, 14.5 with contiguous runs per XCD;
-    // 577x400x984 7.7 / 8.2).  Wider ones: 100x5000x4096 24.6 / 17.1; 256x256 tiles, 23x10 of them: 114 / 106.
-    if (d.batch == 1 && tm * tn < 256 && (tm * tn) % 8 != 0 && tn <= tm && c.bm * c.bn <= 128 * 128 && d.K * esize(d.dtype_a) > 512)
+    if (d.batch == 1 && dealt_one_by_one(tm, tn, c.bm * c.bn, d.K * esize(d.dtype_a), c.kind == KIND_MFMA_G && d.layout_b == GEMM_ROW_MAJOR))
       pl.xcd_remap = 0;
     // a batch, one tile per workgroup, on the kernels with a deeper ring: whole problems per XCD as well (512x512x2048,
     // 16 problems: 33 us with a problem's tiles spread over the XCDs)

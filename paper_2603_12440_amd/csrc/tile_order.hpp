@@ -48,6 +48,18 @@ inline bool takes_strips(int64_t tiles_m, int64_t tiles_n, int tile_area, bool t
   return tile_area >= 128 * 128 && k_bytes <= 512 && (n % 8 != 0 || !whole_rows);
 }
 
+// Less than a round of small tiles (up to 128x128), not a multiple of 8: which launches deal the tiles to the XCDs one by one instead of
+// in a run per XCD.  Over 6000 drawn grids (us in runs / dealt): wider than high 0.95 on average (100x5000x4096, 2x79 tiles of
+// 64x64: 17.0 / 24.6), others 1.01 (5712x584x785, 45x5 tiles of 128x128: 14.5 / 13.9).  any_rows: operands of any alignment with B
+// row-major, whose pieces of a row touch two lines each, the neighbouring columns' tiles the same ones: dealt, an XCD has all
+// columns of a tile row, and from 8 rows on that is 1.19 and up to 1.4 ahead (582x661x4110, 10x11 tiles of 64x64: 81 / 57; with 128x128
+// tiles 1.05), as it is 1.1 with up to 8 tile columns or 16 tiles (346x385x4845, 6x7 tiles: 98.6 / 77.6); others are 0.91 in runs.
+inline bool dealt_one_by_one(int64_t tiles_m, int64_t tiles_n, int tile_area, int64_t k_bytes, bool any_rows) {
+  const int64_t n = tiles_m * tiles_n;
+  if (n >= 256 || n % 8 == 0 || tile_area > 128 * 128 || k_bytes <= 512) return false;
+  return tiles_n <= tiles_m || (any_rows && (tiles_m >= 8 || tiles_n <= 8 || n <= 16));
+}
+
 // x / d on the scalar unit (m = ceil(2^32 / d); 2^32 - 1 for d = 1): the estimate is off by one at most.  (A division by a
 // run-time value goes through vector registers, which the K loop of a persistent workgroup has none to spare of.)
 __host__ __device__ __forceinline__ int div_by(int x, int d, uint32_t m) {

@@ -74,6 +74,16 @@ int main() {
       std::printf("%dx%d tiles of area %d, K of %d bytes: expected %s\n", r.m, r.n, r.area, r.k_bytes, r.want ? "strips" : "regions");
       return 1;
     }
+  struct { int m, n, area, k_bytes; bool any_rows, want; } deal[] = {
+      {45, 5, 128 * 128, 1570, false, true},  {2, 79, 64 * 64, 8192, false, false},  {2, 79, 64 * 64, 8192, true, false}, {10, 11, 64 * 64, 8220, true, true},
+      {10, 11, 64 * 64, 8220, false, false},  {10, 11, 64 * 64, 512, true, false},   {8, 9, 64 * 64, 8220, true, false},  {9, 27, 64 * 64, 8220, true, true},
+      {7, 9, 64 * 64, 8220, true, false},     {1, 14, 64 * 64, 8220, true, true},    {1, 14, 64 * 64, 8220, false, false}, {1, 17, 64 * 64, 8220, true, false},
+      {11, 10, 256 * 256, 8192, false, false}, {29, 9, 64 * 64, 8220, true, false}, {6, 7, 64 * 64, 8220, true, true}, {6, 7, 64 * 64, 8220, false, false}};
+  for (const auto& r : deal)
+    if (dealt_one_by_one(r.m, r.n, r.area, r.k_bytes, r.any_rows) != r.want) {
+      std::printf("%dx%d tiles of area %d, K of %d bytes, any rows %d: expected %d\n", r.m, r.n, r.area, r.k_bytes, r.any_rows, r.want);
+      return 1;
+    }
   // the lines of a panel that neighbouring tiles touch: all of them, whatever the number of tiles, and none by more than a
   // workgroup has to
   for (int tiles = 1; tiles <= 20; ++tiles)
