@@ -488,9 +488,8 @@ def test_split_plan_two_launches(g, oracle):
 
 
 def test_fp32_output_of_every_mfma_tile(g, oracle):
-    """fp32 C leaves the matrix-core kernels through an LDS transpose in passes (whole-line
-    stores) when its rows are 16-byte aligned, otherwise straight from the accumulator layout:
-    both routes, ragged edges, padded rows, batches, bias + activation, every tile shape."""
+    """fp32 C leaves the matrix-core kernels through an LDS transpose in passes (16-byte stores), whatever
+    element its rows start at: aligned rows and others, ragged edges, batches, bias + activation, every tile shape."""
     for cfg in mfma_configs(g):
         for (M, N, K, batch, pad_c) in [(300, 520, 136, 1, 0), (300, 520, 136, 1, 4), (257, 522, 72, 1, 0),
                                         (130, 260, 64, 3, 0), (64, 100, 64, 1, 1)]:
@@ -500,6 +499,20 @@ def test_fp32_output_of_every_mfma_tile(g, oracle):
         w = wl.Workload("t", 300, 520, 256, dtype="f8", epilogue="bias_relu", seed_a=11, seed_b=12, seed_bias=13)
         exact_case(g, oracle, w, cfg, out_dtype="f32")
         exact_case(g, oracle, w, cfg, out_dtype="f32", pad_c=1)
+
+
+@pytest.mark.parametrize("N,pad_c", [(519, 0), (520, 1), (513, 2), (261, 3)])
+def test_f8_16_bit_output_rows_at_any_element(g, oracle, N, pad_c):
+    """bf16 C of the fp8 kernels, tiles and rings: odd N and odd leading dimensions, so that a row starts at any element and its last
+    piece is cut; small integers, exact after one rounding."""
+    for cfg in F8_CONFIGS + [n for n in g.config_names() if n.startswith("mfma8_") and n not in F8_CONFIGS]:
+        w = wl.Workload("t", 300, N, 256, dtype="f8", out_dtype="bf16", epilogue="bias_relu", seed_a=N, seed_b=12, seed_bias=13)
+        A, B = (wl.small_integers(s, seed, -1, 1, "f8") for s, seed in zip(wl.operand_shapes(w), (N, 12)))
+        bias = wl.small_integers((N,), 13, -3, 3, "f32")
+        say(f"f8 16-bit rows {cfg} N={N} pad {pad_c}")
+        C = run_gpu(g, w, A, B, bias, config=cfg_index(g, cfg), pad_c=pad_c)
+        want = torch.relu(A[0].float() @ B[0].float().T + bias).to(torch.bfloat16)
+        assert torch.equal(C.reshape(300, N), want), cfg
 
 
 def test_tuning_mode_times_once_per_problem_and_keeps_results_exact(g, oracle):
@@ -737,7 +750,8 @@ def test_persistent_workgroups_exact(g, oracle):
     alternates), ragged edges, both output types, bias + activation, padded C rows, batches.
     Integer data: bit exact against the oracle."""
     for cfg in persistent_configs(g):
-        tile = 128 if "128x128" in cfg else 256
+        bm, bn = (int(x) for x in cfg.split("_")[1].split("x")[:2])
+        tile = bn
         per_round = 512 if tile == 128 else 256            # workgroups the chip holds at once
         for (tiles_m, tiles_n, K, batch) in [(2, 3, 128, 1), (17, 17, 192, 1), (24, 23, 128, 1), (3, 2, 320, 3),
                                              (33, 20, 128, 1),
@@ -746,21 +760,19 @@ def test_persistent_workgroups_exact(g, oracle):
                                              (3, 1, 128, 200 if tile == 128 else 100)]:
             if tile == 256 and tiles_m * tiles_n > 300:
                 continue                                    # (keeps the oracle's share of the test short)
-            M, N = tiles_m * tile - 5, tiles_n * tile - 12
+            M, N = tiles_m * bm - 5, tiles_n * bn - 12
             w = wl.Workload("t", M, N, K, batch=batch, epilogue="bias_relu", seed_a=31, seed_b=32, seed_bias=33)
             say(f"persistent {cfg} {M}x{N}x{K} b{batch}: {tiles_m * tiles_n} tiles on {per_round} workgroups")
             exact_case(g, oracle, w, cfg, lo=-2, hi=2)
             exact_case(g, oracle, wl.scaled(w, epilogue="none"), cfg, out_dtype="f32", pad_c=4)
             if batch > 1 and tiles_m == 4:
-                # C rows that are not 16-byte aligned: the launcher runs one tile per workgroup instead,
-                # with the plan's batch renumbering switched off
+                # C rows that start at any element, under the same batch renumbering
                 exact_case(g, oracle, w, cfg, lo=-2, hi=2, pad_c=3)
 
 
 def test_persistent_workgroups_random_and_misaligned_c(g, oracle):
     """Random data against the oracle on the persistent configurations (several tiles per workgroup,
-    GELU epilogue), and a C whose rows are not 16-byte aligned: the plan must still be right (it
-    falls back to one tile per workgroup)."""
+    GELU epilogue), and a C whose rows are not 16-byte aligned."""
     for cfg in persistent_configs(g):
         tile = 128 if "128x128" in cfg else 256
         n = 23 if tile == 128 else 17

@@ -68,6 +68,15 @@ def test_several_tiles_per_workgroup(g, la, lb):
             run_exact(g, wl.Workload("t", M, N, K, dtype="bf16", layout_a=la, layout_b=lb, batch=batch, seed_a=K, seed_b=N), cfg)
 
 
+@pytest.mark.parametrize("la,lb", [("row", "col"), ("row", "row"), ("col", "row"), ("col", "col")])
+def test_few_tiles_along_a_panel(g, la, lb):
+    """One to five tile rows or columns, where workgroups share the lines they prefetch among fewer than four or eight."""
+    for cfg in configs(g, la, lb):
+        bm = int(cfg.split("_")[1].split("x")[0])
+        for tiles_m, tiles_n, K in ((1, 1, 256), (1, 5, 320), (2, 3, 256), (3, 1, 192), (5, 2, 448)):
+            run_exact(g, wl.Workload("t", tiles_m * bm - 8, tiles_n * 256 - 16, K, dtype="bf16", layout_a=la, layout_b=lb, seed_a=K, seed_b=tiles_n), cfg)
+
+
 def test_built_in_choice(g):
     """A wide tile where it fills the CUs better than 256x256."""
     for M, N, K, la, lb, want in ((3001, 4096, 6144, "row", "row", "192x256"), (777, 14336, 4096, "row", "col", "224x256"),
