@@ -647,8 +647,8 @@ double round_cost(const Config& c, const gemm_desc_t& d, int64_t N, double* roun
 // on a CU and with two (launch 2.7 us; each further round costs 2.4 us of prologue and epilogue that nothing overlaps: 512x512x128,
 // 64 problems, 64x64 tiles: 27 us).  An operand whose rows do not start on 128-byte lines costs a ring 0.35 on top: every piece of
 // 128 bytes touches two lines (384x4104x4104: 43 us, 384x4096x4096: 24 us).  In a batch, the slices of split-K among them, a slab
-// takes a quarter more: 1500 split-K products are then 0.7 % from the better of two estimates' choices, 3.3 % without.  A lone fp8 workgroup on a CU waits for its loads:
-// 0.42 us per slab of the 128x128 tile.
+// takes a quarter more: 1500 split-K products are then 0.7 % from the better of two estimates' choices, 3.3 % without.  A lone
+// fp8 workgroup on a CU waits for its loads: 0.42 us per slab of the 128x128 tile.
 double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
   const int64_t M = d.M, K = d.K, batch = d.batch;
   const int e = esize(d.dtype_a);

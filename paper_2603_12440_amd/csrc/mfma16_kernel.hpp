@@ -114,13 +114,12 @@ struct Mfma16Tile {
   static constexpr int NSUB = KK * G;                    // sub-steps per slab
   static constexpr int ROWB = BK * 2;                    // bytes per slab row
   static constexpr int CPR = ROWB / 16, RPI = 64 / CPR;  // chunks per row, rows per wave-wide load
-  // Rows of A in LDS: a K-strided A is stored in blocks of 64 rows.  K-contiguous, a wave-wide load fills 8 rows; where
-  // those do not divide over the waves, the waves take them in turn and the last ones issue one load less.
-  static constexpr int ROWS = A_KF ? BM : (BM + 63) / 64 * 64;
-  static constexpr int A_UNITS = ROWS / RPI, A_LOADS = (A_UNITS + kWaves - 1) / kWaves, B_LOADS = BN / RPI / kWaves;
+  // A wave-wide load fills 8 rows of A's slab; where those do not divide over the waves, the waves take them in turn and the last
+  // ones issue one load less.  (A K-strided A is stored in blocks of 64 rows: BM is a multiple.)
+  static constexpr int A_UNITS = BM / RPI, A_LOADS = (A_UNITS + kWaves - 1) / kWaves, B_LOADS = BN / RPI / kWaves;
   static constexpr bool UNEVEN = A_UNITS % kWaves != 0;
   static constexpr int A_ID_WAVE = UNEVEN ? 1 : A_LOADS, A_ID_Q = UNEVEN ? kWaves : 1;    // load q of a wave is unit wave * A_ID_WAVE + q * A_ID_Q
-  static constexpr int A_BYTES = ROWS * ROWB, B_BYTES = BN * ROWB;
+  static constexpr int A_BYTES = BM * ROWB, B_BYTES = BN * ROWB;
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
   static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES;
   // the epilogue's staging area of a persistent workgroup: one 16-row band of every wave's block in fp32
@@ -131,6 +130,7 @@ struct Mfma16Tile {
   static constexpr int DUMP_BYTES = PREFETCH ? 256 : 0;
   static_assert(sizeof(T) == 2, "16-bit operands");
   static_assert(BM % (8 * RPI) == 0 || BM % 32 == 0, "whole wave-wide loads");
+  static_assert(A_KF || BM % 64 == 0, "a K-strided A is stored in blocks of 64 rows");
   static_assert(BN % (RPI * kWaves) == 0, "slab rows of B must divide over waves");
   static_assert(!UNEVEN || (NSTAGE == 2 && A_LOADS == B_LOADS), "the load that some waves leave out is the last of a slab's second half");
   static_assert(WTM % 16 == 0 && WTN % 16 == 0 && MT >= G, "wave block in whole sub-steps");
@@ -173,7 +173,7 @@ __device__ __forceinline__ void lds_read_tr16(F& dst, uint32_t addr, int offset)
 // Bound like the K-contiguous variant (power and matrix pipes: the same bytes, loads and MFMAs per slab, twice
 // the LDS read instructions at half the width): 8192^3 bf16 takes 721 us with B row-major, 726 us with A
 // column-major as well, 709 - 726 us K-contiguous on the same box.  These layouts used to run on the fp32
-// matrix-core instruction: 6144 x 4096 x 3001 with both operands strided 2475 us, here 133 us.
+// matrix-core instruction: 6144 x 4096 x 3001 with both operands strided 2475 us, here 118 us.
 // S: slabs in LDS.  Two for the large problems; a lone workgroup on a CU has nothing else to hide a load's latency
 // behind and takes four (one tile per workgroup only).
 template <typename T, typename TO, int BM, int BN, int WM, int WN, int G, bool PERSIST, bool A_KF = true, bool B_KF = true, int S = 2>
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     const int r0 = tm * BM, c0 = tn * BN;
     if constexpr (PF) {
       // Lines of a slab: one per row where K is contiguous, else one per value of K and 64 rows.
-      const int wave_lines = 2 * (pf_a ? Cfg::ROWS : BN) / Cfg::kWaves;
+      const int wave_lines = 2 * (pf_a ? BM : BN) / Cfg::kWaves;
       const int line = (wave % (Cfg::kWaves / 2)) * wave_lines +
                        touched_line(ln, pf_a ? tn : tm, pf_a ? p.touch & 15 : p.touch >> 4, wave_lines);
       const int64_t ld = pf_a ? p.lda : p.ldb;
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
         return (uint32_t)(((int64_t)(line / per_k) * ld + min(line % per_k * 64, left - 8)) * 2);
       };
       if constexpr (A_KF && B_KF) pf_off = row_line();
-      else if (pf_a) pf_off = A_KF ? row_line() : k_line(Cfg::ROWS / 64);
+      else if (pf_a) pf_off = A_KF ? row_line() : k_line(BM / 64);
       else pf_off = B_KF ? row_line() : k_line(BN / 64);
     }
     ld_a = (const char*)((const T*)p.A + (int64_t)lb * p.stride_a + (A_KF ? (int64_t)r0 * p.lda : (int64_t)r0)) + (int64_t)kt * a_step;

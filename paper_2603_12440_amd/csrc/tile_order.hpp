@@ -18,7 +18,8 @@
 //     grids at least twice as wide as high whose tiles do not divide by 8 (bf16, 5x59: 45.8 / 40.6).
 //   * K of at most 512 bytes, where writing C is most of the work: full-width rows of C are written closer together in time.
 //     41x61 tiles of 128x128 but 8 columns, K = 64: bf16 32.5 / 39.1, fp8 27.6 / 35.9; 9x28 tiles of 256x256, K = 64: bf16
-//     18.0 / 18.8.  Unless the tiles divide by 8 and C's rows are whole 16-byte pieces (regions up to 5 % ahead there).
+//     18.0 / 18.8.  Unless the tiles divide by 8 and C's rows are whole 16-byte pieces (regions up to 5 % ahead there;
+//     rows at any element, 4700 drawn products: strips 1.3 % ahead with fp32 results, even with 16-bit ones).
 #pragma once
 
 #include <stdint.h>
