@@ -580,18 +580,19 @@ int find_config(const char* name) {
 // from HBM; those within 30 % of the fastest): 11 % rms for each of these kernels.  Against the fastest kernel the choice costs on
 // average 2.0 % for K of 64 to 768, 0.5 % for one to five rounds of 256x256 tiles, 1.0 % for other layers, 2.1 % for batches and
 // 2.5 % for those with a K up to 8192 (with constants fitted to a long K, a step at K = 512 and no part turns for 128x128 tiles it
-// was 3.9, 0.9, 1.8, 3.8 and 2.9 %: 202 x (387x104x32) 10.4 us, 19.2 so).
+// was 3.9, 0.9, 1.8, 3.8 and 2.9 %: 202 x (387x104x32) 10.4 us, 19.2 so).  (Two slab times by hand, 1.340 and 1.000 for 1.284 and 0.968: of
+// 43 products that took 224-row tiles with one tile per workgroup, 192-row ones were 6 to 7 % faster.)
 const double kLaunchUs = 2.8;
 struct TileTimes { const char* name; double tile, slab, part; };
 const TileTimes kTileTimes[] = {
     {"mfma16_128x128x64_w2x2", 3.77, 0.959, 0.53}, {"mfma16_128x128x64_w2x2_p", 3.30, 0.956, 0.61}, {"mfma16_128x128x64_w2x2_s4", 3.16, 0.531, 0.78},
-    {"mfma16_192x256x64_w2x4", 5.76, 1.217, 0.62}, {"mfma16_192x256x64_w2x4_p", 5.10, 1.151, 0.71}, {"mfma16_224x256x64_w2x4", 6.54, 1.284, 0.65},
+    {"mfma16_192x256x64_w2x4", 5.76, 1.217, 0.62}, {"mfma16_192x256x64_w2x4_p", 5.10, 1.151, 0.71}, {"mfma16_224x256x64_w2x4", 6.54, 1.340, 0.65},
     {"mfma16_224x256x64_w2x4_p", 6.05, 1.274, 0.66}, {"mfma16_256x256x64_w2x2", 9.53, 1.477, 0.67}, {"mfma16_256x256x64_w2x4", 7.98, 1.456, 0.57},
     {"mfma16_256x256x64_w2x4_p", 6.92, 1.445, 0.59}, {"mfma16_64x64_k1_w2x4_s5", 1.87, 0.473, 0.36}, {"mfma16_64x64_k2_w2x4_s4", 1.41, 0.546, 0.60},
     {"mfma16t_128x128x64_w2x2", 3.08, 0.905, 0.50}, {"mfma16t_128x128x64_w2x2_p", 2.61, 0.929, 0.57}, {"mfma16t_128x128x64_w2x2_s4", 2.85, 0.501, 0.69},
     {"mfma16t_192x256x64_w2x4", 6.04, 1.085, 0.55}, {"mfma16t_192x256x64_w2x4_p", 4.62, 1.031, 0.73}, {"mfma16t_256x256x64_w2x4", 8.38, 1.279, 0.53},
     {"mfma16t_256x256x64_w2x4_p", 6.34, 1.246, 0.61}, {"mfma16t_64x64_k1_w2x4_s5", 1.51, 0.507, 0.37}, {"mfma16t_64x64_k2_w2x4_s4", 1.14, 0.583, 0.63},
-    {"mfma_128x128x64_w2x2_s2", 4.48, 0.968, 0.50}, {"mfma_256x128x64_w2x2_s2", 5.67, 0.993, 0.82}, {"mfma_256x192x64_w4x2_s2", 6.16, 1.271, 0.62},
+    {"mfma_128x128x64_w2x2_s2", 4.48, 1.000, 0.50}, {"mfma_256x128x64_w2x2_s2", 5.67, 0.993, 0.82}, {"mfma_256x192x64_w4x2_s2", 6.16, 1.271, 0.62},
     {"mfma_256x256x64_w2x4_s2", 8.48, 1.521, 0.55},
     {"mfma_256x256x64_w2x2_s2", 8.48, 1.521, 0.55},     // (not timed: as the shape with eight waves, which goes first)
 };
