@@ -12,10 +12,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmi355gemm.so")
 SOURCES = [os.path.join(CSRC, f) for f in
-           ("gemm_api.hip", "mfma_bf16_inst.hip", "mfma_f16_inst.hip", "mfma_f8_inst.hip",
+           ("gemm_api.hip", "mfma_bf16_inst.hip", "mfma_f16_inst.hip",
             "mfma16_bf16_inst.hip", "mfma16_f16_inst.hip", "mfma16p_bf16_inst.hip", "mfma16p_f16_inst.hip",
             "mfma16t_nn_bf16_inst.hip", "mfma16t_nn_f16_inst.hip", "mfma16t_tn_bf16_inst.hip", "mfma16t_tn_f16_inst.hip",
-            "mfma16t_tt_bf16_inst.hip", "mfma16t_tt_f16_inst.hip", "mfma16s_bf16_inst.hip", "mfma16s_f16_inst.hip", "ring_bf16_inst.hip", "ring_f16_inst.hip", "ring_f8_inst.hip", "mfma16g_inst.hip", "rope_api.hip", "probe_api.hip")]
+            "mfma16t_tt_bf16_inst.hip", "mfma16t_tt_f16_inst.hip", "mfma16s_bf16_inst.hip", "mfma16s_f16_inst.hip", "mfma16_f8_inst.hip", "mfma16p_f8_inst.hip", "ring_bf16_inst.hip", "ring_f16_inst.hip", "ring_f8_inst.hip", "mfma16g_inst.hip", "rope_api.hip", "probe_api.hip")]
 OBJ_DIR = os.path.join(os.path.dirname(HERE), "_build")
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

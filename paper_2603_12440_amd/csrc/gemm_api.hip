@@ -16,6 +16,7 @@
 #include <map>
 #include <mutex>
 #include <new>
+#include <string>
 #include <vector>
 
 #include "../../include/gemm.h"
@@ -39,9 +40,11 @@ namespace mi355gemm {
                                  MI355GEMM_MFMA_DECLARE(f16_t, f16_t, BM, BN, BK, WM, WN, NS)
 MI355GEMM_MFMA_TILES(X)
 #undef X
-#define X(BM, BN, BK, WM, WN, NS) MI355GEMM_MFMA_DECLARE(f8e4m3_t, bf16_t, BM, BN, BK, WM, WN, NS)
-MI355GEMM_MFMA8_TILES(X)
+#define X(BM, BN, WM, WN, G, P) MI355GEMM_MFMA16_DECLARE(f8e4m3_t, bf16_t, BM, BN, WM, WN, G, P)
+MI355GEMM_MFMA16F8_TILES(X)
+MI355GEMM_MFMA16F8P_TILES(X)
 #undef X
+MI355GEMM_MFMA16F8S_TILES(MI355GEMM_MFMA16F8S_DECLARE)
 #define X(BM, BN, WM, WN, G, P) MI355GEMM_MFMA16_DECLARE(bf16_t, bf16_t, BM, BN, WM, WN, G, P) \
                                 MI355GEMM_MFMA16_DECLARE(f16_t, f16_t, BM, BN, WM, WN, G, P)
 MI355GEMM_MFMA16_TILES(X)
@@ -309,10 +312,16 @@ hipError_t launch_skinny_direct(const gemm_plan& pl, const void* A, const void* 
     { nullptr, launch_mfma16t<bf16_t, BM, BN, WM, WN, G, P != 0>,                          \
       launch_mfma16t<f16_t, BM, BN, WM, WN, G, P != 0> }, P }
 // fp8 (E4M3) operands, bf16 or fp32 output: the same slabs in bytes (BK is twice as many values)
-#define MFMA8_CFG(BM, BN, BK, WM, WN, NS)                                                  \
-  { "mfma8_" #BM "x" #BN "x" #BK "_w" #WM "x" #WN "_s" #NS, KIND_MFMA, BM, BN, BK,         \
-    64 * WM * WN, MfmaTile<f8e4m3_t, BM, BN, BK, WM, WN, NS>::LDS_BYTES,                   \
-    { nullptr, nullptr, nullptr, launch_mfma<f8e4m3_t, bf16_t, BM, BN, BK, WM, WN, NS> } }
+// (persistent workgroups where K is a whole number of slabs, at least two; one tile per workgroup otherwise)
+template <int BM, int BN, int WM, int WN, int G>
+hipError_t launch_mfma16f8(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias, hipStream_t s) {
+  if (persists(*pl.cfg, pl.d)) return launch_mfma16<f8e4m3_t, bf16_t, BM, BN, WM, WN, G, true>(pl, A, B, C, bias, s);
+  return launch_mfma16<f8e4m3_t, bf16_t, BM, BN, WM, WN, G, false>(pl, A, B, C, bias, s);
+}
+#define MFMA16F8_CFG(BM, BN, WM, WN, G)                                                    \
+  { "mfma8_" #BM "x" #BN "x128_w" #WM "x" #WN "_s2", KIND_MFMA, BM, BN, 128, 64 * WM * WN, \
+    Mfma16Tile<f8e4m3_t, BM, BN, WM, WN, G>::LDS_BYTES + Mfma16Tile<f8e4m3_t, BM, BN, WM, WN, G>::EPI_BYTES, \
+    { nullptr, nullptr, nullptr, launch_mfma16f8<BM, BN, WM, WN, G> }, 2 }
 
 // bn = workgroups per CU the grid is sized for
 #define SKINNY_CFG(MB, WAVES, PER_CU)                                                      \
@@ -335,6 +344,10 @@ hipError_t launch_skinny_direct(const gemm_plan& pl, const void* A, const void* 
     Mfma16Tile<bf16_t, BM, BN, WM, WN, G, S>::LDS_BYTES,                                   \
     { nullptr, launch_mfma16<bf16_t, bf16_t, BM, BN, WM, WN, G, false, true, true, S>,     \
       launch_mfma16<f16_t, f16_t, BM, BN, WM, WN, G, false, true, true, S> }, 0, 0.33f, 0.0f },
+#define MFMA16F8S_CFG(BM, BN, WM, WN, G, S)                                                \
+  { "mfma8_" #BM "x" #BN "x128_w" #WM "x" #WN "_s" #S, KIND_MFMA, BM, BN, 128, 64 * WM * WN, \
+    Mfma16Tile<f8e4m3_t, BM, BN, WM, WN, G, S>::LDS_BYTES,                                 \
+    { nullptr, nullptr, nullptr, launch_mfma16<f8e4m3_t, bf16_t, BM, BN, WM, WN, G, false, true, true, S> }, 0, 0.33f, 0.0f },
 #define MFMA16TS_CFG(BM, BN, WM, WN, G, S)                                                 \
   { "mfma16t_" #BM "x" #BN "x64_w" #WM "x" #WN "_s" #S, KIND_MFMA_T, BM, BN, 64, 64 * WM * WN, \
     Mfma16Tile<bf16_t, BM, BN, WM, WN, G, S>::LDS_BYTES,                                   \
@@ -373,9 +386,12 @@ const Config kConfigs[] = {
     MFMA_CFG(256, 128, 64, 2, 2, 2),
     MFMA_CFG(128, 128, 64, 2, 2, 2),
     MFMA_CFG(256, 192, 64, 4, 2, 2),
-    MFMA8_CFG(256, 256, 128, 2, 4, 2),
-    MFMA8_CFG(128, 128, 128, 2, 2, 2),
-    MFMA8_CFG(256, 192, 128, 4, 2, 2),
+    MFMA16F8_CFG(256, 256, 2, 4, 4),
+    MFMA16F8_CFG(128, 128, 2, 2, 4),
+    MFMA16F8_CFG(256, 192, 4, 2, 4),
+    MFMA16F8_CFG(224, 256, 2, 4, 4),
+    MFMA16F8_CFG(192, 256, 2, 4, 4),
+    MI355GEMM_MFMA16F8S_TILES(MFMA16F8S_CFG)
     F32_MFMA_CFG(128, 128),
     F32_MFMA_CFG(64, 64),
     F32_SMALL_CFG(),
@@ -532,9 +548,9 @@ bool applicable(const Config& c, const gemm_desc_t& d) {
     if (d.M >= kMax || d.N >= kMax || d.K >= kMax) return false;
     const int64_t a_rows = ak ? c.bm : c.bk + 1, b_rows = bk ? c.bn : c.bk + 1;
     if (a_rows * d.lda * 2 >= ((int64_t)1 << 32) || b_rows * d.ldb * 2 >= ((int64_t)1 << 32)) return false;
-    if (c.persist && (d.K % c.bk != 0 || d.K < 2 * c.bk)) return false;
+    if (c.persist == 1 && (d.K % c.bk != 0 || d.K < 2 * c.bk)) return false;
     const int64_t tiles = ((d.M + c.bm - 1) / c.bm) * ((d.N + c.bn - 1) / c.bn);
-    return (c.persist || c.t1 > 0 ? tiles * d.batch : tiles) < ((int64_t)1 << 31);
+    return (persists(c, d) || c.t1 > 0 ? tiles * d.batch : tiles) < ((int64_t)1 << 31);
   }
   // The MFMA and skinny kernels take K-contiguous A and B, row-major C, and move
   // 16-byte pieces: every row start must be 16-byte aligned.
@@ -553,14 +569,15 @@ bool applicable(const Config& c, const gemm_desc_t& d) {
   if ((int64_t)c.bm * d.lda * esize(d.dtype_a) >= ((int64_t)1 << 32) ||
       (int64_t)c.bn * d.ldb * esize(d.dtype_a) >= ((int64_t)1 << 32))
     return false;
-  if (c.persist && (d.K % c.bk != 0 || d.K < 2 * c.bk)) return false;   // whole slabs, at least two
+  if (c.persist == 1 && (d.K % c.bk != 0 || d.K < 2 * c.bk)) return false;   // whole slabs, at least two
   const int64_t tiles = ((d.M + c.bm - 1) / c.bm) * ((d.N + c.bn - 1) / c.bn);
-  return (c.persist || c.t1 > 0 ? tiles * d.batch : tiles) < ((int64_t)1 << 31);
+  return (persists(c, d) || c.t1 > 0 ? tiles * d.batch : tiles) < ((int64_t)1 << 31);
 }
 
 // LDS bytes of the kernel a plan runs for 16-byte aligned operands
 int plan_lds_bytes(const gemm_plan& pl) {
   const Config& c = *pl.cfg;
+  if (c.persist == 2 && !persists(c, pl.d)) return 2 * (c.bm + c.bn) * 128 + (c.threads == 512 ? 256 : 0);   // (no staging area)
   if (c.kind != KIND_F32_VEC || f32_takes_ring(pl.d, c.bm)) return c.lds_bytes;
   return f32_mfma_lds(c.bm, pl.d.layout_a == GEMM_ROW_MAJOR) + f32_mfma_lds(c.bm, pl.d.layout_b == GEMM_COL_MAJOR);
 }
@@ -573,7 +590,7 @@ int find_config(const char* name) {
 
 // Cost models of one MFMA tile shape on an M x N x K (x batch) problem, in microseconds.
 //
-// tile_cost, 16-bit operands on tiles of 64x64 and larger: a launch, and as many turns of the workgroups that the chip holds at once
+// tile_cost, fp8 operands, and 16-bit ones on tiles of 64x64 and larger: a launch, and as many turns of the workgroups that the chip holds at once
 // as there are tiles for, each of `tile` us (first loads, C) and `slab` us per slab, a fifth more per operand whose rows do not start
 // on 128-byte lines, and more for fp32 results; a turn that fills the chip to f takes part + (1 - part) f of a full one.  At the
 // other end the bytes of A, B and C.  Fitted to the times of 16000 drawn products (K from 32 to 16384, batches, all layouts, operands
@@ -582,7 +599,10 @@ int find_config(const char* name) {
 // 2.5 % for those with a K up to 8192 (with constants fitted to a long K, a step at K = 512 and no part turns for 128x128 tiles it
 // was 3.9, 0.9, 1.8, 3.8 and 2.9 %: 202 x (387x104x32) 10.4 us, 19.2 so).  (Two slab times by hand, 1.340 and 1.000 for 1.284 and 0.968: of
 // 43 products that took 224-row tiles with one tile per workgroup, 192-row ones were 6 to 7 % faster.)
-const double kLaunchUs = 2.8;
+// fp8, fitted in the same way to 4868 drawn products (M from 16, N and K from 256; K from 64; batches): 10.6 % rms, the choice 1.6 % from
+// the fastest kernel for K of 1024 and more, 2.8 % below, 4.0 % for batches, a percent of which is the measurement's own scatter.
+struct SharedTimes { double launch, off_line, apart, f32, operands, c32, c16; };   // us; shares of a slab; us; TB/s
+const SharedTimes kShared16 = {2.8, 0.171, 0.26, 1.5, 3.68, 4.24, 2.22}, kShared8 = {2.6, 0.171, 0.26, 0.92, 6.39, 4.93, 5.0};
 struct TileTimes { const char* name; double tile, slab, part; };
 const TileTimes kTileTimes[] = {
     {"mfma16_128x128x64_w2x2", 3.77, 0.959, 0.53}, {"mfma16_128x128x64_w2x2_p", 3.30, 0.956, 0.61}, {"mfma16_128x128x64_w2x2_s4", 3.16, 0.531, 0.78},
@@ -595,82 +615,68 @@ const TileTimes kTileTimes[] = {
     {"mfma_128x128x64_w2x2_s2", 4.48, 1.000, 0.50}, {"mfma_256x128x64_w2x2_s2", 5.67, 0.993, 0.82}, {"mfma_256x192x64_w4x2_s2", 6.16, 1.271, 0.62},
     {"mfma_256x256x64_w2x4_s2", 8.48, 1.521, 0.55},
     {"mfma_256x256x64_w2x2_s2", 8.48, 1.521, 0.55},     // (not timed: as the shape with eight waves, which goes first)
+    {"mfma8_128x128x128_w2x2_s2", 4.30, 0.893, 0.31}, {"mfma8_128x128x128_w2x2_s4", 3.06, 0.479, 0.53}, {"mfma8_192x256x128_w2x4_s2", 7.02, 1.129, 0.47},
+    {"mfma8_224x256x128_w2x4_s2", 8.64, 1.232, 0.43}, {"mfma8_256x192x128_w4x2_s2", 7.21, 1.097, 0.51}, {"mfma8_256x256x128_w2x4_s2", 9.76, 1.407, 0.39},
+    {"mfma8_32x32_k2_w2x2_s4", 0.86, 0.307, 0.49}, {"mfma8_32x32_k4_w2x2_s3", 0.79, 0.326, 0.78}, {"mfma8_64x32_k2_w4x2_s4", 0.91, 0.278, 0.68},
+    {"mfma8_64x64_k1_w2x4_s5", 1.70, 0.397, 0.37}, {"mfma8_64x64_k2_w2x4_s4", 1.02, 0.449, 0.65}, {"mfma8_128x128x128_w2x2_p", 2.30, 0.878, 0.41},
+    {"mfma8_192x256x128_w2x4_p", 3.78, 1.145, 0.61}, {"mfma8_224x256x128_w2x4_p", 4.82, 1.290, 0.54}, {"mfma8_256x192x128_w4x2_p", 4.45, 1.127, 0.59},
+    {"mfma8_256x256x128_w2x4_p", 5.52, 1.358, 0.58},
 };
-const TileTimes* tile_times(const Config& c) {
-  static const std::array<const TileTimes*, kNumConfigs> of = [] {
-    std::array<const TileTimes*, kNumConfigs> r{};
-    for (const TileTimes& t : kTileTimes)
-      if (const int i = find_config(t.name); i >= 0) r[(size_t)i] = &t;
+// (fp8 tiles have two rows: "_s2" with one tile per workgroup, "_p" with persistent workgroups)
+const TileTimes* tile_times(const Config& c, const gemm_desc_t& d) {
+  typedef std::array<const TileTimes*, 2 * kNumConfigs> table_t;
+  static const table_t of = [] {
+    table_t r{};
+    for (const TileTimes& t : kTileTimes) {
+      const int i = find_config(t.name);
+      if (i >= 0) r[2 * (size_t)i] = r[2 * (size_t)i + 1] = &t;
+      const std::string n = t.name, other = n.substr(0, n.size() - 2) + "_s2";
+      if (const int q = i < 0 ? find_config(other.c_str()) : -1; q >= 0) r[2 * (size_t)q + 1] = &t;
+    }
     return r;
   }();
-  return of[(size_t)(&c - kConfigs)];
+  return of[2 * (size_t)(&c - kConfigs) + persists(c, d)];
 }
 
 // What the bytes of A, B and C take (TB/s), and that together with the time of the work: near the larger of the two.
 double with_memory(double work, const gemm_desc_t& d, int64_t N) {
+  const SharedTimes& h = d.dtype_a == GEMM_F8E4M3 ? kShared8 : kShared16;
   const double M = (double)d.M, n = (double)N, K = (double)d.K;
-  const double c = d.dtype_c == GEMM_F32 ? M * n * 4.0 / 4.24 : M * n * 2.0 / 2.22;
-  const double memory = kLaunchUs + (double)d.batch * ((M + n) * K * 2.0 / 3.68 + c) / 1e6;
+  const double c = d.dtype_c == GEMM_F32 ? M * n * 4.0 / h.c32 : M * n * 2.0 / h.c16;
+  const double memory = h.launch + (double)d.batch * ((M + n) * K * esize(d.dtype_a) / h.operands + c) / 1e6;
   return std::sqrt(std::cbrt(std::pow(work, 6) + std::pow(memory, 6)));
 }
 
 double tile_cost(const Config& c, const TileTimes& t, const gemm_desc_t& d, int64_t N, double tiles, int off_line) {
   const double at_once = 160 * 1024 / c.lds_bytes, area = (double)c.bm * c.bn / (128 * 128);
+  const SharedTimes& h = d.dtype_a == GEMM_F8E4M3 ? kShared8 : kShared16;
   const double turns = tiles / (num_cus() * at_once), whole = std::floor(turns), part = turns - whole;
   // (of a batch: the kernels that give an XCD whole problems, where tiles divide by 8, find shared panels in its L2)
-  const bool apart = d.batch > 1 && !((c.persist || c.t1 > 0) && std::fmod(tiles, 8.0) == 0);
-  const double turn = t.tile + t.slab * (double)((d.K + c.bk - 1) / c.bk) * (1.0 + 0.171 * off_line + (apart ? 0.26 : 0.0)) +
-                      (d.dtype_c == GEMM_F32 ? 1.5 * area * at_once : 0.0);
-  return with_memory(kLaunchUs + turn * (whole + (part > 0 ? t.part + (1.0 - t.part) * part : 0.0)), d, N);
+  const bool apart = d.batch > 1 && !((persists(c, d) || c.t1 > 0) && std::fmod(tiles, 8.0) == 0);
+  const double turn = t.tile + t.slab * (double)((d.K + c.bk - 1) / c.bk) * (1.0 + h.off_line * off_line + (apart ? h.apart : 0.0)) +
+                      (d.dtype_c == GEMM_F32 ? h.f32 * area * at_once : 0.0);
+  return with_memory(h.launch + turn * (whole + (part > 0 ? t.part + (1.0 - t.part) * part : 0.0)), d, N);
 }
 
-// round_cost, fp8 and the number of split-K slices: rounds over the CUs * work per round / measured relative efficiency of the tile
-// shape; a fixed per-tile cost (prologue latency, epilogue) is worth ~600 columns of K.
-double round_cost(const Config& c, const gemm_desc_t& d, int64_t N, double* rounds_out) {
-  const int64_t M = d.M, K = d.K;
-  const int e = esize(d.dtype_a), area = c.bm * c.bn;
-  const double tiles = (double)((M + c.bm - 1) / c.bm) * (double)((N + c.bn - 1) / c.bn) * (double)d.batch;
-  const double cus = num_cus();
-  const int per_cu = area <= 128 * 128 ? 2 : 1;                 // workgroups that fit one CU's LDS
-  // (256x192 measured: 0.85 - 1.03 of the 256x256 tile per FLOP on 4096x6144x4096, 4096x14336x4096, 8192^3)
-  double eff = area >= 256 * 256 ? 1.0 : (area >= 256 * 192 ? 0.88 : (area >= 256 * 128 ? 0.75 : 0.84));
-  // the 16x16x32 kernels: about a tenth faster per FLOP than the 32x32x16 ones at the same tile shape
-  // (8192^3: 732 against 800 us)
-  if (!std::strncmp(c.name, "mfma16", 6)) eff *= 1.10;
-  const double rounds = (double)(int64_t)((tiles + cus * per_cu - 1) / (cus * per_cu));
-  // workgroups that actually share a CU (a lone workgroup runs about per_cu times faster)
-  const double sharing = tiles >= cus * per_cu ? per_cu : (tiles > cus ? tiles / cus : 1.0);
-  *rounds_out = rounds;
-  return rounds * area * sharing / eff * ((double)K + 600.0) / (e == 1 ? 5.4e6 : 2.7e6);
-}
-
-// The others: fp8; rings of 32 columns and for operands of any alignment, which are weighed by the time of a slab with one workgroup
+// The others, 16-bit rings of 32 columns and for operands of any alignment, are weighed by the time of a slab with one workgroup
 // on a CU and with two (launch 2.7 us; each further round costs 2.4 us of prologue and epilogue that nothing overlaps: 512x512x128,
 // 64 problems, 64x64 tiles: 27 us).  An operand whose rows do not start on 128-byte lines costs a ring 0.35 on top: every piece of
 // 128 bytes touches two lines (384x4104x4104: 43 us, 384x4096x4096: 24 us).  In a batch, the slices of split-K among them, a slab
-// takes a quarter more: 1500 split-K products are then 0.7 % from the better of two estimates' choices, 3.3 % without.  A lone
-// fp8 workgroup on a CU waits for its loads: 0.42 us per slab of the 128x128 tile.
+// takes a quarter more: 1500 split-K products are then 0.7 % from the better of two estimates' choices, 3.3 % without.
 double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
   const int64_t M = d.M, K = d.K, batch = d.batch;
   const int e = esize(d.dtype_a);
-  const int area = c.bm * c.bn;
   const double tiles = (double)((M + c.bm - 1) / c.bm) * (double)((N + c.bn - 1) / c.bn) * (double)batch;
   const double cus = num_cus();
   const int off_line = ((d.lda * e) % 128 != 0) + ((d.ldb * e) % 128 != 0);
-  if (const TileTimes* t = tile_times(c)) return tile_cost(c, *t, d, N, tiles, off_line);
-  if (c.t1 > 0) {
-    const double slabs = (double)((K + c.bk - 1) / c.bk);
-    const double per_cu = (double)(int64_t)((tiles + cus - 1) / cus);
-    const bool tiled16 = e == 2 && c.kind != KIND_MFMA_G, many = tiled16 && batch > 1;
-    const double pitch = c.kind == KIND_MFMA_G ? 1.0 : 1.0 + 0.35 * off_line + (many ? 0.25 : 0.0);
-    const double pairs = c.t2 > 0 ? (double)(int64_t)(per_cu / 2) : 0.0, singles = per_cu - 2 * pairs;
-    const double work = 2.7 + (singles * c.t1 + pairs * c.t2) * slabs * pitch + (singles + pairs - 1) * 2.4 + (many ? 0.7 : 0.0);
-    return tiled16 ? with_memory(work, d, N) : work;           // (those are weighed against tile_cost's)
-  }
-  double rounds = 0;
-  const double work = round_cost(c, d, N, &rounds);
-  const double wait = rounds * ((double)K / c.bk * (area <= 128 * 128 ? 0.42 * (1.0 + 0.5 * off_line) : 0.0) + 3.0);
-  return work > wait ? work : wait;
+  if (const TileTimes* t = tile_times(c, d)) return tile_cost(c, *t, d, N, tiles, off_line);
+  const double slabs = (double)((K + c.bk - 1) / c.bk);
+  const double per_cu = (double)(int64_t)((tiles + cus - 1) / cus);
+  const bool tiled = c.kind != KIND_MFMA_G, many = tiled && batch > 1;
+  const double pitch = c.kind == KIND_MFMA_G ? 1.0 : 1.0 + 0.35 * off_line + (many ? 0.25 : 0.0);
+  const double pairs = c.t2 > 0 ? (double)(int64_t)(per_cu / 2) : 0.0, singles = per_cu - 2 * pairs;
+  const double work = 2.7 + (singles * c.t1 + pairs * c.t2) * slabs * pitch + (singles + pairs - 1) * 2.4 + (many ? 0.7 : 0.0);
+  return tiled ? with_memory(work, d, N) : work;               // (those are weighed against tile_cost's)
 }
 
 int best_mfma(const gemm_desc_t& d, double* cost_out) {
@@ -707,9 +713,9 @@ int64_t split_columns(const gemm_desc_t& d, int big, double single_cost) {
   // What the second launch takes beyond the two estimates, which count a launch each and no overlap.  Where the line lies, over drawn
   // products that can take two launches (1 to 6 rounds, K from 64 to 8192; taken, more than 2 % faster so, more than 2 % slower):
   // 16-bit results 1671: 307, 179, 24 with 1 us; 611, 211, 201 with -2; 218, 144, 14 with 3.  fp32 results 971: 408, 191, 107 with -2
-  // (mean -1.4 %); 302, 168, 46 with -1; 135, 105, 9 with 2 (-1.1 %); 1024x17416x136 takes 29.0 us, 31.7 in one.  fp8, 73 products:
-  // 25, 15, 1 with 7; 54, 16, 27 with 2.
-  const double launch = d.dtype_a == GEMM_F8E4M3 ? 7.0 : d.dtype_c == GEMM_F32 ? -2.0 : 0.5;
+  // (mean -1.4 %); 302, 168, 46 with -1; 135, 105, 9 with 2 (-1.1 %); 1024x17416x136 takes 29.0 us, 31.7 in one.  fp8, 2295
+  // (mean -1.2 %): 598, 339, 72 with 2; 883, 401, 189 with 0; 266, 202, 18 with 7.
+  const double launch = d.dtype_a == GEMM_F8E4M3 ? 2.0 : d.dtype_c == GEMM_F32 ? -2.0 : 0.5;
   return mfma_cost(c, d, n_first) + rest_cost + launch < single_cost ? n_first : 0;
 }
 
@@ -808,7 +814,8 @@ int fill_launch_shape(gemm_plan& pl) {
   } else if (c.kind == KIND_MFMA || c.kind == KIND_MFMA_T || c.kind == KIND_MFMA_G) {
     const int64_t tm = (d.M + c.bm - 1) / c.bm, tn = (d.N + c.bn - 1) / c.bn;
     int64_t wgs = tm * tn;
-    if (c.persist) {
+    const bool persist = persists(c, d);
+    if (persist) {
       // as many workgroups as run at once; workgroup b takes tiles b, b + wgs, ... of all problems of the batch
       const int64_t at_once = (int64_t)num_cus() * (160 * 1024 / c.lds_bytes);
       wgs *= d.batch;
@@ -827,7 +834,7 @@ int fill_launch_shape(gemm_plan& pl) {
       pl.xcd_remap = 3;
     }
     // a batch on persistent workgroups: whole problems per XCD (their tiles share panels)
-    if (c.persist && d.batch > 1 && (tm * tn * d.batch) % 8 == 0 && wgs % 8 == 0) pl.xcd_remap = 2;
+    if (persist && d.batch > 1 && (tm * tn * d.batch) % 8 == 0 && wgs % 8 == 0) pl.xcd_remap = 2;
   } else if (c.kind == KIND_SKINNY_PANEL) {
     pl.grid = dim3((unsigned)((d.N + c.bn - 1) / c.bn), (unsigned)d.batch, 1);
   } else {
@@ -942,6 +949,21 @@ int gemm_create_config(const gemm_desc_t* desc, int config, gemm_plan_t** out_pl
   return create_resolved(d, config, true, out_plan);
 }
 
+// The two-slab tiles as the number of slices weighs them: rounds over the CUs * work per round / measured relative efficiency of the
+// tile shape; a fixed per-tile cost (prologue latency, epilogue) is worth ~600 columns of K.
+static double round_cost(const Config& c, const gemm_desc_t& d) {
+  const int area = c.bm * c.bn;
+  const double tiles = (double)((d.M + c.bm - 1) / c.bm) * (double)((d.N + c.bn - 1) / c.bn) * (double)d.batch;
+  const double cus = num_cus();
+  const int per_cu = area <= 128 * 128 ? 2 : 1;                 // workgroups that fit one CU's LDS
+  double eff = area >= 256 * 256 ? 1.0 : (area >= 256 * 192 ? 0.88 : (area >= 256 * 128 ? 0.75 : 0.84));
+  if (!std::strncmp(c.name, "mfma16", 6)) eff *= 1.10;
+  const double rounds = (double)(int64_t)((tiles + cus * per_cu - 1) / (cus * per_cu));
+  // workgroups that actually share a CU (a lone workgroup runs about per_cu times faster)
+  const double sharing = tiles >= cus * per_cu ? per_cu : (tiles > cus ? tiles / cus : 1.0);
+  return rounds * area * sharing / eff * ((double)d.K + 600.0) / 2.7e6;
+}
+
 // Slices of K for a split-K plan: the count (up to 64, K a multiple of 8 x slices, whole
 // slabs per slice preferred) that minimises the round model of the two-slab tiles on the sliced product plus
 // the traffic of the fp32 partials (written once, read once: priced at 2 TB/s).  512x512x32768 takes 31 / 25 / 38 / 40 us
@@ -965,8 +987,7 @@ static int choose_splits(const gemm_desc_t& d) {
       for (int i = 0; i < kNumConfigs; ++i) {
         const Config& c = kConfigs[i];
         if (c.kind != KIND_MFMA || c.t1 > 0 || c.bm % 128 != 0 || !applicable(c, in)) continue;
-        double rounds = 0;
-        const double t = round_cost(c, in, in.N, &rounds) * (esize(d.dtype_a) == 1 ? 2.0 : 1.0);
+        const double t = round_cost(c, in);
         if (cost == 0 || t < cost) cost = t;
       }
       if (cost == 0) continue;

@@ -1,5 +1,5 @@
-// Matrix-core GEMM for gfx950 on the 16x16x32 MFMA shape: 16-bit operands (bf16 / fp16),
-// fp32 accumulate.
+// Matrix-core GEMM for gfx950 on the 16x16x32 MFMA shape: 16-bit operands (bf16 / fp16), fp32 accumulate; and on the 16x16x128
+// shape: 8-bit floating point (OCP E4M3).
 //
 //   C = act(A . B + bias),  A row-major (K contiguous), B column-major (K contiguous: the
 //   "weight" matrix stored N x K), C row-major; also A column-major and / or B row-major.
@@ -18,6 +18,14 @@
 //   * with two waves per SIMD, each wave lowers its priority as it advances from one
 //     hand-over to the next, so that the wave that is behind gets the matrix pipe and the
 //     two alternate sub-step by sub-step instead of one running ahead to the barrier.
+// fp8: the same slabs, loads and reads in bytes; a slab row of 128 values is one k-step, multiplied in G = 4 sub-steps.  A lane's 32
+// values are the two pieces that two k-steps of 16-bit values would read.  The column fragments are not double-buffered: the last
+// sub-step runs column by column, and each fragment of the next slab is requested behind the last MFMA that takes the registers it
+// goes to, so a wave needs no more fragment registers (64) than with 16-bit operands.  Bound by power: an MFMA-only loop runs at 4.3
+// PFLOP/s (32x32x64: 4.0, with the same error), 8192^3 with operands from HBM takes 358 us = 3.07 PFLOP/s.  The kernel that this
+// one replaced (32x32x64, one tile per workgroup, no prefetch): 8192^3 401 us, 4096x12288x4096 156, 4096^3 52.6 against 49.2, 128x128
+// tiles 486 against 467.  Measured here: loads over one or three sub-steps 383 / 368 us, no prefetch 371 (operands in the
+// last-level cache: 346 without it, 350 with it).
 // Paper taxonomy (Sec. 3.2): d_mem = 3, d_algo = 1 (fused post-op), d_sync = 1.
 #pragma once
 
@@ -27,15 +35,27 @@
 
 namespace mi355gemm {
 
+// kStep: values of K one MFMA takes; kParts: 16-byte LDS reads per fragment and lane where K is contiguous.  (fp8: 32 values of K
+// per lane in two pieces 64 values apart; which of a step's values a lane holds is free as long as A and B agree.)
 template <typename T> struct Frag16;
 template <> struct Frag16<bf16_t> {
+  static constexpr int kStep = 32, kParts = 1;
   static __device__ __forceinline__ void mfma(const u32x4_t& x, const u32x4_t& y, f32x4_t& c) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(x), "v"(y));
   }
 };
 template <> struct Frag16<f16_t> {
+  static constexpr int kStep = 32, kParts = 1;
   static __device__ __forceinline__ void mfma(const u32x4_t& x, const u32x4_t& y, f32x4_t& c) {
     asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(x), "v"(y));
+  }
+};
+typedef uint32_t u32x8_t __attribute__((ext_vector_type(8)));
+template <> struct Frag16<f8e4m3_t> {
+  static constexpr int kStep = 128, kParts = 2;
+  // (both operand formats default to fp8 E4M3, no block scaling)
+  static __device__ __forceinline__ void mfma(const u32x8_t& x, const u32x8_t& y, f32x4_t& c) {
+    asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0" : "+a"(c) : "v"(x), "v"(y));
   }
 };
 
@@ -52,7 +72,8 @@ __device__ __forceinline__ int swz16(int r) { return (r >> 1) & 7; }
 // and, when the next sub-step begins a new k-step, the NT column fragments too (WITH_B).
 // Its own MFMAs run in the order in which their operands were requested one sub-step earlier.
 // RA, RB: LDS reads per row / column fragment (one 16-byte read, or two 8-byte transposing ones).
-template <int MA, int NT, bool WITH_B, int RA, int RB>
+// COLS: the MFMAs run column by column (the last sub-step of a slab of one k-step, whose column fragments are overwritten one by one).
+template <int MA, int NT, bool WITH_B, int RA, int RB, bool COLS = false>
 struct SubOrder {
   static constexpr int kReads = MA * RA + (WITH_B ? NT * RB : 0), kMfma = MA * NT;
   struct Tables {
@@ -88,14 +109,38 @@ struct SubOrder {
         if (used[q]) continue;
         const int m = q / NT, n = q % NT;
         const int p = pos_a[m] > pos_b[n] ? pos_a[m] : pos_b[n];
-        const int key = (p + 1) * kMfma + q;
+        const int key = (p + 1) * kMfma + q + (COLS ? n * (kReads + 2) * kMfma : 0);
         if (best < 0 || key < best_key) { best = q; best_key = key; }
       }
       used[best] = true;
       t.mm[i] = best / NT;
       t.nn[i] = best % NT;
-      t.need[i] = best_key / kMfma - 1;
+      t.need[i] = (best_key / kMfma) % (kReads + 2) - 1;
     }
+    return t;
+  }
+  static constexpr Tables t = make();
+};
+// Behind which MFMA of a sub-step of type Ord each of its requests for the next one (OrdN) goes out: spread over the first MFMAs; a
+// column fragment (KEEP) not before the last MFMA that takes what its registers hold.  at[]: ascending; before[i]: requests ahead of
+// MFMA i.
+template <typename Ord, typename OrdN, bool KEEP>
+struct ReadSlots {
+  struct Tables { int at[OrdN::kReads], before[Ord::kMfma + 1]; };
+  static constexpr Tables make() {
+    Tables t{};
+    constexpr int per_mfma = (OrdN::kReads + Ord::kMfma - 1) / Ord::kMfma;
+    int from = 0;
+    for (int r = 0; r < OrdN::kReads; ++r) {
+      int at = KEEP ? 0 : r / per_mfma;
+      if (KEEP && OrdN::t.r_isb[r])
+        for (int i = 0; i < Ord::kMfma; ++i)
+          if (Ord::t.nn[i] == OrdN::t.r_idx[r] && i > at) at = i;
+      from = at > from ? at : from;
+      t.at[r] = from;
+    }
+    for (int i = 0; i <= Ord::kMfma; ++i)
+      for (int r = 0; r < OrdN::kReads; ++r) t.before[i] += t.at[r] < i ? 1 : 0;
     return t;
   }
   static constexpr Tables t = make();
@@ -103,16 +148,16 @@ struct SubOrder {
 
 template <typename T, int BM, int BN, int WM, int WN, int G, int STAGES = 2, bool A_KF = true>
 struct Mfma16Tile {
-  static constexpr int BK = 64, NSTAGE = STAGES;
+  static constexpr int ES = (int)sizeof(T), BK = 128 / ES, NSTAGE = STAGES;
   static constexpr int kWaves = WM * WN, kThreads = 64 * kWaves;
   static constexpr int WTM = BM / WM, WTN = BN / WN;     // per-wave block
   static constexpr int MT = WTM / 16, NT = WTN / 16;     // 16x16 MFMA tiles per wave
   static constexpr int MA = (MT + G - 1) / G;            // row fragments per sub-step, at most
   static constexpr int group_rows(int g) { return (MT + G - 1 - g) / G; }      // of sub-step g of a k-step (7 = 4 + 3)
   static constexpr int group_first(int g) { return g == 0 ? 0 : group_first(g - 1) + group_rows(g - 1); }
-  static constexpr int KK = BK / 32;                     // k-steps (32 columns) per slab
+  static constexpr int KK = BK / Frag16<T>::kStep;       // k-steps per slab: two, fp8 one
   static constexpr int NSUB = KK * G;                    // sub-steps per slab
-  static constexpr int ROWB = BK * 2;                    // bytes per slab row
+  static constexpr int ROWB = BK * ES;                   // bytes per slab row
   static constexpr int CPR = ROWB / 16, RPI = 64 / CPR;  // chunks per row, rows per wave-wide load
   // A wave-wide load fills 8 rows of A's slab; where those do not divide over the waves, the waves take them in turn and the last
   // ones issue one load less.  (A K-strided A is stored in blocks of 64 rows: BM is a multiple.)
@@ -128,25 +173,28 @@ struct Mfma16Tile {
   // in 256 bytes behind the slabs that nothing reads (a persistent workgroup: in the staging area, idle during the K loop).
   static constexpr bool PREFETCH = NSTAGE == 2 && kWaves == 8;
   static constexpr int DUMP_BYTES = PREFETCH ? 256 : 0;
-  static_assert(sizeof(T) == 2, "16-bit operands");
+  static_assert(ES == 2 || A_KF, "8-bit operands are K-contiguous");
   static_assert(BM % (8 * RPI) == 0 || BM % 32 == 0, "whole wave-wide loads");
   static_assert(A_KF || BM % 64 == 0, "a K-strided A is stored in blocks of 64 rows");
   static_assert(BN % (RPI * kWaves) == 0, "slab rows of B must divide over waves");
   static_assert(!UNEVEN || (NSTAGE == 2 && A_LOADS == B_LOADS), "the load that some waves leave out is the last of a slab's second half");
   static_assert(WTM % 16 == 0 && WTN % 16 == 0 && MT >= G, "wave block in whole sub-steps");
   static_assert(NSUB % 2 == 0, "the row-fragment double buffer alternates per sub-step");
-  static_assert(group_rows(G - 1) * NT >= MA + NT, "a sub-step issues one or two fragment reads behind each MFMA");
+  static_assert(KK == 1 || group_rows(G - 1) * NT >= MA + NT, "a sub-step issues one or two fragment reads behind each MFMA");
   static_assert(LDS_BYTES + (STAGES == 2 ? EPI_BYTES : 0) <= 160 * 1024, "LDS budget");
 };
 
-// The fragment registers of one operand: one 16-byte LDS read (K contiguous in memory) or two 8-byte
+// The fragment registers of one operand: one 16-byte LDS read (K contiguous in memory; fp8: two) or two 8-byte
 // transposing reads, each four of the lane's eight values of K (K strided).
-template <int PARTS> struct FragReg;
-template <> struct FragReg<1> {
-  u32x4_t v;
-  __device__ __forceinline__ u32x4_t get() const { return v; }
+template <typename T, bool KF> struct FragReg {
+  u32x4_t h[1];
+  __device__ __forceinline__ u32x4_t get() const { return h[0]; }
 };
-template <> struct FragReg<2> {
+template <> struct FragReg<f8e4m3_t, true> {
+  u32x4_t h[2];
+  __device__ __forceinline__ u32x8_t get() const { return __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7); }
+};
+template <typename T> struct FragReg<T, false> {
   u32x2_t h[2];
   __device__ __forceinline__ u32x4_t get() const { return __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3); }
 };
@@ -184,8 +232,9 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   constexpr int ROWB = Cfg::ROWB, BK = Cfg::BK, KK = Cfg::KK, NSUB = Cfg::NSUB;
   constexpr bool kEither = kEitherOrder<BM, BN, S, PERSIST>;
   constexpr bool kTwoPerSimd = Cfg::kWaves > 4;          // two waves share a SIMD: alternate by priority
-  constexpr int RA = A_KF ? 1 : 2, RB = B_KF ? 1 : 2;    // LDS reads per fragment
-  static_assert((B_KF || (BN % 64 == 0 && Cfg::WTN % 64 == 0)) && BK == 64,
+  constexpr int ES = Cfg::ES, EPC = 16 / ES;             // bytes per value, values per 16-byte piece
+  constexpr int RA = A_KF ? Frag16<T>::kParts : 2, RB = B_KF ? Frag16<T>::kParts : 2;    // LDS reads per fragment
+  static_assert((B_KF || (BN % 64 == 0 && Cfg::WTN % 64 == 0)) && ((A_KF && B_KF) || BK == 64),
                 "K-strided operands are stored in blocks of 64 rows x 8 values of K");
   // bytes from one slab of an operand to the next
   const int64_t a_step = A_KF ? (int64_t)ROWB : p.lda * (int64_t)(BK * 2);
@@ -284,7 +333,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
                        touched_line(ln, pf_a ? tn : tm, pf_a ? p.touch & 15 : p.touch >> 4, wave_lines);
       const int64_t ld = pf_a ? p.lda : p.ldb;
       const int left = pf_a ? p.M - r0 : p.N - c0;
-      auto row_line = [&]() __attribute__((always_inline)) { return (uint32_t)((int64_t)min(line, left - 1) * ld * 2); };
+      auto row_line = [&]() __attribute__((always_inline)) { return (uint32_t)((int64_t)min(line, left - 1) * ld * ES); };
       auto k_line = [&](int per_k) __attribute__((always_inline)) {
         return (uint32_t)(((int64_t)(line / per_k) * ld + min(line % per_k * 64, left - 8)) * 2);
       };
@@ -305,7 +354,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       const int r = a_unit(q) * RPI + ln / CPR;
       const int c = (ln % CPR) ^ swz16(r);
       const int rr = min(r, p.M - 1 - r0);
-      a_off[q] = (uint32_t)(((int64_t)rr * p.lda + c * 8) * 2);
+      a_off[q] = (uint32_t)(((int64_t)rr * p.lda + c * EPC) * ES);
     }
 #pragma unroll
     for (int q = 0; q < Cfg::B_LOADS; ++q) {
@@ -318,7 +367,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       const int r = (wave * Cfg::B_LOADS + q) * RPI + ln / CPR;
       const int c = (ln % CPR) ^ swz16(r);
       const int rr = min(r, p.N - 1 - c0);
-      b_off[q] = (uint32_t)(((int64_t)rr * p.ldb + c * 8) * 2);
+      b_off[q] = (uint32_t)(((int64_t)rr * p.ldb + c * EPC) * ES);
     }
   };
   locate(p, blockIdx.x);
@@ -387,13 +436,13 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     u32x4_t v = {0u, 0u, 0u, 0u};
     if (q < Cfg::A_LOADS) {
       const int r = a_unit(q) * RPI + lane / CPR;
-      int k = ((lane % CPR) ^ swz16(r)) * 8, row = 0;            // the piece's first value of K
+      int k = ((lane % CPR) ^ swz16(r)) * EPC, row = 0;            // the piece's first value of K
       if constexpr (!A_KF) strided_unit(a_unit(q), lane, k, row);
       if (k < kvalid) v = *(const u32x4_t*)(Ab + (int64_t)kt * a_step + a_off[q < Cfg::A_LOADS ? q : 0]);
     } else {
       const int qb = q >= Cfg::A_LOADS ? q - Cfg::A_LOADS : 0;
       const int r = (wave * Cfg::B_LOADS + qb) * RPI + lane / CPR;
-      int k = ((lane % CPR) ^ swz16(r)) * 8, row = 0;
+      int k = ((lane % CPR) ^ swz16(r)) * EPC, row = 0;
       if constexpr (!B_KF) strided_unit(wave * Cfg::B_LOADS + qb, lane, k, row);
       if (k < kvalid) v = *(const u32x4_t*)(Bb + (int64_t)kt * b_step + b_off[qb]);
     }
@@ -408,11 +457,11 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
 
   // ---- LDS -> fragment addressing ---------------------------------------------------------
   // MFMA 16x16x32 operand: lane l holds 8 consecutive k of row (l % 16), k-octet l / 16 of the
-  // step's four.  Fragment m of the wave is 16*m rows further on: a constant offset.  The
+  // step's four.  (fp8: pieces l / 16 and 4 + l / 16 of the row, what two steps of 16-bit values would read.)  Fragment m of the wave is 16*m rows further on: a constant offset.  The
   // address registers point into the stage being read and move to the other stage at each
   // hand-over (one vector add each), so a fragment read needs no address arithmetic.
   // (K-strided operand: one register for each of the four 32-byte pieces of a 64-row block, see A_KF.)
-  constexpr int NA = A_KF ? KK : 4, NB = B_KF ? KK : 4;
+  constexpr int NA = A_KF ? 2 : 4, NB = B_KF ? 2 : 4;
   uint32_t a_rd[NA], b_rd[NB];
   int rd_delta;                                  // to the other stage (alternates in sign)
   // point the address registers into stage `st` (`ln`: the lane id, see load_tile)
@@ -421,7 +470,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     const int a_row = wm * Cfg::WTM + fr;
     const int b_row = wn * Cfg::WTN + fr;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
+    for (int kk = 0; kk < 2; ++kk) {
       const int c = kk * 4 + fo;
       if constexpr (A_KF) a_rd[kk] = lds_base + st * Cfg::STAGE_BYTES + a_row * ROWB + ((c ^ swz16(a_row)) * 16);
       if constexpr (B_KF) b_rd[kk] = lds_base + st * Cfg::STAGE_BYTES + Cfg::A_BYTES + b_row * ROWB + ((c ^ swz16(b_row)) * 16);
@@ -464,8 +513,9 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
   asm volatile("s_nop 7" ::: "memory");
 
   // Fragment registers: row fragments double-buffered per sub-step, column fragments per k-step.
-  FragReg<RA> af[2][MA];
-  FragReg<RB> bf[2][NT];
+  // (One k-step per slab, KK == 1: one set of column fragments, each overwritten behind the last MFMA of the slab that takes it.)
+  FragReg<T, A_KF> af[2][MA];
+  FragReg<T, B_KF> bf[KK][NT];
 
   // Sub-step u of a slab: k-step u / G, row group u % G.
   // the i-th read of the requests made for sub-step `u` (from the stage the address registers point into)
@@ -475,11 +525,11 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     typedef SubOrder<Cfg::group_rows(g), NT, g == 0, RA, RB> Ord;
     const int idx = Ord::t.r_idx[i], part = Ord::t.r_part[i];
     if (Ord::t.r_isb[i]) {
-      if constexpr (B_KF) lds_read_b128(bf[kk & 1][idx].v, b_rd[kk], idx * (16 * ROWB));
-      else lds_read_tr16(bf[kk & 1][idx].h[part], b_rd[idx & 3], (idx >> 2) * 8192 + kk * 4096 + part * 512);
+      if constexpr (B_KF) lds_read_b128(bf[kk][idx].h[part], b_rd[KK == 1 ? part : kk], idx * (16 * ROWB));
+      else lds_read_tr16(bf[kk][idx].h[part], b_rd[idx & 3], (idx >> 2) * 8192 + kk * 4096 + part * 512);
     } else {
       const int m = Cfg::group_first(g) + idx;
-      if constexpr (A_KF) lds_read_b128(af[u & 1][idx].v, a_rd[kk], m * (16 * ROWB));
+      if constexpr (A_KF) lds_read_b128(af[u & 1][idx].h[part], a_rd[KK == 1 ? part : kk], m * (16 * ROWB));
       else lds_read_tr16(af[u & 1][idx].h[part], a_rd[m & 3], (m >> 2) * 8192 + kk * 4096 + part * 512);
     }
   };
@@ -499,9 +549,10 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     constexpr int u = decltype(u_c)::value;
     constexpr int kk = u / G, g = u % G;
     constexpr int un = (u + 1) % NSUB;                    // the sub-step the reads are for
-    typedef SubOrder<Cfg::group_rows(g), NT, g == 0, RA, RB> Ord;   // how this sub-step's operands were requested
+    constexpr bool keep = KK == 1 && un == 0;             // the requests overwrite column fragments in use
+    typedef SubOrder<Cfg::group_rows(g), NT, g == 0, RA, RB, keep> Ord;   // how this sub-step's operands were requested
     typedef SubOrder<Cfg::group_rows(un % G), NT, (un % G) == 0, RA, RB> OrdN; // this sub-step's own requests
-    constexpr int per_mfma = (OrdN::kReads + Ord::kMfma - 1) / Ord::kMfma;         // requests behind one MFMA
+    typedef ReadSlots<Ord, OrdN, keep> Slots;
     const int nq = q1 - q0;
     int waited = -1;
 #pragma unroll
@@ -509,15 +560,14 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       const int m = Ord::t.mm[i], n = Ord::t.nn[i];
       if (Ord::t.need[i] > waited) {
         // since the needed request: the rest of that sub-step's requests and those of ours so far
-        const int ours = i * per_mfma;
-        const int after = (Ord::kReads - 1 - Ord::t.need[i]) + (reads ? (ours < OrdN::kReads ? ours : OrdN::kReads) : 0);
+        const int after = (Ord::kReads - 1 - Ord::t.need[i]) + (reads ? Slots::t.before[i] : 0);
         wait_lgkmcnt_dyn(after);                 // (the counter holds 15 at most: larger values wait for 15)
         waited = Ord::t.need[i];
       }
-      Frag16<T>::mfma(bf[kk & 1][n].get(), af[u & 1][m].get(), acc[Cfg::group_first(g) + m][n]);
+      Frag16<T>::mfma(bf[kk][n].get(), af[u & 1][m].get(), acc[Cfg::group_first(g) + m][n]);
 #pragma unroll
-      for (int r = i * per_mfma; r < (i + 1) * per_mfma; ++r)
-        if (reads && r < OrdN::kReads) read_one(std::integral_constant<int, un>(), r);
+      for (int r = 0; r < OrdN::kReads; ++r)
+        if (reads && Slots::t.at[r] == i) read_one(std::integral_constant<int, un>(), r);
 #pragma unroll
       for (int j = 0; j < nq; ++j)
         if ((int)((j + 0.5f) * Ord::kMfma / nq) == i) {
@@ -599,13 +649,14 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     constexpr int CH32 = OROWB32 / 16;
     constexpr int kShare = Cfg::LDS_BYTES / Cfg::kWaves;
     static_assert(16 * OROWB32 <= kShare, "one 16-row band of the wave block in fp32 must fit the wave's share of LDS");
-    static_assert(OROWB == 128 || OROWB == 256, "staging rows of 128 or 256 bytes");
+    static_assert(OROWB == 128 || OROWB == 192 || OROWB == 256, "staging rows of 128, 192 or 256 bytes");
     static_assert(2 * 16 * OROWB <= (PERSIST ? Cfg::EPI_BYTES / Cfg::kWaves : kShare), "two 16-bit bands per wave");
     // staging: this wave's share of the idle slab stages, or of the separate area of a persistent workgroup
     unsigned char* wt = PERSIST ? smem + Cfg::LDS_BYTES + wave * (Cfg::EPI_BYTES / Cfg::kWaves) : smem + wave * kShare;
-    // chunk-slot key of staging row r: 128-byte rows alternate between the two halves of the banks,
-    // longer rows all start at bank 0
-    auto osw = [](int r) __attribute__((always_inline)) { return OROWB == 128 ? ((r >> 1) & 7) : (r & 15); };
+    // chunk-slot key of staging row r: 128-byte rows alternate between the two halves of the banks, 192-byte rows
+    // start at each quarter in turn, 256-byte rows all start at bank 0; within groups of 4 (8 in fp32) chunks where a row is no power of two
+    auto osw = [](int r) __attribute__((always_inline)) { return OROWB == 128 ? ((r >> 1) & 7) : OROWB == 192 ? (r >> 2) & 3 : (r & 15); };
+    constexpr int kKey32 = OROWB == 192 ? 7 : 15;
 
     // 16-bit through LDS, pipelined over the 16-row bands of the wave block with two staging
     // buffers: while the rows of band m-1 come back from LDS, the values of band m+1 are computed;
@@ -720,13 +771,13 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) w[e] = actf(acc[m][n][e] + bv[e]);
           const int q = n * 4 + eq;
-          *(f32x4_t*)(wt + er * OROWB32 + ((q ^ (er & 15)) * 16)) = w;
+          *(f32x4_t*)(wt + er * OROWB32 + ((q ^ (er & kKey32)) * 16)) = w;
         }
 #pragma unroll
         for (int it = 0; it < kIt32; ++it) {
           const int e = it * 64 + slane;
           const int r = e / CH32, q = e % CH32;
-          const f32x4_t val = *(const f32x4_t*)(wt + r * OROWB32 + ((q ^ (r & 15)) * 16));
+          const f32x4_t val = *(const f32x4_t*)(wt + r * OROWB32 + ((q ^ (r & kKey32)) * 16));
           if (inside) {
             f32x4_any_t* c = (f32x4_any_t*)(wave_c + (lane_off[it] + (uint32_t)m * band_step));
             if (pe.c_cached) *c = val;             // split-K partials are read by the next kernel
@@ -871,7 +922,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    const int ksteps = (p.K - T_full * BK + 31) / 32;
+    const int ksteps = (p.K - T_full * BK + Frag16<T>::kStep - 1) / Frag16<T>::kStep;
     static_for<0, NSUB>([&](auto u_c) __attribute__((always_inline)) {
       constexpr int u = decltype(u_c)::value;
       if (u / G < ksteps) {

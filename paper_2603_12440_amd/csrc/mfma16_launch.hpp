@@ -54,6 +54,19 @@ hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void
   X(224, 256, 2, 4, 2, true)       \
   X(192, 256, 2, 4, 2, true)       \
   X(128, 128, 2, 2, 2, true)
+// fp8 operands (slabs of 128 columns, one k-step: four sub-steps)
+#define MI355GEMM_MFMA16F8_TILES(X) \
+  X(256, 256, 2, 4, 4, false)       \
+  X(224, 256, 2, 4, 4, false)       \
+  X(192, 256, 2, 4, 4, false)       \
+  X(256, 192, 4, 2, 4, false)       \
+  X(128, 128, 2, 2, 4, false)
+#define MI355GEMM_MFMA16F8P_TILES(X) \
+  X(256, 256, 2, 4, 4, true)         \
+  X(224, 256, 2, 4, 4, true)         \
+  X(192, 256, 2, 4, 4, true)         \
+  X(256, 192, 4, 2, 4, true)         \
+  X(128, 128, 2, 2, 4, true)
 
 // The same for operands whose K is not contiguous, one translation unit per operand type and layout pair
 // (mfma16t_*_inst.hip); the table's entry picks the pair from the plan's layouts.
@@ -78,6 +91,14 @@ hipError_t launch_mfma16(const gemm_plan& pl, const void* A, const void* B, void
       const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
 #define MI355GEMM_MFMA16S_DEFINE(T, BM, BN, WM, WN, G, S, AK, BK)                             \
   template hipError_t launch_mfma16<T, T, BM, BN, WM, WN, G, false, AK, BK, S>(                \
+      const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
+
+#define MI355GEMM_MFMA16F8S_TILES(X) X(128, 128, 2, 2, 4, 4)
+#define MI355GEMM_MFMA16F8S_DECLARE(BM, BN, WM, WN, G, S)                                    \
+  extern template hipError_t launch_mfma16<f8e4m3_t, bf16_t, BM, BN, WM, WN, G, false, true, true, S>( \
+      const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
+#define MI355GEMM_MFMA16F8S_DEFINE(BM, BN, WM, WN, G, S)                                     \
+  template hipError_t launch_mfma16<f8e4m3_t, bf16_t, BM, BN, WM, WN, G, false, true, true, S>( \
       const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
 
 #define MI355GEMM_MFMA16_DECLARE(T, TO, BM, BN, WM, WN, G, P)                               \

@@ -1,5 +1,4 @@
-// Matrix-core GEMM for gfx950: 16-bit operands (bf16 / fp16) or 8-bit floating point
-// (OCP E4M3), fp32 accumulate.
+// Matrix-core GEMM for gfx950: 16-bit operands (bf16 / fp16), fp32 accumulate.
 //
 //   C = act(A . B + bias),  A row-major (K contiguous), B column-major (K
 //   contiguous: the "weight" matrix stored N x K), C row-major.
@@ -44,41 +43,23 @@ template <typename T> struct Frag;
 // ("+a") and, being volatile, the MFMAs keep their program order relative to each
 // other and to the (volatile) fragment reads, which is what the hand-made
 // software pipeline below relies on.
-// A fragment is kParts 16-byte LDS reads per lane: one for the 16-bit types (8 values of K
-// per lane and MFMA), two for fp8, whose v_mfma_f32_32x32x64_f8f6f4 takes 32 values of K per
-// lane (lane l: row l % 32; which 32 values of the step's 64 a lane holds is free as long
-// as A and B agree, so the two reads are the same pair of adjacent 16-byte chunks that two
-// consecutive 16-bit steps would read).  kKStep = values of K one MFMA consumes.
+// A fragment is one 16-byte LDS read per lane (8 values of K); kKStep = values of K one MFMA consumes.
 template <> struct Frag<bf16_t> {
-  static constexpr int kParts = 1, kKStep = 16;
-  static __device__ __forceinline__ void mfma(const u32x4_t (&x)[1], const u32x4_t (&y)[1], f32x16_t& c) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(x[0]), "v"(y[0]));
+  static constexpr int kKStep = 16;
+  static __device__ __forceinline__ void mfma(const u32x4_t& x, const u32x4_t& y, f32x16_t& c) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(x), "v"(y));
   }
 };
 template <> struct Frag<f16_t> {
-  static constexpr int kParts = 1, kKStep = 16;
-  static __device__ __forceinline__ void mfma(const u32x4_t (&x)[1], const u32x4_t (&y)[1], f32x16_t& c) {
-    asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+a"(c) : "v"(x[0]), "v"(y[0]));
-  }
-};
-template <> struct Frag<f8e4m3_t> {
-  static constexpr int kParts = 2, kKStep = 64;
-  static __device__ __forceinline__ void mfma(const u32x4_t (&x)[2], const u32x4_t (&y)[2], f32x16_t& c) {
-    typedef int i32x4_t __attribute__((ext_vector_type(4)));
-    typedef int i32x8_t __attribute__((ext_vector_type(8)));
-    const i32x8_t xv = __builtin_shufflevector(__builtin_bit_cast(i32x4_t, x[0]), __builtin_bit_cast(i32x4_t, x[1]),
-                                               0, 1, 2, 3, 4, 5, 6, 7);
-    const i32x8_t yv = __builtin_shufflevector(__builtin_bit_cast(i32x4_t, y[0]), __builtin_bit_cast(i32x4_t, y[1]),
-                                               0, 1, 2, 3, 4, 5, 6, 7);
-    // both operand formats default to fp8 E4M3, no block scaling
-    asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, %0" : "+a"(c) : "v"(xv), "v"(yv));
+  static constexpr int kKStep = 16;
+  static __device__ __forceinline__ void mfma(const u32x4_t& x, const u32x4_t& y, f32x16_t& c) {
+    asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+a"(c) : "v"(x), "v"(y));
   }
 };
 
 // ---- LDS layout ------------------------------------------------------------------
-// A slab is rows x BK values, i.e. rows of 2*HB bytes = HB/8 chunks of 16 bytes (HB = BK
-// for the 16-bit types, BK/2 for fp8).  Chunk c of row r is stored at chunk slot
-// r*(HB/8) + (c ^ swz<HB>(r)):  the XOR spreads the 32 rows a fragment read touches over
+// A slab is rows x HB = BK values, i.e. rows of 2*HB bytes = HB/8 chunks of 16 bytes.  Chunk c of row r
+// is stored at chunk slot r*(HB/8) + (c ^ swz<HB>(r)):  the XOR spreads the 32 rows a fragment read touches over
 // all LDS banks.
 template <int HB> __device__ __forceinline__ int swz(int r);
 template <> __device__ __forceinline__ int swz<64>(int r) { return (r & 7) ^ ((r >> 3) & 3); }
@@ -197,6 +178,7 @@ struct MfmaTile {
   static constexpr int EPC = 16 / ES;                    // elements per 16-byte chunk
   static constexpr int ROWB = BK * ES;                   // bytes per slab row
   static constexpr int HB = ROWB / 2;                    // key of the swizzle
+  static_assert(ES == 2, "16-bit operands");
   static constexpr int CPR = ROWB / 16;                  // 16-byte chunks per slab row
   static constexpr int RPI = 64 / CPR;                   // slab rows one wave-wide load covers
   static constexpr int A_LOADS = BM / RPI / kWaves;      // direct-to-LDS loads per lane, A slab
@@ -223,15 +205,11 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // T: operand type; TO: the 16-bit output type (outputs may also be fp32: MfmaArgs::c_f32).
-// EITHER: launches may walk the tiles in strips or in regions; otherwise in regions only.  (fp8 has both variants: nothing
-// overlaps the start of a tile here, and the choice cost 4096x14336x4096 0.8 us of 183; 16-bit operands mostly run on the
-// other kernel.)
-template <typename T, typename TO, int BM, int BN, int BK, int WM, int WN, int NSTAGE, bool EITHER>
+template <typename T, typename TO, int BM, int BN, int BK, int WM, int WN, int NSTAGE>
 __global__ __launch_bounds__(64 * WM * WN) void mfma_gemm_kernel(MfmaArgs p) {
   typedef MfmaTile<T, BM, BN, BK, WM, WN, NSTAGE> Cfg;
   constexpr int MT = Cfg::MT, NT = Cfg::NT, CPR = Cfg::CPR, RPI = Cfg::RPI;
   constexpr int ES = Cfg::ES, EPC = Cfg::EPC, ROWB = Cfg::ROWB, HB = Cfg::HB;
-  constexpr int kParts = Frag<T>::kParts;
 
   __shared__ __attribute__((aligned(1024))) unsigned char smem[Cfg::LDS_BYTES];
 
@@ -241,7 +219,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma_gemm_kernel(MfmaArgs p) {
   const int wm = wave / WN, wn = wave % WN;
 
   int tm, tn;
-  tile_coords<EITHER>(p, blockIdx.x, gridDim.x, tm, tn);
+  tile_coords<kEitherOrder<BM, BN, NSTAGE, false>>(p, blockIdx.x, gridDim.x, tm, tn);
   const int row0 = tm * BM, col0 = tn * BN;
   const int64_t batch = blockIdx.y;
 
@@ -334,17 +312,14 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma_gemm_kernel(MfmaArgs p) {
   const int fr = lane & 31, fh = lane >> 5;
   const int a_row = wm * Cfg::WTM + fr;
   const int b_row = wn * Cfg::WTN + fr;
-  // byte offset of (row, chunk c) = row*ROWB + ((c ^ swz(row)) * 16); part j of k-step kk is
-  // chunk (kk*kParts + j)*2 + fh
-  uint32_t a_rd[Cfg::KK][kParts], b_rd[Cfg::KK][kParts];
+  // byte offset of (row, chunk c) = row*ROWB + ((c ^ swz(row)) * 16); k-step kk is chunk kk*2 + fh
+  uint32_t a_rd[Cfg::KK], b_rd[Cfg::KK];
 #pragma unroll
-  for (int kk = 0; kk < Cfg::KK; ++kk)
-#pragma unroll
-    for (int j = 0; j < kParts; ++j) {
-      const int c = (kk * kParts + j) * 2 + fh;
-      a_rd[kk][j] = a_row * ROWB + ((c ^ swz<HB>(a_row)) * 16);
-      b_rd[kk][j] = Cfg::A_BYTES + b_row * ROWB + ((c ^ swz<HB>(b_row)) * 16);
-    }
+  for (int kk = 0; kk < Cfg::KK; ++kk) {
+    const int c = kk * 2 + fh;
+    a_rd[kk] = a_row * ROWB + ((c ^ swz<HB>(a_row)) * 16);
+    b_rd[kk] = Cfg::A_BYTES + b_row * ROWB + ((c ^ swz<HB>(b_row)) * 16);
+  }
 
   f32x16_t acc[MT][NT];
 #pragma unroll
@@ -356,18 +331,15 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma_gemm_kernel(MfmaArgs p) {
 
   // Fragment registers, double-buffered over the MFMA k-steps of a slab: while the
   // MFMAs of step kk run, the LDS reads of step kk+1 are already in flight.
-  u32x4_t af[2][MT][kParts], bf[2][NT][kParts];
+  u32x4_t af[2][MT], bf[2][NT];
   typedef StepOrder<MT, NT> Ord;
   const uint32_t smem_base = lds_base;
 
   auto read_one = [&](int i, int stage, int kk, int buf) __attribute__((always_inline)) {       // i-th read of the fixed read order
     const uint32_t s = smem_base + stage * Cfg::STAGE_BYTES;
     const int idx = Ord::t.r_idx[i];
-#pragma unroll
-    for (int j = 0; j < kParts; ++j) {
-      if (Ord::t.r_isb[i]) lds_read_b128(bf[buf][idx][j], s + b_rd[kk][j], idx * (32 * ROWB));
-      else lds_read_b128(af[buf][idx][j], s + a_rd[kk][j], idx * (32 * ROWB));
-    }
+    if (Ord::t.r_isb[i]) lds_read_b128(bf[buf][idx], s + b_rd[kk], idx * (32 * ROWB));
+    else lds_read_b128(af[buf][idx], s + a_rd[kk], idx * (32 * ROWB));
   };
   auto read_frags = [&](int stage, int kk, int buf) __attribute__((always_inline)) {
 #pragma unroll
@@ -395,7 +367,7 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma_gemm_kernel(MfmaArgs p) {
       // and min(i, kReads) requests of this step have been issued.
       {
         const int after = (Ord::kReads - 1 - Ord::t.need[i]) + (reads ? (i < Ord::kReads ? i : Ord::kReads) : 0);
-        wait_lgkmcnt_dyn(after * kParts);        // (the counter holds 15 at most: larger values wait for 15)
+        wait_lgkmcnt_dyn(after);                 // (the counter holds 15 at most: larger values wait for 15)
       }
       Frag<T>::mfma(bf[cur][n], af[cur][m], acc[m][n]);
       if (reads && i < Ord::kReads) read_one(i, rs, rk, cur ^ 1);

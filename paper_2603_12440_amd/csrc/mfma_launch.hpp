@@ -1,7 +1,6 @@
 // Launcher of the matrix-core kernel and the list of its compiled tile shapes.  The
 // instantiations are spread over one translation unit per operand type
-// (mfma_bf16_inst.hip, mfma_f16_inst.hip, mfma_f8_inst.hip); the table in gemm_api.hip
-// only refers to them.
+// (mfma_bf16_inst.hip, mfma_f16_inst.hip); the table in gemm_api.hip only refers to them.
 #pragma once
 
 #include "plan.hpp"
@@ -30,28 +29,17 @@ hipError_t launch_mfma(const gemm_plan& pl, const void* A, const void* B, void* 
   a.batches = (int)d.batch;
   a.touch = 0;
   set_tile_order<BM, BN, kEitherOrder<BM, BN, 2, false>>(a, pl);
-  if constexpr (sizeof(T) == 1) {                        // fp8: a variant with regions only (see the kernel)
-    if (a.xcd_remap != 4) {
-      mfma_gemm_kernel<T, TO, BM, BN, BK, WM, WN, NS, false><<<pl.grid, pl.block, 0, s>>>(a);
-      return hipGetLastError();
-    }
-  }
-  mfma_gemm_kernel<T, TO, BM, BN, BK, WM, WN, NS, true><<<pl.grid, pl.block, 0, s>>>(a);
+  mfma_gemm_kernel<T, TO, BM, BN, BK, WM, WN, NS><<<pl.grid, pl.block, 0, s>>>(a);
   return hipGetLastError();
 }
 
-// X(BM, BN, BK, WM, WN, NSTAGE): tile, wave grid, LDS stages.  16-bit operands:
+// X(BM, BN, BK, WM, WN, NSTAGE): tile, wave grid, LDS stages
 #define MI355GEMM_MFMA_TILES(X) \
   X(256, 256, 64, 2, 4, 2)      \
   X(256, 256, 64, 2, 2, 2)      \
   X(256, 128, 64, 2, 2, 2)      \
   X(128, 128, 64, 2, 2, 2)      \
   X(256, 192, 64, 4, 2, 2)
-// fp8 operands (BK is twice as many values: the same slabs in bytes):
-#define MI355GEMM_MFMA8_TILES(X) \
-  X(256, 256, 128, 2, 4, 2)      \
-  X(128, 128, 128, 2, 2, 2)      \
-  X(256, 192, 128, 4, 2, 2)
 
 #define MI355GEMM_MFMA_DECLARE(T, TO, BM, BN, BK, WM, WN, NS)                               \
   extern template hipError_t launch_mfma<T, TO, BM, BN, BK, WM, WN, NS>(                      \

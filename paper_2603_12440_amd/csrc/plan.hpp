@@ -61,11 +61,17 @@ struct Config {
   int threads;
   int lds_bytes;
   launch_fn launch[4];    // per operand dtype (GEMM_F32 / BF16 / F16 / F8E4M3); NULL = not compiled
-  int persist;            // 1: workgroups walk over several tiles (grid = workgroups resident at once)
+  int persist;            // 1: workgroups walk over several tiles (grid = workgroups resident at once); 2: where K allows it (persists)
   // more than two slabs in LDS: microseconds a slab takes with one workgroup on a CU and with two (0: two do not
   // fit); t1 == 0 for all other kernels
   float t1, t2;
 };
+
+// Do the workgroups of such a plan walk over several tiles?  (K has to be a whole number of slabs, at least two; a configuration of
+// type 1 takes no other K.)
+inline bool persists(const Config& c, const gemm_desc_t& d) {
+  return c.persist == 1 || (c.persist == 2 && d.K % c.bk == 0 && d.K >= 2 * c.bk);
+}
 
 inline int esize(int dt) { return dt == GEMM_F32 ? 4 : (dt == GEMM_F8E4M3 ? 1 : 2); }
 
