@@ -613,4 +613,152 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_direct_kernel(SkinnyArgs p)
   }
 }
 
+// ---- M up to 16: x held in registers, every workgroup walks over panels of 16 rows of W ---------
+// The kernel above starts a workgroup per 32 rows: each fetches its part of x again (half as many bytes as W at M = 16)
+// and waits for its first slabs with nothing else on the way, and once there are more workgroups than fit at a time (512)
+// they start again all together.  Here one workgroup of eight waves per CU stays: a wave keeps its part of K of all x rows
+// in registers (S slabs of 256 columns; 128 registers at K = 8192) and streams that part of the rows of W, two slabs of
+// 16 rows x 512 bytes requested ahead, from one panel straight into the next.  A panel's eight parts are added through LDS,
+// in the order of K, with one barrier (two buffers).  The first panel requests the pieces of x between the slabs of W that they meet:
+// all of x first or last costs 3 us.  Workgroups begin at different parts of K and different slabs of them (memory
+// channels, see above).  More than two slabs ahead gained nothing (28672x4096: 40.2 -> 40.8 us), nor did adding the parts
+// without a barrier (39.9 -> 43.1).  The bound is HBM: M = 16, operands from HBM: 28672x8192 80.3 -> 73.5 us (6.4 TB/s, 7.0 between
+// the first and the last panel), 28672x4096 48.1 -> 39.0, 14336x8192 43.2 -> 39.1, 6144x4096 14.4 -> 13.1, 2608x8176 20.5 -> 16.1.
+// FULL: K is eight whole parts of S slabs (28672x4096: 39.6 -> 38.9).  One problem per launch.
+constexpr int kSkinnyRowsPanel = 16, kSkinnyRowsMaxK = 8192;
+constexpr int kSkinnyRowsLds = 8 * 16 * 512 + 2 * 8 * 256 * 4;
+template <typename T, int S, bool FULL>
+__global__ __launch_bounds__(512) void skinny_rows_kernel(SkinnyArgs p) {
+  constexpr int kSlab = 16 * 512, DEPTH = 2;           // slabs of W requested ahead
+  __shared__ __attribute__((aligned(1024))) unsigned char slabs[8 * kSlab];
+  __shared__ float red[2][8][256];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int panels = (p.N + 15) / 16;
+  const int mine = (panels - 1 - (int)blockIdx.x) / (int)gridDim.x + 1;
+  const char* const X = (const char*)p.X;
+  const char* const W = (const char*)p.W;
+  const float* bias = p.has_bias ? p.bias : nullptr;
+  // this wave's part of K, columns k0 .. k0 + len (the last ones may be short or empty), and the order of its slabs
+  const int part = (p.K + 511) / 512 * 64;
+  const int k_of = (wave + (int)blockIdx.x) & 7;
+  const int k0 = min(k_of * part, p.K), len = min(part, p.K - k0);
+  const int rot = (int)(blockIdx.x >> 3) % S;
+  const int fr = lane & 15, fo = lane >> 4;
+  const int lr = lane >> 5, lc = lane & 31;
+  int slab_col[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) { int t = s + rot; slab_col[s] = (t >= S ? t - S : t) * 256; }
+
+  // W load q of a slab: 32 lanes cover 512 bytes of one row, two rows at a time; in LDS chunk c of row r sits at slot c ^ r
+  const uint32_t row_bytes = (uint32_t)p.ldw * 2u;
+  const uint32_t voff = (uint32_t)lr * row_bytes + (uint32_t)lc * 16u;
+  u32x4_t wv[DEPTH][8];
+  // slab s of the workgroup's panel j.  Past the last panel, and where the part has no such slab, a piece of x: all loads are
+  // unconditional.  The last panel of an N that is not whole panels ends with the last row of W.
+  auto load_w = [&](u32x4_t (&w)[8], int j, int s) __attribute__((always_inline)) {
+    const bool live = j < mine && (FULL || slab_col[s] < len);
+    const int n0 = min(min((int)blockIdx.x + j * (int)gridDim.x, panels - 1) * 16, p.N - 16);
+    const char* base = live ? W + ((int64_t)n0 * p.ldw + k0 + slab_col[s]) * 2 : X;
+    const uint32_t step = live ? 2u * row_bytes : 0u;
+    uint32_t vo = live ? voff : 0u;
+    if (!FULL) vo = lc * 8 < len - slab_col[s] ? vo : 0u;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      uint32_t o = vo + q * step;
+      asm volatile("" : "+v"(o));                      // (32-bit offsets from a scalar base, formed here)
+      w[q] = __builtin_nontemporal_load((const u32x4_t*)(base + o));
+    }
+  };
+  unsigned char* my = slabs + wave * kSlab;
+  auto write_slab = [&](const u32x4_t (&w)[8], int s) __attribute__((always_inline)) {
+    uint32_t slot = (uint32_t)(lc ^ lr) * 16u;
+    asm volatile("" : "+v"(slot));
+    const bool ok = FULL || lc * 8 < len - slab_col[s];  // (pieces past the part count as zeros)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      u32x4_t v = w[q];
+      if (!FULL)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = ok ? v[e] : 0u;
+      *(u32x4_t*)(my + lr * 512 + q * 1024 + (slot ^ (uint32_t)(2 * q * 16))) = v;
+    }
+  };
+  // x fragment of k-step kk of slab s: 16 bytes at column 32 kk + 8 (l / 16) of row l % 16 (rows past M repeat the last one,
+  // their results are dropped), zeros past the part
+  u32x4_t x[S][8];
+  const char* const xs = X + ((int64_t)min(fr, p.M - 1) * p.ldx + k0) * 2 + fo * 16;
+  auto load_x = [&](u32x4_t (&xf)[8], int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      const bool in = FULL || slab_col[s] + kk * 32 + fo * 8 < len;
+      const u32x4_t v = *(const u32x4_t*)(in ? xs + (slab_col[s] + kk * 32) * 2 : X);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) xf[kk][e] = in ? v[e] : 0u;
+    }
+  };
+  // the first slabs of W and the pieces of x they meet, in the order in which they are needed
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) {
+    load_w(wv[d], d / S, d % S);
+    if (d < S) load_x(x[d], d);
+  }
+  f32x4acc_t acc;
+  auto multiply = [&](const u32x4_t (&xf)[8]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < 8; h += 4) {
+      u32x4_t wf[4];
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) wf[kk] = *(const u32x4_t*)(my + fr * 512 + ((((h + kk) * 4 + fo) ^ fr) * 16));
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) acc = Mfma16<T>::run(xf[h + kk], wf[kk], acc);
+    }
+  };
+  // D[x row][W row]: register e of lane l is x row 4 (l / 16) + e, row l % 16 of W; each wave adds 32 of the panel's 256 sums
+  auto finish = [&](int j) __attribute__((always_inline)) {
+    float (*r)[256] = red[j & 1];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[k_of][e * 64 + lane] = acc[e];
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const int n_at = ((int)blockIdx.x + j * (int)gridDim.x) * 16, n0 = min(n_at, p.N - 16);
+    const int o = wave * 32 + lc, q = o >> 6, l = o & 63;
+    float sum = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) sum += r[w][o];
+    const int m = 4 * (l >> 4) + q, n = n0 + (l & 15);
+    if (lr == 0 && m < p.M && n >= n_at) {
+      const float v = apply_activation(p.act, sum + (bias ? bias[n] : 0.0f), p.scale);
+      const int64_t at = (int64_t)m * p.ldy + n;
+      if (p.y_f32) ((float*)p.Y)[at] = v;
+      else ((T*)p.Y)[at] = from_float<T>(v);
+    }
+  };
+  // slab number j * S + s sits in registers (j * S + s) % DEPTH
+  constexpr int U = S % DEPTH == 0 ? 1 : DEPTH;
+  auto panel = [&](int j, int u, bool first) __attribute__((always_inline)) {
+    acc = f32x4acc_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int d = (u * S + s) % DEPTH;
+      write_slab(wv[d], s);
+      load_w(wv[d], j + (s + DEPTH) / S, (s + DEPTH) % S);
+      if (first && s + DEPTH < S) load_x(x[s + DEPTH], s + DEPTH);
+      multiply(x[s]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    finish(j);
+  };
+  // the first panel also requests the rest of x
+  panel(0, 0, true);
+#pragma unroll 1
+  for (int j = 1; j < mine; j += U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (u == 0 || j + u < mine) panel(j + u, (u + 1) % U, false);
+  }
+}
+
 }  // namespace mi355gemm

@@ -1,0 +1,64 @@
+"""The skinny kernel with x in registers, behind the skinnydirect_d2_b512_w4 plan: exact on small integers at the edges of its parts
+of K, of its panels of 16 rows and of the rule that chooses it; values that are not finite stay in their own outputs."""
+import pytest
+import torch
+
+import workloads as wl
+from test_gpu_wide_tiles import run_exact
+
+pytestmark = pytest.mark.gpu
+CFG = "skinnydirect_d2_b512_w4"
+
+
+@pytest.fixture(scope="module")
+def g():
+    import paper_2603_12440_amd as g
+    g.load_library()
+    assert torch.cuda.is_available()
+    return g
+
+
+# parts of K: one to four slabs, full, one piece short of full, one piece into the next; the last part short or empty
+@pytest.mark.parametrize("K", [1032, 1536, 2040, 2048, 2056, 3592, 4096, 4104, 6136, 6144, 6152, 8184, 8192, 8200])
+def test_parts_and_panels(g, K):
+    for M, N in [(16, 16), (2, 17), (9, 1000), (5, 4113), (16, 8193)] + [(3, 12289)] * (K in (2056, 4096)) + [(16, 16401)] * (K < 2000):
+        w = wl.Workload("t", M, N, K, epilogue="bias_relu", seed_a=K, seed_b=N)
+        run_exact(g, w, CFG, out_dtype="f32")
+        if N < 8000:
+            run_exact(g, w, CFG, pad_c=3)
+
+
+def test_fp16_and_the_rule(g):
+    def block(**kw):
+        p = g.gemm_create(g.GemmDesc(**kw))
+        info = p.info()
+        g.gemm_destroy(p)
+        assert CFG in info
+        return "block=512" in info
+    assert block(M=16, N=28672, K=8192) and block(M=2, N=16, K=1032) and block(M=16, N=8192, K=4096)
+    assert not block(M=16, N=8192, K=8192) and not block(M=16, N=4096, K=1024) and not block(M=16, N=28672, K=8200)
+    assert not block(M=16, N=15, K=4096) and not block(M=16, N=4096, K=4096, batch=2)
+    for M, N, K in [(7, 2000, 1400), (16, 9000, 2824)]:
+        run_exact(g, wl.Workload("t", M, N, K, dtype="f16", epilogue="bias_relu", seed_a=K, seed_b=N), CFG)
+
+
+@pytest.mark.parametrize("K", [1416, 4096, 5000])
+def test_values_that_are_not_finite(g, K):
+    M, N = 5, 3001 if K < 2048 else 9001
+    A = torch.ones(M, K, dtype=torch.bfloat16, device="cuda")
+    B = torch.ones(N, K, dtype=torch.bfloat16, device="cuda")
+    want = torch.full((M, N), float(K))
+    for row, col, v in [(0, 0, float("inf")), (1, K - 1, float("-inf")), (17, K // 2, float("nan")), (N - 1, K - 8, float("inf")), (N - 2, 0, float("nan"))]:
+        B[row, col] = v
+        want[:, row] = v
+    A[M - 1, K - 1] = float("inf")
+    want[M - 1] = torch.where(want[M - 1].isfinite(), float("inf"), want[M - 1])
+    want[M - 1, 1] = float("-inf")
+    C = torch.empty(M, N, device="cuda")
+    p = g.gemm_create(g.GemmDesc(M, N, K, dtype_c=g.F32))
+    assert "block=512" in p.info()
+    g.gemm_run(p, A, B, C, None)
+    torch.cuda.synchronize()
+    g.gemm_destroy(p)
+    want[M - 1, 1] = float("-inf")          # inf * -inf at the last column
+    assert torch.equal(C.cpu().nan_to_num(nan=1e9, posinf=2e9, neginf=-2e9), want.nan_to_num(nan=1e9, posinf=2e9, neginf=-2e9))
