@@ -65,6 +65,11 @@ MI355GEMM_MFMA16T_TILES(X)
   MI355GEMM_RING_DECLARE(f8e4m3_t, bf16_t, BM, BN, WM, WN, KS, NS, true, true)
 MI355GEMM_RINGS(X)
 #undef X
+#define X(BM, BN, WM, WN, KS, NS, T1, T2)                                    \
+  MI355GEMM_RING_DECLARE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, true, true) \
+  MI355GEMM_RING_DECLARE(f16_t, f16_t, BM, BN, WM, WN, KS, NS, true, true)
+MI355GEMM_RINGS16(X)
+#undef X
 #define X(BM, BN, WM, WN, KS, NS, T1, T2)                                      \
   MI355GEMM_RING_DECLARE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, true, false)  \
   MI355GEMM_RING_DECLARE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, false, false) \
@@ -452,6 +457,7 @@ const Config kConfigs[] = {
     MI355GEMM_MFMA16S_TILES(MFMA16S_CFG)
     MI355GEMM_MFMA16S_TILES(MFMA16TS_CFG)
     MI355GEMM_RINGS(RING_CFG)
+    MI355GEMM_RINGS16(RING_CFG)
     MI355GEMM_RINGS_T(RINGT_CFG)
     MI355GEMM_RINGS(RING8_CFG)
     MI355GEMM_MFMA16G_TILES(MFMA16G_CFG)
@@ -610,6 +616,7 @@ bool runs_rows(const Config& c, const gemm_desc_t& d) { return c.persist == 3 &&
 int plan_lds_bytes(const gemm_plan& pl) {
   const Config& c = *pl.cfg;
   if (runs_rows(c, pl.d)) return kSkinnyRowsLds;
+  if (runs_ksplit(c, pl.d, num_cus())) return c.bm == 64 ? kSplitLds<64, 64> : kSplitLds<32, 32>;
   if (c.persist == 2 && !persists(c, pl.d)) return 2 * (c.bm + c.bn) * 128 + (c.threads == 512 ? 256 : 0);   // (no staging area)
   if (c.kind != KIND_F32_VEC || f32_takes_ring(pl.d, c.bm)) return c.lds_bytes;
   return f32_mfma_lds(c.bm, pl.d.layout_a == GEMM_ROW_MAJOR) + f32_mfma_lds(c.bm, pl.d.layout_b == GEMM_COL_MAJOR);
@@ -686,7 +693,7 @@ double tile_cost(const Config& c, const TileTimes& t, const gemm_desc_t& d, int6
   const double turns = tiles / (num_cus() * at_once), whole = std::floor(turns), part = turns - whole;
   // (of a batch: the kernels that give an XCD whole problems, where tiles divide by 8, find shared panels in its L2)
   const bool apart = d.batch > 1 && !((persists(c, d) || c.t1 > 0) && std::fmod(tiles, 8.0) == 0);
-  const double turn = t.tile + t.slab * (double)((d.K + c.bk - 1) / c.bk) * (1.0 + h.off_line * off_line + (apart ? h.apart : 0.0)) +
+  const double turn = t.tile + t.slab * (runs_ksplit(c, d, num_cus()) ? 0.86 : 1.0) * (double)((d.K + c.bk - 1) / c.bk) * (1.0 + h.off_line * off_line + (apart ? h.apart : 0.0)) +
                       (d.dtype_c == GEMM_F32 ? h.f32 * area * at_once : 0.0);
   return with_memory(h.launch + turn * (whole + (part > 0 ? t.part + (1.0 - t.part) * part : 0.0)), d, N);
 }
@@ -696,6 +703,7 @@ double tile_cost(const Config& c, const TileTimes& t, const gemm_desc_t& d, int6
 // 64 problems, 64x64 tiles: 27 us).  An operand whose rows do not start on 128-byte lines costs a ring 0.35 on top: every piece of
 // 128 bytes touches two lines (384x4104x4104: 43 us, 384x4096x4096: 24 us).  In a batch, the slices of split-K among them, a slab
 // takes a quarter more: 1500 split-K products are then 0.7 % from the better of two estimates' choices, 3.3 % without.
+// Where such a tile runs on ksplit_ring_kernel a slab takes 0.86 of its time (both estimates).
 double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
   const int64_t M = d.M, K = d.K, batch = d.batch;
   const int e = esize(d.dtype_a);
@@ -706,7 +714,7 @@ double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
   const double slabs = (double)((K + c.bk - 1) / c.bk);
   const double per_cu = (double)(int64_t)((tiles + cus - 1) / cus);
   const bool tiled = c.kind != KIND_MFMA_G, many = tiled && batch > 1;
-  const double pitch = c.kind == KIND_MFMA_G ? 1.0 : 1.0 + 0.35 * off_line + (many ? 0.25 : 0.0);
+  const double pitch = c.kind == KIND_MFMA_G ? 1.0 : (runs_ksplit(c, d, num_cus()) ? 0.86 : 1.0) + 0.35 * off_line + (many ? 0.25 : 0.0);
   const double pairs = c.t2 > 0 ? (double)(int64_t)(per_cu / 2) : 0.0, singles = per_cu - 2 * pairs;
   const double work = 2.7 + (singles * c.t1 + pairs * c.t2) * slabs * pitch + (singles + pairs - 1) * 2.4 + (many ? 0.7 : 0.0);
   return tiled ? with_memory(work, d, N) : work;               // (those are weighed against tile_cost's)
@@ -840,6 +848,7 @@ int fill_launch_shape(gemm_plan& pl) {
   const Config& c = *pl.cfg;
   pl.block = dim3(c.threads, 1, 1);
   pl.xcd_remap = 0;
+  pl.cus = num_cus();
   if (c.kind == KIND_SIMT || c.kind == KIND_F32_VEC) {
     const int64_t gx = (d.N + c.bn - 1) / c.bn, gy = (d.M + c.bm - 1) / c.bm;
     if (gy > 65535) return GEMM_ERR_BAD_DIM;   // grid.y / grid.z limits
@@ -857,6 +866,7 @@ int fill_launch_shape(gemm_plan& pl) {
     } else {
       pl.grid = dim3((unsigned)wgs, (unsigned)d.batch, 1);
     }
+    if (runs_ksplit(c, d, pl.cus)) pl.block = dim3(64 * kSplitWaves, 1, 1);
     pl.xcd_remap = d.batch == 1 || (tm * tn) % 8 == 0 ? 1 : 0;
     if (d.batch == 1 && dealt_one_by_one(tm, tn, c.bm * c.bn, d.K * esize(d.dtype_a), c.kind == KIND_MFMA_G && d.layout_b == GEMM_ROW_MAJOR))
       pl.xcd_remap = 0;

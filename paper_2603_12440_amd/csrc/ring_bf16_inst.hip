@@ -4,6 +4,7 @@
 namespace mi355gemm {
 #define X(BM, BN, WM, WN, KS, NS, T1, T2) MI355GEMM_RING_DEFINE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, true, true)
 MI355GEMM_RINGS(X)
+MI355GEMM_RINGS16(X)
 #undef X
 #define X(BM, BN, WM, WN, KS, NS, T1, T2)                                   \
   MI355GEMM_RING_DEFINE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, true, false)  \

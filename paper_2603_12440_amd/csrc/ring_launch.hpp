@@ -1,13 +1,19 @@
 // Launcher of the ring kernel and the list of its compiled shapes (instantiated in ring_*_inst.hip).
 #pragma once
 
+#include "ksplit_ring_kernel.hpp"
 #include "mfma16_launch.hpp"
-#include "ring_kernel.hpp"
 
 namespace mi355gemm {
 
 template <typename T, typename TO, int BM, int BN, int WM, int WN, int KS, int NS, bool A_KF, bool B_KF>
 hipError_t launch_ring(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias, hipStream_t s) {
+  if constexpr (A_KF && B_KF && sizeof(T) == 2 && has_ksplit(BM, BN, KS)) {
+    if (runs_ksplit(*pl.cfg, pl.d, pl.cus)) {
+      ksplit_ring_kernel<T, BM, BN><<<pl.grid, pl.block, 0, s>>>(mfma16_args<BM, BN, false>(pl, A, B, C, bias));
+      return hipGetLastError();
+    }
+  }
   ring_gemm_kernel<T, TO, BM, BN, WM, WN, KS, NS, A_KF, B_KF><<<pl.grid, pl.block, 0, s>>>(mfma16_args<BM, BN, kEitherOrder<BM, BN, NS, false>>(pl, A, B, C, bias));
   return hipGetLastError();
 }
@@ -19,6 +25,9 @@ hipError_t launch_ring(const gemm_plan& pl, const void* A, const void* B, void* 
   X(32, 32, 2, 2, 4, 3, 0.40, 0.0)            \
   X(64, 32, 4, 2, 2, 4, 0.30, 0.0)            \
   MI355GEMM_RINGS_T(X)
+// 16-bit operands only: a barrier per 256 values of K instead of 128.  64x6144x4096 12.5 -> 11.9 us with operands in the last-level
+// cache, 16.8 -> 16.6 from HBM; 128x4096x4096 12.6 -> 11.8 and 16.2 -> 15.8.  Six slabs of 128 values were slower (13.5, 17.3).
+#define MI355GEMM_RINGS16(X) X(64, 32, 4, 2, 4, 3, 0.565, 0.0)
 // the shapes that also take operands whose K is not contiguous (blocks of 64 rows)
 #define MI355GEMM_RINGS_T(X)                  \
   X(64, 64, 2, 4, 2, 4, 0.44, 0.0)            \

@@ -1,0 +1,71 @@
+"""The kernel whose waves split K, behind the ring plans of 64x64 and 32x32 tiles: exact on small integers around whole turns of its eight
+waves, K tails, ragged tiles, batches and the rule that chooses it; values that are not finite stay in their own outputs."""
+import pytest
+import torch
+
+import workloads as wl
+from test_gpu_wide_tiles import run_exact
+
+pytestmark = pytest.mark.gpu
+C64, C32, K64x32 = "mfma16_64x64_k2_w2x4_s4", "mfma16_32x32_k4_w2x2_s3", "mfma16_64x32_k4_w4x2_s3"
+
+
+@pytest.fixture(scope="module")
+def g():
+    import paper_2603_12440_amd as g
+    g.load_library()
+    assert torch.cuda.is_available()
+    return g
+
+
+def block(g, cfg, **kw):
+    p = g.gemm_create_config(g.GemmDesc(**kw), g.config_names().index(cfg))
+    info = p.info()
+    g.gemm_destroy(p)
+    return int(info.split("block=")[1].split()[0]), int(info.split("lds=")[1].split()[0])
+
+
+def test_the_rule(g):
+    assert block(g, C32, M=96, N=512, K=1216) == (512, 65536) and block(g, C32, M=17, N=1024, K=2368) == (512, 65536)
+    for kw in (dict(M=96, N=512, K=1152), dict(M=64, N=1024, K=2304), dict(M=96, N=512, K=1224), dict(M=1024, N=512, K=2048), dict(M=96, N=512, K=2048, batch=6)):
+        assert block(g, C32, **kw)[0] == 256, kw
+    assert block(g, C32, M=96, N=512, K=2048, batch=5)[0] == 512
+    assert block(g, C64, M=256, N=256, K=1408)[1] == 131072
+
+
+# 22 to 25 slabs over eight waves, then whole turns and a long K; tails in rows on 128-byte lines (pad)
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("K,pad", [(1408, 0), (1472, 64), (1536, 0), (1600, 0), (1416, 56), (1528, 8), (1544, 56), (2048, 0), (4096, 0)])
+def test_slabs_tails_and_edges(g, dtype, K, pad):
+    for cfg, shapes in ((C64, [(200, 250), (256, 1024), (1001, 250)]), (C32, [(65, 100), (96, 96), (513, 320)]), (K64x32, [(33, 47), (128, 96)])):
+        for M, N in shapes:
+            w = wl.Workload("t", M, N, K, dtype=dtype, epilogue="bias_relu", seed_a=K, seed_b=M)
+            run_exact(g, w, cfg, out_dtype="f32", pad_a=pad, pad_b=pad)
+            run_exact(g, w, cfg, pad_a=pad, pad_b=pad, pad_c=3)
+    w = wl.Workload("t", 70, 96, K, dtype=dtype, batch=8, seed_a=K, seed_b=4)
+    run_exact(g, w, C32, out_dtype="f32", pad_a=pad, pad_b=pad)
+    run_exact(g, wl.Workload("t", 193, 200, K, dtype=dtype, batch=3, seed_a=K, seed_b=4), C64, out_dtype="f32", pad_a=pad, pad_b=pad)
+
+
+@pytest.mark.parametrize("cfg", [C64, C32])
+@pytest.mark.parametrize("K,ld", [(1536, 1536), (1544, 1600)])
+def test_values_that_are_not_finite(g, cfg, K, ld):
+    M, N = 250, 300 if cfg == C64 else 130
+    A = torch.full((M, ld), float("nan"), dtype=torch.bfloat16, device="cuda")     # (what lies behind K is never multiplied)
+    B = torch.full((N, ld), float("nan"), dtype=torch.bfloat16, device="cuda")
+    A[:, :K] = 1
+    B[:, :K] = 1
+    want = torch.full((M, N), float(K))
+    for row, col, v in [(0, 0, float("inf")), (17, K - 1, float("nan")), (N - 1, 700, float("-inf"))]:
+        B[row, col] = v
+        want[:, row] = v
+    A[M - 1, K - 1] = float("inf")
+    want[M - 1] = torch.where(want[M - 1].isfinite(), float("inf"), want[M - 1])
+    want[M - 1, N - 1] = float("nan")
+    C = torch.empty(M, N, device="cuda")
+    p = g.gemm_create_config(g.GemmDesc(M, N, K, lda=ld, ldb=ld, dtype_c=g.F32), g.config_names().index(cfg))
+    assert "block=512" in p.info()
+    g.gemm_run(p, A, B, C, None)
+    torch.cuda.synchronize()
+    g.gemm_destroy(p)
+    assert torch.equal(C.cpu().nan_to_num(nan=1e9, posinf=2e9, neginf=-2e9), want.nan_to_num(nan=1e9, posinf=2e9, neginf=-2e9))
