@@ -70,6 +70,11 @@ MI355GEMM_RINGS(X)
   MI355GEMM_RING_DECLARE(f16_t, f16_t, BM, BN, WM, WN, KS, NS, true, true)
 MI355GEMM_RINGS16(X)
 #undef X
+#define X(BM, BN, W, NS, T1)                              \
+  MI355GEMM_KSPLIT_INST(extern, bf16_t, BM, BN, W, NS)    \
+  MI355GEMM_KSPLIT_INST(extern, f16_t, BM, BN, W, NS)
+MI355GEMM_KSPLITS(X)
+#undef X
 #define X(BM, BN, WM, WN, KS, NS, T1, T2)                                      \
   MI355GEMM_RING_DECLARE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, true, false)  \
   MI355GEMM_RING_DECLARE(bf16_t, bf16_t, BM, BN, WM, WN, KS, NS, false, false) \
@@ -401,6 +406,10 @@ hipError_t launch_mfma16f8(const gemm_plan& pl, const void* A, const void* B, vo
 #define RING8_CFG(BM, BN, WM, WN, KS, NS, T1, T2)                                          \
   RING_ENTRY("mfma8", KIND_MFMA, f8e4m3_t, BM, BN, WM, WN, KS, NS, T1, T2, nullptr, nullptr, \
              launch_ring<f8e4m3_t, bf16_t, BM, BN, WM, WN, KS, NS, true, true>)
+// small tiles, K split over the waves
+#define KSPLIT_CFG(BM, BN, W, NS, T1)                                                      \
+  { "ksplit16_" #BM "x" #BN "_w" #W "_s" #NS, KIND_MFMA, BM, BN, 64, 64 * W, kSplitLds<BM, BN, W, NS>, \
+    { nullptr, launch_ksplit<bf16_t, BM, BN, W, NS>, launch_ksplit<f16_t, BM, BN, W, NS> }, 4, T1##f, 0.0f },
 // 16-bit operands of any alignment, two slabs
 #define MFMA16G_CFG(BM, BN, WM, WN, KS, T1, T2)                                            \
   { "mfma16g_" #BM "x" #BN "_k" #KS "_w" #WM "x" #WN, KIND_MFMA_G, BM, BN, KS * 64, 64 * WM * WN, \
@@ -458,6 +467,7 @@ const Config kConfigs[] = {
     MI355GEMM_MFMA16S_TILES(MFMA16TS_CFG)
     MI355GEMM_RINGS(RING_CFG)
     MI355GEMM_RINGS16(RING_CFG)
+    MI355GEMM_KSPLITS(KSPLIT_CFG)
     MI355GEMM_RINGS_T(RINGT_CFG)
     MI355GEMM_RINGS(RING8_CFG)
     MI355GEMM_MFMA16G_TILES(MFMA16G_CFG)
@@ -616,7 +626,6 @@ bool runs_rows(const Config& c, const gemm_desc_t& d) { return c.persist == 3 &&
 int plan_lds_bytes(const gemm_plan& pl) {
   const Config& c = *pl.cfg;
   if (runs_rows(c, pl.d)) return kSkinnyRowsLds;
-  if (runs_ksplit(c, pl.d, num_cus())) return c.bm == 64 ? kSplitLds<64, 64> : kSplitLds<32, 32>;
   if (c.persist == 2 && !persists(c, pl.d)) return 2 * (c.bm + c.bn) * 128 + (c.threads == 512 ? 256 : 0);   // (no staging area)
   if (c.kind != KIND_F32_VEC || f32_takes_ring(pl.d, c.bm)) return c.lds_bytes;
   return f32_mfma_lds(c.bm, pl.d.layout_a == GEMM_ROW_MAJOR) + f32_mfma_lds(c.bm, pl.d.layout_b == GEMM_COL_MAJOR);
@@ -652,6 +661,7 @@ const TileTimes kTileTimes[] = {
     {"mfma16t_128x128x64_w2x2", 3.08, 0.905, 0.50}, {"mfma16t_128x128x64_w2x2_p", 2.61, 0.929, 0.57}, {"mfma16t_128x128x64_w2x2_s4", 2.85, 0.501, 0.69},
     {"mfma16t_192x256x64_w2x4", 6.04, 1.085, 0.55}, {"mfma16t_192x256x64_w2x4_p", 4.62, 1.031, 0.73}, {"mfma16t_256x256x64_w2x4", 8.38, 1.279, 0.53},
     {"mfma16t_256x256x64_w2x4_p", 6.34, 1.246, 0.61}, {"mfma16t_64x64_k1_w2x4_s5", 1.51, 0.507, 0.37}, {"mfma16t_64x64_k2_w2x4_s4", 1.14, 0.583, 0.63},
+    {"ksplit16_64x64_w8_s1", 1.41, 0.235, 0.60},        // (0.86 of the time of the ring's tile, for half its slab)
     {"mfma_128x128x64_w2x2_s2", 4.48, 1.000, 0.50}, {"mfma_256x128x64_w2x2_s2", 5.67, 0.993, 0.82}, {"mfma_256x192x64_w4x2_s2", 6.16, 1.271, 0.62},
     {"mfma_256x256x64_w2x4_s2", 8.48, 1.521, 0.55},
     {"mfma_256x256x64_w2x2_s2", 8.48, 1.521, 0.55},     // (not timed: as the shape with eight waves, which goes first)
@@ -693,7 +703,7 @@ double tile_cost(const Config& c, const TileTimes& t, const gemm_desc_t& d, int6
   const double turns = tiles / (num_cus() * at_once), whole = std::floor(turns), part = turns - whole;
   // (of a batch: the kernels that give an XCD whole problems, where tiles divide by 8, find shared panels in its L2)
   const bool apart = d.batch > 1 && !((persists(c, d) || c.t1 > 0) && std::fmod(tiles, 8.0) == 0);
-  const double turn = t.tile + t.slab * (runs_ksplit(c, d, num_cus()) ? 0.86 : 1.0) * (double)((d.K + c.bk - 1) / c.bk) * (1.0 + h.off_line * off_line + (apart ? h.apart : 0.0)) +
+  const double turn = t.tile + t.slab * (double)((d.K + c.bk - 1) / c.bk) * (1.0 + h.off_line * off_line + (apart ? h.apart : 0.0)) +
                       (d.dtype_c == GEMM_F32 ? h.f32 * area * at_once : 0.0);
   return with_memory(h.launch + turn * (whole + (part > 0 ? t.part + (1.0 - t.part) * part : 0.0)), d, N);
 }
@@ -703,7 +713,6 @@ double tile_cost(const Config& c, const TileTimes& t, const gemm_desc_t& d, int6
 // 64 problems, 64x64 tiles: 27 us).  An operand whose rows do not start on 128-byte lines costs a ring 0.35 on top: every piece of
 // 128 bytes touches two lines (384x4104x4104: 43 us, 384x4096x4096: 24 us).  In a batch, the slices of split-K among them, a slab
 // takes a quarter more: 1500 split-K products are then 0.7 % from the better of two estimates' choices, 3.3 % without.
-// Where such a tile runs on ksplit_ring_kernel a slab takes 0.86 of its time (both estimates).
 double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
   const int64_t M = d.M, K = d.K, batch = d.batch;
   const int e = esize(d.dtype_a);
@@ -714,18 +723,32 @@ double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
   const double slabs = (double)((K + c.bk - 1) / c.bk);
   const double per_cu = (double)(int64_t)((tiles + cus - 1) / cus);
   const bool tiled = c.kind != KIND_MFMA_G, many = tiled && batch > 1;
-  const double pitch = c.kind == KIND_MFMA_G ? 1.0 : (runs_ksplit(c, d, num_cus()) ? 0.86 : 1.0) + 0.35 * off_line + (many ? 0.25 : 0.0);
+  const double pitch = c.kind == KIND_MFMA_G ? 1.0 : 1.0 + 0.35 * off_line + (many ? 0.25 : 0.0);
   const double pairs = c.t2 > 0 ? (double)(int64_t)(per_cu / 2) : 0.0, singles = per_cu - 2 * pairs;
   const double work = 2.7 + (singles * c.t1 + pairs * c.t2) * slabs * pitch + (singles + pairs - 1) * 2.4 + (many ? 0.7 : 0.0);
   return tiled ? with_memory(work, d, N) : work;               // (those are weighed against tile_cost's)
 }
 
-int best_mfma(const gemm_desc_t& d, double* cost_out) {
+// Where the built-in choice weighs the kernels whose waves split K: rows on 128-byte lines (a slab's rows of 128 bytes touch two
+// otherwise: 502x1838, K = 4224 5 % ahead of the ring kernel, 1034x210, K = 10824 9 to 25 % behind), at most a tile per CU, and a K long
+// enough for the addition of the waves' sums.  Time over the better ring kernel's of the same tile, drawn products, operands from HBM / in the
+// last-level cache: 32x32 tiles, three tile rows and more from K = 1216 0.89 to 1.00 / 0.76 to 0.96, fewer rows from K = 2368 0.91 to 1.02 / 0.72 to
+// 0.99 (below: up to 1.05); 64x64 tiles, four rows and columns of tiles and more from K = 1408 0.87 to 1.04 / 0.82 to 1.06; with fewer rows, where HBM
+// alone is the bound, up to 1.08.
+bool weighs_ksplit(const Config& c, const gemm_desc_t& d) {
+  const int64_t tm = (d.M + c.bm - 1) / c.bm, tn = (d.N + c.bn - 1) / c.bn;
+  if (tm * tn > num_cus() || tm * tn * d.batch > num_cus() || d.lda % 64 != 0 || d.ldb % 64 != 0) return false;
+  return c.bm == 64 ? tm >= 4 && tn >= 4 && d.K >= 1408 : d.K >= (tm >= 3 ? 1216 : 2368);
+}
+
+// (ksplit: may it be one of those?  Not the inner product of a split-K plan, whose slices are parts of K already.)
+int best_mfma(const gemm_desc_t& d, double* cost_out, bool ksplit = true) {
   int best = -1;
   double best_cost = 0;
   for (int i = 0; i < kNumConfigs; ++i) {
     const Config& c = kConfigs[i];
     if ((c.kind != KIND_MFMA && c.kind != KIND_MFMA_T && c.kind != KIND_MFMA_G) || !applicable(c, d)) continue;
+    if (c.persist == 4 && !(ksplit && weighs_ksplit(c, d))) continue;
     const double cost = mfma_cost(c, d, d.N);
     if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
   }
@@ -848,7 +871,6 @@ int fill_launch_shape(gemm_plan& pl) {
   const Config& c = *pl.cfg;
   pl.block = dim3(c.threads, 1, 1);
   pl.xcd_remap = 0;
-  pl.cus = num_cus();
   if (c.kind == KIND_SIMT || c.kind == KIND_F32_VEC) {
     const int64_t gx = (d.N + c.bn - 1) / c.bn, gy = (d.M + c.bm - 1) / c.bm;
     if (gy > 65535) return GEMM_ERR_BAD_DIM;   // grid.y / grid.z limits
@@ -866,7 +888,6 @@ int fill_launch_shape(gemm_plan& pl) {
     } else {
       pl.grid = dim3((unsigned)wgs, (unsigned)d.batch, 1);
     }
-    if (runs_ksplit(c, d, pl.cus)) pl.block = dim3(64 * kSplitWaves, 1, 1);
     pl.xcd_remap = d.batch == 1 || (tm * tn) % 8 == 0 ? 1 : 0;
     if (d.batch == 1 && dealt_one_by_one(tm, tn, c.bm * c.bn, d.K * esize(d.dtype_a), c.kind == KIND_MFMA_G && d.layout_b == GEMM_ROW_MAJOR))
       pl.xcd_remap = 0;
@@ -1076,7 +1097,7 @@ int gemm_create_splitk(const gemm_desc_t* desc, int splits, gemm_plan_t** out_pl
   bool taken = false;
   for (int i = 0; i < kNumConfigs && !taken; ++i) taken = kConfigs[i].kind == KIND_MFMA && kConfigs[i].t1 == 0 && applicable(kConfigs[i], in);
   if (!taken) return GEMM_ERR_UNSUPPORTED;
-  const int inner_cfg = best_mfma(in, nullptr);
+  const int inner_cfg = best_mfma(in, nullptr, false);
   if (inner_cfg < 0) return GEMM_ERR_UNSUPPORTED;
   gemm_plan_t* inner = nullptr;
   rc = create_resolved(in, inner_cfg, false, &inner);

@@ -26,7 +26,6 @@ struct gemm_plan {
   int cfg_index;
   dim3 grid, block;
   int xcd_remap;          // MFMA scheduling
-  int cus;                // compute units the plan was made for
   // Optional second launch for the columns past d.N (a different tile shape for the part of
   // the problem that does not fill whole rounds of the CUs): its own plan, and the element
   // offsets of its B, C and bias.
@@ -62,7 +61,8 @@ struct Config {
   int threads;
   int lds_bytes;
   launch_fn launch[4];    // per operand dtype (GEMM_F32 / BF16 / F16 / F8E4M3); NULL = not compiled
-  int persist;            // 1: workgroups walk over several tiles (grid = workgroups resident at once); 2: where K allows it (persists); 3: skinny_rows_kernel where it is ahead (skinny_takes_rows)
+  int persist;            // 1: workgroups walk over several tiles (grid = workgroups resident at once); 2: where K allows it (persists); 3: skinny_rows_kernel where it is ahead (skinny_takes_rows); 4: ksplit_ring_kernel, one
+                          // tile per workgroup
   // more than two slabs in LDS: microseconds a slab takes with one workgroup on a CU and with two (0: two do not
   // fit); t1 == 0 for all other kernels
   float t1, t2;
@@ -72,23 +72,6 @@ struct Config {
 // type 1 takes no other K.)
 inline bool persists(const Config& c, const gemm_desc_t& d) {
   return c.persist == 1 || (c.persist == 2 && d.K % c.bk == 0 && d.K >= 2 * c.bk);
-}
-
-// Ring configurations (tile, sub-slabs per slab) behind which ksplit_ring_kernel stands as well.
-constexpr bool has_ksplit(int bm, int bn, int ks) { return (bm == 64 && bn == 64 && ks == 2) || (bm == 32 && bn == 32 && ks == 4); }
-
-// Does such a plan run on it?  Both operands K-contiguous, 16-bit, with rows on 128-byte lines (a slab's rows of 128 bytes touch two
-// otherwise: 502x1838 the ring kernel is 5 % behind at K = 4224, 1034x210 9 to 25 % ahead at K = 10824), at most a tile per CU, and a K
-// long enough for the addition of eight sums.  Its time over the better ring kernel's of the same tile, drawn products, operands from HBM /
-// in the last-level cache: 32x32 tiles, three tile rows and more from K = 1216 0.89 to 1.00 / 0.76 to 0.96, fewer rows from K = 2368 0.91 to
-// 1.02 / 0.72 to 0.99 (below: up to 1.05); 64x64 tiles, four rows and columns of tiles and more from K = 1408 0.87 to 1.04 / 0.82 to 1.06; with fewer rows,
-// where HBM alone is the bound, up to 1.08.
-inline bool runs_ksplit(const Config& c, const gemm_desc_t& d, int cus) {
-  if (c.kind != KIND_MFMA || !c.launch[GEMM_BF16] || c.t1 == 0 || !has_ksplit(c.bm, c.bn, c.bk / 64) || (d.dtype_a != GEMM_BF16 && d.dtype_a != GEMM_F16)) return false;
-  const int64_t tm = (d.M + c.bm - 1) / c.bm, tn = (d.N + c.bn - 1) / c.bn;
-  if (tm * tn > cus || tm * tn * d.batch > cus || d.lda % 64 != 0 || d.ldb % 64 != 0) return false;
-  if (c.bm == 64) return tm >= 4 && tn >= 4 && d.K >= 1408;
-  return d.K >= (tm >= 3 ? 1216 : 2368);
 }
 
 inline int esize(int dt) { return dt == GEMM_F32 ? 4 : (dt == GEMM_F8E4M3 ? 1 : 2); }

@@ -12,4 +12,7 @@ MI355GEMM_RINGS16(X)
   MI355GEMM_RING_DEFINE(f16_t, f16_t, BM, BN, WM, WN, KS, NS, false, true)
 MI355GEMM_RINGS_T(X)
 #undef X
+#define X(BM, BN, W, NS, T1) MI355GEMM_KSPLIT_INST(, f16_t, BM, BN, W, NS)
+MI355GEMM_KSPLITS(X)
+#undef X
 }  // namespace mi355gemm

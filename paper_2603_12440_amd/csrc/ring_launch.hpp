@@ -8,15 +8,21 @@ namespace mi355gemm {
 
 template <typename T, typename TO, int BM, int BN, int WM, int WN, int KS, int NS, bool A_KF, bool B_KF>
 hipError_t launch_ring(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias, hipStream_t s) {
-  if constexpr (A_KF && B_KF && sizeof(T) == 2 && has_ksplit(BM, BN, KS)) {
-    if (runs_ksplit(*pl.cfg, pl.d, pl.cus)) {
-      ksplit_ring_kernel<T, BM, BN><<<pl.grid, pl.block, 0, s>>>(mfma16_args<BM, BN, false>(pl, A, B, C, bias));
-      return hipGetLastError();
-    }
-  }
   ring_gemm_kernel<T, TO, BM, BN, WM, WN, KS, NS, A_KF, B_KF><<<pl.grid, pl.block, 0, s>>>(mfma16_args<BM, BN, kEitherOrder<BM, BN, NS, false>>(pl, A, B, C, bias));
   return hipGetLastError();
 }
+
+// waves that split K (instantiated in ring_*_inst.hip): X(BM, BN, WAVES, NSTAGE, t1), t1 as below
+template <typename T, int BM, int BN, int WAVES, int NS>
+hipError_t launch_ksplit(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias, hipStream_t s) {
+  ksplit_ring_kernel<T, BM, BN, WAVES, NS><<<pl.grid, pl.block, 0, s>>>(mfma16_args<BM, BN, false>(pl, A, B, C, bias));
+  return hipGetLastError();
+}
+#define MI355GEMM_KSPLITS(X) \
+  X(64, 64, 8, 1, 0.235)     \
+  X(32, 32, 4, 4, 0.088)
+#define MI355GEMM_KSPLIT_INST(EXTERN, T, BM, BN, W, NS) \
+  EXTERN template hipError_t launch_ksplit<T, BM, BN, W, NS>(const gemm_plan&, const void*, const void*, void*, const void*, hipStream_t);
 
 // X(BM, BN, WM, WN, KS, NSTAGE, t1, t2): t1 and t2 are the microseconds a slab takes (KS * 128 bytes of each row)
 // with one workgroup on a CU and with two (0: two do not fit), as measured on 64 x 6144 x 4096 and its neighbours

@@ -1,4 +1,4 @@
-"""The kernel whose waves split K, behind the ring plans of 64x64 and 32x32 tiles: exact on small integers around whole turns of its eight
+"""The kernels whose waves split K, tiles of 64x64 and 32x32: exact on small integers around whole turns of the
 waves, K tails, ragged tiles, batches and the rule that chooses it; values that are not finite stay in their own outputs."""
 import pytest
 import torch
@@ -7,7 +7,7 @@ import workloads as wl
 from test_gpu_wide_tiles import run_exact
 
 pytestmark = pytest.mark.gpu
-C64, C32, K64x32 = "mfma16_64x64_k2_w2x4_s4", "mfma16_32x32_k4_w2x2_s3", "mfma16_64x32_k4_w4x2_s3"
+C64, C32, K64x32 = "ksplit16_64x64_w8_s1", "ksplit16_32x32_w4_s4", "mfma16_64x32_k4_w4x2_s3"
 
 
 @pytest.fixture(scope="module")
@@ -18,24 +18,20 @@ def g():
     return g
 
 
-def block(g, cfg, **kw):
-    p = g.gemm_create_config(g.GemmDesc(**kw), g.config_names().index(cfg))
-    info = p.info()
-    g.gemm_destroy(p)
-    return int(info.split("block=")[1].split()[0]), int(info.split("lds=")[1].split()[0])
+def test_built_in_choice(g):
+    def kernel(M, N, K, **kw):
+        p = g.gemm_create(g.GemmDesc(M, N, K, **kw))
+        info = p.info()
+        g.gemm_destroy(p)
+        return info
+    assert C32 in kernel(96, 512, 2048) and C32 in kernel(17, 512, 4096) and C64 in kernel(512, 2048, 8192)
+    for kw in (dict(M=96, N=512, K=1152), dict(M=17, N=512, K=2048), dict(M=96, N=512, K=2056), dict(M=4096, N=4096, K=2048)):
+        assert "ksplit16" not in kernel(**kw), kw
 
 
-def test_the_rule(g):
-    assert block(g, C32, M=96, N=512, K=1216) == (512, 65536) and block(g, C32, M=17, N=1024, K=2368) == (512, 65536)
-    for kw in (dict(M=96, N=512, K=1152), dict(M=64, N=1024, K=2304), dict(M=96, N=512, K=1224), dict(M=1024, N=512, K=2048), dict(M=96, N=512, K=2048, batch=6)):
-        assert block(g, C32, **kw)[0] == 256, kw
-    assert block(g, C32, M=96, N=512, K=2048, batch=5)[0] == 512
-    assert block(g, C64, M=256, N=256, K=1408)[1] == 131072
-
-
-# 22 to 25 slabs over eight waves, then whole turns and a long K; tails in rows on 128-byte lines (pad)
+# no slab, fewer slabs than waves, 22 to 25, then whole turns and a long K; tails in rows on 128-byte lines (pad)
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("K,pad", [(1408, 0), (1472, 64), (1536, 0), (1600, 0), (1416, 56), (1528, 8), (1544, 56), (2048, 0), (4096, 0)])
+@pytest.mark.parametrize("K,pad", [(8, 56), (64, 0), (200, 56), (576, 0), (1408, 0), (1472, 64), (1536, 0), (1600, 0), (1416, 56), (1528, 8), (1592, 0), (1544, 56), (2048, 0), (4096, 0)])
 def test_slabs_tails_and_edges(g, dtype, K, pad):
     for cfg, shapes in ((C64, [(200, 250), (256, 1024), (1001, 250)]), (C32, [(65, 100), (96, 96), (513, 320)]), (K64x32, [(33, 47), (128, 96)])):
         for M, N in shapes:
@@ -64,7 +60,6 @@ def test_values_that_are_not_finite(g, cfg, K, ld):
     want[M - 1, N - 1] = float("nan")
     C = torch.empty(M, N, device="cuda")
     p = g.gemm_create_config(g.GemmDesc(M, N, K, lda=ld, ldb=ld, dtype_c=g.F32), g.config_names().index(cfg))
-    assert "block=512" in p.info()
     g.gemm_run(p, A, B, C, None)
     torch.cuda.synchronize()
     g.gemm_destroy(p)
