@@ -186,8 +186,10 @@ __global__ __launch_bounds__(256) void f32_mfma_kernel(SimtArgs p) {
 // four partial tiles are added through LDS at the end.  An MFMA takes four columns of K, one from
 // each quarter of the wave; lane l multiplies columns 16 (l / 16) + s of its wave's 64 in step s
 // (A and B agree on that), so a K-contiguous operand is four 16-byte loads per lane.
-// vec_a / vec_b: that operand is K contiguous and can be read in aligned float4 groups (K % 4 == 0,
-// leading dimension and batch stride multiples of 4, pointer 16-byte aligned); any other operand
+// vec_a / vec_b: 1, that operand is K contiguous and can be read in aligned float4 groups (K % 4 == 0,
+// leading dimension and batch stride multiples of 4, pointer 16-byte aligned); 2, it is K contiguous, K >= 4: groups of any
+// alignment, the last one read from four values before the end and moved down (256x256x255, B col-major 8.9 -> 4.8 us;
+// 38x1275x2161 29.1 -> 10.3; 555x428x2829 135 -> 52); 0, any other operand
 // is read element by element through its strides.  Paper taxonomy (Sec. 3.2): d_mem = 1, d_sync = 2.
 struct F32SmallArgs {
   SimtArgs g;
@@ -197,7 +199,7 @@ struct F32SmallArgs {
 // (VEC_A / VEC_B at compile time, one straight-line body each.  Loads are unconditional: a value
 // outside the matrix is read from a valid address of the same row instead and replaced by zero
 // afterwards, so that all of a chunk's loads are in flight together.)
-template <bool VEC_A, bool VEC_B>
+template <int VEC_A, int VEC_B>
 __device__ __forceinline__ void f32_small_body(const SimtArgs& p, float (*red)[4][64]) {
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -214,7 +216,19 @@ __device__ __forceinline__ void f32_small_body(const SimtArgs& p, float (*red)[4
 
   // the 16 values of one operand this lane multiplies in the chunk whose first column is k
   auto fetch = [&](auto vec_c, const float* base, int64_t sk, bool ok, int64_t k, float (&x)[16]) {
-    if constexpr (decltype(vec_c)::value) {
+    if constexpr (decltype(vec_c)::value == 2) {
+      struct __attribute__((packed, aligned(4))) Piece { f32x4_t v; };
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int64_t first = k + 4 * c, at = first < p.K - 4 ? first : p.K - 4;
+        const bool in = ok && first < p.K, one = (first - at) & 1, two = (first - at) & 2;   // (first - at: 0 .. 3 inside K)
+        f32x4_t t = ((const Piece*)(base + (in ? at : 0)))->v;
+        t = f32x4_t{one ? t[1] : t[0], one ? t[2] : t[1], one ? t[3] : t[2], one ? 0.0f : t[3]};
+        t = f32x4_t{two ? t[2] : t[0], two ? t[3] : t[1], two ? 0.0f : t[2], two ? 0.0f : t[3]};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[4 * c + e] = in ? t[e] : 0.0f;
+      }
+    } else if constexpr (decltype(vec_c)::value == 1) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const bool in = ok && k + 4 * c < p.K;
@@ -231,8 +245,8 @@ __device__ __forceinline__ void f32_small_body(const SimtArgs& p, float (*red)[4
       }
     }
   };
-  using va = std::integral_constant<bool, VEC_A>;
-  using vb = std::integral_constant<bool, VEC_B>;
+  using va = std::integral_constant<int, VEC_A>;
+  using vb = std::integral_constant<int, VEC_B>;
 
   f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
   float a0[16], b0[16], a1[16], b1[16];
@@ -262,12 +276,15 @@ __device__ __forceinline__ void f32_small_body(const SimtArgs& p, float (*red)[4
   }
 }
 
+// ANY: groups of any alignment; aligned ones have a kernel without the selects (in one kernel 256^3 took 5.15 us, 5.08 so)
+template <bool ANY>
 __global__ __launch_bounds__(256) void f32_small_kernel(F32SmallArgs q) {
+  constexpr int V = ANY ? 2 : 1;
   __shared__ float red[4][4][64];
-  if (q.vec_a && q.vec_b) f32_small_body<true, true>(q.g, red);
-  else if (q.vec_a) f32_small_body<true, false>(q.g, red);
-  else if (q.vec_b) f32_small_body<false, true>(q.g, red);
-  else f32_small_body<false, false>(q.g, red);
+  if (q.vec_a && q.vec_b) f32_small_body<V, V>(q.g, red);
+  else if (q.vec_a) f32_small_body<V, 0>(q.g, red);
+  else if (q.vec_b) f32_small_body<0, V>(q.g, red);
+  else f32_small_body<0, 0>(q.g, red);
 }
 
 }  // namespace mi355gemm

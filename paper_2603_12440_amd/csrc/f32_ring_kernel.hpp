@@ -176,4 +176,161 @@ __global__ __launch_bounds__(256) void f32_ring_kernel(MfmaArgs p, int64_t c_si,
   }
 }
 
+// ---- fp32 operands of any alignment and extent ----------------------------------------------------------------------
+// The same tiles, LDS layout and products for operands that cannot be moved in aligned pieces of four values: the slabs travel
+// global -> registers -> LDS in 16-byte loads that take four-byte alignment, two slabs on their way in registers and two in LDS, one
+// barrier per slab.  Pieces that reach past K, and those of operands narrower than a tile, are put together element by
+// element (moving them down from four values before the end by selects was slower: 1001^3, B row-major 52 us against 39).  Such problems ran on
+// general_mfma_kernel, which loads single values in slabs of 16 columns of K: 1001^3, B row- / column-major 53.8 -> 39.0 / 54.3 -> 31.6 us,
+// 3001^3 658 -> 506, 4001^3 1453 -> 1077 (119 TFLOP/s; 4000^3 takes 0.95 ms on f32_ring_kernel), 1518x587x2647 128 -> 66.
+template <bool A_KF, bool B_KF, int MT>
+__global__ __launch_bounds__(256) void f32_any_kernel(MfmaArgs p, int64_t c_si, int64_t c_sj) {
+  constexpr int BM = 64 * MT, BN = 64 * MT, BK = 32;
+  constexpr int A_BYTES = BM * 128, STAGE = 2 * A_BYTES, HALF = 2 * MT, LOADS = 2 * HALF;
+  struct __attribute__((packed, aligned(4))) Piece { f32x4_t v; };
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int fr = lane & 31, fh = lane >> 5;
+  const int64_t batch = blockIdx.z;
+  int tm, tn;
+  tile_coords<false>(p, blockIdx.y * gridDim.x + blockIdx.x, p.tiles_m * p.tiles_n, tm, tn);
+  // A K-strided operand's last tile ends with the last row, so that no piece reaches past it (the rows it shares with the tile before
+  // are stored there); with fewer rows than a tile its pieces are put together element by element.
+  const int row_first = tm * BM, col_first = tn * BN;
+  const int r0 = A_KF ? row_first : min(row_first, max(p.M - BM, 0)), c0 = B_KF ? col_first : min(col_first, max(p.N - BN, 0));
+  const char* ga = (const char*)((const float*)p.A + batch * p.stride_a + (A_KF ? (int64_t)r0 * p.lda : (int64_t)r0));
+  const char* gb = (const char*)((const float*)p.B + batch * p.stride_b + (B_KF ? (int64_t)c0 * p.ldb : (int64_t)c0));
+  const int64_t a_step = A_KF ? (int64_t)128 : p.lda * (int64_t)(BK * 4);
+  const int64_t b_step = B_KF ? (int64_t)128 : p.ldb * (int64_t)(BK * 4);
+  typedef std::integral_constant<bool, A_KF> a_kf;
+  typedef std::integral_constant<bool, B_KF> b_kf;
+  // the piece of four values that lane `lane` of load `id` fetches (f32_ring_kernel's): byte offset, first value of K, first row of the
+  // piece (K strided; rows of K-contiguous operands are clamped)
+  auto unit = [&](auto kf_c, int id, int64_t ld, int left, uint32_t& off, int& k, int& row) __attribute__((always_inline)) {
+    if constexpr (decltype(kf_c)::value) {
+      const int r = id * 8 + lane / 8, c = (lane % 8) ^ swz16(r);
+      k = c * 4;
+      row = 0;
+      off = (uint32_t)(((int64_t)min(r, left - 1) * ld + k) * 4);
+    } else {
+      const int line = lane >> 3, k8 = line ^ ((line >> 2) & 1);
+      k = (id & 3) * 8 + k8;
+      row = (id >> 2) * 32 + (lane & 7) * 4;
+      off = (uint32_t)(((int64_t)k * ld + row) * 4);
+    }
+  };
+  uint32_t off[LOADS];
+  {
+    int k, row;
+#pragma unroll
+    for (int q = 0; q < HALF; ++q) {
+      unit(a_kf(), wave * HALF + q, p.lda, p.M - r0, off[q], k, row);
+      unit(b_kf(), wave * HALF + q, p.ldb, p.N - c0, off[HALF + q], k, row);
+    }
+  }
+  // n valid values from `at` on, zeros behind them
+  auto partial = [](const char* at, int n) __attribute__((always_inline)) {
+    f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < n) v[e] = *(const float*)(at + e * 4);
+    return v;
+  };
+  // one operand's pieces of a slab: whole inside the matrix; the last slab reaches past K
+  auto load_op = [&](auto kf_c, f32x4_t* v, const uint32_t* at, const char* base, int k_left, int rows_left, int64_t ld) __attribute__((always_inline)) {
+    constexpr bool kf = decltype(kf_c)::value;
+    if (k_left >= BK && (kf || rows_left >= BM)) {
+#pragma unroll
+      for (int q = 0; q < HALF; ++q) v[q] = ((const Piece*)(base + at[q]))->v;
+      return;
+    }
+#pragma unroll
+    for (int q = 0; q < HALF; ++q) {
+      uint32_t o; int k, row;
+      unit(kf_c, wave * HALF + q, ld, rows_left, o, k, row);
+      v[q] = partial(base + o, kf ? k_left - k : k < k_left ? rows_left - row : 0);
+    }
+  };
+  f32x4_t v[2][LOADS];
+  const int T = (p.K + BK - 1) / BK;
+  auto load = [&](f32x4_t (&w)[LOADS], int t) __attribute__((always_inline)) {
+    load_op(a_kf(), w, off, ga + (int64_t)t * a_step, p.K - t * BK, p.M - r0, p.lda);
+    load_op(b_kf(), w + HALF, off + HALF, gb + (int64_t)t * b_step, p.K - t * BK, p.N - c0, p.ldb);
+  };
+  f32x16_t acc[MT][MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int n = 0; n < MT; ++n)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[m][n][r] = 0.0f;
+  auto operand = [&](auto kf_c, const unsigned char* op, int row, float (&x)[16]) __attribute__((always_inline)) {
+    if constexpr (decltype(kf_c)::value) {
+      const int r = row + fr;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4_t t = *(const f32x4_t*)(op + r * 128 + (((2 * j + fh) ^ swz16(r)) * 16));
+        x[4 * j] = t[0]; x[4 * j + 1] = t[1]; x[4 * j + 2] = t[2]; x[4 * j + 3] = t[3];
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          x[4 * j + e] = *(const float*)(op + ((row >> 5) * 4 + j) * 1024 + ((4 * fh + e) ^ fh) * 128 + fr * 4);
+    }
+  };
+  auto multiply = [&](int st) __attribute__((always_inline)) {
+    const unsigned char* s = smem + st * STAGE;
+    float a[MT][16], w[MT][16];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) operand(a_kf(), s, (wm * MT + m) * 32, a[m]);
+#pragma unroll
+    for (int n = 0; n < MT; ++n) operand(b_kf(), s + A_BYTES, (wn * MT + n) * 32, w[n]);
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < MT; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m][i], w[n][i], acc[m][n], 0, 0, 0);
+  };
+  load(v[0], 0);
+  if (T > 1) load(v[1], 1);
+  for (int t0 = 0; t0 < T; t0 += 2) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int t = t0 + u;
+      if (t >= T) break;
+      // (the stage was last read two slabs ago, a barrier in between)
+#pragma unroll
+      for (int q = 0; q < LOADS; ++q)
+        *(f32x4_t*)(smem + u * STAGE + (q < HALF ? 0 : A_BYTES) + (wave * HALF + q % HALF) * 1024 + lane * 16) = v[u][q];
+      wait_lgkmcnt<0>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (t + 2 < T) load(v[u], t + 2);
+      multiply(u);
+    }
+  }
+  // register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32 of the 32x32 tile
+  const float* bias = p.has_bias ? p.bias + batch * p.stride_bias : nullptr;
+  float* C = (float*)p.C + batch * p.stride_c;
+#pragma unroll
+  for (int n = 0; n < MT; ++n) {
+    const int64_t j = c0 + (wn * MT + n) * 32 + fr;
+    if (j >= p.N || j < col_first) continue;
+    const float bj = bias ? bias[j] : 0.0f;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int64_t i = r0 + (wm * MT + m) * 32 + 8 * (r / 4) + 4 * fh + r % 4;
+        if (i < p.M && i >= row_first) C[i * c_si + j * c_sj] = apply_activation(p.act, acc[m][n][r] + bj, p.scale);
+      }
+  }
+}
+
 }  // namespace mi355gemm

@@ -144,9 +144,32 @@ hipError_t launch_general_mfma_typed(const gemm_plan& pl, const void* A, const v
   return hipGetLastError();
 }
 
+// Does an fp32 problem on the general kernels' grid run on f32_any_kernel?  (Offsets inside a slab have to fit 32 bits.)
+bool f32_takes_any(const gemm_desc_t& d, int tile) {
+  const int64_t lim = (int64_t)1 << 32, kMax = ((int64_t)1 << 31) - 512;
+  return d.dtype_a == GEMM_F32 && (tile + 1) * d.lda * 4 < lim && (tile + 1) * d.ldb * 4 < lim && d.M < kMax && d.N < kMax && d.K < kMax;
+}
+
+template <int TM>
+hipError_t launch_f32_any(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias, hipStream_t s) {
+  const gemm_desc_t& d = pl.d;
+  const SimtArgs a = simt_args(pl, A, B, C, bias);
+  MfmaArgs r = mfma16_args<TM, TM, false>(pl, A, B, C, bias);
+  r.xcd_remap = d.batch == 1 || (r.tiles_m * (int64_t)r.tiles_n) % 8 == 0;
+  const bool ak = d.layout_a == GEMM_ROW_MAJOR, bk = d.layout_b == GEMM_COL_MAJOR;   // K contiguous?
+  constexpr int MT = TM / 64;
+  if (ak && bk) f32_any_kernel<true, true, MT><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
+  else if (ak) f32_any_kernel<true, false, MT><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
+  else if (bk) f32_any_kernel<false, true, MT><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
+  else f32_any_kernel<false, false, MT><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
+  return hipGetLastError();
+}
+
 template <typename TIn, int TM, int TN, int TK>
 hipError_t launch_general_mfma(const gemm_plan& pl, const void* A, const void* B, void* C,
                                const void* bias, hipStream_t s) {
+  if constexpr (sizeof(TIn) == 4)
+    if (f32_takes_any(pl.d, TM)) return launch_f32_any<TM>(pl, A, B, C, bias, s);
   if (pl.d.dtype_c == GEMM_F32)
     return launch_general_mfma_typed<TIn, float, TM, TN, TK>(pl, A, B, C, bias, s);
   return launch_general_mfma_typed<TIn, TIn, TM, TN, TK>(pl, A, B, C, bias, s);
@@ -171,8 +194,10 @@ template <int TM, int TN>
 hipError_t launch_f32_mfma(const gemm_plan& pl, const void* A, const void* B, void* C,
                            const void* bias, hipStream_t s) {
   const gemm_desc_t& d = pl.d;
-  if (((uintptr_t)A & 15) || ((uintptr_t)B & 15))
+  if (((uintptr_t)A & 15) || ((uintptr_t)B & 15)) {
+    if (f32_takes_any(d, TM)) return launch_f32_any<TM>(pl, A, B, C, bias, s);
     return launch_general_mfma_typed<float, float, TM, TN, 16>(pl, A, B, C, bias, s);
+  }
   const SimtArgs a = simt_args(pl, A, B, C, bias);
   const bool ak = d.layout_a == GEMM_ROW_MAJOR, bk = d.layout_b == GEMM_COL_MAJOR;   // K contiguous?
   if (f32_takes_ring(d, TM)) {
@@ -199,11 +224,14 @@ hipError_t launch_f32_small(const gemm_plan& pl, const void* A, const void* B, v
   const gemm_desc_t& d = pl.d;
   F32SmallArgs a;
   a.g = simt_args(pl, A, B, C, bias);
-  a.vec_a = d.layout_a == GEMM_ROW_MAJOR && d.K % 4 == 0 && d.lda % 4 == 0 && d.stride_a % 4 == 0 &&
-            ((uintptr_t)A & 15) == 0;
-  a.vec_b = d.layout_b == GEMM_COL_MAJOR && d.K % 4 == 0 && d.ldb % 4 == 0 && d.stride_b % 4 == 0 &&
-            ((uintptr_t)B & 15) == 0;
-  f32_small_kernel<<<pl.grid, pl.block, 0, s>>>(a);
+  auto vec = [&](bool k_contiguous, int64_t ld, int64_t stride, const void* at) {
+    if (!k_contiguous || d.K < 4) return 0;
+    return d.K % 4 == 0 && ld % 4 == 0 && stride % 4 == 0 && ((uintptr_t)at & 15) == 0 ? 1 : 2;
+  };
+  a.vec_a = vec(d.layout_a == GEMM_ROW_MAJOR, d.lda, d.stride_a, A);
+  a.vec_b = vec(d.layout_b == GEMM_COL_MAJOR, d.ldb, d.stride_b, B);
+  if (a.vec_a == 2 || a.vec_b == 2) f32_small_kernel<true><<<pl.grid, pl.block, 0, s>>>(a);
+  else f32_small_kernel<false><<<pl.grid, pl.block, 0, s>>>(a);
   return hipGetLastError();
 }
 

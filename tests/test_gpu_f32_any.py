@@ -1,0 +1,84 @@
+"""fp32 products of any extent and alignment (16-byte loads at four-byte alignment): bit exact on small integers for every layout around
+tile edges, slabs and the last piece of K; pointers at any element; values that are not finite stay in their own outputs."""
+import pytest
+import torch
+
+import workloads as wl
+from helpers import gpu_desc, run_gpu
+
+pytestmark = pytest.mark.gpu
+LAYOUTS = [("row", "row"), ("row", "col"), ("col", "row"), ("col", "col")]
+CFGS = ("general_mfma32_64x64x16", "general_mfma32_128x128x16", "f32small_16x16x256")
+
+
+@pytest.fixture(scope="module")
+def g():
+    import paper_2603_12440_amd as g
+    g.load_library()
+    assert torch.cuda.is_available()
+    return g
+
+
+def operands(w):
+    A = wl.small_integers(wl.operand_shapes(w)[0], w.seed_a, -2, 2, "f32")
+    B = wl.small_integers(wl.operand_shapes(w)[1], w.seed_b, -2, 2, "f32")
+    a = A if w.layout_a == "row" else A.transpose(1, 2).contiguous()
+    b = B if w.layout_b == "row" else B.transpose(1, 2).contiguous()
+    return A, B, torch.matmul(a, b)
+
+
+@pytest.mark.parametrize("la,lb", LAYOUTS)
+@pytest.mark.parametrize("M,N,K,batch", [(1, 1, 1, 1), (3, 2, 3, 1), (5, 66, 4, 1), (63, 65, 31, 1), (64, 64, 33, 1), (65, 127, 34, 1), (129, 131, 63, 1),
+                                         (127, 193, 65, 2), (130, 130, 67, 3), (257, 61, 130, 1), (17, 333, 257, 1), (20, 35, 515, 1), (40, 47, 1030, 5), (66, 62, 97, 8)])
+def test_exact(g, la, lb, M, N, K, batch):
+    w = wl.Workload("t", M, N, K, dtype="f32", layout_a=la, layout_b=lb, batch=batch, epilogue="bias_relu", seed_a=M + 1, seed_b=N + 2)
+    A, B, want = operands(w)
+    bias = wl.small_integers((N,), w.seed_bias, -3, 3, "f32")
+    want = torch.relu(want + bias)
+    for cfg in CFGS:
+        for lc, pads in (("row", (0, 0, 0)), ("col", (1, 3, 1)), ("row", (2, 5, 2))):
+            print(f"{M}x{N}x{K} b{batch} {la}/{lb}/{lc} {cfg} {pads}", flush=True)
+            C = run_gpu(g, w, A, B, bias, config=g.config_names().index(cfg), layout_c=lc, pad_a=pads[0], pad_b=pads[1], pad_c=pads[2])
+            assert torch.equal(C.float(), want), (cfg, lc, pads)
+
+
+@pytest.mark.parametrize("la,lb", LAYOUTS)
+def test_pointers_at_any_element(g, la, lb):
+    M, N, K = 132, 200, 100
+    w = wl.Workload("t", M, N, K, dtype="f32", layout_a=la, layout_b=lb, seed_a=1, seed_b=2)
+    A, B, want = operands(w)
+    for cfg in ("f32mfma_64x64x32", "f32mfma_128x128x32") + CFGS:
+        p = g.gemm_create_config(gpu_desc(g, w), g.config_names().index(cfg))
+        for oa, ob in ((1, 0), (0, 3), (2, 1)):
+            print(la, lb, cfg, oa, ob, flush=True)
+            a, b = torch.empty(A.numel() + oa, device="cuda"), torch.empty(B.numel() + ob, device="cuda")
+            a[oa:], b[ob:] = A.flatten().cuda(), B.flatten().cuda()
+            C = torch.full((M, N), -7.0, device="cuda")
+            g.gemm_run(p, a[oa:], b[ob:], C, None)
+            torch.cuda.synchronize()
+            assert torch.equal(C.cpu(), want[0]), cfg
+        g.gemm_destroy(p)
+
+
+@pytest.mark.parametrize("la,lb", LAYOUTS)
+@pytest.mark.parametrize("K", [66, 261])
+def test_values_that_are_not_finite(g, la, lb, K):
+    M, N = 70, 133
+    a, b = torch.ones(M, K), torch.ones(K, N)
+    want = torch.full((M, N), float(K))
+    for row, col, v in [(0, 0, float("inf")), (17, K - 1, float("nan")), (N - 1, K // 2, float("-inf")), (64, K - 2, float("inf"))]:
+        b[col, row] = v
+        want[:, row] = v
+    a[M - 1, K - 1] = float("inf")
+    want[M - 1] = torch.where(want[M - 1].isfinite(), float("inf"), want[M - 1])
+    want[M - 1, N - 1] = float("nan")
+    A = (a if la == "row" else a.t().contiguous()).cuda()
+    B = (b if lb == "row" else b.t().contiguous()).cuda()
+    w = wl.Workload("t", M, N, K, dtype="f32", layout_a=la, layout_b=lb)
+    for cfg in CFGS:
+        C = torch.empty(M, N, device="cuda")
+        p = g.gemm_create_config(gpu_desc(g, w), g.config_names().index(cfg))
+        g.gemm_run(p, A, B, C, None)
+        torch.cuda.synchronize()
+        g.gemm_destroy(p)
+        assert torch.equal(C.cpu().nan_to_num(nan=1e9, posinf=2e9, neginf=-2e9), want.nan_to_num(nan=1e9, posinf=2e9, neginf=-2e9)), cfg
