@@ -643,6 +643,7 @@ bool applicable(const Config& c, const gemm_desc_t& d) {
       (int64_t)c.bn * d.ldb * esize(d.dtype_a) >= ((int64_t)1 << 32))
     return false;
   if (c.persist == 1 && (d.K % c.bk != 0 || d.K < 2 * c.bk)) return false;   // whole slabs, at least two
+  if (c.persist == 4 && (d.lda % 64 != 0 || d.ldb % 64 != 0)) return false;  // rows on 128-byte lines (weighs_ksplit)
   const int64_t tiles = ((d.M + c.bm - 1) / c.bm) * ((d.N + c.bn - 1) / c.bn);
   return (persists(c, d) || c.t1 > 0 ? tiles * d.batch : tiles) < ((int64_t)1 << 31);
 }
@@ -757,15 +758,15 @@ double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
   return tiled ? with_memory(work, d, N) : work;               // (those are weighed against tile_cost's)
 }
 
-// Where the built-in choice weighs the kernels whose waves split K: rows on 128-byte lines (a slab's rows of 128 bytes touch two
-// otherwise: 502x1838, K = 4224 5 % ahead of the ring kernel, 1034x210, K = 10824 9 to 25 % behind), at most a tile per CU, and a K long
+// Where the built-in choice weighs the kernels whose waves split K, which take rows on 128-byte lines only (a slab's rows of 128 bytes
+// touch two otherwise: 502x1838, K = 4224 5 % ahead of the ring kernel, 1034x210, K = 10824 9 to 25 % behind): at most a tile per CU, and a K long
 // enough for the addition of the waves' sums.  Time over the better ring kernel's of the same tile, drawn products, operands from HBM / in the
 // last-level cache: 32x32 tiles, three tile rows and more from K = 1216 0.89 to 1.00 / 0.76 to 0.96, fewer rows from K = 2368 0.91 to 1.02 / 0.72 to
 // 0.99 (below: up to 1.05); 64x64 tiles, four rows and columns of tiles and more from K = 1408 0.87 to 1.04 / 0.82 to 1.06; with fewer rows, where HBM
 // alone is the bound, up to 1.08.
 bool weighs_ksplit(const Config& c, const gemm_desc_t& d) {
   const int64_t tm = (d.M + c.bm - 1) / c.bm, tn = (d.N + c.bn - 1) / c.bn;
-  if (tm * tn > num_cus() || tm * tn * d.batch > num_cus() || d.lda % 64 != 0 || d.ldb % 64 != 0) return false;
+  if (tm * tn > num_cus() || tm * tn * d.batch > num_cus()) return false;
   return c.bm == 64 ? tm >= 4 && tn >= 4 && d.K >= 1408 : d.K >= (tm >= 3 ? 1216 : 2368);
 }
 
