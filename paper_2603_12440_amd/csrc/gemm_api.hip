@@ -817,6 +817,7 @@ int64_t split_columns(const gemm_desc_t& d, int big, double single_cost) {
 int choose_general(const gemm_desc_t& d) {
   //   * fp32, at most four 16x16 tiles per CU: 16x16 tiles with K split over the waves of a workgroup
   //     (256^3: 5 us against 11 us for the next choice; 512^3: 11 to 12 against 19 us);
+  //   * fp32, up to eight 16x16 tiles per CU: those or one 64x64 tile per CU, by an estimate;
   //   * very few 32x32 tiles (16-bit operands in layouts the tiled kernels do not take): the vector-ALU
   //     kernel with 32x32 tiles and the long K step;
   //   * fp32 in float4 groups: the fp32-MFMA kernels with slabs straight to LDS, 128x128 tiles from four
@@ -829,7 +830,20 @@ int choose_general(const gemm_desc_t& d) {
     const int i = find_config("f32small_16x16x256");
     if (i >= 0 && applicable(kConfigs[i], d)) return i;
   }
-  if (tiles32 <= 2.0 * num_cus()) return find_config("simt_32x32x64");
+  if (tiles32 <= 2.0 * num_cus()) {
+    // fp32: up to a 64x64 tile per CU, whose time is that of one tile, against the 16x16 tiles' turns.  Microseconds fitted to 50 drawn
+    // products with 100 to 700 32x32 tiles (1079x467x529: 21.8 on 64x64 tiles, 33 on 16x16 ones, 29 on the vector-ALU kernel that such
+    // products ran on; 2456x110x2930 96, 71 and 122); the rule's choice is 2 % from the better of the two on average.
+    const int small = find_config("f32small_16x16x256"), aligned = find_config("f32mfma_64x64x32");
+    if (d.dtype_a == GEMM_F32 && f32_takes_any(d, 64) && small >= 0 && applicable(kConfigs[small], d)) {
+      const bool k_contiguous = d.layout_b == GEMM_COL_MAJOR, pieces = applicable(kConfigs[aligned], d);
+      const double K = (double)d.K, turns = (double)((d.M + 15) / 16) * (double)((d.N + 15) / 16) * d.batch / num_cus();
+      const double t16 = turns * (1.2 + (k_contiguous ? 0.0035 : 0.0045) * K);
+      const double t64 = 1.0 + (pieces ? (k_contiguous ? 0.0225 : 0.0205) : (k_contiguous ? 0.0262 : 0.033)) * K;
+      return t16 < t64 ? small : pieces ? aligned : find_config("general_mfma32_64x64x16");
+    }
+    return find_config("simt_32x32x64");
+  }
   {                                             // fp32 in float4 groups: 128x128 tiles from four per CU on
     const int i = find_config(tiles128 >= 4.0 * num_cus() ? "f32mfma_128x128x32" : "f32mfma_64x64x32");
     if (i >= 0 && applicable(kConfigs[i], d)) return i;
