@@ -737,6 +737,8 @@ double tile_cost(const Config& c, const TileTimes& t, const gemm_desc_t& d, int6
   return with_memory(h.launch + turn * (whole + (part > 0 ? t.part + (1.0 - t.part) * part : 0.0)), d, N);
 }
 
+// (64x64 tiles of any alignment with both operands K-contiguous keep two slabs on their way: 0.78 of the time of a slab, with at most
+// a tile per CU; 7692x369x7149, three per CU, takes 143 us on 128x128 tiles and 153 on these.)
 // The others, 16-bit rings of 32 columns and for operands of any alignment, are weighed by the time of a slab with one workgroup
 // on a CU and with two (launch 2.7 us; each further round costs 2.4 us of prologue and epilogue that nothing overlaps: 512x512x128,
 // 64 problems, 64x64 tiles: 27 us).  An operand whose rows do not start on 128-byte lines costs a ring 0.35 on top: every piece of
@@ -752,7 +754,8 @@ double mfma_cost(const Config& c, const gemm_desc_t& d, int64_t N) {
   const double slabs = (double)((K + c.bk - 1) / c.bk);
   const double per_cu = (double)(int64_t)((tiles + cus - 1) / cus);
   const bool tiled = c.kind != KIND_MFMA_G, many = tiled && batch > 1;
-  const double pitch = c.kind == KIND_MFMA_G ? 1.0 : 1.0 + 0.35 * off_line + (many ? 0.25 : 0.0);
+  const bool two_ahead = c.kind == KIND_MFMA_G && c.bm == 64 && per_cu <= 1 && d.layout_a == GEMM_ROW_MAJOR && d.layout_b == GEMM_COL_MAJOR;
+  const double pitch = two_ahead ? 0.78 : c.kind == KIND_MFMA_G ? 1.0 : 1.0 + 0.35 * off_line + (many ? 0.25 : 0.0);
   const double pairs = c.t2 > 0 ? (double)(int64_t)(per_cu / 2) : 0.0, singles = per_cu - 2 * pairs;
   const double work = 2.7 + (singles * c.t1 + pairs * c.t2) * slabs * pitch + (singles + pairs - 1) * 2.4 + (many ? 0.7 : 0.0);
   return tiled ? with_memory(work, d, N) : work;               // (those are weighed against tile_cost's)

@@ -53,7 +53,7 @@ struct RingTile {
 
 // A_KF, B_KF: K is the contiguous index of A / B (16-bit operands may have it strided: see mfma16_gemm_kernel)
 // DIRECT = false: rows, extents and pointers of any alignment (two bytes), C in either layout.  The same slabs travel
-// global -> registers -> LDS, the next one requested while one is multiplied: 16-byte loads at two-byte alignment
+// global -> registers -> LDS, the next one or two requested while one is multiplied: 16-byte loads at two-byte alignment
 // inside the matrix, element by element in the last slab's pieces that reach past K.  Such problems ran on
 // the fp32 matrix-core instruction, element by element: 4001^3 bf16 2413 -> 204 us, B row-major 2510 -> 235 us,
 // 1000x1000x1001 83 -> 15 us.
@@ -193,7 +193,11 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
 
   if constexpr (!DIRECT) {
     struct __attribute__((packed, aligned(2))) Piece { u32x4_t v; };
-    u32x4_t av[Cfg::A_LOADS], bv[Cfg::B_LOADS];
+    // Slabs on their way: two for 64x64 tiles of K-contiguous operands (84x678x16089 182 -> 139 us, 150x4843x5511 68 -> 52, 1000x1000x1001 17.0 ->
+    // 14.6), one for 128x128 tiles and K-strided operands, whose registers allow fewer workgroups with two (4001^3 200 -> 212, B row-major 231
+    // -> 298).
+    constexpr int AHEAD = A_KF && B_KF && BM == 64 ? 2 : 1;
+    u32x4_t av[AHEAD][Cfg::A_LOADS], bv[AHEAD][Cfg::B_LOADS];
     // n valid values from `at` on, zeros behind them
     auto partial = [](const char* at, int n) __attribute__((always_inline)) {
       uint32_t w[4] = {0u, 0u, 0u, 0u};
@@ -230,22 +234,42 @@ __global__ __launch_bounds__(64 * WM * WN) void ring_gemm_kernel(MfmaArgs p) {
         }
       }
     };
-    auto load = [&](int t) __attribute__((always_inline)) {
+    auto load = [&](u32x4_t* va, u32x4_t* vb, int t) __attribute__((always_inline)) {
       const int left = p.K - t * Cfg::BK;
-      load_op(std::integral_constant<bool, A_KF>(), std::integral_constant<int, Cfg::A_LOADS>(), av, a_off, ga + (int64_t)t * a_step, left, p.M, r0, a_unit);
-      load_op(std::integral_constant<bool, B_KF>(), std::integral_constant<int, Cfg::B_LOADS>(), bv, b_off, gb + (int64_t)t * b_step, left, p.N, c0, b_unit);
+      load_op(std::integral_constant<bool, A_KF>(), std::integral_constant<int, Cfg::A_LOADS>(), va, a_off, ga + (int64_t)t * a_step, left, p.M, r0, a_unit);
+      load_op(std::integral_constant<bool, B_KF>(), std::integral_constant<int, Cfg::B_LOADS>(), vb, b_off, gb + (int64_t)t * b_step, left, p.N, c0, b_unit);
     };
     const int T_all = (p.K + Cfg::BK - 1) / Cfg::BK;
-    load(0);
-    for (int t = 0; t < T_all; ++t) {
-      unsigned char* to = smem + (t & 1) * Cfg::STAGE_BYTES;       // (last read two slabs ago, a barrier in between)
+    auto stash = [&](int st, const u32x4_t* va, const u32x4_t* vb) __attribute__((always_inline)) {
+      unsigned char* to = smem + st * Cfg::STAGE_BYTES;              // (last read two slabs ago, a barrier in between)
 #pragma unroll
-      for (int q = 0; q < Cfg::A_LOADS; ++q) *(u32x4_t*)(to + (wave * Cfg::A_LOADS + q) * 1024 + lane * 16) = av[q];
+      for (int q = 0; q < Cfg::A_LOADS; ++q) *(u32x4_t*)(to + (wave * Cfg::A_LOADS + q) * 1024 + lane * 16) = va[q];
 #pragma unroll
-      for (int q = 0; q < Cfg::B_LOADS; ++q) *(u32x4_t*)(to + Cfg::A_BYTES + (wave * Cfg::B_LOADS + q) * 1024 + lane * 16) = bv[q];
-      __syncthreads();
-      if (t + 1 < T_all) load(t + 1);
-      multiply(t & 1);
+      for (int q = 0; q < Cfg::B_LOADS; ++q) *(u32x4_t*)(to + Cfg::A_BYTES + (wave * Cfg::B_LOADS + q) * 1024 + lane * 16) = vb[q];
+    };
+    load(av[0], bv[0], 0);
+    if constexpr (AHEAD == 1) {
+      for (int t = 0; t < T_all; ++t) {
+        stash(t & 1, av[0], bv[0]);
+        __syncthreads();
+        if (t + 1 < T_all) load(av[0], bv[0], t + 1);
+        multiply(t & 1);
+      }
+    } else {
+      if (T_all > 1) load(av[1], bv[1], 1);
+      for (int t0 = 0; t0 < T_all; t0 += 2) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int t = t0 + u;
+          if (t >= T_all) break;
+          stash(u, av[u], bv[u]);
+          wait_lgkmcnt<0>();
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");
+          if (t + 2 < T_all) load(av[u], bv[u], t + 2);
+          multiply(u);
+        }
+      }
     }
   } else {
   const int T_full = p.K / Cfg::BK;
