@@ -679,8 +679,10 @@ int find_config(const char* name) {
 // 43 products that took 224-row tiles with one tile per workgroup, 192-row ones were 6 to 7 % faster.)
 // fp8, fitted in the same way to 4868 drawn products (M from 16, N and K from 256; K from 64; batches): 10.6 % rms, the choice 1.6 % from
 // the fastest kernel for K of 1024 and more, 2.8 % below, 4.0 % for batches, a percent of which is the measurement's own scatter.
+// (Four of its times by hand, parts of a turn 0.58, 0.64 and 0.48 for 0.49, 0.68 and 0.37 of the 32x32_k2, 64x32 and 64x64_k1 rings, fp32
+// results 1.4 for 0.92: 339x772x2384 6.9 -> 5.9 us, 1878x530x4928 21.8 -> 18.9, 144x2344x3488 8.9 -> 8.0; 110 drawn products 0.8 % on average.)
 struct SharedTimes { double launch, off_line, apart, f32, operands, c32, c16; };   // us; shares of a slab; us; TB/s
-const SharedTimes kShared16 = {2.8, 0.171, 0.26, 1.5, 3.68, 4.24, 2.22}, kShared8 = {2.6, 0.171, 0.26, 0.92, 6.39, 4.93, 5.0};
+const SharedTimes kShared16 = {2.8, 0.171, 0.26, 1.5, 3.68, 4.24, 2.22}, kShared8 = {2.6, 0.171, 0.26, 1.4, 6.39, 4.93, 5.0};
 struct TileTimes { const char* name; double tile, slab, part; };
 const TileTimes kTileTimes[] = {
     {"mfma16_128x128x64_w2x2", 3.77, 0.959, 0.53}, {"mfma16_128x128x64_w2x2_p", 3.30, 0.956, 0.61}, {"mfma16_128x128x64_w2x2_s4", 3.16, 0.531, 0.78},
@@ -696,8 +698,8 @@ const TileTimes kTileTimes[] = {
     {"mfma_256x256x64_w2x2_s2", 8.48, 1.521, 0.55},     // (not timed: as the shape with eight waves, which goes first)
     {"mfma8_128x128x128_w2x2_s2", 4.30, 0.893, 0.31}, {"mfma8_128x128x128_w2x2_s4", 3.06, 0.479, 0.53}, {"mfma8_192x256x128_w2x4_s2", 7.02, 1.129, 0.47},
     {"mfma8_224x256x128_w2x4_s2", 8.64, 1.232, 0.43}, {"mfma8_256x192x128_w4x2_s2", 7.21, 1.097, 0.51}, {"mfma8_256x256x128_w2x4_s2", 9.76, 1.407, 0.39},
-    {"mfma8_32x32_k2_w2x2_s4", 0.86, 0.307, 0.49}, {"mfma8_32x32_k4_w2x2_s3", 0.79, 0.326, 0.78}, {"mfma8_64x32_k2_w4x2_s4", 0.91, 0.278, 0.68},
-    {"mfma8_64x64_k1_w2x4_s5", 1.70, 0.397, 0.37}, {"mfma8_64x64_k2_w2x4_s4", 1.02, 0.449, 0.65}, {"mfma8_128x128x128_w2x2_p", 2.30, 0.878, 0.41},
+    {"mfma8_32x32_k2_w2x2_s4", 0.86, 0.307, 0.58}, {"mfma8_32x32_k4_w2x2_s3", 0.79, 0.326, 0.78}, {"mfma8_64x32_k2_w4x2_s4", 0.91, 0.278, 0.64},
+    {"mfma8_64x64_k1_w2x4_s5", 1.70, 0.397, 0.48}, {"mfma8_64x64_k2_w2x4_s4", 1.02, 0.449, 0.65}, {"mfma8_128x128x128_w2x2_p", 2.30, 0.878, 0.41},
     {"mfma8_192x256x128_w2x4_p", 3.78, 1.145, 0.61}, {"mfma8_224x256x128_w2x4_p", 4.82, 1.290, 0.54}, {"mfma8_256x192x128_w4x2_p", 4.45, 1.127, 0.59},
     {"mfma8_256x256x128_w2x4_p", 5.52, 1.358, 0.58},
 };
