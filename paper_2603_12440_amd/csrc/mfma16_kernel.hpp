@@ -645,18 +645,14 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     typedef f32x4_t __attribute__((aligned(4))) f32x4_any_t;
     constexpr int OROWB = Cfg::WTN * 2;           // bytes per 16-bit row of the wave's block (128 or 256)
     constexpr int CH = OROWB / 16;
-    constexpr int OROWB32 = Cfg::WTN * 4;         // bytes per fp32 row (256 or 512)
-    constexpr int CH32 = OROWB32 / 16;
     constexpr int kShare = Cfg::LDS_BYTES / Cfg::kWaves;
-    static_assert(16 * OROWB32 <= kShare, "one 16-row band of the wave block in fp32 must fit the wave's share of LDS");
     static_assert(OROWB == 128 || OROWB == 192 || OROWB == 256, "staging rows of 128, 192 or 256 bytes");
     static_assert(2 * 16 * OROWB <= (PERSIST ? Cfg::EPI_BYTES / Cfg::kWaves : kShare), "two 16-bit bands per wave");
     // staging: this wave's share of the idle slab stages, or of the separate area of a persistent workgroup
     unsigned char* wt = PERSIST ? smem + Cfg::LDS_BYTES + wave * (Cfg::EPI_BYTES / Cfg::kWaves) : smem + wave * kShare;
     // chunk-slot key of staging row r: 128-byte rows alternate between the two halves of the banks, 192-byte rows
-    // start at each quarter in turn, 256-byte rows all start at bank 0; within groups of 4 (8 in fp32) chunks where a row is no power of two
+    // start at each quarter in turn, 256-byte rows all start at bank 0; within groups of 4 chunks where a row is no power of two
     auto osw = [](int r) __attribute__((always_inline)) { return OROWB == 128 ? ((r >> 1) & 7) : OROWB == 192 ? (r >> 2) & 3 : (r & 15); };
-    constexpr int kKey32 = OROWB == 192 ? 7 : 15;
 
     // 16-bit through LDS, pipelined over the 16-row bands of the wave block with two staging
     // buffers: while the rows of band m-1 come back from LDS, the values of band m+1 are computed;
@@ -747,11 +743,98 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
       read((MT - 1) & 1);
       store(MT - 1);
     };
-    // fp32 through LDS, one band at a time (one staging buffer: a band is twice the bytes)
-    auto drain32_all = [&](auto actf) __attribute__((always_inline)) {
+    // fp32 through LDS.  128x128 tiles: half a band at a time (16 rows of half the wave's columns, as many bytes as a 16-bit band),
+    // pipelined like those.  What bounds them at a short K is latency: one band at a time, write, wait, read and store in series,
+    // 429x6795x256 with fp8 operands took 10.0 us, 9.4 so (bf16 11.9, 11.2), 4096x4096x512 25.6, 23.7; 3357 drawn fp8 and 4396 bf16 products with
+    // K up to 2048 0.967.  The larger tiles: as many whole bands at a time as the staging area holds, 0.98; in halves, whose stores are
+    // one line, products with 30 million and more results whose rows start off lines took up to 1.02, bands on 128x128 tiles 0.975.
+    // Straight from the accumulators, 64 bytes of a row per store: 0.95 with few tiles, up to 1.24 where C is most of the work.
+    auto put = [&](f32x4_any_t* c, const f32x4_t& v) __attribute__((always_inline)) {
+      if (pe.c_cached) *c = v;                     // split-K partials are read by the next kernel
+      else __builtin_nontemporal_store(v, c);
+    };
+    auto drain32_halves = [&](auto actf) __attribute__((always_inline)) {
+      static_assert(NT % 2 == 0, "half bands of whole fragments");
+      constexpr int NH = NT / 2;
       float* Cf = (float*)pe.C + (int64_t)batch * pe.stride_c;
       const int slane = fresh_lane();
-      constexpr int kIt32 = 16 * CH32 / 64;
+      f32x4_t w[NH];
+      f32x4_t val[kIt16];
+      float bvs[NT][4];                           // the bias of this lane's columns, the same for every band
+#pragma unroll
+      for (int n = 0; n < NT; ++n) bias4(col0 + wn * Cfg::WTN + n * 16 + eq * 4, bvs[n]);
+      auto values = [&](auto h_c) __attribute__((always_inline)) {
+        constexpr int m = decltype(h_c)::value / 2, n0 = decltype(h_c)::value % 2 * NH;
+#pragma unroll
+        for (int n = 0; n < NH; ++n)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) w[n][e] = actf(acc[m][n0 + n][e] + bvs[n0 + n][e]);
+      };
+      auto write = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n = 0; n < NH; ++n) *(f32x4_t*)(wt + buf * kBand16 + er * OROWB + (((n * 4 + eq) ^ osw(er)) * 16)) = w[n];
+      };
+      auto read = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int it = 0; it < kIt16; ++it) {
+          const int e = it * 64 + slane;
+          const int r = e / CH, q = e % CH;
+          val[it] = *(const f32x4_t*)(wt + buf * kBand16 + r * OROWB + ((q ^ osw(r)) * 16));
+        }
+      };
+      const bool inside = row0 + BM <= pe.M && col0 + BN <= pe.N && (int64_t)BM * pe.ldc * 4 < ((int64_t)1 << 31);
+      char* const wave_c = (char*)(Cf + (int64_t)(row0 + wm * Cfg::WTM) * pe.ldc + col0 + wn * Cfg::WTN);
+      const uint32_t band_step = (uint32_t)(16 * pe.ldc * 4);
+      uint32_t lane_off[kIt16];
+#pragma unroll
+      for (int it = 0; it < kIt16; ++it) {
+        const int e = it * 64 + slane;
+        lane_off[it] = (uint32_t)((e / CH) * (int)pe.ldc * 4 + (e % CH) * 16);
+      }
+      auto store = [&](int h) __attribute__((always_inline)) {
+#pragma unroll
+        for (int it = 0; it < kIt16; ++it) {
+          if (inside) {
+            put((f32x4_any_t*)(wave_c + (lane_off[it] + (uint32_t)(h / 2) * band_step + (h % 2) * OROWB)), val[it]);
+            continue;
+          }
+          const int e = it * 64 + slane;
+          const int r = e / CH, q = e % CH;
+          const int i = row0 + wm * Cfg::WTM + h / 2 * 16 + r;
+          const int j = col0 + wn * Cfg::WTN + h % 2 * (NH * 16) + q * 4;
+          if (i < pe.M && j < pe.N) {
+            float* c = Cf + (int64_t)i * pe.ldc + j;
+            if (j + 4 <= pe.N) {
+              put((f32x4_any_t*)c, val[it]);
+            } else {
+#pragma unroll
+              for (int t2 = 0; t2 < 4; ++t2)
+                if (j + t2 < pe.N) c[t2] = val[it][t2];
+            }
+          }
+        }
+      };
+      values(std::integral_constant<int, 0>());
+      static_for<0, 2 * MT>([&](auto h_c) __attribute__((always_inline)) {
+        constexpr int h = decltype(h_c)::value;
+        write(h & 1);
+        if constexpr (h > 0) read((h - 1) & 1);
+        if constexpr (h + 1 < 2 * MT) values(std::integral_constant<int, h + 1>());
+        if constexpr (h > 0) store(h - 1);
+      });
+      read(1);
+      store(2 * MT - 1);
+    };
+    auto drain32_bands = [&](auto actf) __attribute__((always_inline)) {
+      float* Cf = (float*)pe.C + (int64_t)batch * pe.stride_c;
+      const int slane = fresh_lane();
+      constexpr int OROWB32 = Cfg::WTN * 4, CH32 = OROWB32 / 16, kKey32 = OROWB == 192 ? 7 : 15;   // bytes and pieces per fp32 row; chunk-slot key
+      constexpr int kIt32 = 16 * CH32 / 64, kBand32 = 16 * OROWB32;
+      constexpr int kStaging = PERSIST ? Cfg::EPI_BYTES / Cfg::kWaves : kShare, kHeld = kStaging / kBand32 < MT ? kStaging / kBand32 : MT;
+      static_assert(kStaging >= kBand32, "one 16-row band of the wave block in fp32 must fit the wave's staging area");
+      float bvs[NT][4];
+#pragma unroll
+      for (int n = 0; n < NT; ++n) bias4(col0 + wn * Cfg::WTN + n * 16 + eq * 4, bvs[n]);
       const bool inside = row0 + BM <= pe.M && col0 + BN <= pe.N && (int64_t)BM * pe.ldc * 4 < ((int64_t)1 << 31);
       char* const wave_c = (char*)(Cf + (int64_t)(row0 + wm * Cfg::WTM) * pe.ldc + col0 + wn * Cfg::WTN);
       const uint32_t band_step = (uint32_t)(16 * pe.ldc * 4);
@@ -761,48 +844,56 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
         const int e = it * 64 + slane;
         lane_off[it] = (uint32_t)((e / CH32) * (int)pe.ldc * 4 + (e % CH32) * 16);
       }
-      static_for<0, MT>([&](auto m_c) __attribute__((always_inline)) {
-        constexpr int m = decltype(m_c)::value;
+      static_for<0, (MT + kHeld - 1) / kHeld>([&](auto p_c) __attribute__((always_inline)) {
+        constexpr int m0 = decltype(p_c)::value * kHeld, m1 = m0 + kHeld < MT ? m0 + kHeld : MT;
+        static_for<m0, m1>([&](auto m_c) __attribute__((always_inline)) {
+          constexpr int m = decltype(m_c)::value;
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-          float bv[4];
-          bias4(col0 + wn * Cfg::WTN + n * 16 + eq * 4, bv);
-          f32x4_t w;
+          for (int n = 0; n < NT; ++n) {
+            f32x4_t w;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) w[e] = actf(acc[m][n][e] + bv[e]);
-          const int q = n * 4 + eq;
-          *(f32x4_t*)(wt + er * OROWB32 + ((q ^ (er & kKey32)) * 16)) = w;
-        }
-#pragma unroll
-        for (int it = 0; it < kIt32; ++it) {
-          const int e = it * 64 + slane;
-          const int r = e / CH32, q = e % CH32;
-          const f32x4_t val = *(const f32x4_t*)(wt + r * OROWB32 + ((q ^ (r & kKey32)) * 16));
-          if (inside) {
-            f32x4_any_t* c = (f32x4_any_t*)(wave_c + (lane_off[it] + (uint32_t)m * band_step));
-            if (pe.c_cached) *c = val;             // split-K partials are read by the next kernel
-            else __builtin_nontemporal_store(val, c);
-            continue;
+            for (int e = 0; e < 4; ++e) w[e] = actf(acc[m][n][e] + bvs[n][e]);
+            const int q = n * 4 + eq;
+            *(f32x4_t*)(wt + (m - m0) * kBand32 + er * OROWB32 + ((q ^ (er & kKey32)) * 16)) = w;
           }
-          const int i = row0 + wm * Cfg::WTM + m * 16 + r;
-          const int j = col0 + wn * Cfg::WTN + q * 4;
-          if (i < pe.M && j < pe.N) {
-            float* c = Cf + (int64_t)i * pe.ldc + j;
-            if (j + 4 <= pe.N) {
-              if (pe.c_cached) *(f32x4_any_t*)c = val;
-              else __builtin_nontemporal_store(val, (f32x4_any_t*)c);
-            } else {
+        });
+        static_for<m0, m1>([&](auto m_c) __attribute__((always_inline)) {
+          constexpr int m = decltype(m_c)::value;
+          f32x4_t val[kIt32];
 #pragma unroll
-              for (int t2 = 0; t2 < 4; ++t2)
-                if (j + t2 < pe.N) c[t2] = val[t2];
+          for (int it = 0; it < kIt32; ++it) {
+            const int e = it * 64 + slane;
+            const int r = e / CH32, q = e % CH32;
+            val[it] = *(const f32x4_t*)(wt + (m - m0) * kBand32 + r * OROWB32 + ((q ^ (r & kKey32)) * 16));
+          }
+#pragma unroll
+          for (int it = 0; it < kIt32; ++it) {
+            if (inside) {
+              put((f32x4_any_t*)(wave_c + (lane_off[it] + (uint32_t)m * band_step)), val[it]);
+              continue;
+            }
+            const int e = it * 64 + slane;
+            const int r = e / CH32, q = e % CH32;
+            const int i = row0 + wm * Cfg::WTM + m * 16 + r;
+            const int j = col0 + wn * Cfg::WTN + q * 4;
+            if (i < pe.M && j < pe.N) {
+              float* c = Cf + (int64_t)i * pe.ldc + j;
+              if (j + 4 <= pe.N) {
+                put((f32x4_any_t*)c, val[it]);
+              } else {
+#pragma unroll
+                for (int t2 = 0; t2 < 4; ++t2)
+                  if (j + t2 < pe.N) c[t2] = val[it][t2];
+              }
             }
           }
-        }
+        });
       });
     };
     // dest: 1 = 16-bit, 2 = fp32
     auto drain_to = [&](auto actf, auto dest) __attribute__((always_inline)) {
-      if constexpr (decltype(dest)::value == 2) drain32_all(actf);
+      if constexpr (decltype(dest)::value == 2 && BM * BN <= 128 * 128) drain32_halves(actf);
+      else if constexpr (decltype(dest)::value == 2) drain32_bands(actf);
       else drain16_all(actf);
     };
     auto drain_by_activation = [&](auto dest) __attribute__((always_inline)) {
