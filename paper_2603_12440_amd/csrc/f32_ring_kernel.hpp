@@ -183,7 +183,9 @@ __global__ __launch_bounds__(256) void f32_ring_kernel(MfmaArgs p, int64_t c_si,
 // element (moving them down from four values before the end by selects was slower: 1001^3, B row-major 52 us against 39).  Such problems ran on
 // general_mfma_kernel, which loads single values in slabs of 16 columns of K: 1001^3, B row- / column-major 53.8 -> 39.0 / 54.3 -> 31.6 us,
 // 3001^3 658 -> 506, 4001^3 1453 -> 1077 (119 TFLOP/s; 4000^3 takes 0.95 ms on f32_ring_kernel), 1518x587x2647 128 -> 66.
-template <bool A_KF, bool B_KF, int MT>
+// ROWS: a lane holds values of one row of C (of one column otherwise): its neighbours' are next to each other in memory where C is
+// column-major, or row-major with a few columns.
+template <bool A_KF, bool B_KF, int MT, bool ROWS>
 __global__ __launch_bounds__(256) void f32_any_kernel(MfmaArgs p, int64_t c_si, int64_t c_sj) {
   constexpr int BM = 64 * MT, BN = 64 * MT, BK = 32;
   constexpr int A_BYTES = BM * 128, STAGE = 2 * A_BYTES, HALF = 2 * MT, LOADS = 2 * HALF;
@@ -295,7 +297,9 @@ __global__ __launch_bounds__(256) void f32_any_kernel(MfmaArgs p, int64_t c_si, 
 #pragma unroll
       for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int n = 0; n < MT; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m][i], w[n][i], acc[m][n], 0, 0, 0);
+        for (int n = 0; n < MT; ++n)
+          acc[m][n] = ROWS ? __builtin_amdgcn_mfma_f32_32x32x2f32(w[n][i], a[m][i], acc[m][n], 0, 0, 0)
+                           : __builtin_amdgcn_mfma_f32_32x32x2f32(a[m][i], w[n][i], acc[m][n], 0, 0, 0);
   };
   load(v[0], 0);
   if (T > 1) load(v[1], 1);
@@ -315,9 +319,24 @@ __global__ __launch_bounds__(256) void f32_any_kernel(MfmaArgs p, int64_t c_si, 
       multiply(u);
     }
   }
-  // register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32 of the 32x32 tile
+  // register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32 of the 32x32 tile (ROWS: the other way round)
   const float* bias = p.has_bias ? p.bias + batch * p.stride_bias : nullptr;
   float* C = (float*)p.C + batch * p.stride_c;
+  if constexpr (ROWS) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const int64_t i = r0 + (wm * MT + m) * 32 + fr;
+      if (i >= p.M || i < row_first) continue;
+#pragma unroll
+      for (int n = 0; n < MT; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int64_t j = c0 + (wn * MT + n) * 32 + 8 * (r / 4) + 4 * fh + r % 4;
+          if (j < p.N && j >= col_first) C[i * c_si + j * c_sj] = apply_activation(p.act, acc[m][n][r] + (bias ? bias[j] : 0.0f), p.scale);
+        }
+    }
+    return;
+  }
 #pragma unroll
   for (int n = 0; n < MT; ++n) {
     const int64_t j = c0 + (wn * MT + n) * 32 + fr;

@@ -158,11 +158,28 @@ hipError_t launch_f32_any(const gemm_plan& pl, const void* A, const void* B, voi
   r.xcd_remap = d.batch == 1 || (r.tiles_m * (int64_t)r.tiles_n) % 8 == 0;
   const bool ak = d.layout_a == GEMM_ROW_MAJOR, bk = d.layout_b == GEMM_COL_MAJOR;   // K contiguous?
   constexpr int MT = TM / 64;
-  if (ak && bk) f32_any_kernel<true, true, MT><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
-  else if (ak) f32_any_kernel<true, false, MT><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
-  else if (bk) f32_any_kernel<false, true, MT><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
-  else f32_any_kernel<false, false, MT><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
+  // Lanes along rows of C (time over that of lanes along columns, 20000 drawn products): column-major C 0.65 to 0.93; row-major, N <= 24,
+  // 0.71 to 0.99 (139x1x7, 508 problems: 14.0 -> 9.3 us), N of 25 to 48 0.92 to 0.95 with two tiles per CU, 0.98 to 1.13 with more; at most a
+  // tile per CU 0.83 to 0.99 whatever N is; else 1.0 to 1.33.
+  const int64_t tiles = (int64_t)pl.grid.x * pl.grid.y * pl.grid.z;
+  const bool rows = d.layout_c == GEMM_COL_MAJOR || tiles <= num_cus() || d.N <= (tiles <= 2 * num_cus() ? 48 : 24);
+  auto go = [&](auto ak_c, auto bk_c) {
+    constexpr bool AK = decltype(ak_c)::value, BK = decltype(bk_c)::value;
+    if (rows) f32_any_kernel<AK, BK, MT, true><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
+    else f32_any_kernel<AK, BK, MT, false><<<pl.grid, pl.block, 0, s>>>(r, a.c_si, a.c_sj);
+  };
+  typedef std::true_type yes;
+  typedef std::false_type no;
+  if (ak && bk) go(yes(), yes());
+  else if (ak) go(yes(), no());
+  else if (bk) go(no(), yes());
+  else go(no(), no());
   return hipGetLastError();
+}
+
+// the general matrix-core kernel in fp32 whatever the offsets are
+hipError_t launch_f32_general(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias, hipStream_t s) {
+  return launch_general_mfma_typed<float, float, 64, 64, 16>(pl, A, B, C, bias, s);
 }
 
 template <typename TIn, int TM, int TN, int TK>
@@ -349,6 +366,10 @@ hipError_t launch_skinny_direct(const gemm_plan& pl, const void* A, const void* 
 #define F32_SMALL_CFG()                                                                    \
   { "f32small_16x16x256", KIND_SIMT, 16, 16, 256, 256, 4096, { launch_f32_small, nullptr, nullptr } }
 
+// general_mfma32_64x64x16 in fp32 where its offsets would allow f32_any_kernel, too
+#define F32_GENERAL_CFG()                                                                  \
+  { "f32general_64x64x16", KIND_SIMT, 64, 64, 16, 256, (int)(sizeof(float) * 16 * (64 + 4 + 64 + 4)), { launch_f32_general, nullptr, nullptr } }
+
 #define MFMA_CFG(BM, BN, BK, WM, WN, NS)                                                   \
   { "mfma_" #BM "x" #BN "x" #BK "_w" #WM "x" #WN "_s" #NS, KIND_MFMA, BM, BN, BK,          \
     64 * WM * WN, MfmaTile<bf16_t, BM, BN, BK, WM, WN, NS>::LDS_BYTES,                     \
@@ -499,6 +520,7 @@ const Config kConfigs[] = {
     MI355GEMM_RINGS_T(RINGT_CFG)
     MI355GEMM_RINGS(RING8_CFG)
     MI355GEMM_MFMA16G_TILES(MFMA16G_CFG)
+    F32_GENERAL_CFG(),
 };
 constexpr int kNumConfigs = (int)(sizeof(kConfigs) / sizeof(kConfigs[0]));
 
@@ -822,7 +844,7 @@ int64_t split_columns(const gemm_desc_t& d, int big, double single_cost) {
 int choose_general(const gemm_desc_t& d) {
   //   * fp32, at most four 16x16 tiles per CU: 16x16 tiles with K split over the waves of a workgroup
   //     (256^3: 5 us against 11 us for the next choice; 512^3: 11 to 12 against 19 us);
-  //   * fp32, up to eight 16x16 tiles per CU: those or one 64x64 tile per CU, by an estimate;
+  //   * fp32, up to eight 16x16 tiles per CU: those or 64x64 tiles, by an estimate;
   //   * very few 32x32 tiles (16-bit operands in layouts the tiled kernels do not take): the vector-ALU
   //     kernel with 32x32 tiles and the long K step;
   //   * fp32 in float4 groups: the fp32-MFMA kernels with slabs straight to LDS, 128x128 tiles from four
@@ -836,16 +858,22 @@ int choose_general(const gemm_desc_t& d) {
     if (i >= 0 && applicable(kConfigs[i], d)) return i;
   }
   if (tiles32 <= 2.0 * num_cus()) {
-    // fp32: up to a 64x64 tile per CU, whose time is that of one tile, against the 16x16 tiles' turns.  Microseconds fitted to 50 drawn
-    // products with 100 to 700 32x32 tiles (1079x467x529: 21.8 on 64x64 tiles, 33 on 16x16 ones, 29 on the vector-ALU kernel that such
-    // products ran on; 2456x110x2930 96, 71 and 122); the rule's choice is 2 % from the better of the two on average.
+    // fp32: 16x16 tiles or 64x64 ones.  K up to 64: 64x64, within 2 % of the fastest kernel however many there are, 16x16 ones up to three
+    // times that.  Beyond, microseconds fitted to half of 4326 drawn products with 257 to 512 32x32 tiles (all layouts, batches, K to
+    // 4000; rms 15 and 8 %): the choice is 1.5 % from the better kernel on the other half (an estimate that looked at B's layout only and
+    // took every problem for one 64x64 tile per CU: 4.8 %).  1079x467x529: 21.8 on 64x64 tiles, 33 on 16x16 ones, 29 on the vector-ALU
+    // kernel; 2456x110x2930 117, 81 and 129; 512 problems of 32x32x2000 72, 106 and 94; 294 of 10x7x26, A column-major, 6.8, 8.4 and 6.7.
     const int small = find_config("f32small_16x16x256"), aligned = find_config("f32mfma_64x64x32");
     if (d.dtype_a == GEMM_F32 && f32_takes_any(d, 64) && small >= 0 && applicable(kConfigs[small], d)) {
-      const bool k_contiguous = d.layout_b == GEMM_COL_MAJOR, pieces = applicable(kConfigs[aligned], d);
+      const bool pieces = applicable(kConfigs[aligned], d), b_row = d.layout_b == GEMM_ROW_MAJOR;
       const double K = (double)d.K, turns = (double)((d.M + 15) / 16) * (double)((d.N + 15) / 16) * d.batch / num_cus();
-      const double t16 = turns * (1.2 + (k_contiguous ? 0.0035 : 0.0045) * K);
-      const double t64 = 1.0 + (pieces ? (k_contiguous ? 0.0225 : 0.0205) : (k_contiguous ? 0.0262 : 0.033)) * K;
-      return t16 < t64 ? small : pieces ? aligned : find_config("general_mfma32_64x64x16");
+      const double tiles64 = (double)((d.M + 63) / 64) * (double)((d.N + 63) / 64) * d.batch / num_cus();
+      const double k16 = d.layout_a == GEMM_ROW_MAJOR ? (b_row ? 0.0049 : 0.0038) : (b_row ? 0.0053 : 0.0044);
+      const double narrow = (d.M <= 16 || d.N <= 16) && d.K > 256 ? 0.84 : 1.0;      // (64x64 tiles load one piece of a row many times)
+      const double t16 = 4.85 + narrow * std::hypot(turns * (0.82 + k16 * K), 0.37e-6 * 4.0 * (double)(d.M + d.N) * K * d.batch);   // (operands at 2.7 TB/s)
+      const double t64 = pieces ? 6.19 + (1.0 + 0.8 * fmax(0.0, tiles64 - 1.0)) * (0.0207 * K - 0.99)
+                                : 5.11 + (1.0 + 0.8 * fmax(0.0, tiles64 - 1.0)) * ((b_row ? 0.0322 : 0.0253) * K - 0.09);
+      return d.K > 64 && t16 < t64 ? small : pieces ? aligned : find_config("general_mfma32_64x64x16");
     }
     return find_config("simt_32x32x64");
   }
@@ -853,7 +881,17 @@ int choose_general(const gemm_desc_t& d) {
     const int i = find_config(tiles128 >= 4.0 * num_cus() ? "f32mfma_128x128x32" : "f32mfma_64x64x32");
     if (i >= 0 && applicable(kConfigs[i], d)) return i;
   }
-  return find_config(tiles128 >= 4.0 * num_cus() ? "general_mfma32_128x128x16" : "general_mfma32_64x64x16");
+  // fp32 of any alignment, many tiles: f32_any_kernel, whose registers and LDS allow five workgroups on a CU, is 1.02 to 1.24 behind the
+  // general kernel with a few rows or columns and a K of one of that one's steps, 1.0 to 1.1 with K > 64 and more than five tiles per CU, and
+  // 1.1 to 1.3 with K <= 8 and C column-major (20000 drawn products; fewer tiles, a K of one or two slabs: up to 0.8 ahead).
+  const double tiles64 = (double)((d.M + 63) / 64) * (double)((d.N + 63) / 64) * d.batch / num_cus();
+  const int64_t narrow = d.M < d.N ? d.M : d.N;
+  if (d.dtype_a == GEMM_F32 && ((narrow <= 32 && ((d.K <= 16 && tiles64 > 3) || (d.K > 64 && tiles64 > 5))) ||
+                                (d.K <= 8 && d.layout_c == GEMM_COL_MAJOR && tiles64 > 4)))
+    return find_config("f32general_64x64x16");
+  // (128x128 tiles of an fp32 problem that fills half of one: 2054x40x1, 227 problems, 120 us)
+  const bool wide = d.dtype_a != GEMM_F32 || narrow > 64;
+  return find_config(wide && tiles128 >= 4.0 * num_cus() ? "general_mfma32_128x128x16" : "general_mfma32_64x64x16");
 }
 
 // The choice for 16-bit operands of any alignment with K <= 64, where writing C and the fixed cost of a tile are most of the

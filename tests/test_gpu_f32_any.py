@@ -82,3 +82,19 @@ def test_values_that_are_not_finite(g, la, lb, K):
         torch.cuda.synchronize()
         g.gemm_destroy(p)
         assert torch.equal(C.cpu().nan_to_num(nan=1e9, posinf=2e9, neginf=-2e9), want.nan_to_num(nan=1e9, posinf=2e9, neginf=-2e9)), cfg
+
+
+@pytest.mark.parametrize("la,lb", LAYOUTS)
+@pytest.mark.parametrize("M,N,K,batch", [(1100, 1030, 67, 1), (2100, 2200, 35, 1), (70, 130, 40, 70), (200, 24, 33, 150), (139, 1, 7, 508), (100, 49, 33, 300),
+                                         (100, 30, 17, 200), (30, 49, 130, 300)])
+def test_lanes_along_rows_and_columns(g, la, lb, M, N, K, batch):
+    """More and fewer tiles than CUs, few columns and more, C in either layout: a lane holds values of a row or of a column of C."""
+    w = wl.Workload("t", M, N, K, dtype="f32", layout_a=la, layout_b=lb, batch=batch, epilogue="bias_relu", seed_a=M + 1, seed_b=N + 2)
+    A, B, want = operands(w)
+    bias = wl.small_integers((N,), w.seed_bias, -3, 3, "f32")
+    want = torch.relu(want + bias)
+    for cfg in ("general_mfma32_64x64x16", "general_mfma32_128x128x16", "f32general_64x64x16", None):
+        for lc in ("row", "col"):
+            print(f"{M}x{N}x{K} b{batch} {la}/{lb}/{lc} {cfg}", flush=True)
+            C = run_gpu(g, w, A, B, bias, config=-1 if cfg is None else g.config_names().index(cfg), layout_c=lc, pad_a=1, pad_c=1)
+            assert torch.equal(C.float(), want), (cfg, lc)

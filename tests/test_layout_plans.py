@@ -151,3 +151,15 @@ def test_second_launch_of_a_wide_product():
                     (dict(M=1024, N=17416, K=136, layout_b=g.ROW_MAJOR, dtype_c=g.F32), True),     # 29.0; 31.7 in one
                     (dict(M=1024, N=17416, K=136, layout_b=g.ROW_MAJOR), False)):                  # 24.5; 25.5 in two
         assert ("columns=" in info(**kw)) == two, kw
+
+
+@pytest.mark.parametrize("kw,kernel", [
+    (dict(M=10, N=7, K=26, batch=294, layout_a=g.COL_MAJOR, layout_b=g.ROW_MAJOR), "general_mfma32_64x64x16"),       # 6.8 us; 16x16 tiles 8.4
+    (dict(M=32, N=32, K=2000, batch=512), "f32mfma_64x64x32"),                     # 72.0; 16x16 tiles 105
+    (dict(M=1079, N=467, K=529), "general_mfma32_64x64x16"),                       # 21.8; 33
+    (dict(M=2456, N=110, K=2930, layout_b=g.ROW_MAJOR), "f32small_16x16x256"),     # 81; 117
+    (dict(M=139, N=1, K=7, batch=508), "f32general_64x64x16"),                     # 6.8; any-alignment kernel 9.3 and 14.0
+    (dict(M=139, N=1, K=27, batch=508), "general_mfma32_64x64x16"), (dict(M=139, N=1, K=69, batch=508), "f32general_64x64x16")])
+def test_fp32_choice(kw, kernel):
+    """fp32 products between one and two 32x32 tiles per CU, and narrow ones of any alignment in large numbers (us on one box)."""
+    assert "kernel=" + kernel + " " in info(dtype=g.F32, **kw)
