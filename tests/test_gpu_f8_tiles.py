@@ -18,12 +18,13 @@ def g():
 
 
 CONFIGS = ["mfma8_256x256x128_w2x4_s2", "mfma8_224x256x128_w2x4_s2", "mfma8_192x256x128_w2x4_s2", "mfma8_256x192x128_w4x2_s2",
-           "mfma8_128x128x128_w2x2_s2", "mfma8_128x128x128_w2x2_s4"]
+           "mfma8_128x128x128_w2x2_s2", "mfma8_128x128x128_w2x2_s4", "mfma8_256x256x128_w2x4_one", "mfma8_224x256x128_w2x4_one",
+           "mfma8_192x256x128_w2x4_one", "mfma8_256x192x128_w4x2_one", "mfma8_128x128x128_w2x2_one"]
 
 
 @pytest.mark.parametrize("cfg", CONFIGS)
 def test_slabs_tails_edges_and_batches(g, cfg):
-    """Persistent workgroups where K is two or more whole slabs of 128 (the _s2 configurations), one tile per workgroup otherwise.
+    """Persistent workgroups where K is two or more whole slabs of 128 (the _s2 configurations), one tile per workgroup otherwise and on _one.
     (|sum| <= 656 + 3: exact in fp32 output; bf16 output is the same rounding of the same value.)"""
     bm, bn = (int(x) for x in cfg.split("_")[1].split("x")[:2])
     for M, N, K in [(bm, bn, 256), (bm - 8, bn + 8, 384), (bm + 8, bn - 8, 512), (8, 8, 640), (2 * bm + 16, bn + 8, 640), (bm, bn, 128),

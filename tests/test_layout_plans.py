@@ -163,3 +163,30 @@ def test_second_launch_of_a_wide_product():
 def test_fp32_choice(kw, kernel):
     """fp32 products between one and two 32x32 tiles per CU, and narrow ones of any alignment in large numbers (us on one box)."""
     assert "kernel=" + kernel + " " in info(dtype=g.F32, **kw)
+
+
+def by_name(name, **kw):
+    p = g.gemm_create_config(g.GemmDesc(**kw), g.config_names().index(name))
+    text = p.info()
+    g.gemm_destroy(p)
+    return text
+
+
+@pytest.mark.parametrize("tile,shape", [("256x256", "w2x4"), ("224x256", "w2x4"), ("192x256", "w2x4"), ("256x192", "w4x2"), ("128x128", "w2x2")])
+def test_fp8_tiles_with_and_without_persistent_workgroups(tile, shape):
+    """Both kernels of an fp8 tile have a name, whatever K is (_s2: persistent workgroups where K is two or more whole slabs of 128)."""
+    bm, bn = (int(x) for x in tile.split("x"))
+    name = f"mfma8_{tile}x128_{shape}_"
+    kw = dict(M=20 * bm, N=40 * bn, dtype=g.F8E4M3)
+    assert f"grid={512 if tile == '128x128' else 256},1,1" in by_name(name + "s2", K=512, **kw)
+    for k in (512, 528, 128):
+        assert "grid=800,1,1" in by_name(name + "one", K=k, **kw)
+    assert "grid=800,1,1" in by_name(name + "s2", K=528, **kw) and "grid=800,1,1" in by_name(name + "s2", K=128, **kw)
+
+
+def test_fp8_choice_names_the_kernel_that_runs():
+    """A K that is no whole number of slabs: one tile per workgroup."""
+    for k in (144, 272, 1040, 4112):
+        text = info(M=4096, N=8192, K=k, dtype=g.F8E4M3)
+        assert "_s2 " not in text and ("_one " in text or "_s4 " in text or "_s5 " in text), text
+    assert "_s2 " in info(M=8192, N=8192, K=8192, dtype=g.F8E4M3)
