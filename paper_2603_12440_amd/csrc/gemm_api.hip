@@ -305,38 +305,36 @@ hipError_t launch_skinny_stage(const gemm_plan& pl, const void* A, const void* B
   return hipGetLastError();
 }
 
-// Which problems of the skinnydirect_d2_b512_w4 plan run on the kernel with x in registers (skinny_rows_kernel)?  Measured on 166 drawn
+// Which problems does the built-in choice run on the kernel with x in registers (skinny_rows_kernel) instead of skinny_direct_kernel?  Measured on 166 drawn
 // products (M 2 to 16, N 1024 to 130000, K 128 to 8192), its time over the other's: N <= 4096 (a panel per workgroup) 0.69 to 1.02
 // with K > 1024, 1.1 to 1.5 with less (the start of a workgroup of eight waves, eight parts of K to add); N to 8192, where the
 // panels of 32 rows are one round and those of 16 two, 0.90 to 0.96 with K of 3584 to 4096 (parts that fill two slabs, a little of x) and 0.97 to
 // 1.23 otherwise; K <= 2048, where a panel is one slab, 0.89 to 1.24 up to N = 16384; everything else 0.77 to 1.06, 0.90 on average.
 bool skinny_takes_rows(const gemm_desc_t& d) {
-  if (d.batch != 1 || d.M > 16 || d.N < kSkinnyRowsPanel || d.K <= 1024 || d.K > kSkinnyRowsMaxK) return false;
   if (d.N <= 16 * num_cus()) return true;
   if (d.N <= 32 * num_cus()) return d.K > 3584 && d.K <= 4096;
   return d.K > 2048 || d.N > 64 * num_cus();
 }
 
-template <typename T, int S>
-void launch_skinny_rows(const gemm_plan& pl, const SkinnyArgs& a, hipStream_t s) {
-  if (a.K == S * 2048) skinny_rows_kernel<T, S, true><<<pl.grid, pl.block, 0, s>>>(a);
-  else skinny_rows_kernel<T, S, false><<<pl.grid, pl.block, 0, s>>>(a);
+template <typename T>
+hipError_t launch_skinny_rows(const gemm_plan& pl, const void* A, const void* B, void* C, const void* bias, hipStream_t s) {
+  const SkinnyArgs a = skinny_args(pl, A, B, C, bias);
+  auto go = [&](auto slabs) {
+    constexpr int S = decltype(slabs)::value;
+    if (a.K == S * 2048) skinny_rows_kernel<T, S, true><<<pl.grid, pl.block, 0, s>>>(a);
+    else skinny_rows_kernel<T, S, false><<<pl.grid, pl.block, 0, s>>>(a);
+  };
+  if (a.K > 6144) go(std::integral_constant<int, 4>());
+  else if (a.K > 4096) go(std::integral_constant<int, 3>());
+  else if (a.K > 2048) go(std::integral_constant<int, 2>());
+  else go(std::integral_constant<int, 1>());
+  return hipGetLastError();
 }
 
 template <typename T, int DEPTH, int RB, int WAVES>
 hipError_t launch_skinny_direct(const gemm_plan& pl, const void* A, const void* B, void* C,
                                 const void* bias, hipStream_t s) {
-  const SkinnyArgs a = skinny_args(pl, A, B, C, bias);
-  if constexpr (DEPTH == 2 && RB == 512) {
-    if (pl.cfg->persist == 3 && skinny_takes_rows(pl.d)) {
-      if (a.K > 6144) launch_skinny_rows<T, 4>(pl, a, s);
-      else if (a.K > 4096) launch_skinny_rows<T, 3>(pl, a, s);
-      else if (a.K > 2048) launch_skinny_rows<T, 2>(pl, a, s);
-      else launch_skinny_rows<T, 1>(pl, a, s);
-      return hipGetLastError();
-    }
-  }
-  skinny_direct_kernel<T, DEPTH, RB, WAVES><<<pl.grid, pl.block, 0, s>>>(a);
+  skinny_direct_kernel<T, DEPTH, RB, WAVES><<<pl.grid, pl.block, 0, s>>>(skinny_args(pl, A, B, C, bias));
   return hipGetLastError();
 }
 
@@ -426,10 +424,13 @@ hipError_t launch_mfma16f8(const gemm_plan& pl, const void* A, const void* B, vo
   { "skinnystage_d" #DEPTH "_b" #RB, KIND_SKINNY_PANEL, 16, 32, RB / 2, 256, 4 * 48 * RB,     \
     { nullptr, launch_skinny_stage<bf16_t, DEPTH, RB, 4>, launch_skinny_stage<f16_t, DEPTH, RB, 4> } }
 // skinny with W staged through LDS and x fragments straight from L2 (16x16x32 MFMA): same panel shape
-// (ROWS: 3 where the plan runs on skinny_rows_kernel when skinny_takes_rows)
-#define SKINNY_DIRECT_CFG(DEPTH, RB, WAVES, ROWS)                                          \
+#define SKINNY_DIRECT_CFG(DEPTH, RB, WAVES)                                                \
   { "skinnydirect_d" #DEPTH "_b" #RB "_w" #WAVES, KIND_SKINNY_PANEL, 16, 32, RB / 2, 64 * WAVES, WAVES * 32 * RB, \
-    { nullptr, launch_skinny_direct<bf16_t, DEPTH, RB, WAVES>, launch_skinny_direct<f16_t, DEPTH, RB, WAVES> }, ROWS }
+    { nullptr, launch_skinny_direct<bf16_t, DEPTH, RB, WAVES>, launch_skinny_direct<f16_t, DEPTH, RB, WAVES> } }
+// the same with x in registers and panels of 16 rows of W
+#define SKINNY_ROWS_CFG()                                                                  \
+  { "skinnydirect_d2_b512_w4_rows", KIND_SKINNY_PANEL, 16, kSkinnyRowsPanel, 256, 512, kSkinnyRowsLds, \
+    { nullptr, launch_skinny_rows<bf16_t>, launch_skinny_rows<f16_t> }, 3 }
 // 128x128 tiles with four slabs in LDS, one workgroup per CU
 #define MFMA16S_CFG(BM, BN, WM, WN, G, S)                                                  \
   { "mfma16_" #BM "x" #BN "x64_w" #WM "x" #WN "_s" #S, KIND_MFMA, BM, BN, 64, 64 * WM * WN, \
@@ -503,9 +504,9 @@ const Config kConfigs[] = {
     SKINNY_CFG(4, 8, 1),
     SKINNY_STAGE_CFG(3, 256),
     SKINNY_STAGE_CFG(2, 512),
-    SKINNY_DIRECT_CFG(2, 512, 4, 3),
-    SKINNY_DIRECT_CFG(3, 512, 4, 0),
-    SKINNY_DIRECT_CFG(2, 256, 8, 0),
+    SKINNY_DIRECT_CFG(2, 512, 4),
+    SKINNY_DIRECT_CFG(3, 512, 4),
+    SKINNY_DIRECT_CFG(2, 256, 8),
     MFMA16T_CFG("_p", 256, 256, 2, 4, 2, 1),
     MFMA16T_CFG("_p", 128, 128, 2, 2, 2, 1),
     MFMA16T_CFG("", 256, 256, 2, 4, 2, 0),
@@ -530,6 +531,7 @@ const Config kConfigs[] = {
     MFMA16F8_ONE_CFG(224, 256, 2, 4, 4),
     MFMA16F8_ONE_CFG(192, 256, 2, 4, 4),
     F32_GENERAL_CFG(),
+    SKINNY_ROWS_CFG(),
 };
 constexpr int kNumConfigs = (int)(sizeof(kConfigs) / sizeof(kConfigs[0]));
 
@@ -666,6 +668,8 @@ bool applicable(const Config& c, const gemm_desc_t& d) {
       d.K >= ((int64_t)1 << 31) - 512)
     return false;
   if (c.kind == KIND_SKINNY) return d.M <= c.bm;
+  // (x in registers: one problem, a whole panel, what the registers hold; up to K = 1024 it is 1.1 to 1.5 behind: skinny_takes_rows)
+  if (c.persist == 3 && (d.batch != 1 || d.N < c.bn || d.K <= 1024 || d.K > kSkinnyRowsMaxK)) return false;
   if (c.kind == KIND_SKINNY_PANEL)   // 32-bit lane offsets inside a 32-row panel
     return d.M <= c.bm && 32 * d.ldb * 2 < ((int64_t)1 << 32) && 32 * d.lda * 2 < ((int64_t)1 << 32) &&
            (d.N + 31) / 32 < ((int64_t)1 << 31);
@@ -679,13 +683,9 @@ bool applicable(const Config& c, const gemm_desc_t& d) {
   return (persists(c, d) || c.t1 > 0 ? tiles * d.batch : tiles) < ((int64_t)1 << 31);
 }
 
-// Does such a plan run on skinny_rows_kernel?
-bool runs_rows(const Config& c, const gemm_desc_t& d) { return c.persist == 3 && skinny_takes_rows(d); }
-
 // LDS bytes of the kernel a plan runs for 16-byte aligned operands
 int plan_lds_bytes(const gemm_plan& pl) {
   const Config& c = *pl.cfg;
-  if (runs_rows(c, pl.d)) return kSkinnyRowsLds;
   if (c.persist == 2 && !persists(c, pl.d)) return 2 * (c.bm + c.bn) * 128 + (c.threads == 512 ? 256 : 0);   // (no staging area)
   if (c.kind != KIND_F32_VEC || f32_takes_ring(pl.d, c.bm)) return c.lds_bytes;
   return f32_mfma_lds(c.bm, pl.d.layout_a == GEMM_ROW_MAJOR) + f32_mfma_lds(c.bm, pl.d.layout_b == GEMM_COL_MAJOR);
@@ -927,11 +927,12 @@ int choose(const gemm_desc_t& d) {
   // skinny: up to 4 rows of x on the vector ALUs (smallest padded M that fits, first
   // such entry of the table), up to 16 on the matrix cores
   if (d.M > 1 && d.M <= 16) {
-    // W through wave-private LDS slabs, x fragments straight from L2, 16x16x32 MFMA, two slabs
-    // requested ahead per wave (M = 16: 24.3 us at N = K = 8192, 80 us at N = 28672; M = 4: 23.0 and
-    // 72 us, where the vector-ALU kernel below needs 26 and 75 us)
-    const int i = find_config("skinnydirect_d2_b512_w4");
-    if (i >= 0 && applicable(kConfigs[i], d)) return i;
+    // W through wave-private LDS slabs, 16x16x32 MFMA, two slabs requested ahead per wave, x in registers or its fragments
+    // straight from L2 (M = 16: 24.3 us at N = K = 8192, 73.5 at N = 28672; M = 4: 23.0 us at N = 8192, where the vector-ALU
+    // kernel below needs 26)
+    const int rows = find_config("skinnydirect_d2_b512_w4_rows"), i = find_config("skinnydirect_d2_b512_w4");
+    if (applicable(kConfigs[rows], d) && skinny_takes_rows(d)) return rows;
+    if (applicable(kConfigs[i], d)) return i;
   }
   if (d.M <= 4) {
     // two waves per SIMD (8 per workgroup, one workgroup per CU) stream faster than one; for
@@ -990,11 +991,10 @@ int fill_launch_shape(gemm_plan& pl) {
     }
     // a batch on persistent workgroups: whole problems per XCD (their tiles share panels)
     if (persist && d.batch > 1 && (tm * tn * d.batch) % 8 == 0 && wgs % 8 == 0) pl.xcd_remap = 2;
-  } else if (runs_rows(c, d)) {
+  } else if (c.persist == 3) {
     // as many workgroups as share the panels evenly, at most one per CU (896 panels: 224; 14336x8192 39.9 us with 256, 39.1 so)
-    const int64_t panels = (d.N + kSkinnyRowsPanel - 1) / kSkinnyRowsPanel, turns = (panels + num_cus() - 1) / num_cus();
+    const int64_t panels = (d.N + c.bn - 1) / c.bn, turns = (panels + num_cus() - 1) / num_cus();
     pl.grid = dim3((unsigned)((panels + turns - 1) / turns), 1, 1);
-    pl.block = dim3(512, 1, 1);
   } else if (c.kind == KIND_SKINNY_PANEL) {
     pl.grid = dim3((unsigned)((d.N + c.bn - 1) / c.bn), (unsigned)d.batch, 1);
   } else {

@@ -64,3 +64,24 @@ def test_values_that_are_not_finite(g, cfg, K, ld):
     torch.cuda.synchronize()
     g.gemm_destroy(p)
     assert torch.equal(C.cpu().nan_to_num(nan=1e9, posinf=2e9, neginf=-2e9), want.nan_to_num(nan=1e9, posinf=2e9, neginf=-2e9))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("K", [1024, 4096])
+def test_error_on_normal_data(g, dtype, K):
+    """The same products as the tiled kernels, in as many sums as there are waves, added in fp32: within the tiled kernels' bound,
+    2^-24 sqrt(K / 32) for 32 products per addition into the accumulator."""
+    M, N = 136, 264
+    gen = torch.Generator(device="cuda:0").manual_seed(K)
+    A, B = (torch.randn(r, K, generator=gen, device="cuda:0").to(wl.TORCH_DTYPE[dtype]) for r in (M, N))
+    ref = A.double() @ B.double().t().contiguous()
+    code = {"bf16": g.BF16, "f16": g.F16}[dtype]
+    for cfg in (C64, C32):
+        C = torch.full((M, N), float("nan"), device="cuda:0")
+        p = g.gemm_create_config(g.GemmDesc(M, N, K, dtype=code, dtype_c=g.F32), g.config_names().index(cfg))
+        g.gemm_run(p, A, B, C)
+        torch.cuda.synchronize()
+        g.gemm_destroy(p)
+        e = float((C.double() - ref).norm() / ref.norm())
+        print(f"{dtype} K={K} {cfg}: {e:.2e}", flush=True)
+        assert e <= 2.0 ** -24 * (K / 32) ** 0.5, (cfg, e)

@@ -190,3 +190,18 @@ def test_fp8_choice_names_the_kernel_that_runs():
         text = info(M=4096, N=8192, K=k, dtype=g.F8E4M3)
         assert "_s2 " not in text and ("_one " in text or "_s4 " in text or "_s5 " in text), text
     assert "_s2 " in info(M=8192, N=8192, K=8192, dtype=g.F8E4M3)
+
+
+def test_both_skinny_kernels_have_a_name():
+    """x in registers (panels of 16 rows of W, one workgroup of eight waves per CU) and x from L2 (panels of 32, four waves): either can be
+    asked for where the built-in choice takes the other."""
+    direct, rows = "skinnydirect_d2_b512_w4", "skinnydirect_d2_b512_w4_rows"
+    for kw in (dict(M=16, N=8192, K=8192), dict(M=4, N=28672, K=4096), dict(M=9, N=1000, K=1032)):
+        assert "tile=16x32x256" in by_name(direct, **kw) and "block=256 lds=65536" in by_name(direct, **kw)
+        assert "tile=16x16x256" in by_name(rows, **kw) and "block=512 lds=81920" in by_name(rows, **kw)
+    assert f"kernel={direct} " in info(M=16, N=8192, K=8192) and f"kernel={rows} " in info(M=16, N=28672, K=8192)
+    for kw in (dict(M=16, N=8192, K=1024), dict(M=16, N=8192, K=8200), dict(M=16, N=15, K=4096), dict(M=16, N=4096, K=4096, batch=2),
+               dict(M=17, N=4096, K=4096), dict(M=16, N=4096, K=4096, dtype=g.F8E4M3)):
+        with pytest.raises(g.GemmError) as e:
+            by_name(rows, **kw)
+        assert e.value.status == -9, kw
