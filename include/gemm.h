@@ -249,7 +249,8 @@ int gemm_destroy(gemm_plan_t* plan);
 /* Static, human-readable text for a status code (never NULL). */
 const char* gemm_status_string(int status);
 
-/* Writes "kernel=<name> tile=<BM>x<BN>x<BK> grid=<x>,<y>,<z> block=<t> lds=<bytes>"
+/* Writes "kernel=<name> tile=<BM>x<BN>x<BK> grid=<x>,<y>,<z> block=<t> lds=<bytes>", the K step and LDS
+ * bytes being those of the kernel that runs for 16-byte aligned operands,
  * (NUL-terminated, truncated to n bytes) into buf; returns the untruncated length
  * or a negative status. */
 int gemm_plan_info(const gemm_plan_t* plan, char* buf, size_t n);

@@ -351,7 +351,7 @@ hipError_t launch_skinny_direct(const gemm_plan& pl, const void* A, const void* 
   { "general_mfma32_" #TM "x" #TN "x" #TK, KIND_SIMT, TM, TN, TK, 256,                     \
     (int)(sizeof(float) * TK * (TM + 4 + TN + 4)),                                         \
     { launch_general_mfma<float, TM, TN, TK>, launch_general_mfma<bf16_t, TM, TN, TK>,     \
-      launch_general_mfma<f16_t, TM, TN, TK> } }
+      launch_general_mfma<f16_t, TM, TN, TK> }, 5 }
 
 // fp32 operands and output moved as float4 groups, slabs of 32 columns of K
 #define F32_MFMA_CFG(TM, TN)                                                               \
@@ -683,12 +683,15 @@ bool applicable(const Config& c, const gemm_desc_t& d) {
   return (persists(c, d) || c.t1 > 0 ? tiles * d.batch : tiles) < ((int64_t)1 << 31);
 }
 
-// LDS bytes of the kernel a plan runs for 16-byte aligned operands
-int plan_lds_bytes(const gemm_plan& pl) {
+// LDS bytes and K step of the kernel a plan runs for 16-byte aligned operands
+struct Runs { int lds, bk; };
+Runs plan_runs(const gemm_plan& pl) {
   const Config& c = *pl.cfg;
-  if (c.persist == 2 && !persists(c, pl.d)) return 2 * (c.bm + c.bn) * 128 + (c.threads == 512 ? 256 : 0);   // (no staging area)
-  if (c.kind != KIND_F32_VEC || f32_takes_ring(pl.d, c.bm)) return c.lds_bytes;
-  return f32_mfma_lds(c.bm, pl.d.layout_a == GEMM_ROW_MAJOR) + f32_mfma_lds(c.bm, pl.d.layout_b == GEMM_COL_MAJOR);
+  const gemm_desc_t& d = pl.d;
+  if (c.persist == 2 && !persists(c, d)) return {2 * (c.bm + c.bn) * 128 + (c.threads == 512 ? 256 : 0), c.bk};   // (no staging area)
+  if (c.persist == 5 && f32_takes_any(d, c.bm)) return {2 * 2 * c.bm * 128, kF32TileK};                            // f32_any_kernel
+  if (c.kind != KIND_F32_VEC || f32_takes_ring(d, c.bm)) return {c.lds_bytes, c.bk};
+  return {f32_mfma_lds(c.bm, d.layout_a == GEMM_ROW_MAJOR) + f32_mfma_lds(c.bm, d.layout_b == GEMM_COL_MAJOR), c.bk};
 }
 
 int find_config(const char* name) {
@@ -1552,23 +1555,24 @@ int gemm_plan_info(const gemm_plan_t* plan, char* buf, size_t n) {
   }
   const Config& c = *plan->cfg;
   if (plan->inner) {
+    const Runs r = plan_runs(*plan->inner);
     return std::snprintf(buf, n, "kernel=splitk_%d+%s tile=%dx%dx%d grid=%u,%u,%u block=%u lds=%d workspace=%zu",
-                         plan->splits, c.name, c.bm, c.bn, c.bk, plan->grid.x, plan->grid.y, plan->grid.z,
-                         plan->block.x, c.lds_bytes, gemm_workspace_bytes(plan));
+                         plan->splits, c.name, c.bm, c.bn, r.bk, plan->grid.x, plan->grid.y, plan->grid.z,
+                         plan->block.x, r.lds, gemm_workspace_bytes(plan));
   }
+  const Runs r = plan_runs(*plan);
   char other[96] = "";
   if (plan->fallback) std::snprintf(other, sizeof(other), " unaligned A or B: kernel=%s", plan->fallback->cfg->name);
   if (plan->tail) {
     const Config& t = *plan->tail->cfg;
     return std::snprintf(buf, n, "kernel=%s tile=%dx%dx%d grid=%u,%u,%u block=%u lds=%d columns=0..%lld "
-                         "+ kernel=%s grid=%u,%u,%u columns=%lld..%s", c.name, c.bm, c.bn, c.bk,
-                         plan->grid.x, plan->grid.y, plan->grid.z, plan->block.x, c.lds_bytes,
+                         "+ kernel=%s grid=%u,%u,%u columns=%lld..%s", c.name, c.bm, c.bn, r.bk,
+                         plan->grid.x, plan->grid.y, plan->grid.z, plan->block.x, r.lds,
                          (long long)plan->d.N - 1, t.name, plan->tail->grid.x, plan->tail->grid.y,
                          plan->tail->grid.z, (long long)plan->d.N, other);
   }
   return std::snprintf(buf, n, "kernel=%s tile=%dx%dx%d grid=%u,%u,%u block=%u lds=%d%s", c.name,
-                       c.bm, c.bn, c.bk, plan->grid.x, plan->grid.y, plan->grid.z, plan->block.x,
-                       plan_lds_bytes(*plan), other);
+                       c.bm, c.bn, r.bk, plan->grid.x, plan->grid.y, plan->grid.z, plan->block.x, r.lds, other);
 }
 
 }  // extern "C"

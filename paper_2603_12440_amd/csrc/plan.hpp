@@ -62,7 +62,8 @@ struct Config {
   int lds_bytes;
   launch_fn launch[4];    // per operand dtype (GEMM_F32 / BF16 / F16 / F8E4M3); NULL = not compiled
   int persist;            // 1: workgroups walk over several tiles (grid = workgroups resident at once); 2: where K allows it (persists);
-                          // 3: skinny_rows_kernel (over panels of W); 4: ksplit_ring_kernel, one tile per workgroup
+                          // 3: skinny_rows_kernel (over panels of W); 4: ksplit_ring_kernel, one tile per workgroup;
+                          // 5: fp32 on f32_any_kernel (f32_takes_any)
   // more than two slabs in LDS: microseconds a slab takes with one workgroup on a CU and with two (0: two do not
   // fit); t1 == 0 for all other kernels
   float t1, t2;

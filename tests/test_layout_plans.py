@@ -205,3 +205,37 @@ def test_both_skinny_kernels_have_a_name():
         with pytest.raises(g.GemmError) as e:
             by_name(rows, **kw)
         assert e.value.status == -9, kw
+
+
+def field(text, name):
+    return text.split(" " + name + "=")[1].split()[0]
+
+
+@pytest.mark.parametrize("tile", [64, 128])
+def test_plans_of_any_alignment_report_the_kernel_they_run(tile):
+    """fp32: slabs of 32 columns of K and two stages of 128 bytes a row, or, where offsets inside a slab do not fit 32 bits and on
+    f32general_64x64x16, the general kernel's 16 columns."""
+    name, general = f"general_mfma32_{tile}x{tile}x16", 4 * 16 * 2 * (tile + 4)
+    kw = dict(M=1001, N=1001, K=1001, dtype=g.F32)
+    last = ((1 << 32) - 1) // (4 * (tile + 1)) // 4 * 4                           # (tile + 1) rows below 2^32 bytes
+    for extra, k, lds in ((dict(), 32, 512 * tile), (dict(lda=last), 32, 512 * tile), (dict(lda=last + 4), 16, general), (dict(ldb=last + 4), 16, general)):
+        text = by_name(name, **kw, **extra)
+        assert field(text, "tile") == f"{tile}x{tile}x{k}" and int(field(text, "lds")) == lds, (extra, text)
+    assert field(by_name(name, M=1001, N=1001, K=1001), "tile") == f"{tile}x{tile}x16"       # 16-bit operands
+    if tile == 64:
+        assert field(by_name("f32general_64x64x16", **kw), "tile") == "64x64x16" and int(field(by_name("f32general_64x64x16", **kw), "lds")) == general
+
+
+def test_two_launches_and_slices_report_the_lds_of_the_kernel_they_run():
+    """Slabs of 256 + 256 rows of 128 bytes, two of them; a persistent workgroup's staging area or 256 bytes behind them."""
+    slabs = 2 * 512 * 128
+    for k, lds in ((4096, slabs + 32768), (4112, slabs + 256)):
+        text = info(M=4096, N=14336, K=k, dtype=g.F8E4M3)
+        assert "mfma8_256x256x128" in text and int(field(text, "lds")) == lds, text
+    assert int(field(by_name("mfma8_256x256x128_w2x4_s2", M=4096, N=14336, K=4112, dtype=g.F8E4M3), "lds")) == slabs + 256
+    for M, N, K, slices, dtype in ((512, 512, 32768, 16, g.BF16), (512, 512, 32768, 16, g.F8E4M3), (2048, 2048, 16 * 1040, 4, g.F8E4M3)):
+        p = g.gemm_create_splitk(g.GemmDesc(M, N, K, dtype=dtype), slices)
+        name = p.info().split("+")[1].split()[0]
+        inner = by_name(name, M=M, N=N, K=K // slices, dtype=dtype, dtype_c=g.F32)
+        assert field(p.info(), "lds") == field(inner, "lds") and field(p.info(), "tile") == field(inner, "tile"), (p.info(), inner)
+        g.gemm_destroy(p)
