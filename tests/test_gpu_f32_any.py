@@ -98,3 +98,31 @@ def test_lanes_along_rows_and_columns(g, la, lb, M, N, K, batch):
             print(f"{M}x{N}x{K} b{batch} {la}/{lb}/{lc} {cfg}", flush=True)
             C = run_gpu(g, w, A, B, bias, config=-1 if cfg is None else g.config_names().index(cfg), layout_c=lc, pad_a=1, pad_c=1)
             assert torch.equal(C.float(), want), (cfg, lc)
+
+
+@pytest.mark.parametrize("la,lb", LAYOUTS)
+@pytest.mark.parametrize("huge", ["a", "b"])
+def test_offsets_at_and_beyond_32_bits(g, la, lb, huge):
+    """A leading dimension at which 65 or 129 rows just fit 2^32 bytes, the next one in whole pieces, and 2^24: the kernel of 16-byte loads at any
+    alignment, then the general one, on the plans of either tile and, with a pointer displaced by one element, on those for aligned pieces.
+    (Two to five GB of address space, few rows touched.)"""
+    M, N, K = 72, 68, 36
+    w = wl.Workload("t", M, N, K, dtype="f32", layout_a=la, layout_b=lb, epilogue="bias_relu", seed_a=1, seed_b=2)
+    A, B, want = operands(w)
+    bias = wl.small_integers((N,), w.seed_bias, -3, 3, "f32")
+    want = torch.relu(want + bias)
+    Ad, Bd, biasd = A.cuda(), B.cuda(), bias.cuda()
+    src = Ad if huge == "a" else Bd
+    for ld in (8323580, 8323584, 16519104, 16519108, 1 << 24):
+        wide = torch.empty((src.shape[1] - 1) * ld + src.shape[2] + 1, device="cuda")
+        for off in (0, 1):
+            rows = wide[off:].as_strided((src.shape[1], src.shape[2]), (ld, 1))
+            rows.copy_(src[0])
+            for cfg in ("general_mfma32_64x64x16", "general_mfma32_128x128x16", "f32general_64x64x16") + ("f32mfma_64x64x32", "f32mfma_128x128x32") * off:
+                C = torch.full((M, N), -7.0, device="cuda")
+                p = g.gemm_create_config(gpu_desc(g, w, **{"ld" + huge: ld}), g.config_names().index(cfg))
+                print(f"{la}/{lb} {huge} ld={ld} + {off} {p.info()}", flush=True)
+                g.gemm_run(p, rows if huge == "a" else Ad, rows if huge == "b" else Bd, C, biasd)
+                torch.cuda.synchronize()
+                g.gemm_destroy(p)
+                assert torch.equal(C.cpu(), want[0]), (cfg, ld, off)
