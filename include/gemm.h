@@ -114,7 +114,9 @@ typedef struct {
  * holds a general kernel for pointers that are not 16-byte aligned).  Every other 16-bit problem (odd
  * extents, leading dimensions or strides, column-major C) runs on the 16-bit matrix instruction as well,
  * with its operands staged through registers, or, where it is small or its K short, on the general
- * kernels; both need element alignment only.  Products are exact and sums fp32 on all of them.  fp32
+ * kernels; both need element alignment only.  Products are exact and sums fp32 on all of them.  The tiled 16-bit kernels add a row's products
+ * in one order, whatever the tile; the skinny ones, those that split K over a workgroup's waves (few tiles and a long K, which M and N
+ * decide) and split-K add parts of K, so the last bits of a row of C may depend on how many other rows the call has.  fp32
  * operands are multiplied as fp32 (vector-ALU FMA or the fp32 matrix-core instruction), in any layout
  * and at element alignment.  fp8 operands other than the above have no kernel (GEMM_ERR_UNSUPPORTED).
  */

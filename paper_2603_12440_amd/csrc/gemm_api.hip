@@ -204,8 +204,8 @@ bool f32_takes_ring(const gemm_desc_t& d, int tile) {
   return tile != 64 || !fewer_rounds || d.K > (per_cu <= 4 ? 192 : 32);
 }
 
-// fp32 operands in 16-byte pieces (the plan's extents and leading dimensions allow it: applicable());
-// pointers that are not 16-byte aligned take the general kernel on the same grid
+// fp32 operands in 16-byte pieces (the plan's extents and leading dimensions allow it: applicable()); pointers that
+// are not 16-byte aligned take f32_any_kernel on the same grid, or the general kernel where offsets do not fit 32 bits
 template <int TM, int TN>
 hipError_t launch_f32_mfma(const gemm_plan& pl, const void* A, const void* B, void* C,
                            const void* bias, hipStream_t s) {

@@ -14,11 +14,11 @@
 // Strips serve two kinds of launches (us with strips / with regions, operands in the last-level cache):
 //   * 128x128 tiles, two workgroups per CU, between one and two tiles per CU.  All of them run at once; the regions' second
 //     round would give an XCD a few tiles far from its first 32, whose panels nothing else in that L2 reads, and a launch takes
-//     as long as those: bf16, K = 2056, 24x11 tiles 33.8 / 40.3, 59x5 37.5 / 43.2; fp8, K = 2064, 24x11 21.1 / 25.2.  Not for
+//     as long as those: bf16, K = 2056, 24x11 tiles 33.8 / 40.3, 59x5 37.5 / 43.2; fp8, 679 drawn grids with K > 512 0.98.  Not for
 //     grids at least twice as wide as high whose tiles do not divide by 8 (bf16, 5x59: 45.8 / 40.6).
 //   * K of at most 512 bytes, where writing C is most of the work: full-width rows of C are written closer together in time.
-//     41x61 tiles of 128x128 but 8 columns, K = 64: bf16 32.5 / 39.1, fp8 27.6 / 35.9; 9x28 tiles of 256x256, K = 64: bf16
-//     18.0 / 18.8.  Unless the tiles divide by 8 and C's rows are whole 16-byte pieces (regions up to 5 % ahead there;
+//     41x61 tiles of 128x128 but 8 columns, K = 64: bf16 32.5 / 39.1; 9x28 tiles of 256x256, K = 64: bf16
+//     18.0 / 18.8; fp8, 20000 drawn grids: even (0.92 to 1.06; 1.03 with 256 to 512 tiles of 128x128, twice as wide as high).  Unless the tiles divide by 8 and C's rows are whole 16-byte pieces (regions up to 5 % ahead there;
 //     rows at any element, 4700 drawn products: strips 1.3 % ahead with fp32 results, even with 16-bit ones).
 #pragma once
 
