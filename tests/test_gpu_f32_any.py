@@ -126,3 +126,15 @@ def test_offsets_at_and_beyond_32_bits(g, la, lb, huge):
                 torch.cuda.synchronize()
                 g.gemm_destroy(p)
                 assert torch.equal(C.cpu(), want[0]), (cfg, ld, off)
+
+
+@pytest.mark.parametrize("M", [1, 8, 9])
+@pytest.mark.parametrize("K", [1021, 1025, 1031])
+def test_few_rows_and_a_long_k(g, M, K):
+    """16x16 tiles, both operands row-major: A value by value up to eight rows with K > 1024, in groups beyond; at any element."""
+    w = wl.Workload("t", M, 35, K, dtype="f32", layout_a="row", layout_b="row", batch=3, epilogue="bias_relu", seed_a=M, seed_b=K)
+    A, B, want = operands(w)
+    bias = wl.small_integers((35,), w.seed_bias, -3, 3, "f32")
+    for pad in (0, 2):
+        C = run_gpu(g, w, A, B, bias, config=g.config_names().index("f32small_16x16x256"), pad_a=pad, pad_b=pad)
+        assert torch.equal(C.float(), torch.relu(want + bias)), pad
