@@ -746,9 +746,10 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     // fp32 through LDS.  128x128 tiles: half a band at a time (16 rows of half the wave's columns, as many bytes as a 16-bit band),
     // pipelined like those.  What bounds them at a short K is latency: one band at a time, write, wait, read and store in series,
     // 429x6795x256 with fp8 operands took 10.0 us, 9.4 so (bf16 11.9, 11.2), 4096x4096x512 25.6, 23.7; 3357 drawn fp8 and 4396 bf16 products with
-    // K up to 2048 0.967.  The larger tiles: as many whole bands at a time as the staging area holds, 0.98; in halves, whose stores are
-    // one line, products with 30 million and more results whose rows start off lines took up to 1.02, bands on 128x128 tiles 0.975.
-    // Straight from the accumulators, 64 bytes of a row per store: 0.95 with few tiles, up to 1.24 where C is most of the work.
+    // K up to 2048 0.967.  The larger tiles, whose two waves per SIMD overlap each other's bands: one whole band at a time.  Halves there, whose
+    // stores are one line, take up to 1.02 with 30 million and more results in rows off lines; two to four bands before the first store
+    // 0.98 on average, but 1.07 for 985x8779x1024 on 256x192 tiles (20.7 us).  Straight from the accumulators, 64 bytes of a row per
+    // store: 0.95 with few tiles, up to 1.24 where C is most of the work.
     auto put = [&](f32x4_any_t* c, const f32x4_t& v) __attribute__((always_inline)) {
       if (pe.c_cached) *c = v;                     // split-K partials are read by the next kernel
       else __builtin_nontemporal_store(v, c);
@@ -828,13 +829,9 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
     auto drain32_bands = [&](auto actf) __attribute__((always_inline)) {
       float* Cf = (float*)pe.C + (int64_t)batch * pe.stride_c;
       const int slane = fresh_lane();
-      constexpr int OROWB32 = Cfg::WTN * 4, CH32 = OROWB32 / 16, kKey32 = OROWB == 192 ? 7 : 15;   // bytes and pieces per fp32 row; chunk-slot key
-      constexpr int kIt32 = 16 * CH32 / 64, kBand32 = 16 * OROWB32;
-      constexpr int kStaging = PERSIST ? Cfg::EPI_BYTES / Cfg::kWaves : kShare, kHeld = kStaging / kBand32 < MT ? kStaging / kBand32 : MT;
-      static_assert(kStaging >= kBand32, "one 16-row band of the wave block in fp32 must fit the wave's staging area");
-      float bvs[NT][4];
-#pragma unroll
-      for (int n = 0; n < NT; ++n) bias4(col0 + wn * Cfg::WTN + n * 16 + eq * 4, bvs[n]);
+      constexpr int OROWB32 = Cfg::WTN * 4, CH32 = OROWB32 / 16, kIt32 = 16 * CH32 / 64;   // bytes, pieces per fp32 row of the wave's block
+      constexpr int kKey32 = OROWB == 192 ? 7 : 15;          // chunk-slot key, see osw
+      static_assert(16 * OROWB32 <= kShare, "one 16-row band of the wave block in fp32 must fit the wave's share of LDS");
       const bool inside = row0 + BM <= pe.M && col0 + BN <= pe.N && (int64_t)BM * pe.ldc * 4 < ((int64_t)1 << 31);
       char* const wave_c = (char*)(Cf + (int64_t)(row0 + wm * Cfg::WTM) * pe.ldc + col0 + wn * Cfg::WTN);
       const uint32_t band_step = (uint32_t)(16 * pe.ldc * 4);
@@ -844,50 +841,40 @@ __global__ __launch_bounds__(64 * WM * WN) void mfma16_gemm_kernel(MfmaArgs p) {
         const int e = it * 64 + slane;
         lane_off[it] = (uint32_t)((e / CH32) * (int)pe.ldc * 4 + (e % CH32) * 16);
       }
-      static_for<0, (MT + kHeld - 1) / kHeld>([&](auto p_c) __attribute__((always_inline)) {
-        constexpr int m0 = decltype(p_c)::value * kHeld, m1 = m0 + kHeld < MT ? m0 + kHeld : MT;
-        static_for<m0, m1>([&](auto m_c) __attribute__((always_inline)) {
-          constexpr int m = decltype(m_c)::value;
+      static_for<0, MT>([&](auto m_c) __attribute__((always_inline)) {
+        constexpr int m = decltype(m_c)::value;
 #pragma unroll
-          for (int n = 0; n < NT; ++n) {
-            f32x4_t w;
+        for (int n = 0; n < NT; ++n) {
+          float bv[4];
+          bias4(col0 + wn * Cfg::WTN + n * 16 + eq * 4, bv);
+          f32x4_t w;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = actf(acc[m][n][e] + bvs[n][e]);
-            const int q = n * 4 + eq;
-            *(f32x4_t*)(wt + (m - m0) * kBand32 + er * OROWB32 + ((q ^ (er & kKey32)) * 16)) = w;
+          for (int e = 0; e < 4; ++e) w[e] = actf(acc[m][n][e] + bv[e]);
+          const int q = n * 4 + eq;
+          *(f32x4_t*)(wt + er * OROWB32 + ((q ^ (er & kKey32)) * 16)) = w;
+        }
+#pragma unroll
+        for (int it = 0; it < kIt32; ++it) {
+          const int e = it * 64 + slane;
+          const int r = e / CH32, q = e % CH32;
+          const f32x4_t val = *(const f32x4_t*)(wt + r * OROWB32 + ((q ^ (r & kKey32)) * 16));
+          if (inside) {
+            put((f32x4_any_t*)(wave_c + (lane_off[it] + (uint32_t)m * band_step)), val);
+            continue;
           }
-        });
-        static_for<m0, m1>([&](auto m_c) __attribute__((always_inline)) {
-          constexpr int m = decltype(m_c)::value;
-          f32x4_t val[kIt32];
+          const int i = row0 + wm * Cfg::WTM + m * 16 + r;
+          const int j = col0 + wn * Cfg::WTN + q * 4;
+          if (i < pe.M && j < pe.N) {
+            float* c = Cf + (int64_t)i * pe.ldc + j;
+            if (j + 4 <= pe.N) {
+              put((f32x4_any_t*)c, val);
+            } else {
 #pragma unroll
-          for (int it = 0; it < kIt32; ++it) {
-            const int e = it * 64 + slane;
-            const int r = e / CH32, q = e % CH32;
-            val[it] = *(const f32x4_t*)(wt + (m - m0) * kBand32 + r * OROWB32 + ((q ^ (r & kKey32)) * 16));
-          }
-#pragma unroll
-          for (int it = 0; it < kIt32; ++it) {
-            if (inside) {
-              put((f32x4_any_t*)(wave_c + (lane_off[it] + (uint32_t)m * band_step)), val[it]);
-              continue;
-            }
-            const int e = it * 64 + slane;
-            const int r = e / CH32, q = e % CH32;
-            const int i = row0 + wm * Cfg::WTM + m * 16 + r;
-            const int j = col0 + wn * Cfg::WTN + q * 4;
-            if (i < pe.M && j < pe.N) {
-              float* c = Cf + (int64_t)i * pe.ldc + j;
-              if (j + 4 <= pe.N) {
-                put((f32x4_any_t*)c, val[it]);
-              } else {
-#pragma unroll
-                for (int t2 = 0; t2 < 4; ++t2)
-                  if (j + t2 < pe.N) c[t2] = val[it][t2];
-              }
+              for (int t2 = 0; t2 < 4; ++t2)
+                if (j + t2 < pe.N) c[t2] = val[t2];
             }
           }
-        });
+        }
       });
     };
     // dest: 1 = 16-bit, 2 = fp32
