@@ -880,8 +880,15 @@ int choose_general(const gemm_desc_t& d) {
       const double K = (double)d.K, turns = (double)((d.M + 15) / 16) * (double)((d.N + 15) / 16) * d.batch / num_cus();
       const double tiles64 = (double)((d.M + 63) / 64) * (double)((d.N + 63) / 64) * d.batch / num_cus();
       const double k16 = d.layout_a == GEMM_ROW_MAJOR ? (b_row ? 0.0049 : 0.0038) : (b_row ? 0.0053 : 0.0044);
-      const double narrow = (d.M <= 16 || d.N <= 16) && d.K > 256 ? 0.84 : 1.0;      // (64x64 tiles load one piece of a row many times)
-      const double t16 = 4.85 + narrow * std::hypot(turns * (0.82 + k16 * K), 0.37e-6 * 4.0 * (double)(d.M + d.N) * K * d.batch);   // (operands at 2.7 TB/s)
+      // A few rows or columns and 64x64 tiles that take pieces: those load one piece of a row many times, and 16x16 ones read lines that
+      // they share.  Both operands K-contiguous: 16x16 tiles (0.65 to 0.85 of the other's time at K > 256, 0.9 to 1.1 at K of 65 to 160);
+      // else less than they are charged otherwise, least if the wide operand is K-contiguous.  By this rule 22050 drawn products (up to 16 rows or
+      // columns, K from 65) are 1.0 % from the better kernel, from 2.2 % with the factor 0.84 of the other layouts, and 3.8 % of them
+      // more than 10 % (8.1): 139 of 96x2x408 9.9 on 16x16 tiles, 20.1 on 64x64 ones; 70 of 4x208x2132, strided, 45 and 79.
+      const bool few = d.M <= 16 || d.N <= 16, a_k = d.layout_a == GEMM_ROW_MAJOR;
+      if (few && pieces && a_k && !b_row && d.K > 64) return small;
+      const double narrow = few && pieces ? ((d.M < d.N ? !b_row : a_k) ? 0.7 : 0.8) : few && d.K > 256 ? 0.84 : 1.0;
+      const double t16 = (few && pieces ? 5.85 : 4.85) + narrow * std::hypot(turns * (0.82 + k16 * K), 0.37e-6 * 4.0 * (double)(d.M + d.N) * K * d.batch);   // (operands at 2.7 TB/s)
       const double t64 = pieces ? 6.19 + (1.0 + 0.8 * fmax(0.0, tiles64 - 1.0)) * (0.0207 * K - 0.99)
                                 : 5.11 + (1.0 + 0.8 * fmax(0.0, tiles64 - 1.0)) * ((b_row ? 0.0322 : 0.0253) * K - 0.09);
       return d.K > 64 && t16 < t64 ? small : pieces ? aligned : find_config("general_mfma32_64x64x16");

@@ -158,6 +158,9 @@ def test_second_launch_of_a_wide_product():
     (dict(M=32, N=32, K=2000, batch=512), "f32mfma_64x64x32"),                     # 72.0; 16x16 tiles 105
     (dict(M=1079, N=467, K=529), "general_mfma32_64x64x16"),                       # 21.8; 33
     (dict(M=2456, N=110, K=2930, layout_b=g.ROW_MAJOR), "f32small_16x16x256"),     # 81; 117
+    (dict(M=96, N=2, K=408, batch=139), "f32small_16x16x256"),                      # 9.9; 20.1
+    (dict(M=4, N=208, K=2132, batch=70, layout_a=g.COL_MAJOR), "f32small_16x16x256"),                     # 45; 79
+    (dict(M=4, N=584, K=300, batch=26, layout_a=g.COL_MAJOR, layout_b=g.ROW_MAJOR), "f32mfma_64x64x32"),
     (dict(M=139, N=1, K=7, batch=508), "f32general_64x64x16"),                     # 6.8; any-alignment kernel 9.3 and 14.0
     (dict(M=139, N=1, K=27, batch=508), "general_mfma32_64x64x16"), (dict(M=139, N=1, K=69, batch=508), "f32general_64x64x16")])
 def test_fp32_choice(kw, kernel):
