@@ -24,10 +24,9 @@ def g():
 def test_parts_and_panels(g, K):
     for M, N in [(16, 16), (2, 17), (9, 1000), (5, 4113), (16, 8193)] + [(3, 12289)] * (K in (2056, 4096)) + [(16, 16401)] * (K < 2000):
         w = wl.Workload("t", M, N, K, epilogue="bias_relu", seed_a=K, seed_b=N)
-        for cfg in (CFG, ROWS) if K <= 8192 else (CFG,):
-            run_exact(g, w, cfg, out_dtype="f32")
-            if N < 8000:
-                run_exact(g, w, cfg, pad_c=3)
+        run_exact(g, w, CFG, out_dtype="f32")
+        if N < 8000:
+            run_exact(g, w, CFG, pad_c=3)
 
 
 def test_fp16_and_the_rule(g):
@@ -35,13 +34,13 @@ def test_fp16_and_the_rule(g):
         p = g.gemm_create(g.GemmDesc(**kw))
         info = p.info()
         g.gemm_destroy(p)
-        assert CFG in info and (ROWS in info) == ("block=512" in info)
+        assert CFG in info
         return "block=512" in info
     assert block(M=16, N=28672, K=8192) and block(M=2, N=16, K=1032) and block(M=16, N=8192, K=4096)
     assert not block(M=16, N=8192, K=8192) and not block(M=16, N=4096, K=1024) and not block(M=16, N=28672, K=8200)
     assert not block(M=16, N=15, K=4096) and not block(M=16, N=4096, K=4096, batch=2)
     for M, N, K in [(7, 2000, 1400), (16, 9000, 2824)]:
-        run_exact(g, wl.Workload("t", M, N, K, dtype="f16", epilogue="bias_relu", seed_a=K, seed_b=N), ROWS)
+        run_exact(g, wl.Workload("t", M, N, K, dtype="f16", epilogue="bias_relu", seed_a=K, seed_b=N), CFG)
 
 
 @pytest.mark.parametrize("K", [1416, 4096, 5000])
@@ -64,6 +63,26 @@ def test_values_that_are_not_finite(g, K):
     g.gemm_destroy(p)
     want[M - 1, 1] = float("-inf")          # inf * -inf at the last column
     assert torch.equal(C.cpu().nan_to_num(nan=1e9, posinf=2e9, neginf=-2e9), want.nan_to_num(nan=1e9, posinf=2e9, neginf=-2e9))
+
+
+@pytest.mark.parametrize("K", [1032, 1536, 2040, 2048, 2056, 3592, 4096, 4104, 6136, 6144, 6152, 8184, 8192])
+def test_parts_and_panels_on_the_kernel_by_name(g, K):
+    """The products of test_parts_and_panels on the kernel with x in registers, whichever of the two the rule takes."""
+    for M, N in [(16, 16), (2, 17), (9, 1000), (5, 4113), (16, 8193)] + [(3, 12289)] * (K in (2056, 4096)) + [(16, 16401)] * (K < 2000):
+        w = wl.Workload("t", M, N, K, epilogue="bias_relu", seed_a=K, seed_b=N)
+        run_exact(g, w, ROWS, out_dtype="f32")
+        if N < 8000:
+            run_exact(g, w, ROWS, pad_c=3)
+
+
+def test_fp16_and_the_rule_by_name(g):
+    for kw, rows in ((dict(M=16, N=28672, K=8192), True), (dict(M=2, N=16, K=1032), True), (dict(M=16, N=8192, K=4096), True),
+                     (dict(M=16, N=8192, K=8192), False), (dict(M=16, N=4096, K=1024), False), (dict(M=16, N=28672, K=8200), False)):
+        p = g.gemm_create(g.GemmDesc(**kw))
+        assert (ROWS in p.info()) == rows, p.info()
+        g.gemm_destroy(p)
+    for M, N, K in [(7, 2000, 1400), (16, 9000, 2824)]:
+        run_exact(g, wl.Workload("t", M, N, K, dtype="f16", epilogue="bias_relu", seed_a=K, seed_b=N), ROWS)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
